@@ -265,7 +265,7 @@ void encode_kernel(CoderBatch batch)
     uint8_t *dst = a.payload + a.off_bodies + mine * 16;
     if ((long long)(a.off_bodies + (mine + body_units) * 16) > a.capacity) return;      // cannot happen: bodies never exceed raw size
     if (coded) {
-        for (uint32_t o = lane * 16; o < body_units * 16; o += 64 * 16) *(u32x4 *)(dst + o) = *(const u32x4 *)(lds + o);
+        for (uint32_t o = lane * 16; o < body_units * 16; o += 64 * 16) __builtin_nontemporal_store(*(const u32x4 *)(lds + o), (u32x4 *)(dst + o));
     } else {
         // raw chunk: each lane still holds its sub-block (2 rows) in registers
         const int have = min(max(rows - 2 * lane, 0), 2);

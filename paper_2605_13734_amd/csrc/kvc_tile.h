@@ -172,7 +172,7 @@ __device__ __forceinline__ void k_group_params(const u32x4 *raw, uint8_t *xch, u
         u32x2 m;
         m[0] = g0.meta;
         m[1] = g1.meta;
-        *(u32x2 *)(meta_block + (col * 8 + rsub * 2) * 4) = m;
+        put_at<true>(meta_block + (col * 8 + rsub * 2) * 4, m);
     }
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     f32x4 mine = {g0.zero, g0.inv, g1.zero, g1.inv};
@@ -228,15 +228,21 @@ __device__ __forceinline__ void v_row_minmax(const u32x4 &raw, float &mn, float 
 
 struct VParams {
     float zero[8], inv[8];   // of the lane's group in each of its 8 rows
-    uint32_t meta[8];        // meta[i] is meaningful on the lane that owns row i
-    uint32_t owner_mask;     // bit i: this lane computed (and stores the metadata of) row i
+    uint32_t meta[2];        // metadata words of the rows the lane finished: row v_own_row() and, with
+                             // groups of 32 channels, the one 16 rows below
     bool clamp;              // wave-uniform
 };
 
+// The tile row whose group parameters the lane finishes: lane k of a group takes row 4*k + rsub (groups of
+// 128 channels: lanes 0..7 of the group).
+template <int GV> __device__ __forceinline__ int v_own_row()
+{
+    return 4 * (lane_id() & (GV / 8 - 1) & 7) + (lane_id() >> 4);
+}
+
 // Parameters of the lane's group in each of its 8 rows.  The GV/8 lanes of a group hold the
 // same (min, max) after the reduction; each of them finishes one or two of the 8 rows and the
-// results travel back through ds_bpermute.  vp.meta[i] is valid on the lane that owns row i
-// (vp.owner_mask bit i).
+// results travel back through ds_bpermute.
 template <int BITS, int GV, int DT>
 __device__ __forceinline__ void v_pass_params(const u32x4 raw[8], VParams &vp)
 {
@@ -257,9 +263,9 @@ __device__ __forceinline__ void v_pass_params(const u32x4 raw[8], VParams &vp)
             const int src = (base + (i & 3)) << 2;
             vp.zero[i] = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)__float_as_uint(g.zero)));
             vp.inv[i] = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)__float_as_uint(g.inv)));
-            vp.meta[i] = g.meta;
         }
-        vp.owner_mask = (0x11u << k);
+        vp.meta[0] = g0.meta;
+        vp.meta[1] = g1.meta;
     } else {
         // lanes 0..7 of the group finish row k
         const int r = k & 7;
@@ -272,9 +278,8 @@ __device__ __forceinline__ void v_pass_params(const u32x4 raw[8], VParams &vp)
             const int src = (base + i) << 2;
             vp.zero[i] = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)__float_as_uint(g.zero)));
             vp.inv[i] = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)__float_as_uint(g.inv)));
-            vp.meta[i] = g.meta;
         }
-        vp.owner_mask = k < 8 ? (1u << k) : 0u;
+        vp.meta[0] = vp.meta[1] = g.meta;
     }
     vp.clamp = __builtin_amdgcn_ballot_w64(c) != 0;
 }
@@ -296,17 +301,6 @@ template <int BITS, bool SUB> __device__ __forceinline__ uint8_t *code_row(uint8
     return base + r * (16 * BITS);
 }
 
-template <int BITS> __device__ __forceinline__ void store_codes(uint8_t *row, u32x2 w)
-{
-    // for 3 bits, w[0] already went through quad_words_from_24
-    const int col = lane_id() & 15;
-    if (BITS == 3) {
-        if ((col & 3) != 3) *(uint32_t *)(row + (col >> 2) * 12 + (col & 3) * 4) = w[0];
-    } else {
-        store_row_codes<BITS>(row, w);
-    }
-}
-
 template <int BITS, int DT, int P, bool SUB, bool CLAMP, bool FULL>
 __device__ __forceinline__ void k_emit_rows(const u32x4 *raw, const KParams &kp, uint8_t *base, int rows)
 {
@@ -319,7 +313,7 @@ __device__ __forceinline__ void k_emit_rows(const u32x4 *raw, const KParams &kp,
             const int r = p * kPassRows + 4 * i + rsub;
             u32x2 w = k_quant_row<BITS, DT, CLAMP>(raw[p * 8 + i], kp, one);
             if (BITS == 3) w[0] = quad_words_from_24(w[0]);
-            if (FULL || r < rows) store_codes<BITS>(code_row<BITS, SUB>(base, r), w);
+            if (FULL || r < rows) store_row_codes<BITS, !SUB>(code_row<BITS, SUB>(base, r), w);
             // a token block of 64 or 128 rows: keep the scheduler from interleaving all rows, which
             // would hold the floats of every row at once (255 registers and more)
             if (P >= 2) __builtin_amdgcn_sched_barrier(0);
@@ -340,22 +334,29 @@ __device__ __forceinline__ void k_emit(const u32x4 *raw, const KParams &kp, uint
     }
 }
 
-template <int BITS, int GV, int DT, bool SUB, bool CLAMP, bool FULL>
-__device__ __forceinline__ void v_emit_rows(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows,
-                                            uint32_t *meta)
+// The metadata of a pass: every lane stores the words of the rows it finished, so that one store
+// instruction covers 256 contiguous bytes (groups of 128: 128 bytes) and two (one) of them the pass,
+// instead of eight masked stores of 64 bytes, one per row of the lane.
+template <int GV> __device__ __forceinline__ void v_store_meta(const VParams &vp, int rows, uint32_t *meta)
 {
     constexpr int LANES = GV / 8, NG = kDim / GV;
-    const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
+    const int lane = lane_id(), r = v_own_row<GV>();
+    uint32_t *m = meta + r * NG + (lane & 15) / LANES;
+    if ((LANES < 16 || (lane & 15) < 8) && r < rows) put_at<true>(m, vp.meta[0]);
+    if (LANES == 4 && r + 16 < rows) put_at<true>(m + 16 * NG, vp.meta[1]);
+}
+
+template <int BITS, int GV, int DT, bool SUB, bool CLAMP, bool FULL>
+__device__ __forceinline__ void v_emit_rows(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows)
+{
+    const int rsub = lane_id() >> 4;
     const float one = opaque_one();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + rsub;
         u32x2 w = v_quant_row<BITS, DT, CLAMP>(raw[i], vp.zero[i], vp.inv[i], one);
         if (BITS == 3) w[0] = quad_words_from_24(w[0]);
-        if (FULL || r < rows) {
-            store_codes<BITS>(code_row<BITS, SUB>(base, r), w);
-            if (meta && ((vp.owner_mask >> i) & 1u)) meta[r * NG + col / LANES] = vp.meta[i];
-        }
+        if (FULL || r < rows) store_row_codes<BITS, !SUB>(code_row<BITS, SUB>(base, r), w);
     }
 }
 
@@ -364,12 +365,13 @@ template <int BITS, int GV, int DT, bool SUB>
 __device__ __forceinline__ void v_emit(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows, uint32_t *meta)
 {
     const bool full = rows >= kPassRows;
+    if (meta) v_store_meta<GV>(vp, rows, meta);
     if (vp.clamp) {
-        if (full) v_emit_rows<BITS, GV, DT, SUB, true, true>(raw, vp, base, rows, meta);
-        else v_emit_rows<BITS, GV, DT, SUB, true, false>(raw, vp, base, rows, meta);
+        if (full) v_emit_rows<BITS, GV, DT, SUB, true, true>(raw, vp, base, rows);
+        else v_emit_rows<BITS, GV, DT, SUB, true, false>(raw, vp, base, rows);
     } else {
-        if (full) v_emit_rows<BITS, GV, DT, SUB, false, true>(raw, vp, base, rows, meta);
-        else v_emit_rows<BITS, GV, DT, SUB, false, false>(raw, vp, base, rows, meta);
+        if (full) v_emit_rows<BITS, GV, DT, SUB, false, true>(raw, vp, base, rows);
+        else v_emit_rows<BITS, GV, DT, SUB, false, false>(raw, vp, base, rows);
     }
 }
 
