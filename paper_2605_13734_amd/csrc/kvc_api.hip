@@ -587,7 +587,6 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     base.total_chunks = g.chunks_k + g.chunks_v;
     base.slots = any_table ? kTableSlots : 2;
     base.ws.hist = (uint32_t *)ws;
-    base.ws.enc = (uint32_t *)(ws + a256(kTableSlots * 256 * 4));
     base.ws.lut = (uint16_t *)(ws + 2 * a256(kTableSlots * 256 * 4));
     base.ws.ticket = (uint32_t *)(ws + 2 * a256(kTableSlots * 256 * 4) + a256(kTableSlots * 4096 * 2));
     base.ws.state = (unsigned long long *)(ws + p->ws_state_off);

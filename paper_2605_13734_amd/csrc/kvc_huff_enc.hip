@@ -127,16 +127,24 @@ void encode_kernel(CoderBatch batch)
 
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     if (tid == 0) s_ticket = atomicAdd(a.ws.ticket, 1u);
+    // the candidate with the fewest halvings that meets the length limit (two short loads one after the
+    // other, in the time the ticket takes)
+    const CandidateTables *tables = candidate_tables(a.ws, a.tab);
+    const uint32_t complete = lane < kCandidates ? tables->complete[lane] : 0;
+    const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(complete != 0) | (1ull << (kCandidates - 1)));
     for (int k = tid; k < 256; k += NW * 64) {
-        const uint32_t e = a.ws.enc[256 * a.tab + k];             // code | length << 16
-        enc.len[k] = (uint8_t)(e >> 16);
-        enc.code[k] = (uint16_t)((e & 0xfffu) | ((e >> 16) << 12));
+        const uint16_t e = tables->entry[pick][k];
+        enc.len[k] = (uint8_t)(e >> 12);
+        enc.code[k] = e;
     }
     __syncthreads();
     const long long ticket = (unsigned)__builtin_amdgcn_readfirstlane((int)s_ticket);     // global order over K and V workgroups (the same in all lanes)
     const long long chunk = (ticket - a.wg_base) * NW + wave;
     const bool live = chunk < a.chunks;
     uint8_t *lds = lds_all + wave * Geo::kLds;
+    // the table's lengths in the payload, unless the construction without halvings has written them already
+    if (pick != 0 && ticket == a.wg_base)
+        for (int k = tid; k < 256; k += NW * 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
 
     uint32_t body_units = 0;      // body size in 16-byte units
     bool coded = false;

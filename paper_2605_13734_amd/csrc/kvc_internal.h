@@ -124,11 +124,24 @@ constexpr int kTableSlots = 8;
 // Per-request scratch inside the caller's workspace (device memory).
 struct CoderScratch {
     uint32_t *hist;             // [kTableSlots][256] sample histograms
-    uint32_t *enc;              // [kTableSlots][256] code | length << 16
-    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol | length << 8
+    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol | length << 8; while compressing, the
+                                // candidates for the slot's code table (CandidateTables)
     unsigned long long *state;  // scan state, one word per encode workgroup (in launch order)
     uint32_t *ticket;           // work-order counter
 };
+
+// The code tables of a slot for 0, 1, ... halvings of the sample's weights (see build_tables_kernel).
+constexpr int kCandidates = 11;
+struct CandidateTables {
+    uint16_t entry[kCandidates][256];       // code | length << 12, by byte value
+    uint32_t complete[kCandidates];         // the code meets the length limit: the entries exist
+};
+static_assert(sizeof(CandidateTables) <= 4096 * 2, "fits the slot's decode table");
+
+__device__ __forceinline__ CandidateTables *candidate_tables(const CoderScratch &ws, int slot)
+{
+    return (CandidateTables *)(ws.lut + 4096 * slot);
+}
 
 // Chunks (= waves) per encoder workgroup.  One look-back per workgroup is the encoder's serial part,
 // so the variants whose registers allow 512 threads (2- to 4-bit codes, groups of 32, the dense
