@@ -58,6 +58,12 @@ static TableLayout table_layout(long long LH, int tables)
     return t;
 }
 
+// The coder's workspace of a request: [slots][kSampleChunks][256] byte counts, [kTableSlots][4096] table words,
+// the ticket's 256 bytes, the scan state.
+static int table_slots(const kvc_plan_t *p) { return (p->has_table[0] || p->has_table[1]) ? kTableSlots : 2; }
+static size_t lut_offset(const kvc_plan_t *p) { return (size_t)table_slots(p) * kSampleChunks * 256 * 2; }
+static size_t ticket_offset(const kvc_plan_t *p) { return lut_offset(p) + (size_t)kTableSlots * 4096 * 2; }
+
 static int width_at(const kvc_plan_t *p, int is_v, long long lh)
 {
     const uint8_t *t = is_v ? p->strat.head_bits_v : p->strat.head_bits_k;
@@ -281,10 +287,10 @@ extern "C" int kvc_plan(const kvc_model *model, const kvc_strategy *strategy, in
         }
     }
     if (strategy->codec) {
-        // histograms, encode tables, decode tables, ticket, then the scan state
+        // byte counts of the sample, code / decode tables, ticket, then the scan state:
         // one scan-state word per chunk of K and of V
         const long long chunks = (long long)model->layers * model->kv_heads * chunks_per_head(max_tokens);
-        p->ws_state_off = 2 * a256(kTableSlots * 256 * 4) + a256(kTableSlots * 4096 * 2) + 256;
+        p->ws_state_off = ticket_offset(p) + 256;
         p->ws_request = p->ws_state_off + a256((size_t)(2 * chunks) * 8 + 8);
     }
     *out = p;
@@ -574,7 +580,7 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
                           long long capacity, uint64_t *out_bytes, int *status, bool compress, const uint8_t *dev_tables,
                           CoderLaunch out[kTableSlots])
 {
-    const bool any_table = p->has_table[0] || p->has_table[1];
+    const bool any_table = table_slots(p) == kTableSlots;
     const long long LH = (long long)p->model.layers * p->model.kv_heads, cph = chunks_per_head(r->tokens);
     const TableLayout t = table_layout(LH, p->has_table[0] + p->has_table[1]);
     CoderArgs base;
@@ -585,10 +591,10 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     base.off_bodies = g.off_codes_k;
     base.capacity = capacity;
     base.total_chunks = g.chunks_k + g.chunks_v;
-    base.slots = any_table ? kTableSlots : 2;
-    base.ws.hist = (uint32_t *)ws;
-    base.ws.lut = (uint16_t *)(ws + 2 * a256(kTableSlots * 256 * 4));
-    base.ws.ticket = (uint32_t *)(ws + 2 * a256(kTableSlots * 256 * 4) + a256(kTableSlots * 4096 * 2));
+    base.slots = table_slots(p);
+    base.ws.sample = (uint16_t *)ws;
+    base.ws.lut = (uint16_t *)(ws + lut_offset(p));
+    base.ws.ticket = (uint32_t *)(ws + ticket_offset(p));
     base.ws.state = (unsigned long long *)(ws + p->ws_state_off);
     base.out_bytes = (unsigned long long *)out_bytes;
     int n = 0, mask = 0;
@@ -648,9 +654,122 @@ static int check_batch(const kvc_plan_t *p, const kvc_request *reqs, int32_t n, 
 
 #define KVC_TRY(expr) do { int rc__ = (expr); if (rc__ != KVC_OK) return rc__; } while (0)
 
+// What the prologue writes for one request (ws: its part of the coder's workspace, or null).
+static void prologue_item(const kvc_plan_t *plan, const kvc_request *r, uint8_t *payload, void *workspace, uint8_t *ws,
+                          uint64_t *out_bytes, int32_t *status, PrologueItem *item)
+{
+    Geometry g;
+    geometry(plan, r->tokens, &g);
+    PrologueItem &it = *item;
+    it.payload = (uint32_t *)payload;
+    make_header(plan, r->tokens, g, &it.header);
+    // alignment padding after the V metadata and after the coder's or the width tables is zero
+    it.pad_off[0] = g.off_meta_v + g.meta_v;
+    it.pad_words[0] = (int)((a16(g.meta_v) - g.meta_v) / 4);
+    it.pad_off[1] = g.off_aux + g.aux_base;
+    it.pad_words[1] = (int)((a16(g.aux_base) - g.aux_base) / 4);
+    if (plan->blob_bytes) {
+        // the width tables: a copy of the image at the start of the workspace (whole words; the
+        // image is zero behind the tables), then zero up to the next 16-byte boundary
+        it.aux_src = (const uint32_t *)workspace;
+        it.aux_off = g.off_widths;
+        it.aux_words = (g.widths + 3) / 4;
+        it.pad_off[1] = g.off_widths + 4 * it.aux_words;
+        it.pad_words[1] = (int)((g.off_aux + a16(g.aux_base) - it.pad_off[1]) / 4);
+    }
+    it.out_bytes = (unsigned long long *)out_bytes;
+    it.status = status;
+    if (!plan->strat.codec) {
+        it.total = (unsigned long long)g.total;
+        it.write_total = 1;
+        return;
+    }
+    // ticket and scan state start from zero
+    CoderLaunch cl[kTableSlots];
+    coder_launches(plan, r, payload, g, ws, 0, nullptr, status, true, (const uint8_t *)workspace, cl);
+    const CoderArgs &c = cl[0].a;              // (a request has at least one K and one V launch)
+    it.zero = c.ws.ticket;
+    it.zero_words = 64 + 2 * c.total_wgs + 2;
+    if (c.total_chunks == 0) {
+        // empty request: no workgroup runs that could close the directory and header
+        put64((uint8_t *)it.header.w + 40, (uint64_t)g.off_codes_k);
+        put64((uint8_t *)it.header.w + 112, (uint64_t)g.off_codes_k);
+        it.dir0 = (uint32_t *)(payload + g.off_dir);
+        it.total = (unsigned long long)g.off_codes_k;
+        it.write_total = 1;
+    }
+}
+
+// Set-up of all requests of a call with the coder: prologues and table samples, then the code tables.
+static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t n, void *payload, const uint64_t *payload_off,
+                       uint64_t *out_bytes, int32_t *dev_status, void *workspace, hipStream_t s)
+{
+    const kvc_strategy &st = plan->strat;
+    const long long LH = (long long)plan->model.layers * plan->model.kv_heads;
+    const TableLayout t = table_layout(LH, plan->has_table[0] + plan->has_table[1]);
+    SetupArgs sa;
+    memset(&sa, 0, sizeof sa);
+    sa.heads = plan->model.kv_heads;
+    BuildArgs ba;
+    memset(&ba, 0, sizeof ba);
+    ba.slots = table_slots(plan);
+    for (int is_v = 0; is_v < 2; ++is_v) {
+        const int *list = plan->has_table[is_v] ? (const int *)((const uint8_t *)workspace + t.head_list[is_v]) : nullptr;
+        for (int w = 0; w < 4; ++w) {
+            long long heads = 0;
+            if (list) heads = plan->width_count[is_v][w];
+            else if (kWidths[w] == (is_v ? st.bits_v : st.bits_k)) heads = LH;
+            if (heads == 0) continue;
+            SetupTable &tab = sa.table[sa.tables++];
+            tab.head_list = list;
+            if (list) list += heads;
+            tab.heads_covered = (int)heads;
+            tab.slot = ba.slots == kTableSlots ? 4 * is_v + w : is_v;
+            tab.is_v = is_v;
+            tab.bits = kWidths[w];
+            tab.group = is_v ? st.group_v : st.group_k;
+            tab.rotate = st.transform == KVC_T_HADAMARD;
+            tab.anchor_shift = -1;
+            if (st.transform == KVC_T_DELTA) {
+                tab.anchor_shift = 0;
+                while ((1 << tab.anchor_shift) < st.anchor_period) ++tab.anchor_shift;
+            }
+            ba.slot_mask |= 1 << tab.slot;
+        }
+    }
+    for (int first = 0; first < n; first += kSetupBatch) {
+        sa.n = n - first < kSetupBatch ? n - first : kSetupBatch;
+        for (int j = 0; j < sa.n; ++j) {
+            const int i = first + j;
+            SetupItem &it = sa.item[j];
+            memset(&it, 0, sizeof it);
+            uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
+            prologue_item(plan, &reqs[i], (uint8_t *)payload + payload_off[i], workspace, ws, out_bytes + i, dev_status + i, &it.prologue);
+            it.x = view_of(&reqs[i], 0);
+            it.v_base = (uint16_t *)reqs[i].v;
+            it.tokens = reqs[i].tokens;
+            it.sample = (uint16_t *)ws;
+        }
+        KVC_TRY(launch_setup(plan->model.dtype, sa, s));
+    }
+    for (int first = 0; first < n; first += kBuildBatch) {
+        ba.n = n - first < kBuildBatch ? n - first : kBuildBatch;
+        for (int j = 0; j < ba.n; ++j) {
+            const int i = first + j;
+            Geometry g;
+            geometry(plan, reqs[i].tokens, &g);
+            uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
+            ba.item[j].sample = (const uint16_t *)ws;
+            ba.item[j].lut = (uint16_t *)(ws + lut_offset(plan));
+            ba.item[j].lengths = (uint8_t *)payload + payload_off[i] + g.off_aux;
+        }
+        KVC_TRY(launch_build_tables(ba, s));
+    }
+    return KVC_OK;
+}
+
 // The launch sequence of kvc_compress on a given workspace (the caller's, or the library's own
-// static one): one service launch for all requests, then per request the coder's tables and one
-// pass per tensor.
+// static one): the set-up of all requests, then one pass per tensor over the requests of a window.
 static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t n, void *payload,
                        const uint64_t *payload_off, uint64_t *out_bytes, int32_t *dev_status,
                        void *workspace, hipStream_t s)
@@ -666,65 +785,25 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
     const int dt = plan->model.dtype;
     const Marks marks(plan, s);
     marks.at(0, 0);
-    for (int first = 0; first < n; first += kPrologueBatch) {
-        PrologueArgs pa;
-        memset(&pa, 0, sizeof pa);
-        pa.n = n - first < kPrologueBatch ? n - first : kPrologueBatch;
-        for (int j = 0; j < pa.n; ++j) {
-            const int i = first + j;
-            Geometry g;
-            geometry(plan, reqs[i].tokens, &g);
-            uint8_t *pl = (uint8_t *)payload + payload_off[i];
-            PrologueItem &it = pa.item[j];
-            it.payload = (uint32_t *)pl;
-            make_header(plan, reqs[i].tokens, g, &it.header);
-            // alignment padding after the V metadata and after the coder's or the width tables is zero
-            it.pad_off[0] = g.off_meta_v + g.meta_v;
-            it.pad_words[0] = (a16(g.meta_v) - g.meta_v) / 4;
-            it.pad_off[1] = g.off_aux + g.aux_base;
-            it.pad_words[1] = (a16(g.aux_base) - g.aux_base) / 4;
-            if (plan->blob_bytes) {
-                // the width tables: a copy of the image at the start of the workspace (whole words; the
-                // image is zero behind the tables), then zero up to the next 16-byte boundary
-                it.aux_src = (const uint32_t *)workspace;
-                it.aux_off = g.off_widths;
-                it.aux_words = (g.widths + 3) / 4;
-                it.pad_off[1] = g.off_widths + 4 * it.aux_words;
-                it.pad_words[1] = (g.off_aux + a16(g.aux_base) - it.pad_off[1]) / 4;
+    marks.window(0, n, 0);                     // (the set-up of all requests comes first)
+    if (st.codec) {
+        KVC_TRY(coder_setup(plan, reqs, n, payload, payload_off, out_bytes, dev_status, workspace, s));
+    } else {
+        for (int first = 0; first < n; first += kPrologueBatch) {
+            PrologueArgs pa;
+            memset(&pa, 0, sizeof pa);
+            pa.n = n - first < kPrologueBatch ? n - first : kPrologueBatch;
+            for (int j = 0; j < pa.n; ++j) {
+                const int i = first + j;
+                prologue_item(plan, &reqs[i], (uint8_t *)payload + payload_off[i], workspace, nullptr, out_bytes + i, dev_status + i,
+                              &pa.item[j]);
             }
-            it.out_bytes = (unsigned long long *)(out_bytes + i);
-            it.status = dev_status + i;
-            if (!st.codec) {
-                it.total = (unsigned long long)g.total;
-                it.write_total = 1;
-            } else {
-                uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
-                CoderLaunch cl[kTableSlots];
-                const int launches = coder_launches(plan, &reqs[i], pl, g, ws, 0, nullptr, dev_status + i, true,
-                                                    (const uint8_t *)workspace, cl);
-                const CoderArgs &c = cl[0].a;              // (a request has at least one K and one V launch)
-                (void)launches;
-                // histograms, ticket and scan state start from zero
-                it.zero[0] = c.ws.hist;
-                it.zero_words[0] = kTableSlots * 256;
-                it.zero[1] = c.ws.ticket;
-                it.zero_words[1] = 64 + 2 * c.total_wgs + 2;
-                if (c.total_chunks == 0) {
-                    // empty request: no workgroup runs that could close the directory and header
-                    put64((uint8_t *)it.header.w + 40, (uint64_t)g.off_codes_k);
-                    put64((uint8_t *)it.header.w + 112, (uint64_t)g.off_codes_k);
-                    it.dir0 = (uint32_t *)(pl + g.off_dir);
-                    it.total = (unsigned long long)g.off_codes_k;
-                    it.write_total = 1;
-                }
-            }
+            KVC_TRY(launch_compress_prologue(pa, s));
         }
-        KVC_TRY(launch_compress_prologue(pa, s));
     }
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, reqs, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
-        marks.window(first, end, 0);
         if (!st.codec) {
             marks.window(first, end, 1);
             KVC_TRY(launch_tensor(plan, 0, true, quant_batch(plan, reqs, first, end, lead, 0, payload, payload_off, dev_status, true),
@@ -747,9 +826,6 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                                           (long long)(payload_off[i + 1] - payload_off[i]), out_bytes + i, dev_status + i, true,
                                           (const uint8_t *)workspace, cl[k]);
             }
-            for (int j = 0; j < launches; ++j)
-                KVC_TRY(launch_table_sample(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
-            KVC_TRY(launch_build_tables(coder_batch(cl, end - first, 0), s));
             marks.window(first, end, 1);
             for (int j = 0; j < launches; ++j)
                 if (!cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));

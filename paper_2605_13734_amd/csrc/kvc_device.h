@@ -319,16 +319,20 @@ struct GroupParams {
     bool clamp;       // codes of this group can leave [0, 2^bits-1] before clamping
 };
 
-// range / (2^BITS - 1), correctly rounded: product with the rounded reciprocal, one exact
-// residual, one correction.  Equal to IEEE division for every float in [0, 2^17] (checked
-// exhaustively on the device by kvc_selftest).
+// range / qmax for qmax = 2^bits - 1 and c = its rounded reciprocal, correctly rounded: product with
+// the reciprocal, one exact residual, one correction.  Equal to IEEE division for every float in
+// [0, 2^17] (checked exhaustively on the device by kvc_selftest).
+__device__ __forceinline__ float div_levels(float r, float qmax, float c)
+{
+    const float q0 = r * c;
+    const float e = __builtin_fmaf(-q0, qmax, r);
+    return __builtin_fmaf(e, c, q0);
+}
 template <int BITS> __device__ __forceinline__ float div_levels(float r)
 {
     constexpr float qmax = (float)((1 << BITS) - 1);
     constexpr float c = 1.0f / qmax;
-    const float q0 = r * c;
-    const float e = __builtin_fmaf(-q0, qmax, r);
-    return __builtin_fmaf(e, c, q0);
+    return div_levels(r, qmax, c);
 }
 
 // 1 / s for a positive fp16-representable s: hardware estimate plus one Newton step, equal to
@@ -342,14 +346,14 @@ __device__ __forceinline__ float rcp_f16_exact(float s)
 
 // zero = fp16(min), scale = fp16((max - min) / (2^bits - 1)); a zero of either sign is +0.
 // With fp16 input the minimum is its own fp16 rounding and the scale cannot overflow.
-template <int BITS, int DT> __device__ __forceinline__ GroupParams make_group(float mn, float mx)
+template <int DT> __device__ __forceinline__ GroupParams make_group(float mn, float mx, float qmax, float c)
 {
     mn += 0.0f;
     mx += 0.0f;
     float lo = mn;
     if (DT != DT_F16) lo = __builtin_amdgcn_fmed3f(mn, -65504.0f, 65504.0f);
     const uint32_t zb = f32_to_f16_bits(lo);
-    float s = rounded_f32(div_levels<BITS>(mx - mn));
+    float s = rounded_f32(div_levels(mx - mn, qmax, c));
     if (DT != DT_F16) s = fminf(s, 65504.0f);
     const uint32_t sb = f32_to_f16_bits(s);
     const float sh = f16_bits_to_f32(sb);
@@ -361,6 +365,13 @@ template <int BITS, int DT> __device__ __forceinline__ GroupParams make_group(fl
     // [0, 2^bits - 1]; a bfloat16 group can have its zero point or its scale limited to the fp16 range
     g.clamp = sh < 6.103515625e-05f || (DT != DT_F16 && (g.zero != mn || sh >= 65504.0f));
     return g;
+}
+
+template <int BITS, int DT> __device__ __forceinline__ GroupParams make_group(float mn, float mx)
+{
+    constexpr float qmax = (float)((1 << BITS) - 1);
+    constexpr float c = 1.0f / qmax;
+    return make_group<DT>(mn, mx, qmax, c);
 }
 
 // code = clamp(round_half_even((x - zero) * inv), 0, 2^bits - 1); two rounded fp32 operations

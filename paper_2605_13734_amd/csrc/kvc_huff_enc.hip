@@ -129,7 +129,7 @@ void encode_kernel(CoderBatch batch)
     if (tid == 0) s_ticket = atomicAdd(a.ws.ticket, 1u);
     // the candidate with the fewest halvings that meets the length limit (two short loads one after the
     // other, in the time the ticket takes)
-    const CandidateTables *tables = candidate_tables(a.ws, a.tab);
+    const CandidateTables *tables = candidate_tables(a.ws.lut, a.tab);
     const uint32_t complete = lane < kCandidates ? tables->complete[lane] : 0;
     const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(complete != 0) | (1ull << (kCandidates - 1)));
     for (int k = tid; k < 256; k += NW * 64) {

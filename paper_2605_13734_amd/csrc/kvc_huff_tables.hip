@@ -1,45 +1,136 @@
-// Lossless stage, set-up kernels: the table sample (byte histogram of up to 16 chunks per section),
+// Lossless stage, set-up kernels: the call's prologue and the table samples (byte counts of up to 16 chunks per section),
 // the code construction (Huffman lengths, canonical codes) and the decode tables.  See kvc_huff.h.
 
 #include "kvc_huff.h"
 
 namespace kvc {
 
-// ---- table sample: histogram of up to 16 chunks per section ------------------------------------
+// ---- set-up of a call: prologues and table samples -------------------------------------------------
 
-// grid = 16 sample chunks x the units of a chunk, one wave each: the wave quantizes its unit (one
-// load round trip) and counts the byte values of the packed rows.
-template <int BITS, int G, int DT, bool IS_V>
-__global__ __launch_bounds__(64) void hist_kernel(CoderBatch batch)
+// Counts the bytes of the lane's packed codes of its 8 rows (tile row 4*i + rsub of the wave's pass, `rows` of
+// the pass exist).  The width is a run-time value here: this is a few chunks per call, and one kernel for
+// all widths, groups and both tensors lets one launch sample all of them.
+template <int DT, bool IS_V>
+__device__ __forceinline__ void count_rows(const u32x4 raw[8], const float zero[8], const float inv[8], int bits, int rows,
+                                           uint32_t *hist)
 {
-    const CoderArgs &a = batch.item[blockIdx.y];
-    if (a.chunks <= 0) return;
-    using Unit = UnitGeom<BITS, G, DT, IS_V>;
-    constexpr int RW = 4 * BITS;                         // words of a packed row
-    // (a whole chunk's region: the K group parameters travel through the padding of all 64 sub-blocks)
-    __shared__ __attribute__((aligned(16))) uint8_t lds[ChunkGeom<BITS>::kLds];
-    __shared__ uint32_t hist[256];
-    const int i = blockIdx.x / Unit::kUnits, u = blockIdx.x - i * Unit::kUnits, lane = lane_id();
-    const long long n = a.chunks;
-    const long long chunk = (long long)i * n / 16;
-    if (i > 0 && (long long)(i - 1) * n / 16 == chunk) return;      // each chunk counted once
-    ChunkPos c = chunk_pos(a.q, chunk);
-    if (u * Unit::kRows >= c.rows) return;
-    for (int k = lane; k < 256; k += 64) hist[k] = 0;
-    bool bad = false;
-    quantize_unit<BITS, G, DT, IS_V, false>(a.q, c, u, lds, 0, false, bad);
-    wave_sync();
-    const int rows = min(c.rows - u * Unit::kRows, Unit::kRows);
-    for (int w = lane; w < rows * RW; w += 64) {
-        const int r = w / RW;
-        const uint32_t word = *(const uint32_t *)(code_row<BITS, true>(lds, r) + (w - r * RW) * 4);
+    const int rsub = lane_id() >> 4;
+    const float one = opaque_one(), qmax = (float)((1 << bits) - 1);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) atomicAdd(&hist[(word >> (8 * b)) & 255u], 1u);
+    for (int i = 0; i < 8; ++i) {
+        uint32_t q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float t = elem_minus<DT>(raw[i], e, zero[IS_V ? i : e], one) * inv[IS_V ? i : e];
+            q[e] = (uint32_t)__builtin_rintf(__builtin_amdgcn_fmed3f(t, 0.0f, qmax));
+        }
+        if (4 * i + rsub >= rows) continue;
+        if (bits == 8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) atomicAdd(&hist[q[e] & 255u], 1u);
+            continue;
+        }
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w |= q[e] << (bits * e);
+        atomicAdd(&hist[w & 255u], 1u);
+        atomicAdd(&hist[(w >> 8) & 255u], 1u);
+        if (bits > 2) atomicAdd(&hist[(w >> 16) & 255u], 1u);
+        if (bits > 3) atomicAdd(&hist[w >> 24], 1u);
     }
-    wave_sync();
-    uint32_t *g = a.ws.hist + 256 * a.tab;
-    for (int k = lane; k < 256; k += 64)
-        if (hist[k]) atomicAdd(&g[k], hist[k]);
+}
+
+// The byte counts of sample chunk i of a table.  A wave takes 32 rows (one load round trip); the waves whose
+// rows share K groups exchange their minima and maxima.
+template <int DT>
+__device__ __forceinline__ void sample_chunk(const SetupArgs &a, const SetupItem &it, const SetupTable &t, int i)
+{
+    __shared__ uint32_t hist[4][256];                          // one per wave
+    __shared__ __attribute__((aligned(16))) float low[4][kDim], high[4][kDim];       // K: a wave's extremes per channel
+    const int tid = threadIdx.x, wave = wave_id(), lane = lane_id(), col = lane & 15, rsub = lane >> 4;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) hist[w][tid] = 0;
+    __syncthreads();
+    const long long cph = (it.tokens + kChunkRows - 1) / kChunkRows, n = t.heads_covered * cph;
+    const long long chunk = (long long)i * n / kSampleChunks;
+    if (n > 0 && (i == 0 || (long long)(i - 1) * n / kSampleChunks != chunk)) {      // each chunk is counted once
+        const long long slot = chunk / cph, cb = chunk - slot * cph;
+        const long long lh = t.head_list ? t.head_list[slot] : slot, l = lh / a.heads, h = lh - l * a.heads;
+        const long long row0 = cb * kChunkRows + wave * kPassRows, head_off = l * it.x.stride_layer + h * it.x.stride_head;
+        const long long left = it.tokens - row0;
+        const int rows = left < kPassRows ? (int)left : kPassRows;      // (below 1 for a wave behind the end: it counts nothing)
+        TensorView x = it.x;
+        if (t.is_v) x.base = it.v_base;
+        bool bad = false;                                       // (reported by the encoder, which reads the same rows)
+        u32x4 raw[8];
+        load_pass<false>(x, head_off, row0, it.tokens, raw, bad);
+        if (t.rotate) rotate_rows<DT, 8>(raw);
+        if (t.anchor_shift >= 0) delta_rows<DT, false, 8>(x, head_off, row0, it.tokens, t.anchor_shift, nullptr, false, raw, bad);
+        const float qmax = (float)((1 << t.bits) - 1);
+        const float c = t.bits == 2 ? 1.0f / 3 : t.bits == 3 ? 1.0f / 7 : t.bits == 4 ? 1.0f / 15 : 1.0f / 255;
+        float zero[8], inv[8];
+        if (!t.is_v) {
+            float mn2[2], mx2[2];
+            k_stats_own<DT, 8>(raw, mn2, mx2);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                low[wave][col * 8 + rsub * 2 + e] = mn2[e];
+                high[wave][col * 8 + rsub * 2 + e] = mx2[e];
+            }
+            __syncthreads();                                    // (t and the chunk are the same for the whole workgroup)
+            const int share = t.group / kPassRows, w0 = wave & ~(share - 1);
+            float mn[8], mx[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                mn[e] = low[w0][col * 8 + e];
+                mx[e] = high[w0][col * 8 + e];
+            }
+            for (int w = w0 + 1; w < w0 + share; ++w)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    mn[e] = fminf(mn[e], low[w][col * 8 + e]);
+                    mx[e] = fmaxf(mx[e], high[w][col * 8 + e]);
+                }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const GroupParams g = make_group<DT>(mn[e], mx[e], qmax, c);
+                zero[e] = g.zero;
+                inv[e] = g.inv;
+            }
+            count_rows<DT, false>(raw, zero, inv, t.bits, rows, hist[wave]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                float mn, mx;
+                if (t.group == 32) v_row_minmax<32, DT>(raw[r], mn, mx);
+                else if (t.group == 64) v_row_minmax<64, DT>(raw[r], mn, mx);
+                else v_row_minmax<128, DT>(raw[r], mn, mx);
+                const GroupParams g = make_group<DT>(mn, mx, qmax, c);
+                zero[r] = g.zero;
+                inv[r] = g.inv;
+            }
+            count_rows<DT, true>(raw, zero, inv, t.bits, rows, hist[wave]);
+        }
+    }
+    __syncthreads();
+    // (a chunk has at most 16384 bytes)
+    it.sample[(t.slot * kSampleChunks + i) * 256 + tid] = (uint16_t)(hist[0][tid] + hist[1][tid] + hist[2][tid] + hist[3][tid]);
+}
+
+// Everything of a compress call with the coder that depends on nothing: grid = (kSampleChunks workgroups per
+// table, then the slices of the zero fills; requests).  The sample leaves its counts chunk by chunk, so
+// that no histogram has to be cleared first.  One request: 7 us, where a prologue, a K and a V sample in
+// a launch each took 17 us; with the build behind it for all requests of the call at once, the set-up
+// of 32 requests takes 52 us instead of 134 us (four windows of two samples and a build).
+template <int DT> __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
+{
+    const SetupItem &it = a.item[blockIdx.y];
+    const unsigned samples = (unsigned)a.tables * kSampleChunks;
+    if (blockIdx.x >= samples) {
+        write_prologue(it.prologue, (long long)(blockIdx.x - samples) * 256 + threadIdx.x, (long long)(gridDim.x - samples) * 256);
+        return;
+    }
+    sample_chunk<DT>(a, it, a.table[blockIdx.x / kSampleChunks], (int)(blockIdx.x % kSampleChunks));
 }
 
 // ---- code construction ----------------------------------------------------------------------------
@@ -197,19 +288,22 @@ __device__ __forceinline__ uint32_t halved(uint32_t w, int k) { return (w + ((1u
 constexpr int kTableWaves = 8;      // waves that fill a decode table
 
 // grid = kCandidates workgroups of 256 threads (one symbol each) per table slot of the format.
-__global__ __launch_bounds__(256) void build_tables_kernel(CoderBatch batch)
+__global__ __launch_bounds__(256) void build_tables_kernel(BuildArgs a)
 {
-    const CoderArgs &a = batch.item[blockIdx.y];
+    const BuildItem &it = a.item[blockIdx.y];
     const int sec = blockIdx.x / kCandidates, k = blockIdx.x - sec * kCandidates;
     const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
     if (!((a.slot_mask >> sec) & 1)) {                 // a width the tensor does not use: an empty table
-        if (k == 0) a.payload[a.off_aux + 256 * sec + tid] = 0;
+        if (k == 0) it.lengths[256 * sec + tid] = 0;
         return;
     }
     __shared__ __attribute__((aligned(16))) BuildLds s;
     __shared__ uint32_t block_count[4][16];            // symbols of each length in each block of 64 symbols
-    const int L = build_once(s, halved(min(a.ws.hist[256 * sec + tid], 1u << 18) + 1, k));
-    CandidateTables *out = candidate_tables(a.ws, sec);
+    uint32_t count = 0;
+#pragma unroll
+    for (int i = 0; i < kSampleChunks; ++i) count += it.sample[(sec * kSampleChunks + i) * 256 + tid];
+    const int L = build_once(s, halved(min(count, 1u << 18) + 1, k));
+    CandidateTables *out = candidate_tables(it.lut, sec);
     const int too_long = __syncthreads_or(L > kMaxLen);
     if (tid == 0) out->complete[k] = too_long ? 0 : 1;
     if (too_long) return;
@@ -234,7 +328,7 @@ __global__ __launch_bounds__(256) void build_tables_kernel(CoderBatch batch)
     out->entry[k][tid] = (uint16_t)((first + rank) | ((uint32_t)L << 12));
     // no halving is the usual pick (and the only one of an empty request); the encoder's first workgroup
     // writes the lengths of any other
-    if (k == 0) a.payload[a.off_aux + 256 * sec + tid] = (uint8_t)L;
+    if (k == 0) it.lengths[256 * sec + tid] = (uint8_t)L;
 }
 
 struct PrepareLds {
@@ -310,49 +404,23 @@ __global__ __launch_bounds__(kTableWaves * 64) void decode_prepare_kernel(CoderB
 
 // ---- launchers ----------------------------------------------------------------------------------
 
-template <int BITS, int G, int DT, bool IS_V> static int hist_launch(const CoderBatch &b, hipStream_t s)
+int launch_setup(int dtype, const SetupArgs &a, hipStream_t s)
 {
-    bool any = false;
-    for (int i = 0; i < b.n; ++i) any |= b.item[i].chunks > 0;
-    if (!any) return KVC_OK;
-    hipLaunchKernelGGL((hist_kernel<BITS, G, DT, IS_V>), dim3(16 * UnitGeom<BITS, G, DT, IS_V>::kUnits, (unsigned)b.n), dim3(64), 0, s, b);
+    long long most = 1;
+    for (int i = 0; i < a.n; ++i) {
+        const PrologueItem &it = a.item[i].prologue;
+        most = it.zero_words > most ? it.zero_words : most;
+        most = it.aux_words > most ? it.aux_words : most;
+    }
+    const dim3 grid((unsigned)a.tables * kSampleChunks + fill_slices(most), (unsigned)a.n);
+    if (dtype == DT_F16) hipLaunchKernelGGL(setup_kernel<DT_F16>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(setup_kernel<DT_BF16>, grid, dim3(256), 0, s, a);
     return launched();
 }
 
-template <int BITS, int DT, bool ISV> static int hist_g(int group, const CoderBatch &a, hipStream_t s)
+int launch_build_tables(const BuildArgs &a, hipStream_t s)
 {
-    switch (group) {
-    case 32: return hist_launch<BITS, 32, DT, ISV>(a, s);
-    case 64: return hist_launch<BITS, 64, DT, ISV>(a, s);
-    case 128: return hist_launch<BITS, 128, DT, ISV>(a, s);
-    }
-    return KVC_ERR_UNSUPPORTED;
-}
-
-template <int BITS, bool ISV> static int hist_d(int group, int dtype, const CoderBatch &a, hipStream_t s)
-{
-    return dtype == DT_F16 ? hist_g<BITS, DT_F16, ISV>(group, a, s) : hist_g<BITS, DT_BF16, ISV>(group, a, s);
-}
-
-template <bool ISV> static int hist_b(int bits, int group, int dtype, const CoderBatch &a, hipStream_t s)
-{
-    switch (bits) {
-    case 2: return hist_d<2, ISV>(group, dtype, a, s);
-    case 3: return hist_d<3, ISV>(group, dtype, a, s);
-    case 4: return hist_d<4, ISV>(group, dtype, a, s);
-    case 8: return hist_d<8, ISV>(group, dtype, a, s);
-    }
-    return KVC_ERR_UNSUPPORTED;
-}
-
-int launch_table_sample(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s)
-{
-    return b.item[0].is_v ? hist_b<true>(bits, group, dtype, b, s) : hist_b<false>(bits, group, dtype, b, s);
-}
-
-int launch_build_tables(const CoderBatch &b, hipStream_t s)
-{
-    hipLaunchKernelGGL(build_tables_kernel, dim3(b.item[0].slots * kCandidates, (unsigned)b.n), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)(a.slots * kCandidates), (unsigned)a.n), dim3(256), 0, s, a);
     return launched();
 }
 

@@ -79,22 +79,47 @@ KVC_DECLARE_QUANT(2) KVC_DECLARE_QUANT(3) KVC_DECLARE_QUANT(4) KVC_DECLARE_QUANT
 struct PrologueItem {
     uint32_t *payload;              // request payload base
     HeaderBytes header;
-    long long pad_off[2], pad_words[2];     // zero padding: byte offset inside the payload, 32-bit words
+    long long pad_off[2];           // zero padding: byte offset inside the payload, 32-bit words
+    int pad_words[2];
     const uint32_t *aux_src;        // device image of the width tables, copied to payload + aux_off
     long long aux_off, aux_words;
-    uint32_t *zero[2];              // coder scratch that starts from zero: histograms; ticket and scan state
-    long long zero_words[2];
+    uint32_t *zero;                 // coder scratch that starts from zero: ticket and scan state
+    long long zero_words;
     unsigned long long *out_bytes;  // the request's size word
     unsigned long long total;
     int write_total;                // the size is known on the host (no coder, or an empty request)
     uint32_t *dir0;                 // empty request with the coder: the directory's only entry
     int *status;
 };
-constexpr int kPrologueBatch = 12;  // requests per launch (the argument block stays below 4 KB)
+constexpr int kPrologueBatch = 16;  // requests per launch (the argument block stays below 4 KB)
 struct PrologueArgs {
     PrologueItem item[kPrologueBatch];
     int n;
 };
+static_assert(sizeof(PrologueArgs) <= 4000, "kernel arguments are limited to 4 KB");
+
+// The request's status word and header, the zero padding between the parts of the payload, the width
+// tables (copied from their device image), the coder's work-order counter and scan state, and whatever the
+// host already knows of the result (the payload size without the coder; the closed directory of an empty
+// request).  By `step` threads together, the calling one being number `first`.
+__device__ __forceinline__ void write_prologue(const PrologueItem &it, long long first, long long step)
+{
+    if (first < 32) it.payload[first] = it.header.w[first];
+    if (first == 32) *it.status = 0;
+    if (first == 33 && it.write_total) *it.out_bytes = it.total;
+    if (first == 34 && it.dir0) *it.dir0 = 0;
+    for (int k = 0; k < 2; ++k)
+        for (long long i = first; i < it.pad_words[k]; i += step) it.payload[it.pad_off[k] / 4 + i] = 0;
+    for (long long i = first; i < it.aux_words; i += step) it.payload[it.aux_off / 4 + i] = it.aux_src[i];
+    for (long long i = first; i < it.zero_words; i += step) it.zero[i] = 0;
+}
+
+// workgroups of 256 threads that share the zero fill of `words` words: 16 words per thread
+static inline unsigned fill_slices(long long words)
+{
+    const long long n = (words + 4095) / 4096;
+    return (unsigned)(n < 1 ? 1 : (n > 256 ? 256 : n));
+}
 
 // Header (and width table) check of one request before it is decompressed.
 struct CheckItem {
@@ -121,9 +146,12 @@ int launch_fill_u32(uint32_t *dst, uint32_t value, long long n, hipStream_t s);
 // (slot 4 * is_v + index of the width in 2, 3, 4, 8).
 constexpr int kTableSlots = 8;
 
+// Chunks of a tensor (of a width of a tensor) that its code table is made from.
+constexpr int kSampleChunks = 16;
+
 // Per-request scratch inside the caller's workspace (device memory).
 struct CoderScratch {
-    uint32_t *hist;             // [kTableSlots][256] sample histograms
+    uint16_t *sample;           // [slots][kSampleChunks][256] byte counts of the sample chunks
     uint16_t *lut;              // [kTableSlots][4096] decode table: symbol | length << 8; while compressing, the
                                 // candidates for the slot's code table (CandidateTables)
     unsigned long long *state;  // scan state, one word per encode workgroup (in launch order)
@@ -138,9 +166,9 @@ struct CandidateTables {
 };
 static_assert(sizeof(CandidateTables) <= 4096 * 2, "fits the slot's decode table");
 
-__device__ __forceinline__ CandidateTables *candidate_tables(const CoderScratch &ws, int slot)
+__device__ __forceinline__ CandidateTables *candidate_tables(uint16_t *lut, int slot)
 {
-    return (CandidateTables *)(ws.lut + 4096 * slot);
+    return (CandidateTables *)(lut + 4096 * slot);
 }
 
 // Chunks (= waves) per encoder workgroup.  One look-back per workgroup is the encoder's serial part,
@@ -187,8 +215,43 @@ struct CoderBatch {
 static_assert(sizeof(CoderBatch) <= 4000, "kernel arguments are limited to 4 KB");
 static_assert(sizeof(QuantBatch) <= 4000, "kernel arguments are limited to 4 KB");
 
-int launch_table_sample(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
-int launch_build_tables(const CoderBatch &b, hipStream_t s);
+// Set-up of the requests of a call that is compressed with the coder: the prologue and the table samples
+// of every request in one launch, then the code tables of all requests.
+struct SetupTable {             // a table of the plan, the same for all requests
+    const int *head_list;       // the heads it covers (null: all in their own order)
+    int heads_covered, slot, is_v, bits, group;
+    int anchor_shift;           // delta transform of this tensor (-1: none)
+    int rotate;
+};
+struct SetupItem {
+    PrologueItem prologue;
+    TensorView x;               // the request's K
+    uint16_t *v_base;           // and where V lies
+    long long tokens;
+    uint16_t *sample;           // CoderScratch::sample
+};
+constexpr int kSetupBatch = 8;  // requests per launch (the argument block stays below 4 KB)
+struct SetupArgs {
+    SetupItem item[kSetupBatch];
+    SetupTable table[kTableSlots];
+    int n, tables, heads;
+};
+static_assert(sizeof(SetupArgs) <= 4000, "kernel arguments are limited to 4 KB");
+
+struct BuildItem {
+    const uint16_t *sample;
+    uint16_t *lut;
+    uint8_t *lengths;           // the payload's code tables
+};
+constexpr int kBuildBatch = 128;
+struct BuildArgs {
+    BuildItem item[kBuildBatch];
+    int n, slots, slot_mask;
+};
+static_assert(sizeof(BuildArgs) <= 4000, "kernel arguments are limited to 4 KB");
+
+int launch_setup(int dtype, const SetupArgs &a, hipStream_t s);
+int launch_build_tables(const BuildArgs &a, hipStream_t s);
 int launch_encode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
 int launch_decode_prepare(const CoderBatch &b, hipStream_t s);
 int launch_decode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);

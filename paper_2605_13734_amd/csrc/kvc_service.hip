@@ -35,27 +35,10 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(QuantBatch batch)
 
 // ---- service kernels: everything of a call that is not a tensor pass, for all requests at once ----
 
-// Before compression: the request's status word and header, the zero padding between the parts
-// of the payload, the width tables (copied from their device image), the coder's histograms,
-// work-order counter and scan state, and whatever the host already knows of the result (the
-// payload size without the coder; the closed directory of an empty request).
-// grid = (slices, requests); the zero fills are spread over the slices.
+// Before compression without the coder (see write_prologue).  grid = (slices, requests)
 __global__ __launch_bounds__(256) void compress_prologue_kernel(PrologueArgs a)
 {
-    const PrologueItem &it = a.item[blockIdx.y];
-    const long long first = (long long)blockIdx.x * 256 + threadIdx.x, step = (long long)gridDim.x * 256;
-    if (blockIdx.x == 0) {
-        const int t = threadIdx.x;
-        if (t < 32) it.payload[t] = it.header.w[t];
-        if (t == 32) *it.status = 0;
-        if (t == 33 && it.write_total) *it.out_bytes = it.total;
-        if (t == 34 && it.dir0) *it.dir0 = 0;
-    }
-    for (int k = 0; k < 2; ++k)
-        for (long long i = first; i < it.pad_words[k]; i += step) it.payload[it.pad_off[k] / 4 + i] = 0;
-    for (long long i = first; i < it.aux_words; i += step) it.payload[it.aux_off / 4 + i] = it.aux_src[i];
-    for (int k = 0; k < 2; ++k)
-        for (long long i = first; i < it.zero_words[k]; i += step) it.zero[k][i] = 0;
+    write_prologue(a.item[blockIdx.y], (long long)blockIdx.x * 256 + threadIdx.x, (long long)gridDim.x * 256);
 }
 
 // Before decompression: the status word of every request, set to KVC_DEV_BAD_HEADER when the
@@ -107,11 +90,8 @@ int launch_decompress_tensor(int is_v, int bits, int group, int dtype, const Qua
 int launch_compress_prologue(const PrologueArgs &a, hipStream_t s)
 {
     long long most = 1;
-    for (int i = 0; i < a.n; ++i)
-        for (int k = 0; k < 2; ++k) most = a.item[i].zero_words[k] > most ? a.item[i].zero_words[k] : most;
-    long long slices = (most + 4095) / 4096;           // 16 words per thread
-    slices = slices < 1 ? 1 : (slices > 256 ? 256 : slices);
-    hipLaunchKernelGGL(compress_prologue_kernel, dim3((unsigned)slices, (unsigned)a.n), dim3(256), 0, s, a);
+    for (int i = 0; i < a.n; ++i) most = a.item[i].aux_words > most ? a.item[i].aux_words : most;
+    hipLaunchKernelGGL(compress_prologue_kernel, dim3(fill_slices(most), (unsigned)a.n), dim3(256), 0, s, a);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }
 

@@ -1,10 +1,11 @@
 """GPU parity at the edges of tiles, units and launches (run with -m gpu): payload bytes and
 reconstruction against the oracle, both bit for bit (the wire format fixes them)."""
+import numpy as np
 import pytest
 import torch
 
-from paper_2605_13734_amd import kvgen
-from test_gpu_parity import check_contiguous
+from paper_2605_13734_amd import kvc, kvgen
+from test_gpu_parity import check_contiguous, gpu_compress
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +53,31 @@ def test_code_construction(ref, kind):
     x = kvgen.make_kv(400, 1, 1, 128, T, torch.float16)
     x[0, 1, 0] = _codes_as_values(codes)
     check_contiguous(ref, x, 4, 8, 32, 32, codec=1)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bk,bv,gk,gv", [(2, 3, 32, 128), (3, 8, 64, 64), (4, 2, 128, 32), (8, 4, 128, 128)])
+@pytest.mark.parametrize("T", [1, 20, 45, 70, 100, 128 * 17 + 33])
+def test_table_sample(ref, T, bk, bv, gk, gv, dtype):
+    """Sample chunks that end inside a wave's rows, inside a K group shared by several waves, and before whole
+    waves; fewer and more chunks than the sample takes."""
+    x = kvgen.make_kv(500 + T, 1, 2, 128, T, dtype)
+    check_contiguous(ref, x, bk, bv, gk, gv, codec=1)
+    check_contiguous(ref, x, bk, bv, gk, gv, codec=1, transform=1)
+    check_contiguous(ref, x, bk, bv, gk, gv, codec=1, transform=2, anchor_period=16)
+
+
+def test_more_requests_than_a_launch_takes(ref):
+    """Set-up launches take eight requests: a call of nineteen, some of them empty."""
+    L, H = 1, 2
+    lens = [0, 5, 128, 300, 0, 77, 1, 129, 64, 256, 33, 0, 400, 31, 2, 96, 127, 200, 0]
+    plan = kvc.Plan(kvc.F16, L, H, 128, 4, 2, 32, 64, 1, max_tokens=max(lens), max_batch=len(lens))
+    xs = [kvgen.make_kv(600 + i, L, H, 128, max(T, 1), torch.float16) for i, T in enumerate(lens)]
+    xd = [x.cuda() for x in xs]
+    buf = gpu_compress(plan, [kvc.contiguous_request(x, T) for x, T in zip(xd, lens)], lens)
+    cfg = ref.config(dtype=1, layers=L, heads=H, bits_k=4, bits_v=2, group_k=32, group_v=64, codec=1)
+    for i, (x, T) in enumerate(zip(xs, lens)):
+        xu = kvgen.as_u16(x)
+        want = ref.compress(cfg, xu[0, 0], xu[0, 1], ref.contiguous_layout(H, max(T, 1), 128), T)
+        assert int(buf.status[i]) == 0
+        assert np.array_equal(buf.payload_of(i), want), i
