@@ -901,33 +901,66 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
     const int dt = plan->model.dtype;
     const Marks marks(plan, s);
     marks.at(0, 0);
-    for (int first = 0; first < n; first += kCheckBatch) {
-        CheckArgs ca;
-        memset(&ca, 0, sizeof ca);
-        ca.n = n - first < kCheckBatch ? n - first : kCheckBatch;
-        for (int j = 0; j < ca.n; ++j) {
-            const int i = first + j;
-            Geometry g;
-            geometry(plan, dst[i].tokens, &g);
-            const uint8_t *pl = (const uint8_t *)payload + payload_off[i];
-            CheckItem &it = ca.item[j];
-            it.payload = (const uint32_t *)pl;
-            make_header(plan, dst[i].tokens, g, &it.expect);
-            // words 10/11 (total), 26..31 (code sizes) depend on the data when the coder is on
-            it.mask = st.codec ? 0x03fff3ffu : 0xffffffffu;
-            if (plan->blob_bytes) {       // the payload's width tables must be the plan's
-                it.tables = pl + g.off_widths;
-                it.plan_tables = (const uint8_t *)workspace;
-                it.table_bytes = g.widths;
+    marks.window(0, n, 0);                     // (the checks of all requests come first)
+    if (st.codec) {
+        DecodeSetupArgs da;
+        memset(&da, 0, sizeof da);
+        da.mask = 0x03fff3ffu;                 // words 10/11 (total) and 26..31 (code sizes) depend on the data
+        da.slots = table_slots(plan);
+        for (int is_v = 0; is_v < 2; ++is_v)
+            for (int w = 0; w < 4; ++w) {
+                if (plan->has_table[is_v] ? plan->width_count[is_v][w] > 0 : kWidths[w] == (is_v ? st.bits_v : st.bits_k))
+                    da.slot_mask |= 1 << (da.slots == kTableSlots ? 4 * is_v + w : is_v);
             }
-            it.status = dev_status + i;
+        for (int first = 0; first < n; first += kDecodeSetupBatch) {
+            da.n = n - first < kDecodeSetupBatch ? n - first : kDecodeSetupBatch;
+            for (int j = 0; j < da.n; ++j) {
+                const int i = first + j;
+                Geometry g;
+                geometry(plan, dst[i].tokens, &g);
+                const uint8_t *pl = (const uint8_t *)payload + payload_off[i];
+                DecodeSetupItem &it = da.item[j];
+                memset(&it, 0, sizeof it);
+                it.payload = (const uint32_t *)pl;
+                make_header(plan, dst[i].tokens, g, &it.expect);
+                it.off_aux = g.off_aux;
+                if (plan->blob_bytes) {        // the payload's width tables must be the plan's
+                    it.tables = pl + g.off_widths;
+                    it.plan_tables = (const uint8_t *)workspace;
+                    it.table_bytes = g.widths;
+                }
+                it.lut = (uint16_t *)((uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request + lut_offset(plan));
+                it.status = dev_status + i;
+            }
+            KVC_TRY(launch_decode_setup(da, s));
         }
-        KVC_TRY(launch_decompress_prologue(ca, s));
+    } else {
+        for (int first = 0; first < n; first += kCheckBatch) {
+            CheckArgs ca;
+            memset(&ca, 0, sizeof ca);
+            ca.n = n - first < kCheckBatch ? n - first : kCheckBatch;
+            for (int j = 0; j < ca.n; ++j) {
+                const int i = first + j;
+                Geometry g;
+                geometry(plan, dst[i].tokens, &g);
+                const uint8_t *pl = (const uint8_t *)payload + payload_off[i];
+                CheckItem &it = ca.item[j];
+                it.payload = (const uint32_t *)pl;
+                make_header(plan, dst[i].tokens, g, &it.expect);
+                it.mask = 0xffffffffu;
+                if (plan->blob_bytes) {        // the payload's width tables must be the plan's
+                    it.tables = pl + g.off_widths;
+                    it.plan_tables = (const uint8_t *)workspace;
+                    it.table_bytes = g.widths;
+                }
+                it.status = dev_status + i;
+            }
+            KVC_TRY(launch_decompress_prologue(ca, s));
+        }
     }
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
-        marks.window(first, end, 0);
         if (!st.codec) {
             marks.window(first, end, 1);
             KVC_TRY(launch_tensor(plan, 0, false, quant_batch(plan, dst, first, end, lead, 0, const_cast<void *>(payload), payload_off, dev_status, false),
@@ -948,7 +981,6 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                           (long long)(payload_off[i + 1] - payload_off[i]), nullptr, dev_status + i, false,
                                           (const uint8_t *)workspace, cl[k]);
             }
-            KVC_TRY(launch_decode_prepare(coder_batch(cl, end - first, 0), s));
             marks.window(first, end, 1);
             for (int j = 0; j < launches; ++j)
                 if (!cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));

@@ -285,8 +285,6 @@ static_assert(kWeightBits >= 19 && (1 << 18) + 256 < (1 << kWeightBits), "sample
 
 __device__ __forceinline__ uint32_t halved(uint32_t w, int k) { return (w + ((1u << k) - 1u)) >> k; }
 
-constexpr int kTableWaves = 8;      // waves that fill a decode table
-
 // grid = kCandidates workgroups of 256 threads (one symbol each) per table slot of the format.
 __global__ __launch_bounds__(256) void build_tables_kernel(BuildArgs a)
 {
@@ -331,75 +329,80 @@ __global__ __launch_bounds__(256) void build_tables_kernel(BuildArgs a)
     if (k == 0) it.lengths[256 * sec + tid] = (uint8_t)L;
 }
 
-struct PrepareLds {
-    uint32_t count[16], first[16], start[16];
-    uint16_t by_len[256];          // symbols by (length, symbol)
-};
+// ---- set-up of a decompress call with the coder ---------------------------------------------------
 
-// grid = one workgroup of kTableWaves waves per table slot: decode tables from the lengths stored in the payload
-__global__ __launch_bounds__(kTableWaves * 64) void decode_prepare_kernel(CoderBatch batch)
+// grid = (table slots, requests), 512 threads: every workgroup turns the code lengths of its slot into the
+// decode table (entry i describes the code word that is a prefix of the 12-bit string i); the first one
+// also compares the header and the width tables with the plan's, checks the lengths of all slots (a
+// complete prefix code each) and sets the request's status word.  It stays at one launch because
+// nothing waits for the check here: a table is only used by kernels that look at the status first.
+// (A header check and a table launch with one workgroup per slot that searched the lengths one by one: 4.6 + 13 us.)
+__global__ __launch_bounds__(512) void decode_setup_kernel(DecodeSetupArgs a)
 {
-    const CoderArgs &a = batch.item[blockIdx.y];
-    if (!((a.slot_mask >> blockIdx.x) & 1)) return;
-    __shared__ PrepareLds s;
-    __shared__ uint32_t block_count[4][16];            // symbols of each length in each block of 64 symbols
-    __shared__ int s_ok;
+    const DecodeSetupItem &it = a.item[blockIdx.y];
+    __shared__ __attribute__((aligned(16))) uint32_t block_count[16][4];     // symbols of each length in each block of 64 symbols
+    __shared__ uint32_t kraft[kTableSlots];
+    __shared__ int base[16];                           // from a left-aligned code of a length to its symbol's place
+    __shared__ uint16_t by_len[256];                   // symbols by (length, symbol)
     const int sec = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
-    if (*a.q.status & KVC_DEV_BAD_HEADER) return;
+    if (sec > 0 && !((a.slot_mask >> sec) & 1)) return;
+    const uint8_t *lengths = (const uint8_t *)it.payload + it.off_aux;
+    const int mylen = tid < 256 ? lengths[256 * sec + tid] : 0;
+    if (sec == 0) {
+        if (tid < kTableSlots) kraft[tid] = 0;
+        int diff = tid < 32 && ((a.mask >> tid) & 1u) && it.payload[tid] != it.expect.w[tid];
+        for (long long i = tid; i < it.table_bytes; i += 512) diff |= it.tables[i] != it.plan_tables[i];
+        diff = __syncthreads_or(diff);
+        for (int q = tid >> 8; q < a.slots; q += 2) {
+            if (!((a.slot_mask >> q) & 1)) continue;
+            const uint32_t l = lengths[256 * q + (tid & 255)];
+            atomicAdd(&kraft[q], l >= 1 && l <= (uint32_t)kMaxLen ? 1u << (kMaxLen - l) : 1u << 20);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            bool complete = true;
+            for (int q = 0; q < a.slots; ++q) complete &= !((a.slot_mask >> q) & 1) || kraft[q] == 1u << kMaxLen;
+            *it.status = diff ? KVC_DEV_BAD_HEADER : complete ? 0 : KVC_DEV_BAD_TABLE;
+        }
+        if (!((a.slot_mask >> sec) & 1)) return;
+    }
     // canonical order: the first four waves hold one symbol per thread
-    int mylen = 0, within = 0;
+    int within = 0;
     if (tid < 256) {
-        mylen = a.payload[a.off_aux + 256 * sec + tid];
 #pragma unroll
         for (int l = 1; l <= kMaxLen; ++l) {
             const unsigned long long same = __builtin_amdgcn_ballot_w64(mylen == l);
-            if (lane == 0) block_count[wave][l] = (uint32_t)__builtin_popcountll(same);
+            if (lane == 0) block_count[l][wave] = (uint32_t)__builtin_popcountll(same);
             if (mylen == l) within = __builtin_popcountll(same & ((1ull << lane) - 1));
         }
-        const bool in_range = mylen >= 1 && mylen <= kMaxLen;
-        if (lane == 0) block_count[wave][0] = __builtin_amdgcn_ballot_w64(!in_range) != 0 ? 1u : 0u;
     }
     __syncthreads();
-    if (tid == 0) {
-        uint32_t next = 0, at = 0, kraft = 0;
-        for (int l = 1; l <= kMaxLen; ++l) {
-            const uint32_t n = block_count[0][l] + block_count[1][l] + block_count[2][l] + block_count[3][l];
-            s.count[l] = n;
-            s.first[l] = next;
-            s.start[l] = at;
-            next = (next + n) << 1;
-            at += n;
-            kraft += n << (kMaxLen - l);
-        }
-        const bool bad_len = (block_count[0][0] | block_count[1][0] | block_count[2][0] | block_count[3][0]) != 0;
-        const bool ok = !bad_len && kraft == (1u << kMaxLen);          // a complete prefix code
-        s_ok = ok ? 1 : 0;
-        if (!ok) atomicOr(a.q.status, KVC_DEV_BAD_TABLE);
+    uint32_t limit[kMaxLen + 1];                       // end of the codes of a length, left aligned
+    uint32_t first = 0, at = 0, mine = 0;
+#pragma unroll
+    for (int l = 1; l <= kMaxLen; ++l) {
+        const u32x4 c = *(const u32x4 *)block_count[l];
+        const uint32_t n = c[0] + c[1] + c[2] + c[3];
+        if (mylen == l) mine = at + (wave > 0 ? c[0] : 0) + (wave > 1 ? c[1] : 0) + (wave > 2 ? c[2] : 0);
+        if (tid == 0) base[l] = (int)at - (int)first;
+        limit[l] = (first + n) << (kMaxLen - l);
+        first = (first + n) << 1;
+        at += n;
     }
+    // (lengths that are no complete code leave a table that nothing uses; every index stays in range)
+    if (tid < 256 && mylen >= 1 && mylen <= kMaxLen) by_len[(mine + within) & 255u] = (uint16_t)tid;
     __syncthreads();
-    if (s_ok && tid < 256) {
-        uint32_t rank = (uint32_t)within;
-        for (int w = 0; w < wave; ++w) rank += block_count[w][mylen];
-        s.by_len[s.start[mylen] + rank] = (uint16_t)tid;                    // symbols by (length, symbol)
+    u32x4 out;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t i = (uint32_t)tid * 8 + k;
+        int L = 1;
+#pragma unroll
+        for (int l = 1; l < kMaxLen; ++l) L += i >= limit[l] ? 1 : 0;
+        const uint32_t e = by_len[((int)(i >> (kMaxLen - L)) + base[L]) & 255] | ((uint32_t)L << 8);
+        out[k >> 1] = (k & 1) ? out[k >> 1] | (e << 16) : e;
     }
-    __syncthreads();
-    uint16_t *lut = a.ws.lut + 4096 * sec;
-    if (!s_ok) {
-        for (int i = tid; i < 4096; i += kTableWaves * 64) lut[i] = (uint16_t)(1u << 8);      // symbol 0, length 1
-        return;
-    }
-    // entry i describes the code word that is a prefix of the 12-bit string i
-    for (int i = tid; i < 4096; i += kTableWaves * 64) {
-        uint16_t e = (uint16_t)(1u << 8);
-        for (int L = 1; L <= kMaxLen; ++L) {
-            const uint32_t c = (uint32_t)i >> (kMaxLen - L);
-            if (c >= s.first[L] && c - s.first[L] < s.count[L]) {
-                e = (uint16_t)(s.by_len[s.start[L] + c - s.first[L]] | (L << 8));
-                break;
-            }
-        }
-        lut[i] = e;
-    }
+    ((u32x4 *)(it.lut + 4096 * sec))[tid] = out;
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
@@ -424,9 +427,9 @@ int launch_build_tables(const BuildArgs &a, hipStream_t s)
     return launched();
 }
 
-int launch_decode_prepare(const CoderBatch &b, hipStream_t s)
+int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(decode_prepare_kernel, dim3(b.item[0].slots, (unsigned)b.n), dim3(kTableWaves * 64), 0, s, b);
+    hipLaunchKernelGGL(decode_setup_kernel, dim3((unsigned)a.slots, (unsigned)a.n), dim3(512), 0, s, a);
     return launched();
 }
 

@@ -250,10 +250,28 @@ struct BuildArgs {
 };
 static_assert(sizeof(BuildArgs) <= 4000, "kernel arguments are limited to 4 KB");
 
+// Set-up of the requests of a call that is decompressed with the coder (see decode_setup_kernel).
+struct DecodeSetupItem {
+    const uint32_t *payload;
+    HeaderBytes expect;
+    long long off_aux;                      // the code tables' lengths inside the payload
+    const uint8_t *tables, *plan_tables;    // width tables in the payload and their device image
+    long long table_bytes;
+    uint16_t *lut;
+    int *status;
+};
+constexpr int kDecodeSetupBatch = 20;
+struct DecodeSetupArgs {
+    DecodeSetupItem item[kDecodeSetupBatch];
+    uint32_t mask;                          // bit i = compare header word i
+    int n, slots, slot_mask;
+};
+static_assert(sizeof(DecodeSetupArgs) <= 4000, "kernel arguments are limited to 4 KB");
+
 int launch_setup(int dtype, const SetupArgs &a, hipStream_t s);
 int launch_build_tables(const BuildArgs &a, hipStream_t s);
 int launch_encode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
-int launch_decode_prepare(const CoderBatch &b, hipStream_t s);
+int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s);
 int launch_decode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
 // one translation unit per code width (kvc_huff_enc.hip / kvc_huff_dec.hip compiled with -DKVC_BITS=...)
 #define KVC_DECLARE_CODER(B)                                                                  \

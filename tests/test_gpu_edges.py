@@ -81,3 +81,33 @@ def test_more_requests_than_a_launch_takes(ref):
         want = ref.compress(cfg, xu[0, 0], xu[0, 1], ref.contiguous_layout(H, max(T, 1), 128), T)
         assert int(buf.status[i]) == 0
         assert np.array_equal(buf.payload_of(i), want), i
+
+
+@pytest.mark.parametrize("widths", [False, True])
+def test_decode_setup_of_many_requests(ref, widths):
+    """Set-up launches of the decoder take twenty requests; a damaged header, K table and V table each mark their
+    own request and leave the others alone."""
+    L, H = 1, 2
+    lens = [33 + 7 * i for i in range(22)]
+    kw = dict(bits_k=0, bits_v=0, head_bits_k=[4, 2], head_bits_v=[8, 3]) if widths else dict(bits_k=4, bits_v=2)
+    plan = kvc.Plan(kvc.F16, L, H, 128, group_k=32, group_v=64, codec=1, max_tokens=max(lens), max_batch=len(lens), **kw)
+    xs = [kvgen.make_kv(700 + i, L, H, 128, T, torch.float16, "cuda") for i, T in enumerate(lens)]
+    buf = gpu_compress(plan, [kvc.contiguous_request(x) for x in xs], lens)
+    want = [torch.empty_like(x) for x in xs]
+    s = torch.cuda.current_stream().cuda_stream
+    buf.decompress([kvc.contiguous_request(y) for y in want], s)
+    torch.cuda.synchronize()
+    assert buf.status.tolist() == [0] * len(lens)
+    # K table of slot 0 and V table of slot 1 (eight slots with width tables: K width 4 is slot 2, V width 3 slot 5)
+    slots = {4: 2 if widths else 0, 21: 5 if widths else 1}
+    aux = {i: int.from_bytes(buf.payload_of(i)[80:88].tobytes(), "little") for i in slots}
+    buf.payload[buf.offsets[2] + 32] += 1                                     # the token count in a header
+    for i, slot in slots.items():
+        buf.payload[buf.offsets[i] + aux[i] + 256 * slot + 9] = 13 if i == 4 else 1      # too long; no prefix code
+    ys = [torch.full_like(x, 3.0) for x in xs]
+    buf.decompress([kvc.contiguous_request(y) for y in ys], s)
+    torch.cuda.synchronize()
+    for i, y in enumerate(ys):
+        bad = kvc.DEV_BAD_HEADER if i == 2 else kvc.DEV_BAD_TABLE if i in slots else 0
+        assert int(buf.status[i]) == bad, i
+        assert torch.equal(y, torch.full_like(y, 3.0) if bad else want[i]), i
