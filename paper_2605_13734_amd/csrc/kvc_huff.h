@@ -9,7 +9,7 @@
 //
 // One wave owns one chunk: it quantizes the chunk into LDS, every lane then codes one
 // sub-block, and the body is copied to its final place, which comes from a single-pass
-// prefix sum over workgroups (ticket order + look-back on a state word per workgroup).
+// prefix sum over workgroups (ticket order, a state word per workgroup, one scanning wave).
 // Decoding mirrors it: body -> LDS, every lane decodes one sub-block with a 4096-entry
 // table, the packed rows are rebuilt in LDS and dequantized from there.
 //
@@ -23,12 +23,12 @@
 
 namespace kvc {
 
-// Scan state of a workgroup: bits 63:62 = 2 once its inclusive prefix (bits 0..39) is known.
-// Before that, every wave adds its chunk's size to bits 0..39 and its share of kAggComplete to
-// the arrival count in bits 40..47; the sum of sizes is the workgroup's aggregate once the
-// count is complete.  Sizes and prefixes are in 16-byte units.
-constexpr unsigned long long kFlagPrefix = 2ull << 62, kValueMask = (1ull << 40) - 1;
-constexpr int kAggShift = 40, kAggComplete = 8;
+// Scan state of an encode workgroup: 0, then (bits 63:62 = 1) the sum of its chunks' sizes, then (2) the
+// sum of all sizes before it, both in 16-byte units.
+constexpr unsigned long long kFlagSize = 1ull << 62, kFlagPrefix = 2ull << 62, kValueMask = (1ull << 40) - 1;
+constexpr unsigned long long kNoPlace = kValueMask;      // (a scan that gave up)
+constexpr int kScanWindows = 4;
+constexpr int kScanCarry = 4;      // word of the ticket's block where the scan of one launch leaves its end to the next
 constexpr int kSpinLimit = 1 << 20;
 
 template <int BITS> struct ChunkGeom {

@@ -97,36 +97,103 @@ template <int W> __device__ __forceinline__ void encode_two(const uint32_t *sym,
 }
 
 // One workgroup = kWaves chunks.  A chunk's body offset is the sum of all earlier bodies of the
-// request (K chunks first, then V): a single-pass scan over one state word per workgroup.
-// Workgroups take a ticket from a counter; wave 0 publishes the workgroup's total size, looks
-// back over earlier tickets until it meets one that knows its inclusive prefix, and publishes
-// its own.  Ticket order guarantees that every predecessor is already running, so the wait
-// always ends; it is bounded by kSpinLimit all the same.
-// Waves per SIMD the register allocation must leave room for: four where the workgroup has 512
-// threads (see enc_waves); the other variants would spill, so they keep what they need.
-template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF> constexpr int enc_min_waves()
+// request (K chunks first, then V): a single-pass scan over one state word per workgroup, made by one
+// wave per request, the scanner.  Workgroups take a ticket from a counter; as soon as the sizes of its
+// chunks are known, before a code word is written, a workgroup leaves their sum in its state word; the
+// scanner walks the words in ticket order and puts the prefix in their place; the waves of the
+// workgroup, by then mostly done with the code words, pick it up.  The scanners are the first
+// workgroups of the grid, and ticket order guarantees that every predecessor of a workgroup is already
+// running, so the waits always end; they are bounded by kSpinLimit all the same.
+// (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
+// hundreds of waves polling the same lines of memory.  70B shape, half of its layers, compress call: 1369 us
+// with eight chunks per workgroup, now 1213; 2-bit codes / groups of 128 1370 -> 1135, 8 bits (a quarter of
+// the layers) 1235 -> 1058.  With the bodies at fixed places, nothing to wait for, 1165.)
+
+// The scan of one request's launch; the last launch's scanner closes the directory and the header.
+template <int NW, bool IS_V> __device__ __forceinline__ void scan_sizes(const CoderArgs &a)
 {
-    return enc_waves(BITS, G, DT, DENSE, IS_V, XF) == 8 ? 4 : 1;
+    if (a.chunks <= 0) return;                      // an empty request: its directory and header are closed already
+    const int lane = lane_id();
+    unsigned long long *carry = (unsigned long long *)(a.ws.ticket + kScanCarry);      // units before this launch; units of K
+    unsigned long long prefix = carry[0];
+    const long long end = a.wg_base + (a.chunks + NW - 1) / NW;
+    int spins = 0;
+    __builtin_amdgcn_s_setprio(3);
+    // kScanWindows windows of 64 workgroups per look (a look is a round trip to memory, and the scanner has to
+    // keep up with all workgroups of the chip)
+    for (long long next = a.wg_base; next < end;) {
+        unsigned long long v[kScanWindows];
+#pragma unroll
+        for (int k = 0; k < kScanWindows; ++k) {
+            const long long j = next + 64 * k + lane;
+            v[k] = j < end ? __hip_atomic_load(&a.ws.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        }
+        bool moved = false, open = true;
+        const long long base = next;
+#pragma unroll
+        for (int k = 0; k < kScanWindows; ++k) {
+            if (!open) continue;
+            const unsigned long long known = __builtin_amdgcn_ballot_w64((v[k] >> 62) == 1);
+            const int run = known == ~0ull ? 64 : __builtin_ctzll(~known);      // workgroups that have reported, up to the first gap
+            open = run == 64;
+            if (run == 0) continue;
+            const uint32_t size = lane < run ? (uint32_t)v[k] : 0;               // (a workgroup's bodies are at most 8 * 1024 units)
+            const uint32_t incl = wave_inclusive_sum(size);
+            if (lane < run)
+                __hip_atomic_store(&a.ws.state[base + 64 * k + lane], kFlagPrefix | (prefix + incl - size), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            prefix += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            next += run;
+            moved = true;
+        }
+        if (moved) spins = 0;
+        else if (++spins > kSpinLimit) {
+            if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
+            return;
+        }
+    }
+    if (lane != 0) return;
+    const unsigned long long k_units = IS_V ? carry[1] : prefix;
+    carry[0] = prefix;
+    carry[1] = k_units;
+    if (end != a.total_wgs) return;
+    ((uint32_t *)(a.payload + a.off_dir))[a.total_chunks] = (uint32_t)prefix;
+    const unsigned long long total = (unsigned long long)a.off_bodies + prefix * 16;
+    unsigned long long *h = (unsigned long long *)a.payload;
+    h[5] = total;                                   // byte 40: total bytes
+    h[13] = k_units * 16;                           // byte 104: K code bytes
+    h[14] = (unsigned long long)a.off_bodies + k_units * 16;   // byte 112: V code offset
+    h[15] = (prefix - k_units) * 16;                // byte 120: V code bytes
+    *a.out_bytes = total;
 }
 
 template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF>
-__global__ __launch_bounds__(enc_waves(BITS, G, DT, DENSE, IS_V, XF) * 64)
-__attribute__((amdgpu_waves_per_eu(enc_min_waves<BITS, G, DT, IS_V, DENSE, XF>())))
+__global__ __launch_bounds__(enc_waves(BITS) * 64)
+__attribute__((amdgpu_waves_per_eu(enc_min_waves(BITS, G, DT, DENSE, IS_V, XF))))
 void encode_kernel(CoderBatch batch)
 {
     using Geo = ChunkGeom<BITS>;
-    constexpr int W = Geo::kWords, NW = enc_waves(BITS, G, DT, DENSE, IS_V, XF);
+    constexpr int W = Geo::kWords, NW = enc_waves(BITS);
+    if (blockIdx.x < batch.start[0]) {                           // the scanners come first, one wave per request
+        const int item = (int)blockIdx.x * NW + wave_id();
+        if (item < batch.n) scan_sizes<NW, IS_V>(batch.item[item]);
+        return;
+    }
     unsigned wg;
     const CoderArgs &a = batch.item[batch_item(batch, wg)];      // (which of them it is among the item's workgroups does not matter: the chunk comes from the ticket)
     (void)wg;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Geo::kLds];
     __shared__ EncTables enc;
     __shared__ uint32_t s_units[NW];
+    __shared__ uint32_t s_ticket, s_sum, s_reported;
     __shared__ unsigned long long s_excl;
-    __shared__ uint32_t s_ticket;
 
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
-    if (tid == 0) s_ticket = atomicAdd(a.ws.ticket, 1u);
+    if (tid == 0) {
+        s_ticket = atomicAdd(a.ws.ticket, 1u);
+        s_sum = s_reported = 0;
+        s_excl = 0;
+    }
     // the candidate with the fewest halvings that meets the length limit (two short loads one after the
     // other, in the time the ticket takes)
     const CandidateTables *tables = candidate_tables(a.ws.lut, a.tab);
@@ -146,6 +213,19 @@ void encode_kernel(CoderBatch batch)
     if (pick != 0 && ticket == a.wg_base)
         for (int k = tid; k < 256; k += NW * 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
 
+    // the wave's chunk size is known; the last wave of the workgroup to say so passes the sum on
+    int last_to_report = 0;
+    auto report_size = [&](uint32_t units) {
+        if (lane != 0) return;
+        s_units[wave] = units;
+        atomicAdd(&s_sum, units);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (atomicAdd(&s_reported, 1u) != (uint32_t)NW - 1) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const uint32_t sum = *(volatile uint32_t *)&s_sum;
+        last_to_report = 1;
+        __hip_atomic_store(&a.ws.state[ticket], kFlagSize | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     uint32_t body_units = 0;      // body size in 16-byte units
     bool coded = false;
     int rows = 0;
@@ -169,11 +249,8 @@ void encode_kernel(CoderBatch batch)
         const uint32_t coded_bytes = (2 * kSubs + 4 * ((total + 31) / 32) + 15) & ~15u;
         coded = coded_bytes < raw_bytes;
         body_units = (coded ? coded_bytes : raw_bytes) / 16;
-        // the size goes out before the code words are written, so that successors see this
-        // workgroup's aggregate as early as possible
-        if (lane == 0)
-            __hip_atomic_fetch_add(&a.ws.state[ticket], ((unsigned long long)(kAggComplete / NW) << kAggShift) | body_units,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the size goes out before the code words are written
+        report_size(body_units);
         if (coded) {
             wave_sync();                                          // every lane holds its symbols
             u32x4 zero = {0, 0, 0, 0};
@@ -198,82 +275,39 @@ void encode_kernel(CoderBatch batch)
             wave_sync();
         }
     }
-    if (!live && lane == 0)
-        __hip_atomic_fetch_add(&a.ws.state[ticket], (unsigned long long)(kAggComplete / NW) << kAggShift, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    if (lane == 0) s_units[wave] = body_units;
-    __syncthreads();
-
-    // ---- single-pass prefix sum over workgroups, in ticket order ------------------------------
-    if (wave == 0) {
-        unsigned long long agg = 0;
-        for (int w = 0; w < NW; ++w) agg += s_units[w];
-        unsigned long long excl = 0;
-        bool timeout = false;
-        if (ticket > 0) {
-            long long idx = ticket - 1;
-            int spins = 0;
-            for (;;) {
-                const long long j = idx - lane;
-                unsigned long long v = kFlagPrefix;
-                if (j >= 0) v = __hip_atomic_load(&a.ws.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // 2: inclusive prefix, 1: complete aggregate, 0: not all waves have reported yet
-                const unsigned flag = (v >> 62) == 2 ? 2u : ((unsigned)(v >> kAggShift) & 0xffu) == (unsigned)kAggComplete ? 1u : 0u;
-                if (__builtin_amdgcn_ballot_w64(flag == 0) != 0) {
-                    if (++spins > kSpinLimit) { timeout = true; break; }
-                    __builtin_amdgcn_s_sleep(8);
-                    continue;
-                }
-                const unsigned long long pm = __builtin_amdgcn_ballot_w64(flag == 2);
-                const int stop = pm ? __builtin_ctzll(pm) : 63;      // nearest predecessor with a full prefix
-                unsigned long long part = (lane <= stop) ? (v & kValueMask) : 0;
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ d) << 2, (int)(uint32_t)part);
-                    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ d) << 2, (int)(uint32_t)(part >> 32));
-                    part += ((unsigned long long)hi << 32) | lo;
-                }
-                excl += part;
-                if (pm) break;
-                idx -= 64;
+    if (!live) report_size(0);
+    // The workgroup's prefix, left in its state word by the scanner once all its waves have reported.  The wave
+    // that reported last polls for it, the others wait at an LDS word: four thousand waves polling memory would
+    // slow the scanner down.
+    unsigned long long excl;
+    int spins = 0;
+    if (__builtin_amdgcn_readfirstlane(last_to_report)) {
+        while (((excl = __hip_atomic_load(&a.ws.state[ticket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 62) != 2) {
+            if (++spins > kSpinLimit) {
+                if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
+                excl = kFlagPrefix | kNoPlace;
+                break;
             }
+            __builtin_amdgcn_s_sleep(1);
         }
-        if (timeout) {
-            excl = 0;
-            if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
-        }
-        if (lane == 0) {
-            __hip_atomic_store(&a.ws.state[ticket], kFlagPrefix | ((excl + agg) & kValueMask), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            s_excl = timeout ? ~0ull : excl;
-            if (ticket == a.total_wgs - 1 && !timeout) {
-                // the very last workgroup closes the directory and the header
-                const unsigned long long all = excl + agg;
-                uint32_t *dir = (uint32_t *)(a.payload + a.off_dir);
-                dir[a.total_chunks] = (uint32_t)all;
-                unsigned long long k_units = all;          // (this is the last K workgroup only if V has no chunks)
-                if (IS_V)
-                    k_units = a.k_wgs > 0 ? __hip_atomic_load(&a.ws.state[a.k_wgs - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kValueMask : 0;
-                const unsigned long long total = (unsigned long long)a.off_bodies + all * 16;
-                unsigned long long *h = (unsigned long long *)a.payload;
-                h[5] = total;                                   // byte 40: total bytes
-                h[13] = k_units * 16;                           // byte 104: K code bytes
-                h[14] = (unsigned long long)a.off_bodies + k_units * 16;   // byte 112: V code offset
-                h[15] = (all - k_units) * 16;                   // byte 120: V code bytes
-                *a.out_bytes = total;
-            }
-        }
+        if (lane == 0) __hip_atomic_store(&s_excl, excl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+        // (the polling wave always ends: it finds the prefix or its spin limit)
+        while (((excl = __hip_atomic_load(&s_excl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) >> 62) != 2) __builtin_amdgcn_s_sleep(1);
     }
-    __syncthreads();
-    const unsigned long long excl = s_excl;
-    if (!live || excl == ~0ull) return;
+    excl &= kValueMask;
+    if (excl == kNoPlace || !live) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // (the sizes of the other waves are older than the prefix)
     unsigned long long mine = excl;
     for (int w = 0; w < wave; ++w) mine += s_units[w];
     if (lane == 0) ((uint32_t *)(a.payload + a.off_dir))[a.chunk_base + chunk] = (uint32_t)mine;
     uint8_t *dst = a.payload + a.off_bodies + mine * 16;
     if ((long long)(a.off_bodies + (mine + body_units) * 16) > a.capacity) return;      // cannot happen: bodies never exceed raw size
     if (coded) {
-        for (uint32_t o = lane * 16; o < body_units * 16; o += 64 * 16) __builtin_nontemporal_store(*(const u32x4 *)(lds + o), (u32x4 *)(dst + o));
+        // (every store instruction covers whole lines of memory, but for the body's ends)
+        const int skew = (int)((uintptr_t)dst & 127);
+        for (int o = lane * 16 - skew; o < (int)(body_units * 16); o += 64 * 16)
+            if (o >= 0) __builtin_nontemporal_store(*(const u32x4 *)(lds + o), (u32x4 *)(dst + o));
     } else {
         // raw chunk: each lane still holds its sub-block (2 rows) in registers
         const int have = min(max(rows - 2 * lane, 0), 2);
@@ -293,15 +327,16 @@ void encode_kernel(CoderBatch batch)
 template <int BITS, int G, int DT, bool IS_V> static int encode_launch(const CoderBatch &b, hipStream_t s)
 {
     const CoderArgs &a = b.item[0];
-    const int NW = enc_waves(BITS, G, DT, a.q.dense != 0, IS_V, a.q.rotate || a.q.anchors != nullptr);
+    constexpr int NW = enc_waves(BITS);
     CoderBatch placed = b;
-    unsigned need = 0;
+    const unsigned scanners = (unsigned)((b.n + NW - 1) / NW);
+    unsigned need = scanners;
     for (int i = 0; i < b.n; ++i) {
         placed.start[i] = need;
         need += (unsigned)((b.item[i].chunks + NW - 1) / NW);
     }
     placed.start[b.n] = need;
-    if (need == 0) return KVC_OK;
+    if (need == scanners) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
     // K token blocks of 64 and 128 rows, and V groups of 32 channels (the variant that is short of
     // registers), have a kernel of their own for launches without a transform

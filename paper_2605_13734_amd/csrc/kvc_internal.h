@@ -171,13 +171,19 @@ __device__ __forceinline__ CandidateTables *candidate_tables(uint16_t *lut, int 
     return (CandidateTables *)(lut + 4096 * slot);
 }
 
-// Chunks (= waves) per encoder workgroup.  One look-back per workgroup is the encoder's serial part,
-// so the variants whose registers allow 512 threads (2- to 4-bit codes, groups of 32, the dense
-// layout; not the V kernels with the transforms for bf16 rows or 3-bit codes) take eight chunks per workgroup; 8-bit
-// chunks need twice the LDS and take two.  `transform`: the launch applies stage T.
-constexpr int enc_waves(int bits, int group, int dtype, bool dense, bool is_v, bool transform)
+// Chunks (= waves) per encoder workgroup, 8-bit chunks with twice the LDS: two.
+// A workgroup reports its sizes when its slowest wave knows its own, so fewer chunks wait less for
+// each other, and every workgroup costs a ticket and a state word (70B shape, 4 bits, half of the layers:
+// eight 1325 us, four 1226, two 1600).
+constexpr int enc_waves(int bits) { return bits == 8 ? 2 : 4; }
+
+// Waves per SIMD the register allocation must leave room for: the variants that come close to 128 registers
+// by themselves (2- to 4-bit codes, groups of 32, the dense layout; not the V kernels with the transforms for
+// bf16 rows or 3-bit codes) are held to four; the others would spill, so they keep what they need.
+// `transform`: the launch applies stage T.
+constexpr int enc_min_waves(int bits, int group, int dtype, bool dense, bool is_v, bool transform)
 {
-    return bits == 8 ? 2 : (group == 32 && dense && !(is_v && transform && (dtype == DT_BF16 || bits == 3))) ? 8 : 4;
+    return bits != 8 && group == 32 && dense && !(is_v && transform && (dtype == DT_BF16 || bits == 3)) ? 4 : 1;
 }
 
 // One launch of the coder: a tensor, or with per-head widths the heads of one width of a tensor
