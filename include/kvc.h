@@ -251,7 +251,9 @@ int kvc_check_block_table(const int32_t *table, int64_t entries, int32_t num_phy
  * that plan records, per request and on the call's stream, four events: before the set-up work
  * (for the first request of a call: before anything the call enqueues), before the K pass,
  * between the K and V passes, and after the V pass (short requests of one call share their launches
- * and then share these moments).  Returns the number of events recorded since the previous call;
+ * and then share these moments, and with the coder a request below 2^23 token rows per tensor may have
+ * its K and V passes in one launch, after which the last two events are recorded together).  The set-up
+ * of all requests of a call comes before the first K pass.  Returns the number of events recorded since the previous call;
  * NULL uninstalls.  The state lives in the plan.
  */
 int kvc_trace(kvc_plan_t *plan, void **hip_events, int32_t capacity);

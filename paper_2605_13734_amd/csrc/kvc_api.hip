@@ -506,10 +506,11 @@ static int launch_tensor(const kvc_plan_t *p, int is_v, bool compress, QuantBatc
 // have no work in any launch and fit every window.
 static bool dense_layout(const kvc_request *r) { return !r->block_table && r->stride_token == kDim; }
 
+static const long long kSmallRows = 1ll << 21;           // token rows per tensor: 64 Ki work units of 32 rows
+
 static int request_window(const kvc_plan_t *p, const kvc_request *reqs, int n, int first, int limit, int *lead)
 {
     const long long heads = (long long)p->model.layers * p->model.kv_heads;
-    const long long kSmallRows = 1ll << 21;              // token rows per tensor: 64 Ki work units of 32 rows
     int end = first, leader = -1;
     while (end < n && end - first < limit) {
         if (reqs[end].tokens > 0) {
@@ -566,6 +567,48 @@ struct CoderLaunch {
     int bits, group;
 };
 
+// Whether K and V of a request share a launch with the coder: one width and one group for both, no
+// transform (the kernels for both tensors exist for that), and a request that leaves the chip idle between
+// the two passes -- 2^18 rows per tensor are two chunks per SIMD where four fit.  One layer of 32k tokens
+// and 8 heads: encoding 56 us in two launches, 45 in one, decoding 50 and 37; 2^21 rows (bf16): compress call
+// 346 and 303 us.  Requests of 2^23 rows and more gain 2 % and keep their passes apart.  For groups of 64
+// and 128 the K kernels need more registers than the V kernels, and one kernel for both gives V
+// the occupancy of K (70B shape, 2 bits, groups of 128, half of the layers: 1148 and 1275 us), so only small
+// requests share.
+static bool tensors_share(const kvc_plan_t *p)
+{
+    const kvc_strategy &st = p->strat;
+    return !p->has_table[0] && !p->has_table[1] && st.bits_k == st.bits_v && st.group_k == st.group_v && st.transform == KVC_T_NONE;
+}
+
+static bool share_kv(const kvc_plan_t *p, const kvc_request *lead)
+{
+    const long long rows = (long long)p->model.layers * p->model.kv_heads * lead->tokens;
+    return tensors_share(p) && rows < (p->strat.group_k == 32 ? 4 * kSmallRows : kSmallRows);
+}
+
+// Chunks per workgroup of such an encoder launch (0: the usual number): eight where all chunks of the window
+// are resident at once and the usual number would queue for more than 256 tickets, which are one after the
+// other (one layer as above: 74 us per call with four, 69 with eight); with more work the tickets hide
+// behind other workgroups and four wait less for each other (enc_waves).
+static int shared_waves(const kvc_plan_t *p, const kvc_request *reqs, int first, int end)
+{
+    if (p->strat.group_k != 32 || p->strat.bits_k == 8) return 0;
+    long long chunks = 0;
+    for (int i = first; i < end; ++i) chunks += 2ll * p->model.layers * p->model.kv_heads * chunks_per_head(reqs[i].tokens);
+    return chunks > 1024 && chunks <= 4096 ? 8 : 0;
+}
+
+// K and V of the first n requests of a window as one batch
+static CoderBatch coder_batch_both(const CoderLaunch cl[][kTableSlots], int n)
+{
+    CoderBatch b;
+    memset(&b, 0, sizeof b);
+    for (int k = 0; k < 2 * n; ++k) b.item[k] = cl[k / 2][k & 1].a;
+    b.n = 2 * n;
+    return b;
+}
+
 // launch j of the first n requests of a window as one batch
 static CoderBatch coder_batch(const CoderLaunch cl[][kTableSlots], int n, int j)
 {
@@ -578,7 +621,7 @@ static CoderBatch coder_batch(const CoderLaunch cl[][kTableSlots], int n, int j)
 
 static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *payload, const Geometry &g, uint8_t *ws,
                           long long capacity, uint64_t *out_bytes, int *status, bool compress, const uint8_t *dev_tables,
-                          CoderLaunch out[kTableSlots])
+                          CoderLaunch out[kTableSlots], int waves = 0)
 {
     const bool any_table = table_slots(p) == kTableSlots;
     const long long LH = (long long)p->model.layers * p->model.kv_heads, cph = chunks_per_head(r->tokens);
@@ -623,7 +666,7 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
             L.a.chunks = heads * cph;
             L.a.chunk_base = chunk_at;
             L.a.wg_base = wg_at;
-            const int nw = enc_waves(L.bits);
+            const int nw = waves ? waves : enc_waves(L.bits);
             chunk_at += L.a.chunks;
             wg_at += (L.a.chunks + nw - 1) / nw;
             mask |= 1 << L.a.tab;
@@ -801,9 +844,10 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             KVC_TRY(launch_compress_prologue(pa, s));
         }
     }
+    const int coder_limit = tensors_share(plan) ? kCoderBatch / 2 : kCoderBatch;
     for (int first = 0; first < n;) {
         int lead;
-        const int end = request_window(plan, reqs, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
+        const int end = request_window(plan, reqs, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
         if (!st.codec) {
             marks.window(first, end, 1);
             KVC_TRY(launch_tensor(plan, 0, true, quant_batch(plan, reqs, first, end, lead, 0, payload, payload_off, dev_status, true),
@@ -817,6 +861,8 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             // widths ascending), then launch by launch over the requests together
             CoderLaunch cl[kCoderBatch][kTableSlots];
             int launches = 0;
+            const bool share = share_kv(plan, &reqs[lead]);
+            const int waves = share ? shared_waves(plan, reqs, first, end) : 0;
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);
                 Geometry g;
@@ -824,14 +870,23 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                 uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
                 launches = coder_launches(plan, &reqs[i], (uint8_t *)payload + payload_off[i], g, ws,
                                           (long long)(payload_off[i + 1] - payload_off[i]), out_bytes + i, dev_status + i, true,
-                                          (const uint8_t *)workspace, cl[k]);
+                                          (const uint8_t *)workspace, cl[k], waves);
             }
             marks.window(first, end, 1);
+            if (share) {
+                CoderBatch both = coder_batch_both(cl, end - first);
+                both.waves = waves;
+                KVC_TRY(launch_encode_section(2, cl[0][0].bits, cl[0][0].group, dt, both, s));
+                marks.window(first, end, 2);
+                marks.window(first, end, 3);
+                first = end;
+                continue;
+            }
             for (int j = 0; j < launches; ++j)
-                if (!cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
+                if (!cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].a.is_v, cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
             marks.window(first, end, 2);
             for (int j = 0; j < launches; ++j)
-                if (cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
+                if (cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].a.is_v, cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
             marks.window(first, end, 3);
         }
         first = end;
@@ -958,9 +1013,10 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
+    const int coder_limit = tensors_share(plan) ? kCoderBatch / 2 : kCoderBatch;
     for (int first = 0; first < n;) {
         int lead;
-        const int end = request_window(plan, dst, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
+        const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
         if (!st.codec) {
             marks.window(first, end, 1);
             KVC_TRY(launch_tensor(plan, 0, false, quant_batch(plan, dst, first, end, lead, 0, const_cast<void *>(payload), payload_off, dev_status, false),
@@ -982,11 +1038,18 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                           (const uint8_t *)workspace, cl[k]);
             }
             marks.window(first, end, 1);
+            if (share_kv(plan, &dst[lead])) {
+                KVC_TRY(launch_decode_section(2, cl[0][0].bits, dt, coder_batch_both(cl, end - first), s));
+                marks.window(first, end, 2);
+                marks.window(first, end, 3);
+                first = end;
+                continue;
+            }
             for (int j = 0; j < launches; ++j)
-                if (!cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
+                if (!cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].a.is_v, cl[0][j].bits, dt, coder_batch(cl, end - first, j), s));
             marks.window(first, end, 2);
             for (int j = 0; j < launches; ++j)
-                if (cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
+                if (cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].a.is_v, cl[0][j].bits, dt, coder_batch(cl, end - first, j), s));
             marks.window(first, end, 3);
         }
         first = end;

@@ -113,7 +113,8 @@ __device__ __forceinline__ void dequant_chunk(const CoderArgs &a, const ChunkPos
 // TR: the inverse of stage T that the launch applies (see dequant_pass_rows).  One kernel per
 // transform: in one kernel, every path pays for the registers of the most expensive one (the anchors
 // of short runs, the rotation) with its fourth wave per SIMD.
-template <int BITS, int DT, bool IS_V, bool DENSE, int TR>
+// KV: the launch's tensor, K (0), V (1) or both (2: the batch holds items of either; without a transform).
+template <int BITS, int DT, int KV, bool DENSE, int TR>
 __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel(CoderBatch batch)
 {
     using Geo = ChunkGeom<BITS>;
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
     constexpr int W = Geo::kWords, NW = Geo::kDecWaves;
     unsigned wg;
     const CoderArgs &a = batch.item[batch_item(batch, wg)];
+    const bool is_v = KV == 2 ? a.is_v != 0 : KV == 1;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Dec::kLds];
     __shared__ uint16_t lut[4096];
 
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
             const uint32_t o = (k * 64 + lane) * 16;
             if (o < size) bodyv[k] = __builtin_nontemporal_load((const u32x4 *)(body + o));
         }
-        if (!IS_V) load_meta_k(a.q, c, 0, meta0, meta1);
+        if (!is_v) load_meta_k(a.q, c, 0, meta0, meta1);
         else load_meta_v(a.q, c, 0, metav);
         if (!DENSE && a.q.x.block_table != nullptr && a.q.x.bt_wave) blocks0 = pass_blocks(a.q.x, c.row0, c.row0 + c.rows);
         if (TR == 2)
@@ -255,13 +257,14 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
 
     // dequantize the rows from LDS
     bool bad = false;
-    dequant_chunk<BITS, DT, IS_V, DENSE, TR>(a, c, lds, meta0, meta1, metav, anchor0, blocks0, bad);
+    if (is_v) dequant_chunk<BITS, DT, true, DENSE, TR>(a, c, lds, meta0, meta1, metav, anchor0, blocks0, bad);
+    else dequant_chunk<BITS, DT, false, DENSE, TR>(a, c, lds, meta0, meta1, metav, anchor0, blocks0, bad);
     if (bad) atomicOr(a.q.status, KVC_DEV_BAD_BLOCK);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
 
-template <int BITS, int DT, bool IS_V> static int decode_launch(const CoderBatch &b, hipStream_t s)
+template <int BITS, int DT, int KV> static int decode_launch(const CoderBatch &b, hipStream_t s)
 {
     constexpr int NW = ChunkGeom<BITS>::kDecWaves;
     const CoderArgs &a = b.item[0];
@@ -275,11 +278,18 @@ template <int BITS, int DT, bool IS_V> static int decode_launch(const CoderBatch
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
     const int tr = a.q.rotate ? 1 : !a.q.anchors ? 0 : a.q.anchor_shift >= 5 ? 2 : 3;
-#define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, IS_V, D, T>), grid, block, 0, s, placed)
+#define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, KV, D, T>), grid, block, 0, s, placed)
+    if (KV == 2) {
+        if (tr != 0) return KVC_ERR_UNSUPPORTED;
+        if (a.q.dense) KVC_DECODE(true, 0); else KVC_DECODE(false, 0);
+        return launched();
+    }
+    // (the transforms are not instantiated for both tensors together)
+    constexpr int kRot = KV == 2 ? 0 : 1, kOne = KV == 2 ? 0 : 2, kShort = KV == 2 ? 0 : 3;
     if (a.q.dense) {
-        if (tr == 0) KVC_DECODE(true, 0); else if (tr == 1) KVC_DECODE(true, 1); else if (tr == 2) KVC_DECODE(true, 2); else KVC_DECODE(true, 3);
+        if (tr == 0) KVC_DECODE(true, 0); else if (tr == 1) KVC_DECODE(true, kRot); else if (tr == 2) KVC_DECODE(true, kOne); else KVC_DECODE(true, kShort);
     } else {
-        if (tr == 0) KVC_DECODE(false, 0); else if (tr == 1) KVC_DECODE(false, 1); else if (tr == 2) KVC_DECODE(false, 2); else KVC_DECODE(false, 3);
+        if (tr == 0) KVC_DECODE(false, 0); else if (tr == 1) KVC_DECODE(false, kRot); else if (tr == 2) KVC_DECODE(false, kOne); else KVC_DECODE(false, kShort);
     }
 #undef KVC_DECODE
     return launched();
@@ -288,10 +298,13 @@ template <int BITS, int DT, bool IS_V> static int decode_launch(const CoderBatch
 #define KVC_PASTE2(a, b) a##b
 #define KVC_PASTE(a, b) KVC_PASTE2(a, b)
 
-int KVC_PASTE(launch_decode_bits, KVC_BITS)(int dtype, const CoderBatch &a, hipStream_t s)
+int KVC_PASTE(launch_decode_bits, KVC_BITS)(int kv, int dtype, const CoderBatch &a, hipStream_t s)
 {
-    if (a.item[0].is_v) return dtype == DT_F16 ? decode_launch<KVC_BITS, DT_F16, true>(a, s) : decode_launch<KVC_BITS, DT_BF16, true>(a, s);
-    return dtype == DT_F16 ? decode_launch<KVC_BITS, DT_F16, false>(a, s) : decode_launch<KVC_BITS, DT_BF16, false>(a, s);
+    switch (kv) {
+    case 0: return dtype == DT_F16 ? decode_launch<KVC_BITS, DT_F16, 0>(a, s) : decode_launch<KVC_BITS, DT_BF16, 0>(a, s);
+    case 1: return dtype == DT_F16 ? decode_launch<KVC_BITS, DT_F16, 1>(a, s) : decode_launch<KVC_BITS, DT_BF16, 1>(a, s);
+    }
+    return dtype == DT_F16 ? decode_launch<KVC_BITS, DT_F16, 2>(a, s) : decode_launch<KVC_BITS, DT_BF16, 2>(a, s);
 }
 
 }  // namespace kvc

@@ -101,22 +101,21 @@ template <int W> __device__ __forceinline__ void encode_two(const uint32_t *sym,
 // wave per request, the scanner.  Workgroups take a ticket from a counter; as soon as the sizes of its
 // chunks are known, before a code word is written, a workgroup leaves their sum in its state word; the
 // scanner walks the words in ticket order and puts the prefix in their place; the waves of the
-// workgroup, by then mostly done with the code words, pick it up.  The scanners are the first
-// workgroups of the grid, and ticket order guarantees that every predecessor of a workgroup is already
-// running, so the waits always end; they are bounded by kSpinLimit all the same.
+// workgroup, by then mostly done with the code words, pick it up.  The scanner is the first wave of the
+// workgroup with the launch's first ticket, and ticket order guarantees that every predecessor of a
+// workgroup is already running, so the waits always end; they are bounded by kSpinLimit all the same.
 // (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
 // hundreds of waves polling the same lines of memory.  70B shape, half of its layers, compress call: 1369 us
 // with eight chunks per workgroup, now 1213; 2-bit codes / groups of 128 1370 -> 1135, 8 bits (a quarter of
 // the layers) 1235 -> 1058.  With the bodies at fixed places, nothing to wait for, 1165.)
 
-// The scan of one request's launch; the last launch's scanner closes the directory and the header.
-template <int NW, bool IS_V> __device__ __forceinline__ void scan_sizes(const CoderArgs &a)
+// The scan of one request's launch, whose last workgroup is `end` - 1; the last launch's scanner closes
+// the directory and the header.
+__device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end)
 {
-    if (a.chunks <= 0) return;                      // an empty request: its directory and header are closed already
     const int lane = lane_id();
     unsigned long long *carry = (unsigned long long *)(a.ws.ticket + kScanCarry);      // units before this launch; units of K
-    unsigned long long prefix = carry[0];
-    const long long end = a.wg_base + (a.chunks + NW - 1) / NW;
+    unsigned long long prefix = carry[0], k_units = carry[1];
     int spins = 0;
     __builtin_amdgcn_s_setprio(3);
     // kScanWindows windows of 64 workgroups per look (a look is a round trip to memory, and the scanner has to
@@ -142,6 +141,8 @@ template <int NW, bool IS_V> __device__ __forceinline__ void scan_sizes(const Co
             if (lane < run)
                 __hip_atomic_store(&a.ws.state[base + 64 * k + lane], kFlagPrefix | (prefix + incl - size), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
+            const long long k_last = a.k_wgs - 1 - (base + 64 * k);              // the last K workgroup among these?
+            if (k_last >= 0 && k_last < run) k_units = prefix + (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)k_last);
             prefix += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             next += run;
             moved = true;
@@ -153,7 +154,6 @@ template <int NW, bool IS_V> __device__ __forceinline__ void scan_sizes(const Co
         }
     }
     if (lane != 0) return;
-    const unsigned long long k_units = IS_V ? carry[1] : prefix;
     carry[0] = prefix;
     carry[1] = k_units;
     if (end != a.total_wgs) return;
@@ -167,21 +167,19 @@ template <int NW, bool IS_V> __device__ __forceinline__ void scan_sizes(const Co
     *a.out_bytes = total;
 }
 
-template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF>
-__global__ __launch_bounds__(enc_waves(BITS) * 64)
-__attribute__((amdgpu_waves_per_eu(enc_min_waves(BITS, G, DT, DENSE, IS_V, XF))))
+// KV: the launch's tensor, K (0), V (1) or both (2: the items of the batch are then a K and a V launch of
+// every request, one after the other).
+template <int BITS, int G, int DT, int KV, bool DENSE, bool XF, int NW>
+__global__ __launch_bounds__(NW * 64)
+__attribute__((amdgpu_waves_per_eu(enc_min_waves(BITS, G, DT, DENSE || KV == 2, KV == 1, XF))))
 void encode_kernel(CoderBatch batch)
 {
     using Geo = ChunkGeom<BITS>;
-    constexpr int W = Geo::kWords, NW = enc_waves(BITS);
-    if (blockIdx.x < batch.start[0]) {                           // the scanners come first, one wave per request
-        const int item = (int)blockIdx.x * NW + wave_id();
-        if (item < batch.n) scan_sizes<NW, IS_V>(batch.item[item]);
-        return;
-    }
+    constexpr int W = Geo::kWords;
+    constexpr int kItems = KV == 2 ? 2 : 1;                      // items per request
     unsigned wg;
-    const CoderArgs &a = batch.item[batch_item(batch, wg)];      // (which of them it is among the item's workgroups does not matter: the chunk comes from the ticket)
-    (void)wg;
+    const int item = kItems * batch_item(batch, wg);
+    const CoderArgs &first = batch.item[item];
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Geo::kLds];
     __shared__ EncTables enc;
     __shared__ uint32_t s_units[NW];
@@ -190,25 +188,46 @@ void encode_kernel(CoderBatch batch)
 
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     if (tid == 0) {
-        s_ticket = atomicAdd(a.ws.ticket, 1u);
+        s_ticket = atomicAdd(first.ws.ticket, 1u);
         s_sum = s_reported = 0;
         s_excl = 0;
     }
     // the candidate with the fewest halvings that meets the length limit (two short loads one after the
     // other, in the time the ticket takes)
-    const CandidateTables *tables = candidate_tables(a.ws.lut, a.tab);
-    const uint32_t complete = lane < kCandidates ? tables->complete[lane] : 0;
-    const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(complete != 0) | (1ull << (kCandidates - 1)));
-    for (int k = tid; k < 256; k += NW * 64) {
-        const uint16_t e = tables->entry[pick][k];
-        enc.len[k] = (uint8_t)(e >> 12);
-        enc.code[k] = e;
-    }
-    __syncthreads();
+    int pick = 0;
+    auto load_table = [&](const CoderArgs &a) {
+        const CandidateTables *tables = candidate_tables(a.ws.lut, a.tab);
+        const uint32_t complete = lane < kCandidates ? tables->complete[lane] : 0;
+        pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(complete != 0) | (1ull << (kCandidates - 1)));
+        for (int k = tid; k < 256; k += NW * 64) {
+            const uint16_t e = tables->entry[pick][k];
+            enc.len[k] = (uint8_t)(e >> 12);
+            enc.code[k] = e;
+        }
+        __syncthreads();
+    };
+    // (both tensors in one launch: the workgroup's number says which it most likely is, its ticket which it is)
+    int second = KV == 2 && wg >= first.k_wgs ? 1 : 0;
+    load_table(batch.item[item + second]);
     const long long ticket = (unsigned)__builtin_amdgcn_readfirstlane((int)s_ticket);     // global order over K and V workgroups (the same in all lanes)
+    if (KV == 2 && second != (ticket >= first.k_wgs ? 1 : 0)) {
+        second = 1 - second;
+        __syncthreads();
+        load_table(batch.item[item + second]);
+    }
+    const CoderArgs &a = batch.item[item + second];
     const long long chunk = (ticket - a.wg_base) * NW + wave;
     const bool live = chunk < a.chunks;
     uint8_t *lds = lds_all + wave * Geo::kLds;
+    // The first workgroup of the launch: its first wave becomes the scanner once its own chunk is done (a
+    // workgroup of its own would hold the LDS of four chunks, and a launch that just fills the chip would
+    // not fit).  What the launch before left is read before any size is reported: the scanner replaces it.
+    const bool leads = ticket == first.wg_base;
+    unsigned long long before = 0;
+    if (leads) {
+        before = ((const volatile unsigned long long *)(a.ws.ticket + kScanCarry))[0];
+        asm volatile("" : "+v"(before));
+    }
     // the table's lengths in the payload, unless the construction without halvings has written them already
     if (pick != 0 && ticket == a.wg_base)
         for (int k = tid; k < 256; k += NW * 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
@@ -234,7 +253,8 @@ void encode_kernel(CoderBatch batch)
         ChunkPos c = chunk_pos(a.q, chunk);
         rows = c.rows;
         bool bad = false;
-        quantize_chunk<BITS, G, DT, IS_V, DENSE, XF>(a.q, c, lds, true, bad);
+        if (KV == 2 ? second != 0 : KV == 1) quantize_chunk<BITS, G, DT, true, DENSE, XF>(a.q, c, lds, true, bad);
+        else quantize_chunk<BITS, G, DT, false, DENSE, XF>(a.q, c, lds, true, bad);
         if (bad) atomicOr(a.q.status, KVC_DEV_BAD_BLOCK);
         wave_sync();
         load_sub<BITS>(lds, sym);
@@ -278,10 +298,14 @@ void encode_kernel(CoderBatch batch)
     if (!live) report_size(0);
     // The workgroup's prefix, left in its state word by the scanner once all its waves have reported.  The wave
     // that reported last polls for it, the others wait at an LDS word: four thousand waves polling memory would
-    // slow the scanner down.
+    // slow the scanner down.  (The first workgroup of the launch, whose first wave is the scanner, knows its
+    // prefix: the end of the launch before.)
     unsigned long long excl;
     int spins = 0;
-    if (__builtin_amdgcn_readfirstlane(last_to_report)) {
+    if (leads) {
+        excl = before;
+        while (wave > 0 && __hip_atomic_load(&s_reported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != (uint32_t)NW) __builtin_amdgcn_s_sleep(1);
+    } else if (__builtin_amdgcn_readfirstlane(last_to_report)) {
         while (((excl = __hip_atomic_load(&a.ws.state[ticket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 62) != 2) {
             if (++spins > kSpinLimit) {
                 if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
@@ -302,8 +326,9 @@ void encode_kernel(CoderBatch batch)
     for (int w = 0; w < wave; ++w) mine += s_units[w];
     if (lane == 0) ((uint32_t *)(a.payload + a.off_dir))[a.chunk_base + chunk] = (uint32_t)mine;
     uint8_t *dst = a.payload + a.off_bodies + mine * 16;
-    if ((long long)(a.off_bodies + (mine + body_units) * 16) > a.capacity) return;      // cannot happen: bodies never exceed raw size
-    if (coded) {
+    if ((long long)(a.off_bodies + (mine + body_units) * 16) > a.capacity) {
+        // cannot happen: bodies never exceed raw size
+    } else if (coded) {
         // (every store instruction covers whole lines of memory, but for the body's ends)
         const int skew = (int)((uintptr_t)dst & 127);
         for (int o = lane * 16 - skew; o < (int)(body_units * 16); o += 64 * 16)
@@ -320,43 +345,53 @@ void encode_kernel(CoderBatch batch)
                 p[k] = v;
             }
     }
+    if (leads && wave == 0) scan_sizes(first, KV == 2 ? first.total_wgs : first.wg_base + (first.chunks + NW - 1) / NW);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
 
-template <int BITS, int G, int DT, bool IS_V> static int encode_launch(const CoderBatch &b, hipStream_t s)
+template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(const CoderBatch &b, hipStream_t s)
 {
     const CoderArgs &a = b.item[0];
-    constexpr int NW = enc_waves(BITS);
     CoderBatch placed = b;
-    const unsigned scanners = (unsigned)((b.n + NW - 1) / NW);
-    unsigned need = scanners;
-    for (int i = 0; i < b.n; ++i) {
+    if (KV == 2) placed.n = b.n / 2;                  // requests
+    unsigned need = 0;
+    for (int i = 0; i < placed.n; ++i) {
         placed.start[i] = need;
-        need += (unsigned)((b.item[i].chunks + NW - 1) / NW);
+        need += KV == 2 ? (unsigned)b.item[2 * i].total_wgs : (unsigned)((b.item[i].chunks + NW - 1) / NW);
     }
-    placed.start[b.n] = need;
-    if (need == scanners) return KVC_OK;
+    placed.start[placed.n] = need;
+    if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
-    // K token blocks of 64 and 128 rows, and V groups of 32 channels (the variant that is short of
-    // registers), have a kernel of their own for launches without a transform
-    constexpr bool kSplit = IS_V ? G == 32 : G >= 64;
-    if (kSplit && !a.q.rotate && !a.q.anchors) {
-        if (a.q.dense) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, IS_V, true, !kSplit>), grid, block, 0, s, placed);
-        else hipLaunchKernelGGL((encode_kernel<BITS, G, DT, IS_V, false, !kSplit>), grid, block, 0, s, placed);
+#define KVC_ENCODE(D, X) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, X, NW>), grid, block, 0, s, placed)
+    // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
+    // transform (its code costs the plain path registers); both tensors together run without one only
+    constexpr bool kPlain = KV != 1 || G == 32;
+    if (kPlain && !a.q.rotate && !a.q.anchors) {
+        if (a.q.dense) KVC_ENCODE(true, !kPlain); else KVC_ENCODE(false, !kPlain);
         return launched();
     }
-    if (a.q.dense) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, IS_V, true, true>), grid, block, 0, s, placed);
-    else hipLaunchKernelGGL((encode_kernel<BITS, G, DT, IS_V, false, true>), grid, block, 0, s, placed);
+    if (KV == 2) return KVC_ERR_UNSUPPORTED;
+    if (a.q.dense) KVC_ENCODE(true, KV != 2); else KVC_ENCODE(false, KV != 2);
+#undef KVC_ENCODE
     return launched();
 }
 
-template <int DT, bool ISV> static int encode_g(int group, const CoderBatch &a, hipStream_t s)
+// (the kernels for both tensors come with four and, where the registers allow, with eight chunks per
+// workgroup, see shared_waves)
+template <int BITS, int G, int DT, int KV> static int encode_waves(const CoderBatch &b, hipStream_t s)
+{
+    if constexpr (KV == 2 && G == 32 && BITS != 8)
+        if (b.waves == 8) return encode_launch<BITS, G, DT, KV, 8>(b, s);
+    return encode_launch<BITS, G, DT, KV, enc_waves(BITS)>(b, s);
+}
+
+template <int DT, int KV> static int encode_g(int group, const CoderBatch &a, hipStream_t s)
 {
     switch (group) {
-    case 32: return encode_launch<KVC_BITS, 32, DT, ISV>(a, s);
-    case 64: return encode_launch<KVC_BITS, 64, DT, ISV>(a, s);
-    case 128: return encode_launch<KVC_BITS, 128, DT, ISV>(a, s);
+    case 32: return encode_waves<KVC_BITS, 32, DT, KV>(a, s);
+    case 64: return encode_waves<KVC_BITS, 64, DT, KV>(a, s);
+    case 128: return encode_waves<KVC_BITS, 128, DT, KV>(a, s);
     }
     return KVC_ERR_UNSUPPORTED;
 }
@@ -364,10 +399,13 @@ template <int DT, bool ISV> static int encode_g(int group, const CoderBatch &a, 
 #define KVC_PASTE2(a, b) a##b
 #define KVC_PASTE(a, b) KVC_PASTE2(a, b)
 
-int KVC_PASTE(launch_encode_bits, KVC_BITS)(int group, int dtype, const CoderBatch &a, hipStream_t s)
+int KVC_PASTE(launch_encode_bits, KVC_BITS)(int kv, int group, int dtype, const CoderBatch &a, hipStream_t s)
 {
-    if (a.item[0].is_v) return dtype == DT_F16 ? encode_g<DT_F16, true>(group, a, s) : encode_g<DT_BF16, true>(group, a, s);
-    return dtype == DT_F16 ? encode_g<DT_F16, false>(group, a, s) : encode_g<DT_BF16, false>(group, a, s);
+    switch (kv) {
+    case 0: return dtype == DT_F16 ? encode_g<DT_F16, 0>(group, a, s) : encode_g<DT_BF16, 0>(group, a, s);
+    case 1: return dtype == DT_F16 ? encode_g<DT_F16, 1>(group, a, s) : encode_g<DT_BF16, 1>(group, a, s);
+    }
+    return dtype == DT_F16 ? encode_g<DT_F16, 2>(group, a, s) : encode_g<DT_BF16, 2>(group, a, s);
 }
 
 }  // namespace kvc

@@ -433,25 +433,24 @@ int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s)
     return launched();
 }
 
-int launch_encode_section(int bits, int group, int dtype, const CoderBatch &a, hipStream_t s)
+int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &a, hipStream_t s)
 {
     switch (bits) {
-    case 2: return launch_encode_bits2(group, dtype, a, s);
-    case 3: return launch_encode_bits3(group, dtype, a, s);
-    case 4: return launch_encode_bits4(group, dtype, a, s);
-    case 8: return launch_encode_bits8(group, dtype, a, s);
+    case 2: return launch_encode_bits2(kv, group, dtype, a, s);
+    case 3: return launch_encode_bits3(kv, group, dtype, a, s);
+    case 4: return launch_encode_bits4(kv, group, dtype, a, s);
+    case 8: return launch_encode_bits8(kv, group, dtype, a, s);
     }
     return KVC_ERR_UNSUPPORTED;
 }
 
-int launch_decode_section(int bits, int group, int dtype, const CoderBatch &a, hipStream_t s)
+int launch_decode_section(int kv, int bits, int dtype, const CoderBatch &a, hipStream_t s)
 {
-    (void)group;
     switch (bits) {
-    case 2: return launch_decode_bits2(dtype, a, s);
-    case 3: return launch_decode_bits3(dtype, a, s);
-    case 4: return launch_decode_bits4(dtype, a, s);
-    case 8: return launch_decode_bits8(dtype, a, s);
+    case 2: return launch_decode_bits2(kv, dtype, a, s);
+    case 3: return launch_decode_bits3(kv, dtype, a, s);
+    case 4: return launch_decode_bits4(kv, dtype, a, s);
+    case 8: return launch_decode_bits8(kv, dtype, a, s);
     }
     return KVC_ERR_UNSUPPORTED;
 }

@@ -215,8 +215,9 @@ struct CoderArgs {
 constexpr int kCoderBatch = 8;      // (the argument block stays below 4 KB)
 struct CoderBatch {
     CoderArgs item[kCoderBatch];
-    unsigned start[kCoderBatch + 1];    // encoder and decoder: first workgroup of every item (set by the launcher)
+    unsigned start[kCoderBatch + 1];    // first workgroup of every item (both tensors together: of every request; set by the launcher)
     int n;
+    int waves;                          // encoder, both tensors together: chunks per workgroup
 };
 static_assert(sizeof(CoderBatch) <= 4000, "kernel arguments are limited to 4 KB");
 static_assert(sizeof(QuantBatch) <= 4000, "kernel arguments are limited to 4 KB");
@@ -276,13 +277,14 @@ static_assert(sizeof(DecodeSetupArgs) <= 4000, "kernel arguments are limited to 
 
 int launch_setup(int dtype, const SetupArgs &a, hipStream_t s);
 int launch_build_tables(const BuildArgs &a, hipStream_t s);
-int launch_encode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
+// kv: the tensor of the launch, K (0), V (1) or both (2: a K and a V item of every request in turn)
+int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
 int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s);
-int launch_decode_section(int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
+int launch_decode_section(int kv, int bits, int dtype, const CoderBatch &b, hipStream_t s);
 // one translation unit per code width (kvc_huff_enc.hip / kvc_huff_dec.hip compiled with -DKVC_BITS=...)
 #define KVC_DECLARE_CODER(B)                                                                  \
-    int launch_encode_bits##B(int group, int dtype, const CoderBatch &b, hipStream_t s);      \
-    int launch_decode_bits##B(int dtype, const CoderBatch &b, hipStream_t s);
+    int launch_encode_bits##B(int kv, int group, int dtype, const CoderBatch &b, hipStream_t s); \
+    int launch_decode_bits##B(int kv, int dtype, const CoderBatch &b, hipStream_t s);
 KVC_DECLARE_CODER(2) KVC_DECLARE_CODER(3) KVC_DECLARE_CODER(4) KVC_DECLARE_CODER(8)
 #undef KVC_DECLARE_CODER
 

@@ -111,3 +111,40 @@ def test_decode_setup_of_many_requests(ref, widths):
         bad = kvc.DEV_BAD_HEADER if i == 2 else kvc.DEV_BAD_TABLE if i in slots else 0
         assert int(buf.status[i]) == bad, i
         assert torch.equal(y, torch.full_like(y, 3.0) if bad else want[i]), i
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("T", [128 * 64, 128 * 64 + 1])
+def test_both_tensors_in_a_launch(ref, T, bits):
+    """K and V of one width and group share the coder's launches: 1024 chunks in all, and a few more (eight chunks
+    per workgroup instead of four where the registers allow it)."""
+    x = kvgen.make_kv(800, 1, 8, 128, T, torch.float16 if bits != 3 else torch.bfloat16)
+    check_contiguous(ref, x, bits, bits, 32, 32, codec=1)
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_both_tensors_of_many_paged_requests(ref, group):
+    """Requests that share a launch, four at a time, in pages; the last workgroups of K and of V are not full."""
+    L, H, bt = 1, 3, 16
+    lens = [130, 1, 500, 128, 257, 31, 640]
+    plan = kvc.Plan(kvc.F16, L, H, 128, 4, 4, group, group, 1, max_tokens=max(lens), max_batch=len(lens))
+    xs = [kvgen.make_kv(820 + i, L, H, 128, T, torch.float16) for i, T in enumerate(lens)]
+    tabs = [kvgen.block_table(5 + i, -(-T // bt), 48) for i, T in enumerate(lens)]
+    pools = [kvgen.to_paged(x, t, bt, 48).cuda() for x, t in zip(xs, tabs)]
+    tabd = [t.cuda() for t in tabs]
+    buf = gpu_compress(plan, [kvc.paged_request(p, t, T) for p, t, T in zip(pools, tabd, lens)], lens)
+    outs = [torch.zeros_like(p) for p in pools]
+    want_status = [0] * len(lens)
+    assert buf.status.tolist() == want_status
+    buf.decompress([kvc.paged_request(o, t, T) for o, t, T in zip(outs, tabd, lens)], torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert buf.status.tolist() == want_status
+    cfg = ref.config(dtype=1, layers=L, heads=H, bits_k=4, bits_v=4, group_k=group, group_v=group, codec=1)
+    for i, T in enumerate(lens):
+        xu = kvgen.as_u16(xs[i])
+        lay = ref.contiguous_layout(H, T, 128)
+        want = ref.compress(cfg, xu[0, 0], xu[0, 1], lay, T)
+        assert np.array_equal(buf.payload_of(i), want), i
+        back = np.zeros_like(xu)
+        assert ref.decompress(want, back[0, 0], back[0, 1], lay, cfg) == 0
+        assert np.array_equal(kvgen.as_u16(kvgen.from_paged(outs[i].cpu(), tabs[i], T)), back), i
