@@ -40,18 +40,22 @@ template <int BITS> struct ChunkGeom {
     static constexpr int kDecWaves = BITS == 8 ? 2 : 4;    // decoder: waves per workgroup (they share the 8 KB table)
 };
 
-// The decoder's LDS layout of a chunk.  4-bit codes: sub-blocks without padding, pieces rotated
-// (fetch_codes, LAYOUT 2), 8 KB per wave, so that four workgroups of four waves and their 8 KB
-// tables fill a compute unit's 160 KB exactly.  Other widths: the encoder's padded layout.
+// The decoder's LDS layout of a chunk.  4- and 8-bit codes: sub-blocks without padding, pieces rotated
+// (fetch_codes, LAYOUT 2), 8 or 16 KB per wave, so that four workgroups (of four or two waves) and their
+// 8 KB tables fill a compute unit's 160 KB exactly.  Other widths: the encoder's padded layout.
+// (8-bit codes: eight waves per unit instead of the six that fit with padding.  The chain of table look-ups of a
+// sub-block's 256 symbols is what bounds them, so the time follows the waves: 70B shape, a quarter of the
+// layers, decompress call 1418 -> 1057 us.  Smaller shares of a chunk per wave, each lane reading its stream from
+// memory, let sixteen waves in and took 1630 us: the lines of a body came from L2 several times.)
 template <int BITS> struct DecGeom {
-    static constexpr bool kRotated = BITS == 4;
+    static constexpr bool kRotated = BITS == 4 || BITS == 8;
     static constexpr int kLayout = kRotated ? 2 : 1;
     static constexpr int kStride = kRotated ? ChunkGeom<BITS>::kSubBytes : ChunkGeom<BITS>::kSubStride;
     static constexpr int kLds = kSubs * kStride;
     // address of 16-byte piece `piece` of sub-block `sub`
     static __device__ __forceinline__ uint8_t *piece_ptr(uint8_t *lds, uint32_t sub, uint32_t piece)
     {
-        if (kRotated) return lds + sub * kStride + (((piece + sub) & 7u) << 4);
+        if (kRotated) return lds + sub * kStride + (((piece + sub) & (kStride / 16 - 1u)) << 4);
         return lds + sub * kStride + piece * 16;
     }
 };

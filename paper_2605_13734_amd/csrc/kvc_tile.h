@@ -440,17 +440,23 @@ __device__ __forceinline__ bool v_meta_floats(const uint32_t mw[8], float scale[
 
 // The lane's packed codes of row r.  LAYOUT 0: rows back to back (payload section); 1: the
 // coder's LDS layout, sub-blocks of two rows, each padded by 16 bytes; 2: the decoder's LDS
-// layout for 4-bit codes, sub-blocks of two rows without padding whose eight 16-byte pieces are
-// rotated by the sub-block's number (piece p of sub-block s sits at position (p + s) mod 8), so
-// that both the row-wise and the sub-block-wise accesses spread over the banks.
+// layout for 4- and 8-bit codes, sub-blocks of two rows without padding whose 16-byte pieces (eight or
+// sixteen) are rotated by the sub-block's number (piece p of sub-block s sits at position (p + s) modulo
+// their count), so that both the row-wise and the sub-block-wise accesses spread over the banks.
 template <int BITS, int LAYOUT> __device__ __forceinline__ u32x2 fetch_codes(uint8_t *codes, int r)
 {
     if (LAYOUT == 2) {
-        static_assert(LAYOUT != 2 || BITS == 4, "rotated layout is for 4-bit codes");
-        const int col = lane_id() & 15, sub = r >> 1, piece = ((r & 1) << 2) + (col >> 2);
+        static_assert(LAYOUT != 2 || BITS == 4 || BITS == 8, "rotated layout is for 4- and 8-bit codes");
+        const int col = lane_id() & 15, sub = r >> 1;
         u32x2 w;
-        w[0] = *(const uint32_t *)(codes + sub * 128 + (((piece + sub) & 7) << 4) + ((col & 3) << 2));
-        w[1] = 0;
+        if (BITS == 4) {
+            const int piece = ((r & 1) << 2) + (col >> 2);
+            w[0] = *(const uint32_t *)(codes + sub * 128 + (((piece + sub) & 7) << 4) + ((col & 3) << 2));
+            w[1] = 0;
+        } else {
+            const int piece = ((r & 1) << 3) + (col >> 1);
+            w = *(const u32x2 *)(codes + sub * 256 + (((piece + sub) & 15) << 4) + ((col & 1) << 3));
+        }
         return w;
     }
     return load_row_codes<BITS>(code_row<BITS, LAYOUT == 1>(codes, r));
