@@ -121,6 +121,33 @@ static inline unsigned fill_slices(long long words)
     return (unsigned)(n < 1 ? 1 : (n > 256 ? 256 : n));
 }
 
+// A small call without the coder in one launch (see compress_call_kernel): K and V of its requests in turn.
+constexpr int kSmallRequests = 4;
+struct SmallCompressArgs {
+    QuantArgs item[2 * kSmallRequests];
+    unsigned start[2 * kSmallRequests + 1];     // first workgroup of every item (set by the launcher)
+    int n, requests;
+    PrologueItem prologue[kSmallRequests];
+};
+struct SmallCheck {
+    const uint32_t *payload;
+    HeaderBytes expect;
+};
+struct SmallDecompressArgs {
+    QuantArgs item[2 * kSmallRequests];
+    unsigned start[2 * kSmallRequests + 1];
+    int n, requests;
+    SmallCheck check[kSmallRequests];
+};
+static_assert(sizeof(SmallCompressArgs) <= 4000 && sizeof(SmallDecompressArgs) <= 4000, "kernel arguments are limited to 4 KB");
+int launch_compress_call(int bits, int group, int dtype, SmallCompressArgs &b, hipStream_t s);
+int launch_decompress_call(int bits, int dtype, SmallDecompressArgs &b, hipStream_t s);
+#define KVC_DECLARE_CALL(B)                                                                              \
+    int launch_compress_call_bits##B(int group, int dtype, SmallCompressArgs &b, hipStream_t s);        \
+    int launch_decompress_call_bits##B(int dtype, SmallDecompressArgs &b, hipStream_t s);
+KVC_DECLARE_CALL(2) KVC_DECLARE_CALL(3) KVC_DECLARE_CALL(4) KVC_DECLARE_CALL(8)
+#undef KVC_DECLARE_CALL
+
 // Header (and width table) check of one request before it is decompressed.
 struct CheckItem {
     const uint32_t *payload;

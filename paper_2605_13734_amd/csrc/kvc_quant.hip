@@ -19,11 +19,8 @@ namespace kvc {
 // XF = false leaves the code of stage T out (for launches without a transform): sharing a kernel
 // with it doubles the registers of the plain path for token blocks of 64 and 128 rows.
 template <int BITS, int G, int DT, bool DENSE, bool XF>
-__global__ __launch_bounds__(256) void compress_k_kernel(QuantBatch b)
+__device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg, float *xch_all)
 {
-    unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
-    __shared__ __attribute__((aligned(16))) float xch_all[4 * kXchFloats];
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
     constexpr int P = G / kPassRows;
@@ -46,14 +43,22 @@ __global__ __launch_bounds__(256) void compress_k_kernel(QuantBatch b)
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE>
-__global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
+template <int BITS, int G, int DT, bool DENSE, bool XF>
+__global__ __launch_bounds__(256) void compress_k_kernel(QuantBatch b)
 {
+    __shared__ __attribute__((aligned(16))) float xch_all[4 * kXchFloats];
     unsigned wg;
     const QuantArgs &a = b.item[batch_item(b, wg)];
+    compress_k_unit<BITS, G, DT, DENSE, XF>(a, wg, xch_all);
+}
+
+// `refused()`: the request's payload does not fit the plan; asked once everything a unit reads is requested.
+// XF = false leaves the inverse transforms out.
+template <int BITS, int DT, bool DENSE, bool XF, class Refused>
+__device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned wg, Refused &&refused)
+{
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
-    if (*a.status & KVC_DEV_BAD_HEADER) return;
     const int col = lane_id() & 15;
     const long long row0 = u.blk * kPassRows;
     const long long tb = row0 / a.group, nb = (a.tokens + a.group - 1) / a.group;
@@ -64,22 +69,32 @@ __global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
     const int rows = left < kPassRows ? (int)left : kPassRows;
     PassFetch f;
     pass_fetch<BITS, DENSE, 0>(f, codes, a.x, u.head_off, row0, rows);
+    if (refused()) return;
     float scale[8], zero[8];
     const bool clamp = k_meta_floats<BITS, DT>(m0, m1, scale, zero);
     bool bad = false;
-    dequant_pass_any<BITS, DT, false, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
-                                             a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
-                                             a.anchor_shift);
+    if (XF)
+        dequant_pass_any<BITS, DT, false, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
+                                                 a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
+                                                 a.anchor_shift);
+    else dequant_pass<BITS, DT, false, DENSE, 0>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
     report(a.status, bad);
+}
+
+template <int BITS, int DT, bool DENSE>
+__global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
+{
+    unsigned wg;
+    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const int status = *a.status;
+    decompress_k_unit<BITS, DT, DENSE, true>(a, wg, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
 }
 
 // ---- V: groups along channels, one set per token -----------------------------------------------
 
-template <int BITS, int GV, int DT, bool DENSE>
-__global__ __launch_bounds__(256) void compress_v_kernel(QuantBatch b)
+template <int BITS, int GV, int DT, bool DENSE, bool XF>
+__device__ __forceinline__ void compress_v_unit(const QuantArgs &a, unsigned wg)
 {
-    unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
     constexpr int NG = kDim / GV;
@@ -87,8 +102,8 @@ __global__ __launch_bounds__(256) void compress_v_kernel(QuantBatch b)
     bool bad = false;
     u32x4 raw[8];
     load_pass<DENSE>(a.x, u.head_off, row0, a.tokens, raw, bad);
-    if (a.rotate) rotate_rows<DT, 8>(raw);
-    if (a.anchors)
+    if (XF && a.rotate) rotate_rows<DT, 8>(raw);
+    if (XF && a.anchors)
         delta_rows<DT, DENSE, 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,
                                  head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift), true, raw, bad);
     VParams vp;
@@ -101,14 +116,19 @@ __global__ __launch_bounds__(256) void compress_v_kernel(QuantBatch b)
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE>
-__global__ __launch_bounds__(256) void decompress_v_kernel(QuantBatch b)
+template <int BITS, int GV, int DT, bool DENSE>
+__global__ __launch_bounds__(256) void compress_v_kernel(QuantBatch b)
 {
     unsigned wg;
     const QuantArgs &a = b.item[batch_item(b, wg)];
+    compress_v_unit<BITS, GV, DT, DENSE, true>(a, wg);
+}
+
+template <int BITS, int DT, bool DENSE, bool XF, class Refused>
+__device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned wg, Refused &&refused)
+{
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
-    if (*a.status & KVC_DEV_BAD_HEADER) return;
     const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
     const long long row0 = u.blk * kPassRows;
     const int lanes_shift = a.group == 32 ? 2 : (a.group == 64 ? 3 : 4), ng = kDim / a.group;
@@ -121,13 +141,65 @@ __global__ __launch_bounds__(256) void decompress_v_kernel(QuantBatch b)
     uint8_t *codes = head_codes<BITS>(a, u.lh) + row0 * (16 * BITS);
     PassFetch f;
     pass_fetch<BITS, DENSE, 0>(f, codes, a.x, u.head_off, row0, rows);
+    if (refused()) return;
     float scale[8], zero[8];
     const bool clamp = v_meta_floats<BITS, DT>(mw, scale, zero);
     bool bad = false;
-    dequant_pass_any<BITS, DT, true, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
-                                            a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
-                                            a.anchor_shift);
+    if (XF)
+        dequant_pass_any<BITS, DT, true, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
+                                                a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
+                                                a.anchor_shift);
+    else dequant_pass<BITS, DT, true, DENSE, 0>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
     report(a.status, bad);
+}
+
+template <int BITS, int DT, bool DENSE>
+__global__ __launch_bounds__(256) void decompress_v_kernel(QuantBatch b)
+{
+    unsigned wg;
+    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const int status = *a.status;
+    decompress_v_unit<BITS, DT, DENSE, true>(a, wg, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
+}
+
+// ---- a whole small call in one launch -------------------------------------------------------------
+
+// Items 2r and 2r + 1 of the batch are K and V of request r; the first workgroups are the requests' prologues,
+// which nothing in the launch waits for (the requests have no block table, so no unit has anything to
+// report in the status word).  A call of 4 MB is launches and latency: prologue, K and V in turn were
+// 1.6 + 5 + 4.8 us of kernels, 16 us per call; together 8.3.
+template <int BITS, int G, int DT, bool DENSE>
+__global__ __launch_bounds__(256) void compress_call_kernel(SmallCompressArgs b)
+{
+    __shared__ __attribute__((aligned(16))) float xch_all[4 * kXchFloats];
+    if (blockIdx.x < (unsigned)b.requests) {
+        write_prologue(b.prologue[blockIdx.x], threadIdx.x, 256);
+        return;
+    }
+    unsigned wg;
+    const int i = batch_item(b, wg);
+    if (i & 1) compress_v_unit<BITS, G, DT, DENSE, false>(b.item[i], wg);
+    else compress_k_unit<BITS, G, DT, DENSE, false>(b.item[i], wg, xch_all);
+}
+
+// The same for decompression: every wave compares the header with the plan's for itself (its 128 bytes travel
+// with the unit's own loads), the request's first workgroup writes the status word.
+template <int BITS, int DT, bool DENSE>
+__global__ __launch_bounds__(256) void decompress_call_kernel(SmallDecompressArgs b)
+{
+    unsigned wg;
+    const int i = blockIdx.x < (unsigned)b.requests ? 2 * (int)blockIdx.x : batch_item(b, wg);
+    const SmallCheck &check = b.check[i >> 1];
+    const int word = lane_id() & 31;
+    const uint32_t got = check.payload[word];
+    auto refused = [&]() { return __builtin_amdgcn_ballot_w64(got != check.expect.w[word]) != 0; };
+    if (blockIdx.x < (unsigned)b.requests) {
+        const bool bad = refused();
+        if (threadIdx.x == 0) *b.item[i].status = bad ? KVC_DEV_BAD_HEADER : 0;
+        return;
+    }
+    if (i & 1) decompress_v_unit<BITS, DT, DENSE, false>(b.item[i], wg, refused);
+    else decompress_k_unit<BITS, DT, DENSE, false>(b.item[i], wg, refused);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
@@ -181,6 +253,45 @@ int KVC_PASTE(launch_compress_bits, KVC_BITS)(int is_v, int group, int dtype, co
 int KVC_PASTE(launch_decompress_bits, KVC_BITS)(int is_v, int dtype, const QuantBatch &b, hipStream_t s)
 {
     return b.item[0].dense ? decompress_bits_dense<KVC_BITS, true>(is_v, dtype, b, s) : decompress_bits_dense<KVC_BITS, false>(is_v, dtype, b, s);
+}
+
+// units of four per workgroup behind the workgroups of the requests themselves
+template <class Args> static unsigned place_call(Args &b)
+{
+    unsigned at = (unsigned)b.requests;
+    for (int i = 0; i < b.n; ++i) {
+        b.start[i] = at;
+        at += (unsigned)((b.item[i].total_units + 3) / 4);
+    }
+    b.start[b.n] = at;
+    return at;
+}
+
+template <int G> static void compress_call(int dtype, const SmallCompressArgs &b, unsigned wgs, hipStream_t s)
+{
+#define KVC_CALL(DT, D) hipLaunchKernelGGL((compress_call_kernel<KVC_BITS, G, DT, D>), dim3(wgs), dim3(256), 0, s, b)
+    if (b.item[0].dense) { if (dtype == DT_F16) KVC_CALL(DT_F16, true); else KVC_CALL(DT_BF16, true); }
+    else if (dtype == DT_F16) KVC_CALL(DT_F16, false); else KVC_CALL(DT_BF16, false);
+#undef KVC_CALL
+}
+
+int KVC_PASTE(launch_compress_call_bits, KVC_BITS)(int group, int dtype, SmallCompressArgs &b, hipStream_t s)
+{
+    const unsigned wgs = place_call(b);
+    if (group == 32) compress_call<32>(dtype, b, wgs, s);
+    else if (group == 64) compress_call<64>(dtype, b, wgs, s);
+    else compress_call<128>(dtype, b, wgs, s);
+    return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
+}
+
+int KVC_PASTE(launch_decompress_call_bits, KVC_BITS)(int dtype, SmallDecompressArgs &b, hipStream_t s)
+{
+    const unsigned wgs = place_call(b);
+#define KVC_CALL(DT, D) hipLaunchKernelGGL((decompress_call_kernel<KVC_BITS, DT, D>), dim3(wgs), dim3(256), 0, s, b)
+    if (b.item[0].dense) { if (dtype == DT_F16) KVC_CALL(DT_F16, true); else KVC_CALL(DT_BF16, true); }
+    else if (dtype == DT_F16) KVC_CALL(DT_F16, false); else KVC_CALL(DT_BF16, false);
+#undef KVC_CALL
+    return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }
 
 }  // namespace kvc

@@ -87,6 +87,28 @@ int launch_decompress_tensor(int is_v, int bits, int group, int dtype, const Qua
     return KVC_ERR_UNSUPPORTED;
 }
 
+int launch_compress_call(int bits, int group, int dtype, SmallCompressArgs &b, hipStream_t s)
+{
+    switch (bits) {
+    case 2: return launch_compress_call_bits2(group, dtype, b, s);
+    case 3: return launch_compress_call_bits3(group, dtype, b, s);
+    case 4: return launch_compress_call_bits4(group, dtype, b, s);
+    case 8: return launch_compress_call_bits8(group, dtype, b, s);
+    }
+    return KVC_ERR_UNSUPPORTED;
+}
+
+int launch_decompress_call(int bits, int dtype, SmallDecompressArgs &b, hipStream_t s)
+{
+    switch (bits) {
+    case 2: return launch_decompress_call_bits2(dtype, b, s);
+    case 3: return launch_decompress_call_bits3(dtype, b, s);
+    case 4: return launch_decompress_call_bits4(dtype, b, s);
+    case 8: return launch_decompress_call_bits8(dtype, b, s);
+    }
+    return KVC_ERR_UNSUPPORTED;
+}
+
 int launch_compress_prologue(const PrologueArgs &a, hipStream_t s)
 {
     long long most = 1;

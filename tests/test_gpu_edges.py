@@ -148,3 +148,47 @@ def test_both_tensors_of_many_paged_requests(ref, group):
         back = np.zeros_like(xu)
         assert ref.decompress(want, back[0, 0], back[0, 1], lay, cfg) == 0
         assert np.array_equal(kvgen.as_u16(kvgen.from_paged(outs[i].cpu(), tabs[i], T)), back), i
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("strided", [False, True])
+def test_small_calls_in_one_launch(ref, group, bits, dtype, strided):
+    """Calls of one to four requests whose prologue, K and V are one launch: lengths around a unit, an empty request,
+    rows of a head apart from each other, and a header that does not fit, which leaves its request alone."""
+    L, H = 2, 3
+    lens = [33, 0, 130, 1]
+    plan = kvc.Plan(kvc.F16 if dtype == torch.float16 else kvc.BF16, L, H, 128, bits, bits, group, group, 0,
+                    max_tokens=max(lens), max_batch=len(lens))
+    xs = [kvgen.make_kv(900 + i, L, H, 128, max(T, 1), dtype) for i, T in enumerate(lens)]
+
+    def place(x):
+        """[L, 2, H, T, 128] on the GPU, for `strided` with a gap of 64 elements behind every row."""
+        wide = torch.full(x.shape[:4] + (192 if strided else 128,), 5.0, dtype=x.dtype, device="cuda")
+        wide[..., :128] = x.cuda()
+        return wide[..., :128]
+
+    xd = [place(x) for x in xs]
+    buf = gpu_compress(plan, [kvc.contiguous_request(x, T) for x, T in zip(xd, lens)], lens)
+    assert buf.status.tolist() == [0] * len(lens)
+    cfg = ref.config(dtype=1 if dtype == torch.float16 else 2, layers=L, heads=H, bits_k=bits, bits_v=bits, group_k=group,
+                     group_v=group)
+    want = []
+    for i, (x, T) in enumerate(zip(xs, lens)):
+        xu = kvgen.as_u16(x)
+        lay = ref.contiguous_layout(H, max(T, 1), 128)
+        pay = ref.compress(cfg, xu[0, 0], xu[0, 1], lay, T)
+        assert np.array_equal(buf.payload_of(i), pay), i
+        back = np.full_like(xu, 0x4700)                    # 7.0 in fp16
+        assert ref.decompress(pay, back[0, 0], back[0, 1], lay, cfg) == 0
+        want.append(back)
+    buf.payload[buf.offsets[2] + 22] += 1                  # the K group in a header
+    yd = [place(torch.from_numpy(np.full(x.shape, 0x4700, np.int16)).view(x.dtype)) for x in xs]
+    buf.status.fill_(77)
+    buf.decompress([kvc.contiguous_request(y, T) for y, T in zip(yd, lens)], torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert buf.status.tolist() == [0, 0, kvc.DEV_BAD_HEADER, 0]
+    for i, y in enumerate(yd):
+        got = kvgen.as_u16(y.cpu().contiguous())
+        assert np.array_equal(got, want[i] if i != 2 else np.full_like(got, 0x4700)), i
