@@ -587,6 +587,25 @@ static bool share_kv(const kvc_plan_t *p, const kvc_request *lead)
     return tensors_share(p) && rows < (p->strat.group_k == 32 ? 4 * kSmallRows : kSmallRows);
 }
 
+// The decoder has no order to keep and takes the group as a run-time value, so there K and V share a launch for
+// every width that both have: also with different groups, and with width tables (half of the heads at
+// 8 bits, half at 2, 2^21 rows: decompress call 411 us with K and V apart, 367 together).
+static bool common_width(const kvc_plan_t *p)
+{
+    for (int w = 0; w < 4; ++w) {
+        bool both = true;
+        for (int is_v = 0; is_v < 2; ++is_v)
+            both &= p->has_table[is_v] ? p->width_count[is_v][w] > 0 : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k);
+        if (both) return p->strat.transform == KVC_T_NONE;
+    }
+    return false;
+}
+
+static bool widths_share(const kvc_plan_t *p, const kvc_request *lead)
+{
+    return common_width(p) && (long long)p->model.layers * p->model.kv_heads * lead->tokens < 4 * kSmallRows;
+}
+
 // Chunks per workgroup of such an encoder launch (0: the usual number): eight where all chunks of the window
 // are resident at once and the usual number would queue for more than 256 tickets, which are one after the
 // other (one layer as above: 74 us per call with four, 69 with eight); with more work the tickets hide
@@ -1069,7 +1088,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
-    const int coder_limit = tensors_share(plan) ? kCoderBatch / 2 : kCoderBatch;
+    const int coder_limit = common_width(plan) ? kCoderBatch / 2 : kCoderBatch;
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
@@ -1094,8 +1113,20 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                           (const uint8_t *)workspace, cl[k]);
             }
             marks.window(first, end, 1);
-            if (share_kv(plan, &dst[lead])) {
-                KVC_TRY(launch_decode_section(2, cl[0][0].bits, dt, coder_batch_both(cl, end - first), s));
+            if (widths_share(plan, &dst[lead])) {
+                // width by width, K and V together
+                for (int w = 0; w < 4; ++w) {
+                    CoderBatch b;
+                    memset(&b, 0, sizeof b);
+                    int kinds = 0;                        // bit 0: K, bit 1: V
+                    for (int k = 0; k < end - first; ++k)
+                        for (int j = 0; j < launches; ++j)
+                            if (cl[k][j].bits == kWidths[3 - w]) {
+                                b.item[b.n++] = cl[k][j].a;
+                                kinds |= 1 << cl[k][j].a.is_v;
+                            }
+                    if (b.n > 0) KVC_TRY(launch_decode_section(kinds == 3 ? 2 : kinds - 1, kWidths[3 - w], dt, b, s));
+                }
                 marks.window(first, end, 2);
                 marks.window(first, end, 3);
                 first = end;
