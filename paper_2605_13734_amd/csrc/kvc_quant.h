@@ -59,12 +59,28 @@ static inline unsigned place_items(QuantBatch &b)
     return at;
 }
 
-#define KVC_LAUNCH(kernel, batch, s)                                                    \
-    do {                                                                                \
-        QuantBatch placed_ = batch;                                                     \
-        const unsigned wgs_ = place_items(placed_);                                     \
-        if (wgs_ > 0) hipLaunchKernelGGL(kernel, dim3(wgs_), dim3(256), 0, s, placed_); \
-        return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;               \
+// Dynamic LDS that nothing uses: it bounds the workgroups of a compute unit, and with them the window of the
+// tensor that the chip reads or writes at a time (a wave's rows are 8 KB), which memory takes better when it
+// is small.  Launches without a transform only: its arithmetic needs the waves.  Call times with the registers as
+// the only bound, with 32000, 40000 and 53000 bytes:
+//   decompress  70B shape (half)  f16 4 bits       1186  1180  1188  1290      94 layers bf16 4/2 bits  1026  1021   992  1081
+//               8B shape bf16 2 bits                193   187   183   182      paged f16 4 bits         1300  1302  1281  1258
+//   compress    70B shape (half)  f16 4 bits       1176  1162  1153  1204      94 layers bf16 4/2 bits  1013  1015  1003  1012
+//               8B shape bf16 2 bits                223   222   220   233      paged f16 4 bits         1232  1209  1249  1401
+//   with the rotation, compress / decompress     291/259 294/260 296/267 333/281
+static inline unsigned window_lds(const QuantBatch &b, bool compress)
+{
+    const QuantArgs &a = b.item[0];
+    if (a.rotate || a.anchors) return 0;
+    return compress && !a.dense ? 32000 : 40000;
+}
+
+#define KVC_LAUNCH(kernel, batch, lds, s)                                                 \
+    do {                                                                                  \
+        QuantBatch placed_ = batch;                                                       \
+        const unsigned wgs_ = place_items(placed_);                                       \
+        if (wgs_ > 0) hipLaunchKernelGGL(kernel, dim3(wgs_), dim3(256), lds, s, placed_); \
+        return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;                 \
     } while (0)
 
 }  // namespace kvc

@@ -210,19 +210,19 @@ template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, in
     if (!is_v) {
         const bool xf = a.rotate || a.anchors;
         switch (group) {
-        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, s);
+        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, window_lds(b, true), s);
         case 64:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, window_lds(b, true), s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, window_lds(b, true), s);
         case 128:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, window_lds(b, true), s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, window_lds(b, true), s);
         }
     } else {
         switch (group) {
-        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, s);
-        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, s);
-        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, s);
+        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, window_lds(b, true), s);
+        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, window_lds(b, true), s);
+        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, window_lds(b, true), s);
         }
     }
     return KVC_ERR_UNSUPPORTED;
@@ -231,11 +231,11 @@ template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, in
 template <int BITS, bool DENSE> static int decompress_bits_dense(int is_v, int dtype, const QuantBatch &b, hipStream_t s)
 {
     if (!is_v) {
-        if (dtype == DT_F16) KVC_LAUNCH((decompress_k_kernel<BITS, DT_F16, DENSE>), b, s);
-        KVC_LAUNCH((decompress_k_kernel<BITS, DT_BF16, DENSE>), b, s);
+        if (dtype == DT_F16) KVC_LAUNCH((decompress_k_kernel<BITS, DT_F16, DENSE>), b, window_lds(b, false), s);
+        KVC_LAUNCH((decompress_k_kernel<BITS, DT_BF16, DENSE>), b, window_lds(b, false), s);
     }
-    if (dtype == DT_F16) KVC_LAUNCH((decompress_v_kernel<BITS, DT_F16, DENSE>), b, s);
-    KVC_LAUNCH((decompress_v_kernel<BITS, DT_BF16, DENSE>), b, s);
+    if (dtype == DT_F16) KVC_LAUNCH((decompress_v_kernel<BITS, DT_F16, DENSE>), b, window_lds(b, false), s);
+    KVC_LAUNCH((decompress_v_kernel<BITS, DT_BF16, DENSE>), b, window_lds(b, false), s);
 }
 
 #define KVC_PASTE2(a, b) a##b
