@@ -87,8 +87,8 @@ __device__ __forceinline__ ChunkPos chunk_pos(const QuantArgs &a, long long chun
     return c;
 }
 
-// Quantize and pack the chunk's rows into the wave's LDS region (sub-block layout) and,
-// when `write_meta`, store the group metadata to the payload.  K group parameters are
+// Quantize and pack the chunk's rows into the wave's LDS region (sub-block layout) and
+// store the group metadata to the payload.  K group parameters are
 // exchanged through the 16 padding bytes that follow each sub-block.
 // XF = false leaves the code of stage T out (for launches that have no transform): in one kernel
 // with the plain path it costs the plain path its registers, most of all for token blocks of 64
@@ -102,7 +102,7 @@ template <int BITS, int G, int DT, bool IS_V> struct UnitGeom {
 // packed; their codes go to the rows lds_row0 ... of the LDS region.
 template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF = true>
 __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos &c, int u, uint8_t *lds, int lds_row0,
-                                              bool write_meta, bool &bad, bool have_blocks = false, const int *blocks = nullptr)
+                                              bool &bad, bool have_blocks = false, const int *blocks = nullptr)
 {
     constexpr int RU = UnitGeom<BITS, G, DT, IS_V>::kRows, PU = UnitGeom<BITS, G, DT, IS_V>::kPasses;
     const long long row0 = c.row0 + u * RU;
@@ -113,11 +113,11 @@ __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos
     if (XF && a.rotate) rotate_rows<DT, PU * 8>(raw);
     if (XF && a.anchors)
         delta_rows<DT, DENSE, PU * 8>(a.x, c.head_off, row0, a.tokens, a.anchor_shift,
-                                      head_anchors(a.anchors, c.lh, a.tokens, a.anchor_shift), write_meta, raw, bad);
+                                      head_anchors(a.anchors, c.lh, a.tokens, a.anchor_shift), true, raw, bad);
     if (!IS_V) {
         const long long nb = (a.tokens + G - 1) / G;
         KParams kp;
-        uint8_t *meta_block = write_meta ? a.meta + (c.lh * nb + row0 / G) * (kDim * 4) : nullptr;
+        uint8_t *meta_block = a.meta + (c.lh * nb + row0 / G) * (kDim * 4);
         k_group_params<BITS, DT, PU * 8, ChunkGeom<BITS>::kSubStride>(raw, lds + ChunkGeom<BITS>::kSubBytes, meta_block, kp);
         forget_unpacked<DT, PU * 8>(raw);
         k_emit<BITS, DT, PU, true>(raw, kp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU);
@@ -126,14 +126,13 @@ __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos
         VParams vp;
         v_pass_params<BITS, G, DT>(raw, vp);
         forget_unpacked<DT, PU * 8>(raw);
-        uint32_t *meta = write_meta ? (uint32_t *)a.meta + (c.lh * a.tokens + row0) * NG : nullptr;
+        uint32_t *meta = (uint32_t *)a.meta + (c.lh * a.tokens + row0) * NG;
         v_emit<BITS, G, DT, true>(raw, vp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU, meta);
     }
 }
 
 template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF = true>
-__device__ __forceinline__ void quantize_chunk(const QuantArgs &a, const ChunkPos &c, uint8_t *lds, bool write_meta,
-                                               bool &bad)
+__device__ __forceinline__ void quantize_chunk(const QuantArgs &a, const ChunkPos &c, uint8_t *lds, bool &bad)
 {
     constexpr int RU = UnitGeom<BITS, G, DT, IS_V>::kRows, NU = UnitGeom<BITS, G, DT, IS_V>::kUnits;
     constexpr int PU = UnitGeom<BITS, G, DT, IS_V>::kPasses;
@@ -149,7 +148,7 @@ __device__ __forceinline__ void quantize_chunk(const QuantArgs &a, const ChunkPo
 #pragma unroll
             for (int p = 0; p < PU; ++p) blocks_next[p] = pass_blocks(a.x, c.row0 + (u + 1) * RU + p * kPassRows, a.tokens);
         }
-        quantize_unit<BITS, G, DT, IS_V, DENSE, XF>(a, c, u, lds, u * RU, write_meta, bad, paged, blocks);
+        quantize_unit<BITS, G, DT, IS_V, DENSE, XF>(a, c, u, lds, u * RU, bad, paged, blocks);
 #pragma unroll
         for (int p = 0; p < PU; ++p) blocks[p] = blocks_next[p];
     }

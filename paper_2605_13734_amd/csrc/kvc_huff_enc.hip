@@ -253,8 +253,8 @@ void encode_kernel(CoderBatch batch)
         ChunkPos c = chunk_pos(a.q, chunk);
         rows = c.rows;
         bool bad = false;
-        if (KV == 2 ? second != 0 : KV == 1) quantize_chunk<BITS, G, DT, true, DENSE, XF>(a.q, c, lds, true, bad);
-        else quantize_chunk<BITS, G, DT, false, DENSE, XF>(a.q, c, lds, true, bad);
+        if (KV == 2 ? second != 0 : KV == 1) quantize_chunk<BITS, G, DT, true, DENSE, XF>(a.q, c, lds, bad);
+        else quantize_chunk<BITS, G, DT, false, DENSE, XF>(a.q, c, lds, bad);
         if (bad) atomicOr(a.q.status, KVC_DEV_BAD_BLOCK);
         wave_sync();
         load_sub<BITS>(lds, sym);

@@ -159,7 +159,7 @@ struct KParams {
 // Parameters of the 128 per-channel groups of one token block.  Each of the four lanes that
 // share a channel octet computes two channels, stores their metadata (scale, zero as fp16)
 // and publishes (zero, 1/scale) through 64 LDS slots of 16 bytes, XSTRIDE bytes apart, at `xch`.
-// meta_block: the 512 bytes of this token block's metadata, or null to skip the store.
+// meta_block: the 512 bytes of this token block's metadata.
 template <int BITS, int DT, int N, int XSTRIDE>
 __device__ __forceinline__ void k_group_params(const u32x4 *raw, uint8_t *xch, uint8_t *meta_block, KParams &kp)
 {
@@ -168,12 +168,10 @@ __device__ __forceinline__ void k_group_params(const u32x4 *raw, uint8_t *xch, u
     k_stats_own<DT, N>(raw, mn2, mx2);
     const GroupParams g0 = make_group<BITS, DT>(mn2[0], mx2[0]);
     const GroupParams g1 = make_group<BITS, DT>(mn2[1], mx2[1]);
-    if (meta_block) {
-        u32x2 m;
-        m[0] = g0.meta;
-        m[1] = g1.meta;
-        put_at<true>(meta_block + (col * 8 + rsub * 2) * 4, m);
-    }
+    u32x2 m;
+    m[0] = g0.meta;
+    m[1] = g1.meta;
+    put_at<true>(meta_block + (col * 8 + rsub * 2) * 4, m);
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     f32x4 mine = {g0.zero, g0.inv, g1.zero, g1.inv};
     wave_sync();                                  // earlier readers of xch are done
@@ -365,7 +363,7 @@ template <int BITS, int GV, int DT, bool SUB>
 __device__ __forceinline__ void v_emit(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows, uint32_t *meta)
 {
     const bool full = rows >= kPassRows;
-    if (meta) v_store_meta<GV>(vp, rows, meta);
+    v_store_meta<GV>(vp, rows, meta);
     if (vp.clamp) {
         if (full) v_emit_rows<BITS, GV, DT, SUB, true, true>(raw, vp, base, rows);
         else v_emit_rows<BITS, GV, DT, SUB, true, false>(raw, vp, base, rows);
