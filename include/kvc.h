@@ -195,7 +195,7 @@ int kvc_compress(const kvc_plan_t *plan, const kvc_request *reqs, int32_t n, voi
 /*
  * kvc_compress for callers that cannot allocate device memory and have no workspace to hand in:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments and results as kvc_compress, without the workspace: the coder's scratch (histograms,
+ * arguments and results as kvc_compress, without the workspace: the coder's scratch (byte counts,
  * code tables, work-order counter, chunk-offset scan state) lives in a static device array of
  * KVC_STATIC_WORKSPACE_BYTES inside the library, one copy per GPU, held until the process ends.
  * The call allocates nothing and clears what must start from zero itself.
