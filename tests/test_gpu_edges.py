@@ -192,3 +192,55 @@ def test_small_calls_in_one_launch(ref, group, bits, dtype, strided):
     for i, y in enumerate(yd):
         got = kvgen.as_u16(y.cpu().contiguous())
         assert np.array_equal(got, want[i] if i != 2 else np.full_like(got, 0x4700)), i
+
+
+@pytest.mark.parametrize("codec", [0, 1])
+def test_shared_launches_under_capture(codec):
+    """The one-launch calls recorded into a graph: every replay, with new inputs in the same buffers and eager work
+    in between, gives what the eager call gives."""
+    L, H, T = 2, 4, 128 * 5 + 9
+    plan = kvc.Plan(kvc.F16, L, H, 128, 4, 4, 32, 32, codec, max_tokens=T)
+    x = kvgen.make_kv(950, L, H, 128, T, torch.float16, "cuda")
+    y = torch.zeros_like(x)
+    buf, eager = kvc.Buffers(plan, [T]), kvc.Buffers(plan, [T])
+    out = torch.zeros_like(x)
+
+    def run(b, dst, stream):
+        b.compress([kvc.contiguous_request(x)], stream)
+        b.decompress([kvc.contiguous_request(dst)], stream)
+
+    run(buf, y, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        run(buf, y, side.cuda_stream)
+    for rep in range(4):
+        x.copy_(kvgen.make_kv(951 + rep, L, H, 128, T, torch.float16, "cuda"))
+        for t in (buf.payload, eager.payload, y, out):
+            t.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        run(eager, out, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int(buf.status[0]) == 0 and int(eager.status[0]) == 0
+        assert int(buf.out_bytes[0]) == int(eager.out_bytes[0])
+        assert torch.equal(buf.payload, eager.payload) and torch.equal(y, out), rep
+
+
+def test_calls_on_two_streams():
+    """Encoder launches that wait for their own workgroups, on two streams at once: each as it is alone."""
+    L, H, T, calls = 1, 8, 8192, 12
+    plan = kvc.Plan(kvc.F16, L, H, 128, 4, 4, 32, 32, 1, max_tokens=T)
+    xs = [kvgen.make_kv(970 + i, L, H, 128, T, torch.float16, "cuda") for i in range(calls)]
+    bufs = [kvc.Buffers(plan, [T]) for _ in xs]
+    alone = kvc.Buffers(plan, [T])
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for i, x in enumerate(xs):
+        bufs[i].compress([kvc.contiguous_request(x)], streams[i % 2].cuda_stream)
+    torch.cuda.synchronize()
+    for i, x in enumerate(xs):
+        alone.compress([kvc.contiguous_request(x)], torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int(bufs[i].status[0]) == 0 and int(alone.status[0]) == 0
+        assert np.array_equal(bufs[i].payload_of(0), alone.payload_of(0)), i
