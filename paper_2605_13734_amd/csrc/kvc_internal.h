@@ -205,8 +205,9 @@ __device__ __forceinline__ CandidateTables *candidate_tables(uint16_t *lut, int 
 constexpr int enc_waves(int bits) { return bits == 8 ? 2 : 4; }
 
 // Waves per SIMD the register allocation must leave room for: the variants that come close to 128 registers
-// by themselves (2- to 4-bit codes, groups of 32, the dense layout or both tensors together; not the V kernels with the transforms for
-// bf16 rows or 3-bit codes) are held to four; the others would spill, so they keep what they need.
+// by themselves (2- to 4-bit codes, groups of 32, the dense layout or both tensors together; not the V
+// kernels with the transforms for bf16 rows or 3-bit codes) are held to four; the others would spill, so
+// they keep what they need.
 // `transform`: the launch applies stage T.
 constexpr int enc_min_waves(int bits, int group, int dtype, bool dense, bool is_v, bool transform)
 {
