@@ -278,13 +278,16 @@ int kvc_stream_probe(int mode, const void *src, void *dst, int64_t rows, int32_t
 
 /*
  * Device self-test of the quantizer's arithmetic shortcuts (stage Q of section 5.1 fixes the
- * results; the kernels reach them with cheaper instruction sequences).  Each count is the
+ * results; the kernels reach them with cheaper instruction sequences) and of the waits of the
+ * lossless stage's encoder.  Each of the first seven counts is the
  * number of inputs, over the whole domain a shortcut is used on, for which it differs from
  * the plain IEEE operation; every count must be zero.
  *   counts[0..3]  min((max - min) / (2^b - 1), 65504) for b = 2, 3, 4, 8: all floats >= 0 and +infinity
  *   counts[4]     1 / scale: all positive finite fp16 scales
  *   counts[5]     x - zero read from a packed fp16 pair: all pairs of finite fp16 values
  *   counts[6]     float -> byte with insertion: round-to-nearest-even, all floats in [0, 255]
+ *   counts[7]     workgroups of the encoder's prefix sum that do not end as they should when one of them
+ *                 starts late (the device memory of this check is static: one self-test at a time per GPU)
  * `counts` is DEVICE memory, KVC_SELFTEST_COUNTS 64-bit words, 8-byte aligned, owned by the
  * caller; it is cleared and filled on `stream` (asynchronous: synchronize before reading).
  * Returns KVC_OK, KVC_ERR_ARG for a null pointer, KVC_ERR_DEVICE if a launch failed.

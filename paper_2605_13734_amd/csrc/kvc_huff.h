@@ -23,14 +23,6 @@
 
 namespace kvc {
 
-// Scan state of an encode workgroup: 0, then (bits 63:62 = 1) the sum of its chunks' sizes, then (2) the
-// sum of all sizes before it, both in 16-byte units.
-constexpr unsigned long long kFlagSize = 1ull << 62, kFlagPrefix = 2ull << 62, kValueMask = (1ull << 40) - 1;
-constexpr unsigned long long kNoPlace = kValueMask;      // (a scan that gave up)
-constexpr int kScanWindows = 4;
-constexpr int kScanCarry = 4;      // word of the ticket's block where the scan of one launch leaves its end to the next
-constexpr int kSpinLimit = 1 << 20;
-
 template <int BITS> struct ChunkGeom {
     static constexpr int kRowBytes = 16 * BITS;            // packed bytes of one token row
     static constexpr int kSubBytes = 2 * kRowBytes;        // one sub-block

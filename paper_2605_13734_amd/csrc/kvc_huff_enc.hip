@@ -1,8 +1,9 @@
 // Lossless stage, encoder: quantize + pack + Huffman-code one chunk per wave and place the body
 // through a single-pass prefix sum over workgroups.  Compiled once per code width (-DKVC_BITS=2, 3,
-// 4 or 8).  See kvc_huff.h for the format and the division of work.
+// 4 or 8).  See kvc_huff.h for the format and the division of work, kvc_scan.h for
+// the prefix sum.
 
-#include "kvc_huff.h"
+#include "kvc_scan.h"
 
 #ifndef KVC_BITS
 #error "compile with -DKVC_BITS=2, 3, 4 or 8"
@@ -94,77 +95,6 @@ template <int W> __device__ __forceinline__ void encode_two(const uint32_t *sym,
             if (b & 1) { flush(b0); flush(b1); }
         }
     }
-}
-
-// One workgroup = kWaves chunks.  A chunk's body offset is the sum of all earlier bodies of the
-// request (K chunks first, then V): a single-pass scan over one state word per workgroup, made by one
-// wave per request, the scanner.  Workgroups take a ticket from a counter; as soon as the sizes of its
-// chunks are known, before a code word is written, a workgroup leaves their sum in its state word; the
-// scanner walks the words in ticket order and puts the prefix in their place; the waves of the
-// workgroup, by then mostly done with the code words, pick it up.  The scanner is the first wave of the
-// workgroup with the launch's first ticket, and ticket order guarantees that every predecessor of a
-// workgroup is already running, so the waits always end; they are bounded by kSpinLimit all the same.
-// (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
-// hundreds of waves polling the same lines of memory.  70B shape, half of its layers, compress call: 1369 us
-// with eight chunks per workgroup, now 1213; 2-bit codes / groups of 128 1370 -> 1135, 8 bits (a quarter of
-// the layers) 1235 -> 1058.  With the bodies at fixed places, nothing to wait for, 1165.)
-
-// The scan of one request's launch, whose last workgroup is `end` - 1; the last launch's scanner closes
-// the directory and the header.
-__device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end)
-{
-    const int lane = lane_id();
-    unsigned long long *carry = (unsigned long long *)(a.ws.ticket + kScanCarry);      // units before this launch; units of K
-    unsigned long long prefix = carry[0], k_units = carry[1];
-    int spins = 0;
-    __builtin_amdgcn_s_setprio(3);
-    // kScanWindows windows of 64 workgroups per look (a look is a round trip to memory, and the scanner has to
-    // keep up with all workgroups of the chip)
-    for (long long next = a.wg_base; next < end;) {
-        unsigned long long v[kScanWindows];
-#pragma unroll
-        for (int k = 0; k < kScanWindows; ++k) {
-            const long long j = next + 64 * k + lane;
-            v[k] = j < end ? __hip_atomic_load(&a.ws.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-        }
-        bool moved = false, open = true;
-        const long long base = next;
-#pragma unroll
-        for (int k = 0; k < kScanWindows; ++k) {
-            if (!open) continue;
-            const unsigned long long known = __builtin_amdgcn_ballot_w64((v[k] >> 62) == 1);
-            const int run = known == ~0ull ? 64 : __builtin_ctzll(~known);      // workgroups that have reported, up to the first gap
-            open = run == 64;
-            if (run == 0) continue;
-            const uint32_t size = lane < run ? (uint32_t)v[k] : 0;               // (a workgroup's bodies are at most 8 * 1024 units)
-            const uint32_t incl = wave_inclusive_sum(size);
-            if (lane < run)
-                __hip_atomic_store(&a.ws.state[base + 64 * k + lane], kFlagPrefix | (prefix + incl - size), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            const long long k_last = a.k_wgs - 1 - (base + 64 * k);              // the last K workgroup among these?
-            if (k_last >= 0 && k_last < run) k_units = prefix + (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)k_last);
-            prefix += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            next += run;
-            moved = true;
-        }
-        if (moved) spins = 0;
-        else if (++spins > kSpinLimit) {
-            if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
-            return;
-        }
-    }
-    if (lane != 0) return;
-    carry[0] = prefix;
-    carry[1] = k_units;
-    if (end != a.total_wgs) return;
-    ((uint32_t *)(a.payload + a.off_dir))[a.total_chunks] = (uint32_t)prefix;
-    const unsigned long long total = (unsigned long long)a.off_bodies + prefix * 16;
-    unsigned long long *h = (unsigned long long *)a.payload;
-    h[5] = total;                                   // byte 40: total bytes
-    h[13] = k_units * 16;                           // byte 104: K code bytes
-    h[14] = (unsigned long long)a.off_bodies + k_units * 16;   // byte 112: V code offset
-    h[15] = (prefix - k_units) * 16;                // byte 120: V code bytes
-    *a.out_bytes = total;
 }
 
 // KV: the launch's tensor, K (0), V (1) or both (2: the items of the batch are then a K and a V launch of
@@ -301,19 +231,11 @@ void encode_kernel(CoderBatch batch)
     // slow the scanner down.  (The first workgroup of the launch, whose first wave is the scanner, knows its
     // prefix: the end of the launch before.)
     unsigned long long excl;
-    int spins = 0;
     if (leads) {
         excl = before;
         while (wave > 0 && __hip_atomic_load(&s_reported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != (uint32_t)NW) __builtin_amdgcn_s_sleep(1);
     } else if (__builtin_amdgcn_readfirstlane(last_to_report)) {
-        while (((excl = __hip_atomic_load(&a.ws.state[ticket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 62) != 2) {
-            if (++spins > kSpinLimit) {
-                if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
-                excl = kFlagPrefix | kNoPlace;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
+        excl = wait_for_place(a, ticket);
         if (lane == 0) __hip_atomic_store(&s_excl, excl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {
         // (the polling wave always ends: it finds the prefix or its spin limit)

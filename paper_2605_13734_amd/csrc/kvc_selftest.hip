@@ -1,9 +1,8 @@
 // Exhaustive device-side checks of the arithmetic shortcuts the quantizer kernels rely on.
 // Each check counts, over the whole domain on which the kernels use a shortcut, the inputs for
 // which it differs from the plain IEEE operation it stands for; all counts must be zero.
-#include "kvc_device.h"
-#include "kvc_internal.h"
-#include "../../include/kvc.h"
+// The last count is for the waits of the encoder's prefix sum.
+#include "kvc_scan.h"
 
 namespace kvc {
 
@@ -86,6 +85,87 @@ __global__ __launch_bounds__(256) void selftest_byte_kernel(unsigned long long *
     count(slot, bad);
 }
 
+// ---- the waits of the encoder's prefix sum (kvc_scan.h), with a limit of about a millisecond ----------
+
+constexpr int kScanTestLimit = 1024;
+constexpr int kScanTestWgs = 3;                    // one K workgroup, two V workgroups, one wave each
+
+static __device__ struct ScanTestMemory {
+    unsigned long long state[8];
+    uint32_t ticket[64];
+    uint32_t payload[64];                          // header, then the directory
+    unsigned long long out_bytes;
+    int status;
+} scan_test;
+
+__device__ __forceinline__ CoderArgs scan_test_args()
+{
+    CoderArgs a = {};
+    a.payload = (uint8_t *)scan_test.payload;
+    a.off_dir = 128;
+    a.off_bodies = 256;
+    a.total_chunks = a.total_wgs = kScanTestWgs;
+    a.k_wgs = 1;
+    a.ws.state = scan_test.state;
+    a.ws.ticket = scan_test.ticket;
+    a.out_bytes = &scan_test.out_bytes;
+    a.q.status = &scan_test.status;
+    return a;
+}
+
+__device__ __forceinline__ unsigned long long scan_test_units(long long ticket) { return 5 + 10 * ticket; }
+
+__global__ __launch_bounds__(64) void selftest_scan_start_kernel()
+{
+    uint32_t *words = (uint32_t *)&scan_test;
+    for (unsigned i = threadIdx.x; i < sizeof scan_test / 4; i += 64) words[i] = 0;
+}
+
+// Waits (for a few seconds at most) until `ticket` is the next one, sleeps `naps` times 3 us, takes it and, unless
+// `silent`, reports a size.
+__device__ __forceinline__ bool scan_test_enter(const CoderArgs &a, unsigned ticket, int naps, bool silent)
+{
+    int spins = 0;
+    while (__hip_atomic_load(a.ws.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ticket) {
+        if (++spins > (1 << 20)) return false;
+        __builtin_amdgcn_s_sleep(32);
+    }
+    for (int i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(127);
+    if (lane_id() == 0) {
+        atomicAdd(a.ws.ticket, 1u);
+        if (!silent)
+            __hip_atomic_store(&a.ws.state[ticket], kFlagSize | scan_test_units(ticket), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return true;
+}
+
+// The last ticket of a launch is taken 20 ms after the others, as when other work holds the chip: the scanner
+// waits for it, however short its limit.
+__global__ __launch_bounds__(64) void selftest_scan_late_kernel(unsigned long long *slot)
+{
+    const CoderArgs a = scan_test_args();
+    const unsigned me = blockIdx.x;
+    bool good = scan_test_enter(a, me, me == 2 ? 6000 : 0, false);
+    if (good && me == 0) scan_sizes(a, kScanTestWgs, kScanTestLimit);
+    else if (good) {
+        unsigned long long before = 0;
+        for (unsigned i = 0; i < me; ++i) before += scan_test_units(i);
+        good = wait_for_place(a, me) == (kFlagPrefix | before);
+    }
+    if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
+}
+
+// ... and closes directory and header as if nothing had happened.
+__global__ __launch_bounds__(64) void selftest_scan_closed_kernel(unsigned long long *slot)
+{
+    if (threadIdx.x != 0) return;
+    const unsigned long long k = scan_test_units(0), v = scan_test_units(1) + scan_test_units(2);
+    const unsigned long long *h = (const unsigned long long *)scan_test.payload;
+    const bool good = scan_test.status == 0 && scan_test.out_bytes == 256 + 16 * (k + v) && h[5] == 256 + 16 * (k + v) &&
+                      h[13] == 16 * k && h[14] == 256 + 16 * k && h[15] == 16 * v && scan_test.payload[32 + kScanTestWgs] == k + v;
+    if (!good) atomicAdd(slot, 1ull);
+}
+
 } // namespace kvc
 
 extern "C" int kvc_selftest(uint64_t *counts, void *stream)
@@ -102,5 +182,8 @@ extern "C" int kvc_selftest(uint64_t *counts, void *stream)
     selftest_rcp_kernel<<<124, 256, 0, s>>>(c + 4);
     selftest_minus_kernel<<<65536, 256, 0, s>>>(c + 5);
     selftest_byte_kernel<<<4096, 256, 0, s>>>(c + 6);
+    selftest_scan_start_kernel<<<1, 64, 0, s>>>();
+    selftest_scan_late_kernel<<<kScanTestWgs, 64, 0, s>>>(c + 7);
+    selftest_scan_closed_kernel<<<1, 64, 0, s>>>(c + 7);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }

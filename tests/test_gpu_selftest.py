@@ -19,3 +19,12 @@ def test_arithmetic_shortcuts_are_exact():
     print("selftest mismatch counts:", dict(zip(NAMES, got)))
     assert got[:len(NAMES)] == [0] * len(NAMES), dict(zip(NAMES, got))
     assert got[len(NAMES):] == [0] * (kvc.SELFTEST_COUNTS - len(NAMES))
+
+
+def test_place_scan_waits_for_workgroups_that_start_late():
+    """The encoder's scanner gives up on a running workgroup that reports nothing, not on one that other work on the GPU
+    keeps from starting: the self-test lets the last of three start twenty times the scanner's limit late."""
+    counts = torch.full((kvc.SELFTEST_COUNTS,), -1, dtype=torch.int64, device="cuda:0")
+    assert kvc.selftest(counts.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert counts.cpu().tolist()[7] == 0
