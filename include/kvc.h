@@ -48,7 +48,8 @@ enum {
     KVC_DEV_BAD_HEADER = 2,    /* payload header does not match the plan / request            */
     KVC_DEV_BAD_CHUNK = 4,     /* coder directory or chunk body inconsistent                  */
     KVC_DEV_BAD_TABLE = 8,     /* code-length table is not a complete prefix code             */
-    KVC_DEV_SCAN_TIMEOUT = 16  /* internal: chunk-offset scan gave up waiting                 */
+    KVC_DEV_SCAN_TIMEOUT = 16  /* internal: chunk-offset scan gave up waiting; the payload's
+                                  directory, header sizes and size word are not written       */
 };
 
 enum { KVC_F16 = 1, KVC_BF16 = 2 };
@@ -287,7 +288,8 @@ int kvc_stream_probe(int mode, const void *src, void *dst, int64_t rows, int32_t
  *   counts[5]     x - zero read from a packed fp16 pair: all pairs of finite fp16 values
  *   counts[6]     float -> byte with insertion: round-to-nearest-even, all floats in [0, 255]
  *   counts[7]     workgroups of the encoder's prefix sum that do not end as they should when one of them
- *                 starts late (the device memory of this check is static: one self-test at a time per GPU)
+ *                 starts late or never reports (the device memory of this check is static: one
+ *                 self-test at a time per GPU)
  * `counts` is DEVICE memory, KVC_SELFTEST_COUNTS 64-bit words, 8-byte aligned, owned by the
  * caller; it is cleared and filled on `stream` (asynchronous: synchronize before reading).
  * Returns KVC_OK, KVC_ERR_ARG for a null pointer, KVC_ERR_DEVICE if a launch failed.

@@ -155,7 +155,7 @@ void encode_kernel(CoderBatch batch)
     const bool leads = ticket == first.wg_base;
     unsigned long long before = 0;
     if (leads) {
-        before = ((const volatile unsigned long long *)(a.ws.ticket + kScanCarry))[0];
+        before = *(const volatile unsigned long long *)scan_carry(a);
         asm volatile("" : "+v"(before));
     }
     // the table's lengths in the payload, unless the construction without halvings has written them already

@@ -9,7 +9,7 @@ namespace kvc {
 // Scan state of an encode workgroup: 0, then (bits 63:62 = 1) the sum of its chunks' sizes, then (2) the
 // sum of all sizes before it, both in 16-byte units.
 constexpr unsigned long long kFlagSize = 1ull << 62, kFlagPrefix = 2ull << 62, kValueMask = (1ull << 40) - 1;
-constexpr unsigned long long kNoPlace = kValueMask;      // (a scan that gave up)
+constexpr unsigned long long kNoPlace = kValueMask;      // in the carry word: a scan of this request gave up
 constexpr int kScanWindows = 4;
 constexpr int kScanCarry = 4;      // word of the ticket's block where the scan of one launch leaves its end to the next
 constexpr int kSpinLimit = 1 << 20;
@@ -25,18 +25,38 @@ constexpr int kSpinCheck = 256;    // looks between two questions whether the wa
 // earlier tickets: all of them are running, so the wait ends; it is bounded by kSpinLimit all the same.
 // The scanner waits for running workgroups too, but also for tickets that nobody has taken, for as long as
 // other work keeps the rest of the launch off the chip; only the first kind of wait is bounded.
+// Whoever gives up marks the request's carry word: everybody else who waits stops too, no later launch of the
+// request places a body, and directory and header stay open.
 // (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
 // hundreds of waves polling the same lines of memory.  70B shape, half of its layers, compress call: 1369 us
 // with eight chunks per workgroup, now 1213; 2-bit codes / groups of 128 1370 -> 1135, 8 bits (a quarter of
 // the layers) 1235 -> 1058.  With the bodies at fixed places, nothing to wait for, 1165.)
+
+__device__ __forceinline__ unsigned long long *scan_carry(const CoderArgs &a)
+{
+    return (unsigned long long *)(a.ws.ticket + kScanCarry);      // units before this launch; units of K
+}
+
+__device__ __forceinline__ bool scan_failed(const CoderArgs &a)
+{
+    return __hip_atomic_load(scan_carry(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoPlace;
+}
+
+__device__ __forceinline__ void give_up(const CoderArgs &a)
+{
+    if (lane_id() != 0) return;
+    __hip_atomic_store(scan_carry(a), kNoPlace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
+}
 
 // The scan of one request's launch, whose last workgroup is `end` - 1; the last launch's scanner closes
 // the directory and the header.  limit: looks without progress at a workgroup that is running.
 __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, int limit = kSpinLimit)
 {
     const int lane = lane_id();
-    unsigned long long *carry = (unsigned long long *)(a.ws.ticket + kScanCarry);      // units before this launch; units of K
+    unsigned long long *carry = scan_carry(a);
     unsigned long long prefix = carry[0], k_units = carry[1];
+    if (prefix == kNoPlace) return;
     int spins = 0;
     bool nobody = false;               // the next ticket has not been taken
     __builtin_amdgcn_s_setprio(3);
@@ -74,15 +94,13 @@ __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, in
             nobody = false;
         } else if ((++spins & (kSpinCheck - 1)) == 0) {
             nobody = (unsigned)next >= __hip_atomic_load(a.ws.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (scan_failed(a)) return;
             if (nobody) spins = 0;
-            else if (spins > limit) {
-                if (lane == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
-                return;
-            }
+            else if (spins > limit) return give_up(a);
         }
         if (nobody) __builtin_amdgcn_s_sleep(32);
     }
-    if (lane != 0) return;
+    if (lane != 0 || scan_failed(a)) return;
     carry[0] = prefix;
     carry[1] = k_units;
     if (end != a.total_wgs) return;
@@ -96,14 +114,14 @@ __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, in
     *a.out_bytes = total;
 }
 
-// The prefix of the workgroup with this ticket, left in its state word by the scanner.
+// The prefix of the workgroup with this ticket, left in its state word by the scanner, or kNoPlace.
 __device__ __forceinline__ unsigned long long wait_for_place(const CoderArgs &a, long long ticket, int limit = kSpinLimit)
 {
     unsigned long long excl;
     int spins = 0;
     while (((excl = __hip_atomic_load(&a.ws.state[ticket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 62) != 2) {
-        if (++spins > limit) {
-            if (lane_id() == 0) atomicOr(a.q.status, KVC_DEV_SCAN_TIMEOUT);
+        if ((++spins & (kSpinCheck - 1)) == 0 && (spins > limit || scan_failed(a))) {
+            give_up(a);
             return kFlagPrefix | kNoPlace;
         }
         __builtin_amdgcn_s_sleep(1);

@@ -166,6 +166,44 @@ __global__ __launch_bounds__(64) void selftest_scan_closed_kernel(unsigned long 
     if (!good) atomicAdd(slot, 1ull);
 }
 
+// A running workgroup that reports nothing: the scanner gives up, and the one that waits for its place, with the
+// encoder's limit of about a second, stops soon after.
+__global__ __launch_bounds__(64) void selftest_scan_silent_kernel(unsigned long long *slot)
+{
+    const CoderArgs a = scan_test_args();
+    const unsigned me = blockIdx.x;
+    bool good = scan_test_enter(a, me, 0, me == 1);
+    const long long start = wall_clock64();                     // (100 MHz)
+    if (good && me == 0) scan_sizes(a, kScanTestWgs, kScanTestLimit);
+    else if (good && me == 2) good = wait_for_place(a, me) == (kFlagPrefix | kNoPlace);
+    good = good && wall_clock64() - start < 20000000;           // 200 ms
+    if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
+}
+
+// The request's next launch, two more workgroups, places nothing and waits for nothing.
+__global__ __launch_bounds__(64) void selftest_scan_after_kernel(unsigned long long *slot)
+{
+    CoderArgs a = scan_test_args();
+    a.wg_base = kScanTestWgs;
+    a.total_wgs = kScanTestWgs + 2;
+    const unsigned me = kScanTestWgs + blockIdx.x;
+    bool good = scan_test_enter(a, me, 0, false);
+    const long long start = wall_clock64();
+    if (good && me == kScanTestWgs) scan_sizes(a, a.total_wgs, kScanTestLimit);
+    else if (good) good = wait_for_place(a, me) == (kFlagPrefix | kNoPlace);
+    good = good && wall_clock64() - start < 20000000;
+    if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
+}
+
+// Nothing has been closed and the request's status says so.
+__global__ __launch_bounds__(64) void selftest_scan_open_kernel(unsigned long long *slot)
+{
+    if (threadIdx.x != 0) return;
+    bool good = scan_test.status == KVC_DEV_SCAN_TIMEOUT && scan_test.out_bytes == 0;
+    for (int i = 0; i < 64; ++i) good = good && scan_test.payload[i] == 0;
+    if (!good) atomicAdd(slot, 1ull);
+}
+
 } // namespace kvc
 
 extern "C" int kvc_selftest(uint64_t *counts, void *stream)
@@ -185,5 +223,9 @@ extern "C" int kvc_selftest(uint64_t *counts, void *stream)
     selftest_scan_start_kernel<<<1, 64, 0, s>>>();
     selftest_scan_late_kernel<<<kScanTestWgs, 64, 0, s>>>(c + 7);
     selftest_scan_closed_kernel<<<1, 64, 0, s>>>(c + 7);
+    selftest_scan_start_kernel<<<1, 64, 0, s>>>();
+    selftest_scan_silent_kernel<<<kScanTestWgs, 64, 0, s>>>(c + 7);
+    selftest_scan_after_kernel<<<2, 64, 0, s>>>(c + 7);
+    selftest_scan_open_kernel<<<1, 64, 0, s>>>(c + 7);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }
