@@ -9,6 +9,9 @@ count in about one execution of eight (a stand-alone kernel that does nothing el
 120 registers allocated, or the count in v109, it never does).  LLVM describes and works around
 the same fault for gfx90a only.  A kernel that trips the check gets register headroom: an empty
 asm statement naming a higher register (see decode_kernel).
+
+A second check keeps kernels whose time depends on their waves (min_waves in kvc_quant.hip) within the
+registers that leave room for them.
 """
 import os
 import re
@@ -65,6 +68,22 @@ def spilling_kernels(asm_path):
     return out
 
 
+# (kernel symbol, registers): six waves per SIMD for the compress kernels of one pass for bf16 rows that are not
+# dense, five for 8-bit codes
+REGISTERS = [(r"compress_(?:k_kernelILi[234]ELi32|v_kernelILi[234]ELi\d+)ELi2ELb0E", 80),
+             (r"compress_(?:k_kernelILi8ELi32|v_kernelILi8ELi\d+)ELi2ELb0E", 96)]
+
+
+def over_budget(asm_path):
+    """[(kernel symbol, registers, budget)] of the kernels that need more registers than REGISTERS gives them."""
+    text = open(asm_path).read()
+    out = []
+    for k, body in re.findall(r"\.amdhsa_kernel (\w+)\n(.*?)\.end_amdhsa_kernel", text, re.S):
+        n = int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", body).group(1))
+        out += [(k, n, most) for pattern, most in REGISTERS if re.search(pattern, k) and n > most]
+    return out
+
+
 def _compile(job):
     name, width = job
     stem = name.replace(".hip", "") + ("_b%d" % width if width else "")
@@ -84,6 +103,10 @@ def _compile(job):
     if hits:
         raise RuntimeError("%s: 64-bit shift with its count in the last allocated VGPR (give the kernel register "
                            "headroom):\n%s" % (name, "\n".join("  %s: %s" % h for h in hits[:20])))
+    over = over_budget(asm)
+    if over:
+        raise RuntimeError("%s: more registers than the kernel's waves leave room for:\n%s" % (
+            name, "\n".join("  %s: %d of %d" % h for h in over[:20])))
     spills = spilling_kernels(asm)
     if spills:
         err += "\n%s: %d kernels spill registers (most: %d bytes per lane): %s" % (

@@ -231,6 +231,22 @@ def test_build_check_finds_a_shift_count_in_the_last_vgpr(tmp_path):
         assert all(h[0] == "kern" for h in hits)
 
 
+def test_build_check_finds_kernels_over_their_registers(tmp_path):
+    """The build's register check: the kernels for strided bf16 rows may take 80 registers (8-bit codes 96), others what they need."""
+    from paper_2605_13734_amd import build
+    cases = [("_ZN3kvc17compress_k_kernelILi4ELi32ELi2ELb0ELb1EEEvNS_10QuantBatchE", 118, 1),
+             ("_ZN3kvc17compress_k_kernelILi4ELi32ELi2ELb0ELb1EEEvNS_10QuantBatchE", 80, 0),
+             ("_ZN3kvc17compress_v_kernelILi2ELi128ELi2ELb0EEEvNS_10QuantBatchE", 121, 1),
+             ("_ZN3kvc17compress_v_kernelILi8ELi64ELi2ELb0EEEvNS_10QuantBatchE", 123, 1),
+             ("_ZN3kvc17compress_v_kernelILi8ELi64ELi2ELb0EEEvNS_10QuantBatchE", 82, 0),
+             ("_ZN3kvc17compress_v_kernelILi4ELi32ELi2ELb1EEEvNS_10QuantBatchE", 114, 0),       # dense
+             ("_ZN3kvc17compress_k_kernelILi4ELi64ELi2ELb0ELb0EEEvNS_10QuantBatchE", 109, 0)]   # two passes
+    for i, (name, regs, want) in enumerate(cases):
+        p = tmp_path / ("k%d.s" % i)
+        p.write_text("\t.amdhsa_kernel %s\n\t\t.amdhsa_next_free_vgpr %d\n\t.end_amdhsa_kernel\n" % (name, regs))
+        assert build.over_budget(str(p)) == ([(name, regs, 96 if "ILi8" in name else 80)] if want else []), name
+
+
 def test_inspect_never_accepts_a_damaged_header(lib, ref):
     """Every single-byte change of a valid header is either rejected by kvc_payload_inspect or
     leaves a header that the oracle also accepts with the same sections; without the lossless stage
