@@ -61,18 +61,34 @@ static inline unsigned place_items(QuantBatch &b)
 
 // Dynamic LDS that nothing uses: it bounds the workgroups of a compute unit, and with them the window of the
 // tensor that the chip reads or writes at a time (a wave's rows are 8 KB), which memory takes better when it
-// is small.  Launches without a transform only: its arithmetic needs the waves.  Call times with the registers as
-// the only bound, with 32000, 40000 and 53000 bytes:
-//   decompress  70B shape (half)  f16 4 bits       1186  1180  1188  1290      94 layers bf16 4/2 bits  1026  1021   992  1081
-//               8B shape bf16 2 bits                193   187   183   182      paged f16 4 bits         1300  1302  1281  1258
-//   compress    70B shape (half)  f16 4 bits       1176  1162  1153  1204      94 layers bf16 4/2 bits  1013  1015  1003  1012
-//               8B shape bf16 2 bits                223   222   220   233      paged f16 4 bits         1232  1209  1249  1401
-//   with the rotation, compress / decompress     291/259 294/260 296/267 333/281
-static inline unsigned window_lds(const QuantBatch &b, bool compress)
+// is small.  What pays was measured kernel by kernel (K and V apart; change of the call's time against no bound; 32
+// layers of 16384 tokens and 94 x 4 heads of 24576, groups of 32, 64 and 128, fp16 and bf16), and the bound
+// is off where it did not pay.  With 40000 bytes a unit takes four workgroups (three of a K compression, which has
+// 4096 of its own; with 36000 four), with 32000 five (four).  Launches with a transform have none: its
+// arithmetic needs the waves (rotation, 40000: compress +2 %, decompress +3 %).
+//   decompress, dense    2 bits -1 to -5 % with 40000, 3 bits 0 to -2 %, 8 bits +1 to +2 %; 4 bits (the call) below 2^22
+//                        rows -1 to -6 % with 40000, above up to +5 % with 40000 and -1 % with 32000
+//   decompress, strided  4 bits -2 to -6 % (bf16 -1 to 0 %) with 40000, fp16 2 and 3 bits up to +4 %, others 0
+//   compress, dense      K, groups of 32: fp16 2 and 3 bits -1 to -4 % with 36000 (40000: -2 to +1 %), bf16 2 to 4 bits 0 to -1 % (+2
+//                        to +6 %), fp16 4 bits and 8 bits -1 to -3 % with 40000; groups of 64 -1 to -3 % with 40000, of 128
+//                        and V 0
+//   compress, strided    K, groups of 32: fp16 4 bits and 8 bits -1 to -3 % with 32000, 2 and 3 bits and bf16 4 bits +2 to +7 %;
+//                        V: fp16 0 to -2 % with 32000, bf16 0 to +2 %
+static inline unsigned window_lds(const QuantBatch &b, bool compress, bool is_v, int bits, int group, int dtype)
 {
     const QuantArgs &a = b.item[0];
     if (a.rotate || a.anchors) return 0;
-    return compress && !a.dense ? 32000 : 40000;
+    if (!compress) {
+        if (!a.dense) return bits == 4 ? 40000 : 0;
+        if (bits != 4) return bits < 4 ? 40000 : 0;
+        long long units = 0;                             // of 32 rows
+        for (int i = 0; i < b.n; ++i) units += b.item[i].total_units;
+        return units < (1ll << 22) / kPassRows ? 40000 : 32000;
+    }
+    if (is_v) return !a.dense && dtype == DT_F16 ? 32000 : 0;
+    const bool wide = bits == 8 || (bits == 4 && dtype == DT_F16);
+    if (a.dense) return group > 32 || wide ? 40000 : 36000;
+    return group == 32 && wide ? 32000 : 0;
 }
 
 #define KVC_LAUNCH(kernel, batch, lds, s)                                                 \

@@ -219,22 +219,23 @@ __global__ __launch_bounds__(256) void decompress_call_kernel(SmallDecompressArg
 template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, int group, const QuantBatch &b, hipStream_t s)
 {
     const QuantArgs &a = b.item[0];
+    const unsigned lds = window_lds(b, true, is_v, BITS, group, DT);
     if (!is_v) {
         const bool xf = a.rotate || a.anchors;
         switch (group) {
-        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, window_lds(b, true), s);
+        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, lds, s);
         case 64:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, window_lds(b, true), s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, window_lds(b, true), s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, lds, s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, lds, s);
         case 128:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, window_lds(b, true), s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, window_lds(b, true), s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, lds, s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, lds, s);
         }
     } else {
         switch (group) {
-        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, window_lds(b, true), s);
-        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, window_lds(b, true), s);
-        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, window_lds(b, true), s);
+        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, lds, s);
+        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, lds, s);
+        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, lds, s);
         }
     }
     return KVC_ERR_UNSUPPORTED;
@@ -242,12 +243,13 @@ template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, in
 
 template <int BITS, bool DENSE> static int decompress_bits_dense(int is_v, int dtype, const QuantBatch &b, hipStream_t s)
 {
+    const unsigned lds = window_lds(b, false, is_v, BITS, 0, dtype);
     if (!is_v) {
-        if (dtype == DT_F16) KVC_LAUNCH((decompress_k_kernel<BITS, DT_F16, DENSE>), b, window_lds(b, false), s);
-        KVC_LAUNCH((decompress_k_kernel<BITS, DT_BF16, DENSE>), b, window_lds(b, false), s);
+        if (dtype == DT_F16) KVC_LAUNCH((decompress_k_kernel<BITS, DT_F16, DENSE>), b, lds, s);
+        KVC_LAUNCH((decompress_k_kernel<BITS, DT_BF16, DENSE>), b, lds, s);
     }
-    if (dtype == DT_F16) KVC_LAUNCH((decompress_v_kernel<BITS, DT_F16, DENSE>), b, window_lds(b, false), s);
-    KVC_LAUNCH((decompress_v_kernel<BITS, DT_BF16, DENSE>), b, window_lds(b, false), s);
+    if (dtype == DT_F16) KVC_LAUNCH((decompress_v_kernel<BITS, DT_F16, DENSE>), b, lds, s);
+    KVC_LAUNCH((decompress_v_kernel<BITS, DT_BF16, DENSE>), b, lds, s);
 }
 
 #define KVC_PASTE2(a, b) a##b

@@ -1,0 +1,114 @@
+"""Which launches a call consists of (run with -m gpu): the kernels, their dynamic LDS and their number on both sides of
+the lines that the launch rules draw.  The call is captured, the nodes of the graph are read, nothing runs."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2605_13734_amd import kvc, kvgen
+
+pytestmark = pytest.mark.gpu
+
+
+class _Dim3(C.Structure):
+    _fields_ = [("x", C.c_uint), ("y", C.c_uint), ("z", C.c_uint)]
+
+
+class _KernelNode(C.Structure):
+    _fields_ = [("block", _Dim3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", _Dim3), ("params", C.c_void_p),
+                ("lds", C.c_uint)]
+
+
+def _hip():
+    with open("/proc/self/maps") as f:
+        path = next(l.split()[-1] for l in f if "libamdhip64" in l)
+    lib = C.CDLL(path)
+    lib.hipKernelNameRefByPtr.restype = C.c_char_p
+    lib.hipKernelNameRefByPtr.argtypes = [C.c_void_p, C.c_void_p]
+    return lib
+
+
+def launches(call):
+    """[(kernel, workgroups, dynamic LDS)] of what `call(stream)` enqueues."""
+    hip, g, side = _hip(), torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=side):
+        call(side.cuda_stream)
+    n, graph = C.c_size_t(0), C.c_void_p(g.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        name = hip.hipKernelNameRefByPtr(p.func, None).decode()
+        out.append((name, p.grid.x * p.grid.y, p.lds))
+    return out
+
+
+def call_of(direction, L, H, T, n=1, dtype=torch.float16, paged=False, **strategy):
+    """A compress or decompress call over n requests of T tokens (one tensor for all: nothing runs)."""
+    code = kvc.F16 if dtype == torch.float16 else kvc.BF16
+    plan = kvc.Plan(code, L, H, 128, max_tokens=T, max_batch=n, **strategy)
+    sizes = [plan.payload_size(T)[0]] * n
+    offsets = [0]
+    for s in sizes:
+        offsets.append(offsets[-1] + (s + 255) // 256 * 256)
+    if paged:
+        pages = -(-T // 16)
+        x = torch.empty((L, 2, pages, 16, H, 128), dtype=dtype, device="cuda")
+        table = kvgen.block_table(3, pages, pages, "cuda")
+        reqs = [kvc.paged_request(x, table, T)] * n
+    else:
+        table = None
+        x = torch.empty((L, 2, H, T, 128), dtype=dtype, device="cuda")
+        reqs = [kvc.contiguous_request(x)] * n
+    payload = torch.empty(offsets[-1], dtype=torch.uint8, device="cuda")
+    words = torch.zeros(2 * n, dtype=torch.int64, device="cuda")
+    ws = torch.empty(max(plan.workspace_size(), 256), dtype=torch.uint8, device="cuda")
+
+    def call(stream):
+        if direction == "compress":
+            kvc.compress(plan, reqs, payload.data_ptr(), offsets, words.data_ptr(), words[n:].data_ptr(), ws.data_ptr(), stream)
+        else:
+            kvc.decompress(plan, payload.data_ptr(), offsets, reqs, words[n:].data_ptr(), ws.data_ptr(), stream)
+    call.keep = (x, table, payload, words, ws)
+    return call
+
+
+def lds_of(found, kernel):
+    sizes = {lds for name, _, lds in found if kernel in name}
+    assert len(sizes) == 1, (kernel, found)
+    return sizes.pop()
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("paged", [False, True])
+def test_bound_on_the_workgroups_of_a_unit(bits, paged, dtype):
+    """Kernels that gain nothing from a smaller window of the tensor, or lose by it, run without the bound."""
+    f16 = dtype == torch.float16
+    L, H, T = 4, 8, 300                                  # (K and V groups differ: three launches at any size)
+    kw = dict(dtype=dtype, paged=paged, bits_k=bits, bits_v=bits, group_v=64)
+    wide = bits == 8 or (bits == 4 and f16)
+    for group in (32, 128):
+        found = launches(call_of("compress", L, H, T, group_k=group, **kw))
+        assert len(found) == 3
+        dense_k, strided_k = (40000 if wide or group > 32 else 36000), (32000 if wide and group == 32 else 0)
+        assert lds_of(found, "compress_k_kernel") == (strided_k if paged else dense_k)
+        assert lds_of(found, "compress_v_kernel") == (32000 if paged and f16 else 0)
+    found = launches(call_of("decompress", L, H, T, group_k=32, **kw))
+    want = (40000 if bits == 4 else 0) if paged else (40000 if bits <= 4 else 0)
+    assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
+
+
+@pytest.mark.parametrize("T,lds", [(65536 - 32, 40000), (65536, 32000)])
+def test_bound_of_large_four_bit_decompressions(T, lds):
+    found = launches(call_of("decompress", 8, 8, T, bits_k=4, bits_v=4, group_k=32, group_v=64))
+    assert lds_of(found, "decompress_k_kernel") == lds and lds_of(found, "decompress_v_kernel") == lds
+
+
+@pytest.mark.parametrize("kw", [dict(transform=1), dict(transform=2, anchor_period=16)])
+def test_no_bound_with_a_transform(kw):
+    for direction in ("compress", "decompress"):
+        assert all(lds == 0 for _, _, lds in launches(call_of(direction, 2, 4, 200, group_k=64, group_v=32, **kw)))
