@@ -71,23 +71,23 @@ static inline unsigned place_items(QuantBatch &b)
 //   decompress, strided  4 bits -2 to -6 % (bf16 -1 to 0 %) with 40000, fp16 2 and 3 bits up to +4 %, others 0
 //   compress, dense      K, groups of 32: fp16 2 and 3 bits -1 to -4 % with 36000 (40000: -2 to +1 %), bf16 2 to 4 bits 0 to -1 % (+2
 //                        to +6 %), fp16 4 bits and 8 bits -1 to -3 % with 40000; groups of 64 -1 to -3 % with 40000, of 128
-//                        and V 0
+//                        and V 0; below 2^20 rows, where the tensor is a few generations of workgroups, 0 to +2 %
 //   compress, strided    K, groups of 32: fp16 4 bits and 8 bits -1 to -3 % with 32000, 2 and 3 bits and bf16 4 bits +2 to +7 %;
 //                        V: fp16 0 to -2 % with 32000, bf16 0 to +2 %
 static inline unsigned window_lds(const QuantBatch &b, bool compress, bool is_v, int bits, int group, int dtype)
 {
     const QuantArgs &a = b.item[0];
     if (a.rotate || a.anchors) return 0;
+    long long rows = 0;
+    for (int i = 0; i < b.n; ++i) rows += b.item[i].total_units * (compress && !is_v ? group : kPassRows);
     if (!compress) {
         if (!a.dense) return bits == 4 ? 40000 : 0;
         if (bits != 4) return bits < 4 ? 40000 : 0;
-        long long units = 0;                             // of 32 rows
-        for (int i = 0; i < b.n; ++i) units += b.item[i].total_units;
-        return units < (1ll << 22) / kPassRows ? 40000 : 32000;
+        return rows < (1ll << 22) ? 40000 : 32000;
     }
     if (is_v) return !a.dense && dtype == DT_F16 ? 32000 : 0;
     const bool wide = bits == 8 || (bits == 4 && dtype == DT_F16);
-    if (a.dense) return group > 32 || wide ? 40000 : 36000;
+    if (a.dense) return rows < (1ll << 20) ? 0 : group > 32 || wide ? 40000 : 36000;
     return group == 32 && wide ? 32000 : 0;
 }
 

@@ -94,12 +94,20 @@ def test_bound_on_the_workgroups_of_a_unit(bits, paged, dtype):
     for group in (32, 128):
         found = launches(call_of("compress", L, H, T, group_k=group, **kw))
         assert len(found) == 3
-        dense_k, strided_k = (40000 if wide or group > 32 else 36000), (32000 if wide and group == 32 else 0)
-        assert lds_of(found, "compress_k_kernel") == (strided_k if paged else dense_k)
+        assert lds_of(found, "compress_k_kernel") == (32000 if paged and wide and group == 32 else 0)
         assert lds_of(found, "compress_v_kernel") == (32000 if paged and f16 else 0)
     found = launches(call_of("decompress", L, H, T, group_k=32, **kw))
     want = (40000 if bits == 4 else 0) if paged else (40000 if bits <= 4 else 0)
     assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
+
+
+@pytest.mark.parametrize("T", [16384 - 128, 16384])
+def test_bound_of_large_compressions(T):
+    """2^20 rows: below, a tensor is a few generations of workgroups and has no window to keep small."""
+    for bits, group, lds in ((4, 32, 40000), (3, 32, 36000), (3, 128, 40000)):
+        found = launches(call_of("compress", 8, 8, T, bits_k=bits, bits_v=bits, group_k=group, group_v=64))
+        assert lds_of(found, "compress_k_kernel") == (lds if T == 16384 else 0)
+        assert lds_of(found, "compress_v_kernel") == 0
 
 
 @pytest.mark.parametrize("T,lds", [(65536 - 32, 40000), (65536, 32000)])
