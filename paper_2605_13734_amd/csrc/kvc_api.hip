@@ -718,10 +718,12 @@ static int check_batch(const kvc_plan_t *p, const kvc_request *reqs, int32_t n, 
 
 // A call without the coder that fits one launch: up to four requests without a block table, of one layout
 // class, K and V of one width and group, no transform and no width tables, and few enough rows that
-// launches, latency and the tail of the K pass are part of what the call costs (compress / decompress call,
-// rows per tensor: 2^10 rows 15.4 / 14.7 us in three launches, 7.6 / 7.6 in one; 2^18 43 / 37 and 33 / 30;
-// 2^20 123 / 107 and 114 / 100; at 2^21 rows one launch is the faster one in two measurements of four,
-// 222 / 191 and 215 / 210 for bf16 at 2 bits).
+// launches, latency and the tail of the K pass are part of what the call costs.  One launch is the
+// faster one at every size below the line, in both directions, for both types, all widths and groups
+// (compress / decompress call, fp16, rows per tensor, in three launches and in one: 2 bits g64 2^16 17.8 / 14.2 and 11.8 /
+// 8.9 us, 2^18 39 / 31 and 31 / 26, 2^20 109 / 95 and 101 / 88, just below 2^21 213 / 182 and 210 / 177; 8 bits g32
+// 17.9 / 15.5 and 11.2 / 10.0, 45 / 44 and 37 / 38, 141 / 140 and 133 / 133, 269 / 276 and 266 / 266).  Above it
+// K and V of a request are long enough to be worth a mark each (kvc_trace).
 static const long long kSmallCallRows = 1ll << 21;       // token rows per tensor of the whole call
 
 static bool small_call(const kvc_plan_t *p, const kvc_request *reqs, int n)

@@ -281,6 +281,13 @@ template <class Args> static unsigned place_call(Args &b)
     return at;
 }
 
+// LDS that nothing uses, as in window_lds, for decompression calls; compression calls gain nothing from it (2^21 rows, fp16,
+// with 32000 bytes: 2 bits g64 210 and 210 us, 4 bits g64 227 and 229, 4 bits g32 230 and 224; bf16 231 and 233).
+// Call times without and with 40000 bytes at 2^20, 1.5 * 2^20 and just below 2^21 rows:
+//   2 bits g64  93 / 88, 145 / 132, 196 / 180        4 bits g32  117 / 113, 152 / 150, 230 / 219 (bf16 230 / 235)
+//   3 bits g32  97 / 95, 143 / 141, 198 / 188        8 bits g32  136 / 133, 203 / 200, 271 / 265
+constexpr unsigned kCallLds = 40000;
+
 template <int G> static void compress_call(int dtype, const SmallCompressArgs &b, unsigned wgs, hipStream_t s)
 {
 #define KVC_CALL(DT, D) hipLaunchKernelGGL((compress_call_kernel<KVC_BITS, G, DT, D>), dim3(wgs), dim3(256), 0, s, b)
@@ -301,7 +308,7 @@ int KVC_PASTE(launch_compress_call_bits, KVC_BITS)(int group, int dtype, SmallCo
 int KVC_PASTE(launch_decompress_call_bits, KVC_BITS)(int dtype, SmallDecompressArgs &b, hipStream_t s)
 {
     const unsigned wgs = place_call(b);
-#define KVC_CALL(DT, D) hipLaunchKernelGGL((decompress_call_kernel<KVC_BITS, DT, D>), dim3(wgs), dim3(256), 0, s, b)
+#define KVC_CALL(DT, D) hipLaunchKernelGGL((decompress_call_kernel<KVC_BITS, DT, D>), dim3(wgs), dim3(256), kCallLds, s, b)
     if (b.item[0].dense) { if (dtype == DT_F16) KVC_CALL(DT_F16, true); else KVC_CALL(DT_BF16, true); }
     else if (dtype == DT_F16) KVC_CALL(DT_F16, false); else KVC_CALL(DT_BF16, false);
 #undef KVC_CALL

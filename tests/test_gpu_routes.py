@@ -120,3 +120,14 @@ def test_bound_of_large_four_bit_decompressions(T, lds):
 def test_no_bound_with_a_transform(kw):
     for direction in ("compress", "decompress"):
         assert all(lds == 0 for _, _, lds in launches(call_of(direction, 2, 4, 200, group_k=64, group_v=32, **kw)))
+
+
+@pytest.mark.parametrize("bits,group", [(2, 64), (4, 32), (8, 128)])
+def test_one_launch_below_two_mebirows(bits, group):
+    """Decompression in one launch reads and writes the same window of the tensor as in three."""
+    for T, n in ((32768 - 32, 1), (32768, 3)):
+        for direction in ("compress", "decompress"):
+            found = launches(call_of(direction, 8, 8, T, bits_k=bits, bits_v=bits, group_k=group, group_v=group))
+            assert len(found) == n
+            if n == 1:
+                assert lds_of(found, "_call_kernel") == (40000 if direction == "decompress" else 0)
