@@ -567,24 +567,53 @@ struct CoderLaunch {
     int bits, group;
 };
 
-// Whether K and V of a request share a launch with the coder: one width and one group for both, no
-// transform (the kernels for both tensors exist for that), and a request that leaves the chip idle between
-// the two passes -- 2^18 rows per tensor are two chunks per SIMD where four fit.  One layer of 32k tokens
-// and 8 heads: encoding 56 us in two launches, 45 in one, decoding 50 and 37; 2^21 rows (bf16): compress call
-// 346 and 303 us.  Requests of 2^23 rows and more gain 2 % and keep their passes apart.  For groups of 64
-// and 128 the K kernels need more registers than the V kernels, and one kernel for both gives V
-// the occupancy of K (70B shape, 2 bits, groups of 128, half of the layers: 1148 and 1275 us), so only small
-// requests share.
+// Whether K and V of the requests of a window share a launch with the coder.  The kernels for both tensors
+// exist for one width and one group for both and no transform, and a shared launch takes half as many
+// requests.  It pays where the two passes would leave the chip idle: one layer of 32k tokens and 8 heads: encoding
+// 56 us in two launches, 45 in one, decoding 50 and 37; 2^21 rows (fp16, 4 bits): compress call 319 and
+// 280 us; requests of 2^23 rows and more gain 2 % and keep their passes apart.
+// - More than four requests: eight of them, K and V apart, take as many launches with twice the work in
+//   each (time apart / shared, fp16, 4 bits, 5 to 8 requests of 2^14, 2^16, 2^18 and 2^19 rows each: groups of 32 1.00 0.99
+//   0.95 1.01, of 64 1.00 0.92 0.95 1.00, of 128 0.99 0.95 0.89 0.89).  8-bit codes share four at a time (groups of 128, six
+//   requests of 2^16 rows 1.07, others 1.00 to 1.04).
+// - Groups of 64 and 128: a K kernel needs more registers than a V kernel, and in a shared launch V has the
+//   waves of K.  Groups of 64 (three waves per SIMD) lose nothing by it below 2^21 rows (apart / shared, one request: 2^18 1.05,
+//   2^20 1.21, 2^21 1.12).  Groups of 128 (two) do with more than 2^20 rows in the window (2^16 1.43, 2^18 0.95 to
+//   0.99, 2^19 1.04 to 1.12, 2^20 1.02 to 1.10, 2^20.6 0.96 to 1.03, 2^21 0.93 to 0.98), but for 8 bits, where LDS bounds
+//   the waves of either (2^21 1.10).  The strided bf16 kernel at groups of 128 has one wave per SIMD: shared only
+//   while all chunks are resident at once (2^16 1.40, 2^17 0.87, 2^20 0.75, 2^21 0.72).
 static bool tensors_share(const kvc_plan_t *p)
 {
     const kvc_strategy &st = p->strat;
     return !p->has_table[0] && !p->has_table[1] && st.bits_k == st.bits_v && st.group_k == st.group_v && st.transform == KVC_T_NONE;
 }
 
-static bool share_kv(const kvc_plan_t *p, const kvc_request *lead)
+static const int kUnits = 256;                       // compute units
+
+// chunks of K and V of a window; *largest: of its largest request
+static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, long long *largest)
 {
-    const long long rows = (long long)p->model.layers * p->model.kv_heads * lead->tokens;
-    return tensors_share(p) && rows < (p->strat.group_k == 32 ? 4 * kSmallRows : kSmallRows);
+    long long chunks = 0;
+    *largest = 0;
+    for (int i = first; i < end; ++i) {
+        const long long c = 2ll * p->model.layers * p->model.kv_heads * chunks_per_head(reqs[i].tokens);
+        chunks += c;
+        *largest = c > *largest ? c : *largest;
+    }
+    return chunks;
+}
+
+static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
+{
+    if (!tensors_share(p) || end - first > kCoderBatch / 2) return false;
+    const long long rows = (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens;
+    if (p->strat.group_k == 32) return rows < 4 * kSmallRows;
+    if (rows >= kSmallRows) return false;
+    if (p->strat.group_k == 64) return true;
+    long long largest;
+    const long long chunks = window_chunks(p, reqs, first, end, &largest);
+    if (p->model.dtype == KVC_BF16 && !dense_layout(&reqs[lead])) return chunks <= 4 * kUnits;
+    return p->strat.bits_k == 8 || chunks <= kSmallRows / kChunkRows;        // 2^20 rows of K and of V
 }
 
 // The decoder has no order to keep and takes the group as a run-time value, so there K and V share a launch for
@@ -903,10 +932,19 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             KVC_TRY(launch_compress_prologue(pa, s));
         }
     }
-    const int coder_limit = tensors_share(plan) ? kCoderBatch / 2 : kCoderBatch;
     for (int first = 0; first < n;) {
         int lead;
-        const int end = request_window(plan, reqs, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
+        int end = request_window(plan, reqs, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
+        bool share = st.codec && share_kv(plan, reqs, first, end, lead);
+        if (st.codec && st.bits_k == 8 && end - first > kCoderBatch / 2) {
+            int lead_half;
+            const int half = request_window(plan, reqs, n, first, kCoderBatch / 2, &lead_half);
+            share = share_kv(plan, reqs, first, half, lead_half);
+            if (share) {
+                end = half;
+                lead = lead_half;
+            }
+        }
         if (!st.codec) {
             marks.window(first, end, 1);
             KVC_TRY(launch_tensor(plan, 0, true, quant_batch(plan, reqs, first, end, lead, 0, payload, payload_off, dev_status, true),
@@ -920,7 +958,6 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             // widths ascending), then launch by launch over the requests together
             CoderLaunch cl[kCoderBatch][kTableSlots];
             int launches = 0;
-            const bool share = share_kv(plan, &reqs[lead]);
             const int waves = share ? shared_waves(plan, reqs, first, end) : 0;
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);

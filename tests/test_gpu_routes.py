@@ -1,6 +1,7 @@
 """Which launches a call consists of (run with -m gpu): the kernels, their dynamic LDS and their number on both sides of
 the lines that the launch rules draw.  The call is captured, the nodes of the graph are read, nothing runs."""
 import ctypes as C
+import re
 
 import pytest
 import torch
@@ -131,3 +132,30 @@ def test_one_launch_below_two_mebirows(bits, group):
             assert len(found) == n
             if n == 1:
                 assert lds_of(found, "_call_kernel") == (40000 if direction == "decompress" else 0)
+
+
+def encoders(found):
+    """(tensor: 0 K, 1 V, 2 both; chunks per workgroup) of the encoder launches."""
+    names = [re.search(r"encode_kernelILi\d+ELi\d+ELi\dELi(\d)ELb\dELb\dELi(\d)E", name) for name, _, _ in found]
+    return [(int(m.group(1)), int(m.group(2))) for m in names if m]
+
+
+@pytest.mark.parametrize("dtype,paged,bits,group,L,T,shared", [
+    (torch.bfloat16, True, 4, 128, 1, 8192, True), (torch.bfloat16, True, 4, 128, 1, 8193, False),      # one wave per SIMD
+    (torch.bfloat16, True, 8, 128, 1, 8193, False), (torch.bfloat16, False, 4, 128, 1, 8193, True),
+    (torch.float16, False, 4, 128, 8, 16384, True), (torch.float16, False, 4, 128, 8, 16385, False),    # two
+    (torch.float16, True, 2, 128, 8, 16384, True), (torch.float16, False, 8, 128, 8, 16385, True),
+    (torch.bfloat16, True, 4, 64, 8, 16385, True), (torch.float16, False, 4, 64, 8, 32768, False),
+    (torch.float16, False, 4, 32, 8, 32768, True)])
+def test_encoder_shares_a_launch_where_it_pays(dtype, paged, bits, group, L, T, shared):
+    found = launches(call_of("compress", L, 8, T, dtype=dtype, paged=paged, bits_k=bits, bits_v=bits, group_k=group, group_v=group, codec=1))
+    assert [kv for kv, _ in encoders(found)] == ([2] if shared else [0, 1])
+
+
+@pytest.mark.parametrize("n,want", [(1, [2]), (4, [2]), (5, [0, 1]), (8, [0, 1]), (11, [0, 1, 2])])
+def test_encoder_windows(n, want):
+    """Up to four requests share a launch for K and V, more of them take the passes apart, eight at a time."""
+    found = launches(call_of("compress", 1, 4, 700, n=n, bits_k=4, bits_v=4, codec=1))
+    assert [kv for kv, _ in encoders(found)] == want
+    found = launches(call_of("compress", 1, 4, 700, n=n, bits_k=8, bits_v=8, codec=1))
+    assert [kv for kv, _ in encoders(found)] == [2] * -(-n // 4)                  # (8 bits: four at a time)
