@@ -619,20 +619,29 @@ static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, in
 // The decoder has no order to keep and takes the group as a run-time value, so there K and V share a launch for
 // every width that both have: also with different groups, and with width tables (half of the heads at
 // 8 bits, half at 2, 2^21 rows: decompress call 411 us with K and V apart, 367 together).
-static bool common_width(const kvc_plan_t *p)
+// Of the widths that K or V have: 2 if both have all of them, 1 some, 0 none (or a transform).
+static int common_widths(const kvc_plan_t *p)
 {
+    int any = 0, both = 0;
     for (int w = 0; w < 4; ++w) {
-        bool both = true;
+        int has = 0;
         for (int is_v = 0; is_v < 2; ++is_v)
-            both &= p->has_table[is_v] ? p->width_count[is_v][w] > 0 : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k);
-        if (both) return p->strat.transform == KVC_T_NONE;
+            has += p->has_table[is_v] ? p->width_count[is_v][w] > 0 : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k);
+        any += has > 0;
+        both += has == 2;
     }
-    return false;
+    if (both == 0 || p->strat.transform != KVC_T_NONE) return 0;
+    return both == any ? 2 : 1;
 }
 
-static bool widths_share(const kvc_plan_t *p, const kvc_request *lead)
+// A shared launch takes four requests.  Where both tensors have all widths, two windows of four take as many launches
+// as one of eight with K and V apart; where one of them has a width of its own they take more, and
+// windows of more than four requests stay apart (K 4 and 3 bits, V 4 and 2, five requests of 2^14, 2^16 and 2^18 rows:
+// 66 81 208 us apart, 88 100 203 shared; K 8, 4 and 2 bits, V 8 and 2: 106 120 304 and 125 139 291).
+static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
 {
-    return common_width(p) && (long long)p->model.layers * p->model.kv_heads * lead->tokens < 4 * kSmallRows;
+    return common_widths(p) > 0 && end - first <= kCoderBatch / 2 &&
+           (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens < 4 * kSmallRows;
 }
 
 // Chunks per workgroup of such an encoder launch (0: the usual number): eight where all chunks of the window
@@ -1127,7 +1136,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
-    const int coder_limit = common_width(plan) ? kCoderBatch / 2 : kCoderBatch;
+    const int coder_limit = common_widths(plan) == 2 ? kCoderBatch / 2 : kCoderBatch;
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
@@ -1152,7 +1161,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                           (const uint8_t *)workspace, cl[k]);
             }
             marks.window(first, end, 1);
-            if (widths_share(plan, &dst[lead])) {
+            if (widths_share(plan, dst, first, end, lead)) {
                 // width by width, K and V together
                 for (int w = 0; w < 4; ++w) {
                     CoderBatch b;

@@ -159,3 +159,14 @@ def test_encoder_windows(n, want):
     assert [kv for kv, _ in encoders(found)] == want
     found = launches(call_of("compress", 1, 4, 700, n=n, bits_k=8, bits_v=8, codec=1))
     assert [kv for kv, _ in encoders(found)] == [2] * -(-n // 4)                  # (8 bits: four at a time)
+
+
+@pytest.mark.parametrize("n", [1, 4, 5, 8])
+def test_decoder_windows(n):
+    """Width tables: where K or V has a width of its own, more than four requests keep K and V apart."""
+    def decoders(tab_k, tab_v):
+        found = launches(call_of("decompress", 1, 4, 300, n=n, head_bits_k=tab_k, head_bits_v=tab_v, codec=1))
+        return sum("decode_kernel" in name for name, _, _ in found)
+    assert decoders([8, 2, 2, 8], [2, 8, 8, 8]) == (2 if n <= 4 else 4)
+    assert decoders([4, 3, 3, 4], [4, 2, 4, 2]) == (3 if n <= 4 else 4)
+    assert decoders([3, 3, 3, 3], [4, 2, 4, 2]) == 3
