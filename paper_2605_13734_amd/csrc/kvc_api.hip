@@ -644,16 +644,20 @@ static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first
            (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens < 4 * kSmallRows;
 }
 
-// Chunks per workgroup of such an encoder launch (0: the usual number): eight where all chunks of the window
-// are resident at once and the usual number would queue for more than 256 tickets, which are one after the
-// other (one layer as above: 74 us per call with four, 69 with eight); with more work the tickets hide
-// behind other workgroups and four wait less for each other (enc_waves).
+// Chunks per workgroup of an encoder launch for both tensors (0: the usual number), where all chunks of
+// the window are resident at once (16 waves per compute unit) and the usual number would queue for more than 256
+// tickets, which are one after the other (one layer as above: 72 us per call with four, 66 with eight).  With
+// more work the tickets hide behind other workgroups and four wait less for each other (enc_waves).  Between 8
+// and 12 waves per unit three workgroups of four share the work evenly, where some units have two of eight and
+// others one (2432 chunks of four requests 59 us with eight, 53 with four); a single request's tickets cost more than
+// that from 10 waves per unit up (2816 chunks, 2 bits, 53.5 and 54.6, 3072 54.5 and 57.0; 4 bits level).
 static int shared_waves(const kvc_plan_t *p, const kvc_request *reqs, int first, int end)
 {
     if (p->strat.group_k != 32 || p->strat.bits_k == 8) return 0;
-    long long chunks = 0;
-    for (int i = first; i < end; ++i) chunks += 2ll * p->model.layers * p->model.kv_heads * chunks_per_head(reqs[i].tokens);
-    return chunks > 1024 && chunks <= 4096 ? 8 : 0;
+    long long largest;
+    const long long chunks = window_chunks(p, reqs, first, end, &largest);
+    if (chunks <= 4 * kUnits || chunks > 16 * kUnits) return 0;
+    return chunks > 8 * kUnits && chunks <= 12 * kUnits && largest <= 10 * kUnits ? 0 : 8;
 }
 
 // K and V of the first n requests of a window as one batch

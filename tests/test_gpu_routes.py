@@ -170,3 +170,13 @@ def test_decoder_windows(n):
     assert decoders([8, 2, 2, 8], [2, 8, 8, 8]) == (2 if n <= 4 else 4)
     assert decoders([4, 3, 3, 4], [4, 2, 4, 2]) == (3 if n <= 4 else 4)
     assert decoders([3, 3, 3, 3], [4, 2, 4, 2]) == 3
+
+
+@pytest.mark.parametrize("n,T,waves", [
+    (1, 8192, 4), (1, 8193, 8), (1, 16384, 8), (1, 16385, 4), (1, 20480, 4), (1, 20481, 8), (1, 32768, 8), (1, 32769, 4),
+    (2, 8192, 8), (2, 8193, 4), (4, 4800, 4), (4, 6144, 4), (4, 6145, 8), (4, 8192, 8), (4, 8193, 4)])
+def test_chunks_per_encoder_workgroup(n, T, waves):
+    """16 chunks per 128 tokens, 256 compute units: eight per workgroup above 1024 chunks and up to 4096, but for 2049 to
+    3072 chunks unless 2560 of them are one request's."""
+    found = launches(call_of("compress", 1, 8, T, n=n, bits_k=4, bits_v=4, codec=1))
+    assert encoders(found) == [(2, waves)]
