@@ -251,10 +251,13 @@ int kvc_check_block_table(const int32_t *table, int64_t entries, int32_t num_phy
  * array, owned by the caller) is installed in a plan, every kvc_compress / kvc_decompress with
  * that plan records, per request and on the call's stream, four events: before the set-up work
  * (for the first request of a call: before anything the call enqueues), before the K pass,
- * between the K and V passes, and after the V pass (short requests of one call share their launches
- * and then share these moments, and with the coder a request below 2^23 token rows per tensor may have
- * its K and V passes in one launch, after which the last two events are recorded together).  The set-up
- * of all requests of a call comes before the first K pass.  Returns the number of events recorded since the previous call;
+ * between the K and V passes, and after the V pass.  Short requests of one call share their
+ * launches and then share these moments, and the set-up of all requests of a call comes before the
+ * first K pass.  Where K and V have one launch, the time between the second and the third event is
+ * that of both passes and the last two are recorded together: with the coder, requests below 2^23
+ * token rows per tensor may; without it, a call of up to four contiguous requests below 2^21 rows in
+ * all (K and V of one width and group, no transform, no width tables), whose one launch also
+ * is the set-up.  Returns the number of events recorded since the previous call;
  * NULL uninstalls.  The state lives in the plan.
  */
 int kvc_trace(kvc_plan_t *plan, void **hip_events, int32_t capacity);

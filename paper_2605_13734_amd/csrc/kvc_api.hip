@@ -695,13 +695,12 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     base.off_bodies = g.off_codes_k;
     base.capacity = capacity;
     base.total_chunks = g.chunks_k + g.chunks_v;
-    base.slots = table_slots(p);
     base.ws.sample = (uint16_t *)ws;
     base.ws.lut = (uint16_t *)(ws + lut_offset(p));
     base.ws.ticket = (uint32_t *)(ws + ticket_offset(p));
     base.ws.state = (unsigned long long *)(ws + p->ws_state_off);
     base.out_bytes = (unsigned long long *)out_bytes;
-    int n = 0, mask = 0;
+    int n = 0;
     long long chunk_at = 0, wg_at = 0, k_wgs = 0;
     for (int is_v = 0; is_v < 2; ++is_v) {
         const QuantArgs q = quant_args(p, r, is_v, payload, g, status, compress);
@@ -730,14 +729,12 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
             const int nw = waves ? waves : enc_waves(L.bits);
             chunk_at += L.a.chunks;
             wg_at += (L.a.chunks + nw - 1) / nw;
-            mask |= 1 << L.a.tab;
         }
         if (!is_v) k_wgs = wg_at;
     }
     for (int i = 0; i < n; ++i) {
         out[i].a.k_wgs = k_wgs;
         out[i].a.total_wgs = wg_at;
-        out[i].a.slot_mask = mask;
     }
     return n;
 }
@@ -1129,7 +1126,6 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                 CheckItem &it = ca.item[j];
                 it.payload = (const uint32_t *)pl;
                 make_header(plan, dst[i].tokens, g, &it.expect);
-                it.mask = 0xffffffffu;
                 if (plan->blob_bytes) {        // the payload's width tables must be the plan's
                     it.tables = pl + g.off_widths;
                     it.plan_tables = (const uint8_t *)workspace;

@@ -20,7 +20,6 @@ constexpr int kHeader = 128;
 
 enum { DT_F16 = 1, DT_BF16 = 2 };
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -34,11 +33,6 @@ struct TensorView {
     int bt_wave;                // blocks of 4 tokens or more whose rows lie within 2^31 elements at a stride
                                 // below 2^24: a pass needs one table entry per 4 rows, read once per wave
 };
-
-// Bit casts go through by-value scalars: applying __builtin_bit_cast directly to an element
-// of an ext_vector (v[i]) reads element 0 with this compiler.
-__device__ __forceinline__ half2_t as_half2(uint32_t u) { return __builtin_bit_cast(half2_t, u); }
-__device__ __forceinline__ uint32_t as_u32(half2_t h) { return __builtin_bit_cast(uint32_t, h); }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 // The wave's index inside its workgroup, as a value the compiler knows to be the same in all lanes:
@@ -141,11 +135,6 @@ __device__ __forceinline__ uint32_t f32_to_f16_bits(float f)
 {
     return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)f);     // round to nearest even
 }
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;                  // nearest even, finite input
-}
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -194,12 +183,6 @@ constexpr int DPP_HALF_MIRROR = 0x141;     // reverse within 8 lanes
 constexpr int DPP_MIRROR = 0x140;          // reverse within 16 lanes
 constexpr int DPP_QUAD_NEXT = 0xF9;        // quad_perm [1,2,3,3]: lane k reads lane k+1
 constexpr int DPP_QUAD_PREV = 0x90;        // quad_perm [0,0,1,2]: lane k reads lane k-1
-
-__device__ __forceinline__ float xlane_f32(float v, int xor_mask)
-{
-    return __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(((lane_id() ^ xor_mask) << 2),
-                                                                  (int)__float_as_uint(v)));
-}
 
 // min and max over the `LANES` (4, 8 or 16) adjacent lanes that share a V group
 template <int LANES> __device__ __forceinline__ void group_minmax(float &mn, float &mx)

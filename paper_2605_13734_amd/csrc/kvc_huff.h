@@ -54,11 +54,6 @@ template <int BITS> struct DecGeom {
 
 // ---- chunk <-> LDS -------------------------------------------------------------------------
 
-template <int BITS> __device__ __forceinline__ uint8_t *lds_row(uint8_t *lds, int r)
-{
-    return code_row<BITS, true>(lds, r);
-}
-
 struct ChunkPos {
     long long lh, cb, head_off, row0;
     int rows;
@@ -155,18 +150,6 @@ template <int BITS> __device__ __forceinline__ void load_sub(const uint8_t *lds,
     for (int k = 0; k < W / 4; ++k) {
         u32x4 v = p[k];
         sym[4 * k] = v[0]; sym[4 * k + 1] = v[1]; sym[4 * k + 2] = v[2]; sym[4 * k + 3] = v[3];
-    }
-}
-
-template <int BITS> __device__ __forceinline__ void store_sub(uint8_t *lds, const uint32_t *sym)
-{
-    constexpr int W = ChunkGeom<BITS>::kWords;
-    u32x4 *p = (u32x4 *)(lds + lane_id() * ChunkGeom<BITS>::kSubStride);
-#pragma unroll
-    for (int k = 0; k < W / 4; ++k) {
-        u32x4 v;
-        v[0] = sym[4 * k]; v[1] = sym[4 * k + 1]; v[2] = sym[4 * k + 2]; v[3] = sym[4 * k + 3];
-        p[k] = v;
     }
 }
 

@@ -152,7 +152,6 @@ KVC_DECLARE_CALL(2) KVC_DECLARE_CALL(3) KVC_DECLARE_CALL(4) KVC_DECLARE_CALL(8)
 struct CheckItem {
     const uint32_t *payload;
     HeaderBytes expect;
-    uint32_t mask;                  // bit i = compare header word i
     const uint8_t *tables, *plan_tables;    // width tables in the payload and their device image
     long long table_bytes;
     int *status;
@@ -232,14 +231,13 @@ struct CoderArgs {
     long long total_chunks;     // K and V together
     int is_v;
     int tab;                    // table slot of this launch
-    int slots, slot_mask;       // table slots of the request's format (2 or 8) and the ones in use
     CoderScratch ws;
     unsigned long long *out_bytes;   // device: true payload size (written by the last workgroup)
 };
 
-// One launch of the coder for several requests of a call (the table kernels: blockIdx.y picks the
-// request; encoder and decoder: the requests' workgroups one after the other).  All items are
-// the same launch of their request (same tensor, width and kernel variant; see request_window).
+// One launch of the encoder or decoder for the requests of a window (see request_window), the items' workgroups one
+// after the other: a launch of every request (one tensor and width), or, where K and V share a launch, a
+// K and a V item of every request.  All items have one width and take the same kernel.
 constexpr int kCoderBatch = 8;      // (the argument block stays below 4 KB)
 struct CoderBatch {
     CoderArgs item[kCoderBatch];

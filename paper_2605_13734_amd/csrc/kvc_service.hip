@@ -42,13 +42,13 @@ __global__ __launch_bounds__(256) void compress_prologue_kernel(PrologueArgs a)
 }
 
 // Before decompression: the status word of every request, set to KVC_DEV_BAD_HEADER when the
-// payload's header (the words selected by `mask`) or its width tables differ from the plan's.
+// payload's header or its width tables differ from the plan's.
 // grid = requests, one workgroup each.
 __global__ __launch_bounds__(256) void decompress_prologue_kernel(CheckArgs a)
 {
     const CheckItem &it = a.item[blockIdx.x];
     const int t = threadIdx.x;
-    int diff = t < 32 && ((it.mask >> t) & 1u) && it.payload[t] != it.expect.w[t];
+    int diff = t < 32 && it.payload[t] != it.expect.w[t];
     for (long long i = t; i < it.table_bytes; i += 256) diff |= it.tables[i] != it.plan_tables[i];
     diff = __syncthreads_or(diff);
     if (t == 0) *it.status = diff ? KVC_DEV_BAD_HEADER : 0;
