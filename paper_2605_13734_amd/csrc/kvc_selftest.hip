@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64) void selftest_scan_silent_kernel(unsigned long 
     const long long start = wall_clock64();                     // (100 MHz)
     if (good && me == 0) scan_sizes(a, kScanTestWgs, kScanTestLimit);
     else if (good && me == 2) good = wait_for_place(a, me) == (kFlagPrefix | kNoPlace);
-    good = good && wall_clock64() - start < 20000000;           // 200 ms
+    good = good && wall_clock64() - start < 5000000;            // 50 ms
     if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
 }
 
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(64) void selftest_scan_after_kernel(unsigned long l
     const long long start = wall_clock64();
     if (good && me == kScanTestWgs) scan_sizes(a, a.total_wgs, kScanTestLimit);
     else if (good) good = wait_for_place(a, me) == (kFlagPrefix | kNoPlace);
-    good = good && wall_clock64() - start < 20000000;
+    good = good && wall_clock64() - start < 5000000;
     if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
 }
 

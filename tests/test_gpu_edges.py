@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2605_13734_amd import kvc, kvgen
+from test_gpu_full_size import check_sampled_bodies
 from test_gpu_parity import check_contiguous, gpu_compress
 
 pytestmark = pytest.mark.gpu
@@ -227,9 +228,12 @@ def test_shared_launches_under_capture(codec):
         assert torch.equal(buf.payload, eager.payload) and torch.equal(y, out), rep
 
 
-def test_calls_on_two_streams():
-    """Encoder launches that wait for their own workgroups, on two streams at once: each as it is alone."""
-    L, H, T, calls = 1, 8, 8192, 12
+@pytest.mark.parametrize("L,T,calls", [(1, 8192, 12), (1, 32768, 8), (8, 32768, 6)])
+def test_calls_on_two_streams(L, T, calls):
+    """Encoder launches on two streams at once, each as it is alone: launches that fit the chip together (1024 chunks of
+    K and V), that fill it each by itself, eight chunks per workgroup (4096), and of several times what it holds (32768), where the
+    scanners wait for workgroups that the other stream's launch keeps from starting."""
+    H = 8
     plan = kvc.Plan(kvc.F16, L, H, 128, 4, 4, 32, 32, 1, max_tokens=T)
     xs = [kvgen.make_kv(970 + i, L, H, 128, T, torch.float16, "cuda") for i in range(calls)]
     bufs = [kvc.Buffers(plan, [T]) for _ in xs]
@@ -242,5 +246,30 @@ def test_calls_on_two_streams():
     for i, x in enumerate(xs):
         alone.compress([kvc.contiguous_request(x)], torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
-        assert int(bufs[i].status[0]) == 0 and int(alone.status[0]) == 0
-        assert np.array_equal(bufs[i].payload_of(0), alone.payload_of(0)), i
+        n = int(alone.out_bytes[0])
+        assert int(bufs[i].status[0]) == 0 and int(alone.status[0]) == 0 and int(bufs[i].out_bytes[0]) == n
+        assert torch.equal(bufs[i].payload[:n], alone.payload[:n]), i
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bits,T", [(4, 32768 + 77), (2, 4 * 32768 - 128)])
+def test_both_tensors_of_large_requests(ref, bits, T, dtype):
+    """K and V in one encoder and one decoder launch just above 2^21 and just below 2^23 rows: sampled bodies against the
+    oracle, the reconstruction against the one without the lossless stage."""
+    L, H, dt = 8, 8, 1 if dtype == torch.float16 else 2
+    x = kvgen.make_kv(980 + bits, L, H, 128, T, dtype, "cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    back = []
+    for codec in (0, 1):
+        plan = kvc.Plan(dt, L, H, 128, bits, bits, 32, 32, codec, max_tokens=T)
+        buf = kvc.Buffers(plan, [T])
+        y = torch.full_like(x, 7.0)
+        buf.compress([kvc.contiguous_request(x)], s)
+        buf.decompress([kvc.contiguous_request(y)], s)
+        torch.cuda.synchronize()
+        assert int(buf.status[0]) == 0
+        back.append(y)
+    assert torch.equal(back[0].view(torch.int16), back[1].view(torch.int16))
+    n = L * H * -(-T // 128)
+    picks = [(0, 0), (0, n - 1), (1, 0), (1, n - 1), (0, n // 3), (1, n // 2 + 1)]
+    check_sampled_bodies(ref, buf, lambda l, kv, h: x[l, kv, h].cpu(), L, H, T, dt, bits, bits, 32, 32, picks)
