@@ -224,7 +224,7 @@ def other_configs(steps):
 
     # tiny: launch-bound, reported as latency per call
     contiguous("tiny_fp16_int4g32", 1, 8, 1024, torch.float16, kvc.F16, 4, 4, 32, 32, 0, 200)
-    out[-1]["note"] = "4 MB of KV: the times are launch latencies per call (prologue + K pass + V pass)"
+    out[-1]["note"] = "4 MB of KV: the times are launch latencies per call (one launch)"
     contiguous("tiny_fp16_int4g32_huff8", 1, 8, 1024, torch.float16, kvc.F16, 4, 4, 32, 32, 1, 200)
     # Llama-3.1-8B shape, 8192 tokens, bf16, both strategies
     contiguous("llama8b_8k_bf16_int2g64", 32, 8, 8192, torch.bfloat16, kvc.BF16, 2, 2, 64, 64, 0, 20)

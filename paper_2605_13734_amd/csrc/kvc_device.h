@@ -453,7 +453,9 @@ __device__ __forceinline__ uint32_t quad_24_from_words(uint32_t word)
 // and memory takes the mix of reads and writes better that way (a kernel that only reads 32 KB and
 // writes 10 KB per wave: 5.2 -> 5.8 TB/s; the compress calls with it, and with the metadata of
 // v_store_meta: 70B shape 2677 -> 2636 us, 8B shape bf16 2-bit / group 64 230 -> 220 us, with the rotation
-// 292 -> 279 us, 32 short requests with the lossless stage 1858 -> 1749 us).
+// 292 -> 279 us, 32 short requests with the lossless stage 1858 -> 1749 us).  Only where a call rewrites a
+// payload that the last-level cache (256 MB) still holds do plain stores win: 2^19.7 rows, 4 bits, two payload buffers in
+// turn 105 against 102 us, eight in turn 106 against 112.
 template <bool STREAM, typename T> __device__ __forceinline__ void put_at(void *p, T v)
 {
     if (STREAM) __builtin_nontemporal_store(v, (T *)p);
