@@ -68,7 +68,9 @@ static inline unsigned place_items(QuantBatch &b)
 // arithmetic needs the waves (rotation, 40000: compress +2 %, decompress +3 %).
 //   decompress, dense    2 bits -1 to -5 % with 40000, 3 bits 0 to -2 %, 8 bits +1 to +2 %; 4 bits (the call) below 2^22
 //                        rows -1 to -6 % with 40000, above up to +5 % with 40000 and -1 % with 32000
-//   decompress, strided  4 bits -2 to -6 % (bf16 -1 to 0 %) with 40000, fp16 2 and 3 bits up to +4 %, others 0
+//   decompress, strided  with 40000: 4 bits 0 to -6 %, fp16 2 and 3 bits up to +4 %; from 2^19 rows bf16 2 bits 0 to
+//                        -3 %, 8 bits -1 to -3 % (from 2^22: 0 to +1 %); from 2^21 bf16 3 bits +1 to -3 %; below these 0
+//                        to +5 %
 //   compress, dense      K, groups of 32: fp16 2 and 3 bits -1 to -4 % with 36000 (40000: -2 to +1 %), bf16 2 to 4 bits 0 to -1 % (+2
 //                        to +6 %), fp16 4 bits and 8 bits -1 to -3 % with 40000; groups of 64 -1 to -3 % with 40000, of 128
 //                        and V 0; below 2^20 rows, where the tensor is a few generations of workgroups, 0 to +2 %
@@ -81,7 +83,11 @@ static inline unsigned window_lds(const QuantBatch &b, bool compress, bool is_v,
     long long rows = 0;
     for (int i = 0; i < b.n; ++i) rows += b.item[i].total_units * (compress && !is_v ? group : kPassRows);
     if (!compress) {
-        if (!a.dense) return bits == 4 ? 40000 : 0;
+        if (!a.dense) {
+            if (bits == 8) return rows >= (1ll << 19) && rows < (1ll << 22) ? 40000 : 0;
+            if (bits < 4) return dtype == DT_BF16 && rows >= (bits == 2 ? 1ll << 19 : 1ll << 21) ? 40000 : 0;
+            return 40000;
+        }
         if (bits != 4) return bits < 4 ? 40000 : 0;
         return rows < (1ll << 22) ? 40000 : 32000;
     }

@@ -100,6 +100,10 @@ def test_bound_on_the_workgroups_of_a_unit(bits, paged, dtype):
     found = launches(call_of("decompress", L, H, T, group_k=32, **kw))
     want = (40000 if bits == 4 else 0) if paged else (40000 if bits <= 4 else 0)
     assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
+    if paged:                                            # 2^19 rows and more
+        found = launches(call_of("decompress", 8, 8, 8192, group_k=32, **kw))
+        want = 40000 if bits in (4, 8) or (bits == 2 and not f16) else 0
+        assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
 
 
 @pytest.mark.parametrize("T", [16384 - 128, 16384])
