@@ -66,8 +66,10 @@ static inline unsigned place_items(QuantBatch &b)
 // is off where it did not pay.  With 40000 bytes a unit takes four workgroups (three of a K compression, which has
 // 4096 of its own; with 36000 four), with 32000 five (four).  Launches with a transform have none: its
 // arithmetic needs the waves (rotation, 40000: compress +2 %, decompress +3 %).
-//   decompress, dense    2 bits -1 to -5 % with 40000, 3 bits 0 to -2 %, 8 bits +1 to +2 %; 4 bits (the call) below 2^22
-//                        rows -1 to -6 % with 40000, above up to +5 % with 40000 and -1 % with 32000
+//   decompress, dense    2 bits -1 to -7 % with 40000, 3 bits 0 to -2 %, 8 bits +1 to +2 %; 4 bits (the call) below 2^22
+//                        rows -1 to -6 % (bf16 from 2^21.5: 0 to +3 %) with 40000, above up to +5 % with 40000 and -1 % with 32000;
+//                        several requests in a launch, 2^21 rows and more: 4 bits 0 to +5 % with 40000, 3 bits -1 to
+//                        +3 %, either 0 to -1 % with 32000
 //   decompress, strided  with 40000: 4 bits 0 to -6 %, fp16 2 and 3 bits up to +4 %; from 2^19 rows bf16 2 bits 0 to
 //                        -3 %, 8 bits -1 to -3 % (from 2^22: 0 to +1 %); from 2^21 bf16 3 bits +1 to -3 %; below these 0
 //                        to +5 %
@@ -88,8 +90,9 @@ static inline unsigned window_lds(const QuantBatch &b, bool compress, bool is_v,
             if (bits < 4) return dtype == DT_BF16 && rows >= (bits == 2 ? 1ll << 19 : 1ll << 21) ? 40000 : 0;
             return 40000;
         }
-        if (bits != 4) return bits < 4 ? 40000 : 0;
-        return rows < (1ll << 22) ? 40000 : 32000;
+        if (bits == 8) return 0;
+        const bool narrow = bits == 2 || rows < (1ll << 21) || (b.n == 1 && (bits == 3 || rows < (1ll << 22)));
+        return narrow ? 40000 : 32000;
     }
     if (is_v) return !a.dense && dtype == DT_F16 ? 32000 : 0;
     const bool wide = bits == 8 || (bits == 4 && dtype == DT_F16);

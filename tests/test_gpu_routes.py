@@ -121,6 +121,14 @@ def test_bound_of_large_four_bit_decompressions(T, lds):
     assert lds_of(found, "decompress_k_kernel") == lds and lds_of(found, "decompress_v_kernel") == lds
 
 
+@pytest.mark.parametrize("bits,lds", [(2, 40000), (3, 32000), (4, 32000), (8, 0)])
+def test_bound_of_decompressions_of_many_requests(bits, lds):
+    """Eight requests in a launch, just below 2^21 rows together and 2^21."""
+    for T, want in ((4096 - 32, 40000 if bits < 8 else 0), (4096, lds)):
+        found = launches(call_of("decompress", 8, 8, T, n=8, bits_k=bits, bits_v=bits, group_k=32, group_v=64))
+        assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
+
+
 @pytest.mark.parametrize("kw", [dict(transform=1), dict(transform=2, anchor_period=16)])
 def test_no_bound_with_a_transform(kw):
     for direction in ("compress", "decompress"):
