@@ -14,6 +14,7 @@ constexpr int kScanWindows = 4;
 constexpr int kScanCarry = 4;      // word of the ticket's block where the scan of one launch leaves its end to the next
 constexpr int kSpinLimit = 1 << 20;
 constexpr int kSpinCheck = 256;    // looks between two questions whether the wait is for somebody
+constexpr long long kStartLimit = 1000000000;      // ticks of 10 ns: the longest wait for a workgroup to start
 
 // One workgroup = kWaves chunks.  A chunk's body offset is the sum of all earlier bodies of the
 // request (K chunks first, then V): a single-pass scan over one state word per workgroup, made by one
@@ -24,7 +25,8 @@ constexpr int kSpinCheck = 256;    // looks between two questions whether the wa
 // workgroup with the launch's first ticket.  A workgroup waits for the scanner and for workgroups with
 // earlier tickets: all of them are running, so the wait ends; it is bounded by kSpinLimit all the same.
 // The scanner waits for running workgroups too, but also for tickets that nobody has taken, for as long as
-// other work keeps the rest of the launch off the chip; only the first kind of wait is bounded.
+// other work keeps the rest of the launch off the chip: looks count only in the first kind of wait, the second
+// ends after ten seconds (calls that overlap on one workspace may have taken each other's tickets).
 // Whoever gives up marks the request's carry word: everybody else who waits stops too, no later launch of the
 // request places a body, and directory and header stay open.
 // (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
@@ -50,8 +52,9 @@ __device__ __forceinline__ void give_up(const CoderArgs &a)
 }
 
 // The scan of one request's launch, whose last workgroup is `end` - 1; the last launch's scanner closes
-// the directory and the header.  limit: looks without progress at a workgroup that is running.
-__device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, int limit = kSpinLimit)
+// the directory and the header.  limit: looks without progress at a workgroup that is running; start_limit: ticks
+// without progress for one that is not.
+__device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, int limit = kSpinLimit, long long start_limit = kStartLimit)
 {
     const int lane = lane_id();
     unsigned long long *carry = scan_carry(a);
@@ -59,6 +62,7 @@ __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, in
     if (prefix == kNoPlace) return;
     int spins = 0;
     bool nobody = false;               // the next ticket has not been taken
+    long long since = 0;               // since when (0: it has, as far as known)
     __builtin_amdgcn_s_setprio(3);
     // kScanWindows windows of 64 workgroups per look (a look is a round trip to memory, and the scanner has to
     // keep up with all workgroups of the chip)
@@ -91,12 +95,17 @@ __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, in
         }
         if (moved) {
             spins = 0;
+            since = 0;
             nobody = false;
         } else if ((++spins & (kSpinCheck - 1)) == 0) {
             nobody = (unsigned)next >= __hip_atomic_load(a.ws.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (scan_failed(a)) return;
-            if (nobody) spins = 0;
-            else if (spins > limit) return give_up(a);
+            if (nobody) {
+                const long long now = wall_clock64();
+                if (since == 0) since = now;
+                if (now - since > start_limit) return give_up(a);
+                spins = 0;
+            } else if (spins > limit) return give_up(a);
         }
         if (nobody) __builtin_amdgcn_s_sleep(32);
     }

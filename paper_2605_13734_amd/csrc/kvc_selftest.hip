@@ -195,6 +195,18 @@ __global__ __launch_bounds__(64) void selftest_scan_after_kernel(unsigned long l
     if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
 }
 
+// A workgroup that never starts: the scanner gives up after the time that it is given, 2 ms here.
+__global__ __launch_bounds__(64) void selftest_scan_absent_kernel(unsigned long long *slot)
+{
+    const CoderArgs a = scan_test_args();
+    bool good = scan_test_enter(a, 0, 0, false);
+    const long long start = wall_clock64();
+    if (good) scan_sizes(a, kScanTestWgs, kScanTestLimit, 200000);
+    const long long took = wall_clock64() - start;
+    good = good && took >= 200000 && took < 5000000;
+    if (!good && lane_id() == 0) atomicAdd(slot, 1ull);
+}
+
 // Nothing has been closed and the request's status says so.
 __global__ __launch_bounds__(64) void selftest_scan_open_kernel(unsigned long long *slot)
 {
@@ -226,6 +238,9 @@ extern "C" int kvc_selftest(uint64_t *counts, void *stream)
     selftest_scan_start_kernel<<<1, 64, 0, s>>>();
     selftest_scan_silent_kernel<<<kScanTestWgs, 64, 0, s>>>(c + 7);
     selftest_scan_after_kernel<<<2, 64, 0, s>>>(c + 7);
+    selftest_scan_open_kernel<<<1, 64, 0, s>>>(c + 7);
+    selftest_scan_start_kernel<<<1, 64, 0, s>>>();
+    selftest_scan_absent_kernel<<<1, 64, 0, s>>>(c + 7);
     selftest_scan_open_kernel<<<1, 64, 0, s>>>(c + 7);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }

@@ -24,7 +24,8 @@ def test_arithmetic_shortcuts_are_exact():
 def test_place_scan_waits():
     """The encoder's scanner gives up on a running workgroup that reports nothing, not on one that other work on the GPU
     keeps from starting: the self-test lets the last of three start twenty times the scanner's limit late.  Where one of
-    them never reports, the others stop within 50 ms, and nothing is placed or closed, by the next launch either."""
+    them never reports, the others stop within 50 ms, and nothing is placed or closed, by the next launch either; one
+    that never starts is waited for as long as the scanner is told."""
     counts = torch.full((kvc.SELFTEST_COUNTS,), -1, dtype=torch.int64, device="cuda:0")
     assert kvc.selftest(counts.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
