@@ -60,6 +60,11 @@ WORKLOADS = {
 }
 
 
+def progress(what):
+    """One line on stderr per stage (the result is one line on stdout, at the end)."""
+    print("bench: " + what, file=sys.stderr, flush=True)
+
+
 def host_cores():
     """Cores this process may use: the scheduler's affinity set, at most the 16 a one-GPU job is given."""
     try:
@@ -84,6 +89,7 @@ def cpu_baseline(x_dev, layers, heads, tokens, dt, bits_k, bits_v, gk, gv, codec
                      head_bits_k=head_bits[0][:sample_layers * heads] if head_bits else None,
                      head_bits_v=head_bits[1][:sample_layers * heads] if head_bits else None)
     lay = ref.contiguous_layout(heads, tokens, 128)
+    progress("oracle, one core")
     t0 = time.perf_counter()
     payload = ref.compress(cfg, xu[0, 0], xu[0, 1], lay, tokens)
     t1 = time.perf_counter()
@@ -111,6 +117,7 @@ def cpu_baseline(x_dev, layers, heads, tokens, dt, bits_k, bits_v, gk, gv, codec
                         head_bits_v=head_bits[1][l * heads:(l + 1) * heads] if head_bits else None)
         p = ref.compress(c1, xa[l, 0], xa[l, 1], lay, tokens)
         assert ref.decompress(p, back[l, 0], back[l, 1], lay, c1) == 0
+        progress("oracle, all cores: layer %d done" % l)
         return p.size
 
     t0 = time.perf_counter()
@@ -214,6 +221,7 @@ def other_configs(steps):
     out = []
 
     def contiguous(name, L, H, T, dtype, dt, bk, bv, gk, gv, codec, n):
+        progress(name)
         x = kvgen.make_kv(0, L, H, 128, T, dtype, dev)
         y = torch.empty_like(x)
         plan = kvc.Plan(dt, L, H, 128, bk, bv, gk, gv, codec, max_tokens=T)
@@ -232,6 +240,7 @@ def other_configs(steps):
     torch.cuda.empty_cache()
 
     # Qwen3-235B attention shape: 94 layers, 4 KV heads, bf16, ragged batch of 4, K 4-bit / V 2-bit, group 64
+    progress("qwen3_235b_ragged4, short requests, paged sweep")
     L, H = 94, 4
     lens = kvgen.request_lengths(0, 4, 16384, 32768)
     xs = [kvgen.make_kv(100 + i, L, H, 128, T, torch.bfloat16, dev) for i, T in enumerate(lens)]
@@ -300,6 +309,7 @@ def streamed(x, y, dt, L, H, T, bk, bv, gk, gv, codec, single_ms):
              ("decompress", lambda l, s: bufs[l].decompress([kvc.contiguous_request(y[l:l + 1])], s.cuda_stream)))
     for name, call in calls:
         for ns, key in ((2, name + "_ms"), (4, name + "_ms_4_streams")):
+            progress("streamed %s, %d streams" % (name, ns))
             for rep in range(2):                                      # the first round warms up
                 torch.cuda.synchronize()
                 t0 = time.perf_counter()
@@ -318,6 +328,7 @@ def streamed(x, y, dt, L, H, T, bk, bv, gk, gv, codec, single_ms):
         y_eager = y[:L].clone()
         s0, s1 = streams[0], streams[1]
         for name, call in calls:
+            progress("streamed %s, graph" % name)
             g = torch.cuda.CUDAGraph()
             torch.cuda.synchronize()
             with torch.cuda.graph(g, stream=s0):
@@ -424,6 +435,7 @@ def main():
         buf.compress(src, stream)
         buf.decompress(dst, stream)
 
+    progress(args.workload)
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
