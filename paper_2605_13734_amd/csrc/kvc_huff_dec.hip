@@ -12,37 +12,60 @@ namespace kvc {
 
 // ---- decoder ---------------------------------------------------------------------------------
 
+typedef __attribute__((address_space(3))) const uint32_t *LdsWords;
+
 struct BitReader {
-    unsigned long long window;   // upcoming bits, left aligned
-    int avail;
-    const uint32_t *next;        // next word (LDS)
-    const uint32_t *last;        // last readable word
+    uint32_t hi, lo, ahead;      // the word being read, the next one, and the one after that, in flight
+    uint32_t rest;               // low byte: bits of `hi` that are still to be read, 0..31 (the other bytes: anything)
+    uint32_t next, last;         // where `ahead` comes from and the last readable word (LDS addresses)
 };
 
-__device__ __forceinline__ void refill(BitReader &br)
+__device__ __forceinline__ uint32_t lds_word(uint32_t at) { return *(LdsWords)at; }
+
+// The stream starts at bit `bit` of the words behind the body's 64 bit counts; the body has `size` bytes.
+__device__ __forceinline__ void reader_start(BitReader &br, const uint8_t *body, uint32_t bit, uint32_t size)
 {
-    if (br.avail <= 32) {
-        br.window |= (unsigned long long)(*br.next) << (32 - br.avail);
-        br.avail += 32;
-        if (br.next < br.last) ++br.next;
-    }
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint8_t *)body;
+    br.last = base + size - 4;
+    uint32_t at = base + 2 * kSubs + 4 * ((int)(bit - 1) >> 5);       // (bit 0: all of the word before the stream has been read)
+    at = min(at, br.last);
+    br.hi = lds_word(at);
+    at = min(at + 4, br.last);
+    br.lo = lds_word(at);
+    br.next = min(at + 4, br.last);
+    br.ahead = lds_word(br.next);
+    br.rest = (0u - bit) & 31;
+}
+
+// Two symbols (24 bits at most).  A table entry is symbol << 8 | (256 - length): its low five bits shift the
+// window by the length as they are, and added up they count `rest` down, so that no field is taken
+// out of an entry before the symbols are collected.  The word that a refill brings in was requested a pair
+// earlier, so the chain is two table look-ups, and a lane that needs no word asks for the same one again instead of
+// branching.  15 vector operations per pair; a 64-bit window with a load in every refill took 21 and a third LDS
+// round trip (decompress calls of 2^21 rows: 8 bits 449 -> 368 us, 4 bits 254 -> 247, half of the heads at 8 and half at
+// 2 bits 370 -> 325; one layer of 32k tokens, 4 bits, 42.7 -> 41.2).
+__device__ __forceinline__ void decode_pair(const uint16_t *lut, BitReader &br, uint32_t &e0, uint32_t &e1)
+{
+    const uint32_t window = __builtin_amdgcn_alignbit(br.hi, br.lo, br.rest);
+    e0 = lut[window >> 20];
+    e1 = lut[__builtin_amdgcn_alignbit(window, 0, e0) >> 20];
+    const uint32_t rest = br.rest + e0 + e1, over = (rest >> 7) & 1;
+    br.hi = over ? br.lo : br.hi;
+    br.lo = over ? br.ahead : br.lo;
+    br.rest = rest + (over << 5);
+    br.next = min(br.next + (over << 2), br.last);
+    br.ahead = lds_word(br.next);
 }
 
 template <int W> __device__ __forceinline__ void decode_half(uint32_t *sym, const uint16_t *lut, int half, BitReader &br)
 {
 #pragma unroll
     for (int k = 0; k < W / 2; ++k) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t e = lut[(uint32_t)(br.window >> 52)];
-            const uint32_t len = e >> 8;
-            w = __builtin_amdgcn_alignbit(e, w, 8);      // symbol byte enters at the top; after 4 symbols the first is lowest
-            br.window <<= len;
-            br.avail -= (int)len;
-            if (b & 1) refill(br);
-        }
-        sym[half * (W / 2) + k] = w;
+        uint32_t e[4];
+        decode_pair(lut, br, e[0], e[1]);
+        decode_pair(lut, br, e[2], e[3]);
+        const uint32_t low = __builtin_amdgcn_perm(e[1], e[0], 0x0c0c0501u), high = __builtin_amdgcn_perm(e[3], e[2], 0x0c0c0501u);
+        sym[half * (W / 2) + k] = __builtin_amdgcn_perm(high, low, 0x05040100u);
     }
 }
 
@@ -225,18 +248,8 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
             return;
         }
         const uint32_t start = incl - bits;
-        const uint32_t *words = (const uint32_t *)(lds + 2 * kSubs);
         BitReader br;
-        br.last = (const uint32_t *)(lds + size) - 1;
-        const uint32_t *p = words + (start >> 5);
-        p = p < br.last ? p : br.last;
-        const uint32_t w0 = *p;
-        p = p < br.last ? p + 1 : p;
-        const uint32_t w1 = *p;
-        p = p < br.last ? p + 1 : p;
-        br.window = (((unsigned long long)w0 << 32) | w1) << (start & 31);
-        br.avail = 64 - (int)(start & 31);
-        br.next = p;
+        reader_start(br, lds, start, (uint32_t)size);
         uint32_t sym[W];
 #pragma unroll
         for (int k = 0; k < W; ++k) sym[k] = 0;

@@ -399,7 +399,7 @@ __global__ __launch_bounds__(512) void decode_setup_kernel(DecodeSetupArgs a)
         int L = 1;
 #pragma unroll
         for (int l = 1; l < kMaxLen; ++l) L += i >= limit[l] ? 1 : 0;
-        const uint32_t e = by_len[((int)(i >> (kMaxLen - L)) + base[L]) & 255] | ((uint32_t)L << 8);
+        const uint32_t e = (uint32_t)by_len[((int)(i >> (kMaxLen - L)) + base[L]) & 255] << 8 | (256u - (uint32_t)L);
         out[k >> 1] = (k & 1) ? out[k >> 1] | (e << 16) : e;
     }
     ((u32x4 *)(it.lut + 4096 * sec))[tid] = out;

@@ -178,7 +178,7 @@ constexpr int kSampleChunks = 16;
 // Per-request scratch inside the caller's workspace (device memory).
 struct CoderScratch {
     uint16_t *sample;           // [slots][kSampleChunks][256] byte counts of the sample chunks
-    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol | length << 8; while compressing, the
+    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol << 8 | (256 - length); while compressing, the
                                 // candidates for the slot's code table (CandidateTables)
     unsigned long long *state;  // scan state, one word per encode workgroup (in launch order)
     uint32_t *ticket;           // work-order counter
