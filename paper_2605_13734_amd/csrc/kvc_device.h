@@ -137,6 +137,7 @@ __device__ __forceinline__ uint32_t f32_to_f16_bits(float f)
 }
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 // Keeps the compiler from merging an fp32 operation with a following conversion to fp16 into
@@ -161,7 +162,8 @@ template <int DT, bool CLAMP> __device__ __forceinline__ uint32_t pack_out(float
             a = rounded_f32(a);
             b = rounded_f32(b);
         }
-        return f32_to_f16_bits(a) | (f32_to_f16_bits(b) << 16);
+        f32x2_t v = {a, b};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));       // v_cvt_pk_f16_f32
     }
     f32x2_t v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));      // v_cvt_pk_bf16_f32
@@ -212,8 +214,6 @@ template <int MASK> __device__ __forceinline__ float xor_lane_f32(float v)
     // ds_swizzle, bit-mask mode: and 0x1f, or 0, xor MASK (no LDS memory is touched)
     return __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(v), (MASK << 10) | 0x1f));
 }
-
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 
 // One row of 128 values, 8 per lane over 16 lanes (lane & 15 = col holds channels 8*col ...):
 // y = H x * scale, H the Walsh-Hadamard matrix in natural order, as the fast transform with the
@@ -412,23 +412,45 @@ template <int BITS, bool CLAMP> __device__ __forceinline__ u32x2 codes8(float t[
     return r;
 }
 
-// The lane's 8 codes as floats.  4- and 8-bit codes go through the byte-to-float conversions.
-template <int BITS> __device__ __forceinline__ void unpack8(u32x2 w, float q[8])
+// The lane's 8 codes as fp16 subnormals: word k holds code k in its low and code k + 4 in its high half, at bit
+// code_shift(k) of the mantissa, which as a half-precision number is code * 2^(code_shift(k) - 24).  The
+// mixed-precision FMA reads such a half directly, so that a code costs a mask (two codes at a time) and no
+// conversion: with a scale that carries the factor 2^(24 - code_shift(k)) the product is the same exact number.
+template <int BITS> constexpr int code_shift(int k)
+{
+    return BITS == 4 ? 4 * (k & 1) : BITS == 3 ? (k == 3 ? 0 : 3 * k) : BITS == 2 ? 2 * k : 0;
+}
+// 2^(24 - code_shift(k))
+template <int BITS> constexpr float code_factor(int k) { return (float)(1 << (24 - code_shift<BITS>(k))); }
+
+template <int BITS> __device__ __forceinline__ void unpack8(u32x2 w, uint32_t p[4])
 {
     if (BITS == 8) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = (float)((w[e >> 2] >> ((e & 3) * 8)) & 0xffu);
+        p[0] = __builtin_amdgcn_perm(w[1], w[0], 0x0c040c00u);
+        p[1] = __builtin_amdgcn_perm(w[1], w[0], 0x0c050c01u);
+        p[2] = __builtin_amdgcn_perm(w[1], w[0], 0x0c060c02u);
+        p[3] = __builtin_amdgcn_perm(w[1], w[0], 0x0c070c03u);
     } else if (BITS == 4) {
-        const uint32_t lo = w[0] & 0x0f0f0f0fu, hi = (w[0] >> 4) & 0x0f0f0f0fu;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            q[2 * k] = (float)((lo >> (8 * k)) & 0xffu);
-            q[2 * k + 1] = (float)((hi >> (8 * k)) & 0xffu);
-        }
+        const uint32_t high = w[0] >> 8;
+        p[0] = w[0] & 0x000f000fu;
+        p[1] = w[0] & 0x00f000f0u;
+        p[2] = high & 0x000f000fu;
+        p[3] = high & 0x00f000f0u;
+    } else if (BITS == 3) {
+        const uint32_t v = (w[0] & 0xffffu) | ((w[0] << 4) & 0xffff0000u);      // codes 4..7 (from bit 12 on) to the upper half
+        p[0] = v & 0x00070007u;
+        p[1] = v & 0x00380038u;
+        p[2] = v & 0x01c001c0u;
+        p[3] = (v >> 9) & 0x00070007u;
     } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = (float)((w[0] >> (e * BITS)) & ((1u << BITS) - 1u));
+        const uint32_t v = w[0] | (w[0] << 8);                                  // codes 4..7 (from bit 8 on) to the upper half
+        p[0] = v & 0x00030003u;
+        p[1] = v & 0x000c000cu;
+        p[2] = v & 0x00300030u;
+        p[3] = v & 0x00c000c0u;
     }
+    // (otherwise the compiler takes every code out of the word for itself)
+    asm("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
 }
 
 // 3-bit rows: the 4 lanes of a quad hold 4 x 24 bits = three aligned words.  Lane k < 3 of

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
     using Dec = DecGeom<BITS>;
     constexpr int W = Geo::kWords, NW = Geo::kDecWaves;
     unsigned wg;
-    const CoderArgs &a = batch.item[batch_item(batch, wg)];
+    const CoderArgs &a = batch.item[place_item_at_once(batch.at, place_of_workgroup(batch.at), wg)];
     const bool is_v = KV == 2 ? a.is_v != 0 : KV == 1;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Dec::kLds];
     __shared__ uint16_t lut[4096];
@@ -277,6 +277,32 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
 
 // ---- launchers ----------------------------------------------------------------------------------
 
+// Runs of workgroups per XCD (place_of_workgroup) and LDS that nothing uses (as for the codec-free kernels: 14000 more leave three
+// workgroups to a compute unit, 40000 two).  Decompress calls in us, as they were (a conversion per code, neither) / now:
+//   dense    rows    2^18        2^19.6      2^20.6      2^21.6      2^22.6      2^23.3 (a launch per tensor)
+//   2 bits   38.4 / 38.2   95 / 91   197 / 167   373 / 317   759 / 642   1080 / 1076
+//   3 bits   35.5 / 35.5   94 / 91   180 / 165   390 / 313   773 / 636   1143 / 1121
+//   4 bits   43.0 / 41.6  106 / 104  190 / 190   375 / 357   799 / 715   1206 / 1200
+//   (2^21 rows, 4 bits: with run 64 249, 16 258, without 268; 3 bits with 14000 225, 40000 218; 8 bits, bound by the table
+//   look-ups: without either 377, runs 384; 2^23.3 rows and more in one launch, run 64 for 16: +2 %)
+//   paged    2 bits, 14000 below the large ones: 2^21 rows 239 / 231 (without 259), 2^23.3 1262 / 1220 (with it 1346); 3 bits
+//   131 / 129, 757 / 730
+//   launches that are resident at once or nearly gain nothing
+struct DecodeShape {
+    unsigned lds = 0;
+    int run = 0;
+};
+
+template <int BITS> static DecodeShape decode_shape(unsigned wgs, bool both, bool dense, bool transform)
+{
+    constexpr unsigned kResident = 4 * 256;
+    if (transform || BITS == 8 || wgs < 3 * kResident) return {};
+    const bool large = !both && wgs >= 16 * kResident;
+    if (!dense) return {BITS != 4 && !large ? 14000u : 0u, 0};
+    if (large) return {BITS == 3 ? 14000u : 0u, 16};
+    return {BITS == 2 ? 14000u : BITS == 3 ? 40000u : 0u, 64};
+}
+
 template <int BITS, int DT, int KV> static int decode_launch(const CoderBatch &b, hipStream_t s)
 {
     constexpr int NW = ChunkGeom<BITS>::kDecWaves;
@@ -284,14 +310,15 @@ template <int BITS, int DT, int KV> static int decode_launch(const CoderBatch &b
     CoderBatch placed = b;
     unsigned need = 0;
     for (int i = 0; i < b.n; ++i) {
-        placed.start[i] = need;
+        placed.at.start[i] = need;
         need += (unsigned)((b.item[i].chunks + NW - 1) / NW);
     }
-    placed.start[b.n] = need;
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
     const int tr = a.q.rotate ? 1 : !a.q.anchors ? 0 : a.q.anchor_shift >= 5 ? 2 : 3;
-#define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, KV, D, T>), grid, block, 0, s, placed)
+    const DecodeShape shape = decode_shape<BITS>(need, KV == 2, a.q.dense != 0, tr != 0);
+    close_places(placed.at, b.n, need, shape.run);
+#define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, KV, D, T>), grid, block, shape.lds, s, placed)
     if (KV == 2) {
         if (tr != 0) return KVC_ERR_UNSUPPORTED;
         if (a.q.dense) KVC_DECODE(true, 0); else KVC_DECODE(false, 0);

@@ -108,7 +108,7 @@ void encode_kernel(CoderBatch batch)
     constexpr int W = Geo::kWords;
     constexpr int kItems = KV == 2 ? 2 : 1;                      // items per request
     unsigned wg;
-    const int item = kItems * batch_item(batch, wg);
+    const int item = kItems * place_item(batch.at, blockIdx.x, wg);
     const CoderArgs &first = batch.item[item];
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Geo::kLds];
     __shared__ EncTables enc;
@@ -279,10 +279,10 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
     if (KV == 2) placed.n = b.n / 2;                  // requests
     unsigned need = 0;
     for (int i = 0; i < placed.n; ++i) {
-        placed.start[i] = need;
+        placed.at.start[i] = need;
         need += KV == 2 ? (unsigned)b.item[2 * i].total_wgs : (unsigned)((b.item[i].chunks + NW - 1) / NW);
     }
-    placed.start[placed.n] = need;
+    close_places(placed.at, placed.n, need, 0);
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
 #define KVC_ENCODE(D, X) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, X, NW>), grid, block, 0, s, placed)

@@ -48,64 +48,97 @@ __device__ __forceinline__ void report(int *status, bool bad)
 }
 
 // workgroups of four units, item after item
-static inline unsigned place_items(QuantBatch &b)
+static inline unsigned place_items(QuantBatch &b, int run)
 {
-    unsigned at = 0;
+    unsigned total = 0;
     for (int i = 0; i < b.n; ++i) {
-        b.start[i] = at;
-        at += (unsigned)((b.item[i].total_units + 3) / 4);
+        b.at.start[i] = total;
+        total += (unsigned)((b.item[i].total_units + 3) / 4);
     }
-    b.start[b.n] = at;
-    return at;
+    close_places(b.at, b.n, total, run);
+    return total;
 }
 
-// Dynamic LDS that nothing uses: it bounds the workgroups of a compute unit, and with them the window of the
-// tensor that the chip reads or writes at a time (a wave's rows are 8 KB), which memory takes better when it
-// is small.  What pays was measured kernel by kernel (K and V apart; change of the call's time against no bound; 32
-// layers of 16384 tokens and 94 x 4 heads of 24576, groups of 32, 64 and 128, fp16 and bf16), and the bound
-// is off where it did not pay.  With 40000 bytes a unit takes four workgroups (three of a K compression, which has
-// 4096 of its own; with 36000 four), with 32000 five (four).  Launches with a transform have none: its
-// arithmetic needs the waves (rotation, 40000: compress +2 %, decompress +3 %).
-//   decompress, dense    2 bits -1 to -7 % with 40000, 3 bits 0 to -2 %, 8 bits +1 to +2 %; 4 bits (the call) below 2^22
-//                        rows -1 to -6 % (bf16 from 2^21.5: 0 to +3 %) with 40000, above up to +5 % with 40000 and -1 % with 32000;
-//                        several requests in a launch, 2^21 rows and more: 4 bits 0 to +5 % with 40000, 3 bits -1 to
-//                        +3 %, either 0 to -1 % with 32000
-//   decompress, strided  with 40000: 4 bits 0 to -6 %, fp16 2 and 3 bits up to +4 %; from 2^19 rows bf16 2 bits 0 to
-//                        -3 %, 8 bits -1 to -3 % (from 2^22: 0 to +1 %); from 2^21 bf16 3 bits +1 to -3 %; below these 0
-//                        to +5 %
-//   compress, dense      K, groups of 32: fp16 2 and 3 bits -1 to -4 % with 36000 (40000: -2 to +1 %), bf16 2 to 4 bits 0 to -1 % (+2
-//                        to +6 %), fp16 4 bits and 8 bits -1 to -3 % with 40000; groups of 64 -1 to -3 % with 40000, of 128
-//                        and V 0; below 2^20 rows, where the tensor is a few generations of workgroups, 0 to +2 %
-//   compress, strided    K, groups of 32: fp16 4 bits and 8 bits -1 to -3 % with 32000, 2 and 3 bits and bf16 4 bits +2 to +7 %;
-//                        V: fp16 0 to -2 % with 32000, bf16 0 to +2 %
-static inline unsigned window_lds(const QuantBatch &b, bool compress, bool is_v, int bits, int group, int dtype)
+// How a launch is spread over the chip and over time.  Memory takes few, steady streams of stores better than many
+// bursts, so the less arithmetic a kernel has, the more its time depends on these.
+//
+// lds: dynamic LDS that nothing uses.  It bounds the workgroups of a compute unit, and with them the window of the
+// tensor that the chip reads or writes at a time (a wave's rows are 8 KB): with 80000 bytes two workgroups, 52000
+// three, 40000 four (a K compression, which has 4096 of its own, three; with 36000 four), 32000 five.
+// run: see place_of_workgroup.  pace: 64-cycle waits between the row stores of a unit.
+// What pays was measured kernel by kernel, and each is off where it did not pay.  Launches with a transform have none:
+// the arithmetic needs the waves (rotation, 40000: compress +2 %, decompress +3 %).
+//
+// Decompress calls in us, as they were (a conversion per code, holds of 0 to 40000) / now; groups of 32, 2 bits 64:
+//            rows     2^21        2^21.6       2^22        2^22.6      2^23.2       2^23.3        2^23.9
+//   dense    4 bits   229 / 226   343 / 336    456 / 440   732 / 670  1086 /  997   1158 / 1069   1757 / 1593
+//            8 bits   274 / 273   408 / 405    548 / 530   886 / 844  1333 / 1241   1423 / 1331   2179 / 1949
+//            3 bits   198 / 189   335 / 322    427 / 424   704 / 660   978 /  979   1041 / 1044   1610 / 1557
+//            2 bits   183 / 173   290 / 251    413 / 409   656 / 634   923 /  935    982 / 1000   1547 / 1537
+//       bf16 2 bits   182 / 174   291 / 253    420 / 405   665 / 632   960 /  937   1001 /  999   1590 / 1490
+//   paged    4 bits   239 / 240   344 / 344    457 / 456   713 / 699  1141 / 1094   1280 / 1227   1869 / 1789
+//       bf16 4 bits   247 / 241   365 / 346    485 / 461   758 / 702  1189 / 1085   1284 / 1222   1904 / 1785
+//            8 bits   295 / 282   432 / 409    582 / 544   900 / 844  1393 / 1292   1515 / 1449   2224 / 2109
+//            3 bits   200 / 200   352 / 334    465 / 443   718 / 680  1082 / 1031   1233 / 1188   1809 / 1734
+//            2 bits   184 / 176   271 / 263    416 / 401   642 / 631   969 /  966   1094 / 1090   1606 / 1600
+//       bf16 2 bits   184 / 176   271 / 264    430 / 414   655 / 640   981 /  950   1125 / 1090   1674 / 1601
+//   What the neighbours of a choice cost: dense 3 bits 2^23.3 rows, 40000 for 80000 1073, no run 1085; dense fp16 2 bits 1013 with
+//   run 16, 80000; paged 3 bits 32000 1264; a wait more or less 1 to 3 %, on dense rows 40 %.  Between 2^21 and 2^22.6 rows
+//   dense 4 bits would gain another 3 % from 80000 (326 and 426 us); their bound is fixed by the route tests.  Below 2^20 rows
+//   nothing but the runs of dense rows is new.  With the cheaper arithmetic alone, the old holds and no runs: dense 2 bits
+//   1000, paged 4 bits 1292.
+// Compression (32 layers of 16384 tokens and 94 x 4 heads of 24576, groups of 32, 64 and 128; change of the call by the hold):
+//   dense    K, groups of 32: fp16 2 and 3 bits -1 to -4 % with 36000 (40000: -2 to +1 %), bf16 2 to 4 bits 0 to -1 % (+2
+//            to +6 %), fp16 4 bits and 8 bits -1 to -3 % with 40000; groups of 64 -1 to -3 % with 40000, of 128
+//            and V 0; below 2^20 rows, where the tensor is a few generations of workgroups, 0 to +2 %
+//            in runs from 2^22 rows (2^23.3 rows without / with): 4 bits 1137 / 1090, 2 bits 1068 / 1023, 8 bits 1361 / 1307 (run
+//            64; with 16 1336), bf16 4 bits 1138 / 1099, 2 bits 1071 / 1026; at 2^21 level
+//   strided  K, groups of 32: fp16 4 bits and 8 bits -1 to -3 % with 32000, 2 and 3 bits and bf16 4 bits +2 to +7 %;
+//            V: fp16 0 to -2 % with 32000, bf16 0 to +2 %; runs 0 to +3 %
+struct LaunchShape {
+    unsigned lds = 0;
+    int run = 0;
+    int pace = 0;
+};
+
+static inline LaunchShape launch_shape(const QuantBatch &b, bool compress, bool is_v, int bits, int group, int dtype)
 {
     const QuantArgs &a = b.item[0];
-    if (a.rotate || a.anchors) return 0;
+    if (a.rotate || a.anchors) return {};
     long long rows = 0;
     for (int i = 0; i < b.n; ++i) rows += b.item[i].total_units * (compress && !is_v ? group : kPassRows);
-    if (!compress) {
-        if (!a.dense) {
-            if (bits == 8) return rows >= (1ll << 19) && rows < (1ll << 22) ? 40000 : 0;
-            if (bits < 4) return dtype == DT_BF16 && rows >= (bits == 2 ? 1ll << 19 : 1ll << 21) ? 40000 : 0;
-            return 40000;
-        }
-        if (bits == 8) return 0;
-        const bool narrow = bits == 2 || rows < (1ll << 21) || (b.n == 1 && (bits == 3 || rows < (1ll << 22)));
-        return narrow ? 40000 : 32000;
+    if (compress) {
+        if (!a.dense) return {is_v ? (dtype == DT_F16 ? 32000u : 0u) : group == 32 && (bits == 8 || (bits == 4 && dtype == DT_F16)) ? 32000u : 0u};
+        const int run = rows < (1ll << 22) ? 0 : bits == 8 ? 64 : 16;
+        if (is_v || rows < (1ll << 20)) return {0, run};
+        return {group > 32 || bits == 8 || (bits == 4 && dtype == DT_F16) ? 40000u : 36000u, run};
     }
-    if (is_v) return !a.dense && dtype == DT_F16 ? 32000 : 0;
-    const bool wide = bits == 8 || (bits == 4 && dtype == DT_F16);
-    if (a.dense) return rows < (1ll << 20) ? 0 : group > 32 || wide ? 40000 : 36000;
-    return group == 32 && wide ? 32000 : 0;
+    if (a.dense) {
+        const bool one = b.n == 1;
+        if (bits == 8) return {one && rows >= (1ll << 20) ? 80000u : 0u, 16};
+        if (bits == 4) return {rows >= 6ll << 20 ? 80000u : rows < (1ll << 21) || (one && rows < (1ll << 22)) ? 40000u : 32000u, 16};
+        if (bits == 2 && dtype == DT_F16 && rows >= 6ll << 20) return {40000, 8};
+        if (one && rows >= (1ll << 20)) return {80000, 16};
+        return {bits == 3 && rows >= (1ll << 21) ? 32000u : 40000u, 16};
+    }
+    const bool large = rows >= (1ll << 23);
+    if (bits == 4) return large ? LaunchShape{52000, 0, 1} : LaunchShape{40000, 0, rows < (1ll << 20) ? 0 : rows < 5ll << 19 ? 3 : 4};
+    if (rows < (1ll << 19)) return {};
+    if (rows < (1ll << 20)) return {bits == 8 || (bits == 2 && dtype == DT_BF16) ? 40000u : 0u};
+    if (bits == 8) return {52000, 0, rows < (1ll << 21) ? 0 : 2};
+    if (bits == 3) return rows < (1ll << 21) ? LaunchShape{32000, 16} : LaunchShape{40000, 0, dtype == DT_F16 ? 0 : 1};
+    if (rows < 5ll << 19) return {52000, 0, 2};
+    return dtype == DT_F16 ? LaunchShape{32000, 8, 2} : LaunchShape{40000, 0, large ? 3 : 2};
 }
 
-#define KVC_LAUNCH(kernel, batch, lds, s)                                                 \
-    do {                                                                                  \
-        QuantBatch placed_ = batch;                                                       \
-        const unsigned wgs_ = place_items(placed_);                                       \
-        if (wgs_ > 0) hipLaunchKernelGGL(kernel, dim3(wgs_), dim3(256), lds, s, placed_); \
-        return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;                 \
+#define KVC_LAUNCH(kernel, batch, shape, s)                                                     \
+    do {                                                                                        \
+        QuantBatch placed_ = batch;                                                             \
+        const LaunchShape shape_ = shape;                                                       \
+        const unsigned wgs_ = place_items(placed_, shape_.run);                                 \
+        placed_.pace = shape_.pace;                                                             \
+        if (wgs_ > 0) hipLaunchKernelGGL(kernel, dim3(wgs_), dim3(256), shape_.lds, s, placed_); \
+        return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;                       \
     } while (0)
 
 }  // namespace kvc

@@ -59,14 +59,14 @@ void compress_k_kernel(QuantBatch b)
 {
     __shared__ __attribute__((aligned(16))) float xch_all[4 * kXchFloats];
     unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const QuantArgs &a = b.item[place_item(b.at, place_of_workgroup(b.at), wg)];
     compress_k_unit<BITS, G, DT, DENSE, XF>(a, wg, xch_all);
 }
 
 // `refused()`: the request's payload does not fit the plan; asked once everything a unit reads is requested.
-// XF = false leaves the inverse transforms out.
-template <int BITS, int DT, bool DENSE, bool XF, class Refused>
-__device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned wg, Refused &&refused)
+// XF = false leaves the inverse transforms out.  PACED: with waits between the row stores (without a transform only).
+template <int BITS, int DT, bool DENSE, bool XF, bool PACED, class Refused>
+__device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned wg, int pace, Refused &&refused)
 {
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
@@ -88,17 +88,17 @@ __device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned w
         dequant_pass_any<BITS, DT, false, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
                                                  a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
                                                  a.anchor_shift);
-    else dequant_pass<BITS, DT, false, DENSE, 0>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
+    else dequant_pass<BITS, DT, false, DENSE, 0, PACED>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, nullptr, 0, nullptr, pace);
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE>
+template <int BITS, int DT, bool DENSE, bool XF, bool PACED>
 __global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
 {
     unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const QuantArgs &a = b.item[place_item(b.at, place_of_workgroup(b.at), wg)];
     const int status = *a.status;
-    decompress_k_unit<BITS, DT, DENSE, true>(a, wg, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
+    decompress_k_unit<BITS, DT, DENSE, XF, PACED>(a, wg, b.pace, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
 }
 
 // ---- V: groups along channels, one set per token -----------------------------------------------
@@ -132,12 +132,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(B
 void compress_v_kernel(QuantBatch b)
 {
     unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const QuantArgs &a = b.item[place_item(b.at, place_of_workgroup(b.at), wg)];
     compress_v_unit<BITS, GV, DT, DENSE, true>(a, wg);
 }
 
-template <int BITS, int DT, bool DENSE, bool XF, class Refused>
-__device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned wg, Refused &&refused)
+template <int BITS, int DT, bool DENSE, bool XF, bool PACED, class Refused>
+__device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned wg, int pace, Refused &&refused)
 {
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
@@ -161,17 +161,17 @@ __device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned w
         dequant_pass_any<BITS, DT, true, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
                                                 a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
                                                 a.anchor_shift);
-    else dequant_pass<BITS, DT, true, DENSE, 0>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
+    else dequant_pass<BITS, DT, true, DENSE, 0, PACED>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, nullptr, 0, nullptr, pace);
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE>
+template <int BITS, int DT, bool DENSE, bool XF, bool PACED>
 __global__ __launch_bounds__(256) void decompress_v_kernel(QuantBatch b)
 {
     unsigned wg;
-    const QuantArgs &a = b.item[batch_item(b, wg)];
+    const QuantArgs &a = b.item[place_item(b.at, place_of_workgroup(b.at), wg)];
     const int status = *a.status;
-    decompress_v_unit<BITS, DT, DENSE, true>(a, wg, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
+    decompress_v_unit<BITS, DT, DENSE, XF, PACED>(a, wg, b.pace, [&]() { return (status & KVC_DEV_BAD_HEADER) != 0; });
 }
 
 // ---- a whole small call in one launch -------------------------------------------------------------
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void compress_call_kernel(SmallCompressArgs b)
         return;
     }
     unsigned wg;
-    const int i = batch_item(b, wg);
+    const int i = place_item(b.at, blockIdx.x, wg);
     if (i & 1) compress_v_unit<BITS, G, DT, DENSE, false>(b.item[i], wg);
     else compress_k_unit<BITS, G, DT, DENSE, false>(b.item[i], wg, xch_all);
 }
@@ -199,19 +199,22 @@ __global__ __launch_bounds__(256) void compress_call_kernel(SmallCompressArgs b)
 template <int BITS, int DT, bool DENSE>
 __global__ __launch_bounds__(256) void decompress_call_kernel(SmallDecompressArgs b)
 {
-    unsigned wg;
-    const int i = blockIdx.x < (unsigned)b.requests ? 2 * (int)blockIdx.x : batch_item(b, wg);
+    const unsigned place = place_of_workgroup(b.at);
+    const bool leads = place < (unsigned)b.requests;
+    unsigned wg = 0;
+    int i = place_item(b.at, place, wg);
+    if (leads) i = 2 * (int)place;
     const SmallCheck &check = b.check[i >> 1];
     const int word = lane_id() & 31;
     const uint32_t got = check.payload[word];
     auto refused = [&]() { return __builtin_amdgcn_ballot_w64(got != check.expect.w[word]) != 0; };
-    if (blockIdx.x < (unsigned)b.requests) {
+    if (leads) {
         const bool bad = refused();
         if (threadIdx.x == 0) *b.item[i].status = bad ? KVC_DEV_BAD_HEADER : 0;
         return;
     }
-    if (i & 1) decompress_v_unit<BITS, DT, DENSE, false>(b.item[i], wg, refused);
-    else decompress_k_unit<BITS, DT, DENSE, false>(b.item[i], wg, refused);
+    if (i & 1) decompress_v_unit<BITS, DT, DENSE, false, false>(b.item[i], wg, 0, refused);
+    else decompress_k_unit<BITS, DT, DENSE, false, false>(b.item[i], wg, 0, refused);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
@@ -219,37 +222,44 @@ __global__ __launch_bounds__(256) void decompress_call_kernel(SmallDecompressArg
 template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, int group, const QuantBatch &b, hipStream_t s)
 {
     const QuantArgs &a = b.item[0];
-    const unsigned lds = window_lds(b, true, is_v, BITS, group, DT);
+    const LaunchShape shape = launch_shape(b, true, is_v, BITS, group, DT);
     if (!is_v) {
         const bool xf = a.rotate || a.anchors;
         switch (group) {
-        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, lds, s);
+        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, shape, s);
         case 64:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, lds, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, lds, s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, shape, s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, shape, s);
         case 128:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, lds, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, lds, s);
+            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, shape, s);
+            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, shape, s);
         }
     } else {
         switch (group) {
-        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, lds, s);
-        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, lds, s);
-        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, lds, s);
+        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, shape, s);
+        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, shape, s);
+        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, shape, s);
         }
     }
     return KVC_ERR_UNSUPPORTED;
 }
 
-template <int BITS, bool DENSE> static int decompress_bits_dense(int is_v, int dtype, const QuantBatch &b, hipStream_t s)
+// Launches with a transform have kernels of their own, and paced ones, too: what the plain ones do not use costs them
+// registers and moves their stores.
+template <int BITS, int DT, bool DENSE> static int decompress_bits_dt(int is_v, const QuantBatch &b, hipStream_t s)
 {
-    const unsigned lds = window_lds(b, false, is_v, BITS, 0, dtype);
-    if (!is_v) {
-        if (dtype == DT_F16) KVC_LAUNCH((decompress_k_kernel<BITS, DT_F16, DENSE>), b, lds, s);
-        KVC_LAUNCH((decompress_k_kernel<BITS, DT_BF16, DENSE>), b, lds, s);
+    const QuantArgs &a = b.item[0];
+    const LaunchShape shape = launch_shape(b, false, is_v, BITS, 0, DT);
+    if (a.rotate || a.anchors) {
+        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, true, false>), b, shape, s);
+        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, true, false>), b, shape, s);
     }
-    if (dtype == DT_F16) KVC_LAUNCH((decompress_v_kernel<BITS, DT_F16, DENSE>), b, lds, s);
-    KVC_LAUNCH((decompress_v_kernel<BITS, DT_BF16, DENSE>), b, lds, s);
+    if (shape.pace) {
+        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, false, true>), b, shape, s);
+        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, false, true>), b, shape, s);
+    }
+    if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, false, false>), b, shape, s);
+    KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, false, false>), b, shape, s);
 }
 
 #define KVC_PASTE2(a, b) a##b
@@ -266,27 +276,29 @@ int KVC_PASTE(launch_compress_bits, KVC_BITS)(int is_v, int group, int dtype, co
 
 int KVC_PASTE(launch_decompress_bits, KVC_BITS)(int is_v, int dtype, const QuantBatch &b, hipStream_t s)
 {
-    return b.item[0].dense ? decompress_bits_dense<KVC_BITS, true>(is_v, dtype, b, s) : decompress_bits_dense<KVC_BITS, false>(is_v, dtype, b, s);
+    if (b.item[0].dense)
+        return dtype == DT_F16 ? decompress_bits_dt<KVC_BITS, DT_F16, true>(is_v, b, s) : decompress_bits_dt<KVC_BITS, DT_BF16, true>(is_v, b, s);
+    return dtype == DT_F16 ? decompress_bits_dt<KVC_BITS, DT_F16, false>(is_v, b, s) : decompress_bits_dt<KVC_BITS, DT_BF16, false>(is_v, b, s);
 }
 
 // units of four per workgroup behind the workgroups of the requests themselves
-template <class Args> static unsigned place_call(Args &b)
+template <class Args> static unsigned place_call(Args &b, int run)
 {
-    unsigned at = (unsigned)b.requests;
+    unsigned total = (unsigned)b.requests;
     for (int i = 0; i < b.n; ++i) {
-        b.start[i] = at;
-        at += (unsigned)((b.item[i].total_units + 3) / 4);
+        b.at.start[i] = total;
+        total += (unsigned)((b.item[i].total_units + 3) / 4);
     }
-    b.start[b.n] = at;
-    return at;
+    close_places(b.at, b.n, total, run);
+    return total;
 }
 
-// LDS that nothing uses, as in window_lds, for decompression calls; compression calls gain nothing from it (2^21 rows, fp16,
-// with 32000 bytes: 2 bits g64 210 and 210 us, 4 bits g64 227 and 229, 4 bits g32 230 and 224; bf16 231 and 233).
-// Call times without and with 40000 bytes at 2^20, 1.5 * 2^20 and just below 2^21 rows:
-//   2 bits g64  93 / 88, 145 / 132, 196 / 180        4 bits g32  117 / 113, 152 / 150, 230 / 219 (bf16 230 / 235)
-//   3 bits g32  97 / 95, 143 / 141, 198 / 188        8 bits g32  136 / 133, 203 / 200, 271 / 265
-constexpr unsigned kCallLds = 40000;
+// LDS that nothing uses and runs, as in launch_shape, for decompression calls; compression calls gain nothing from the LDS (2^21
+// rows, fp16, with 32000 bytes: 2 bits g64 210 and 210 us, 4 bits g64 227 and 229, 4 bits g32 230 and 224; bf16 231 and 233).
+// Call times in us, without / with runs of 16:
+//   4 bits g32  2^18 rows 27.2 26.6,  2^20 118 112;  bf16 27.4 26.8, 118 113;  2 bits g64  24.4 23.9, 91 87;  bf16 24.3 23.8, 92 85
+//   3 bits g32  26.2 25.7, 96 94;  8 bits g32 level
+constexpr LaunchShape kCallShape = {40000, 16};
 
 template <int G> static void compress_call(int dtype, const SmallCompressArgs &b, unsigned wgs, hipStream_t s)
 {
@@ -298,7 +310,7 @@ template <int G> static void compress_call(int dtype, const SmallCompressArgs &b
 
 int KVC_PASTE(launch_compress_call_bits, KVC_BITS)(int group, int dtype, SmallCompressArgs &b, hipStream_t s)
 {
-    const unsigned wgs = place_call(b);
+    const unsigned wgs = place_call(b, 0);
     if (group == 32) compress_call<32>(dtype, b, wgs, s);
     else if (group == 64) compress_call<64>(dtype, b, wgs, s);
     else compress_call<128>(dtype, b, wgs, s);
@@ -307,8 +319,8 @@ int KVC_PASTE(launch_compress_call_bits, KVC_BITS)(int group, int dtype, SmallCo
 
 int KVC_PASTE(launch_decompress_call_bits, KVC_BITS)(int dtype, SmallDecompressArgs &b, hipStream_t s)
 {
-    const unsigned wgs = place_call(b);
-#define KVC_CALL(DT, D) hipLaunchKernelGGL((decompress_call_kernel<KVC_BITS, DT, D>), dim3(wgs), dim3(256), kCallLds, s, b)
+    const unsigned wgs = place_call(b, kCallShape.run);
+#define KVC_CALL(DT, D) hipLaunchKernelGGL((decompress_call_kernel<KVC_BITS, DT, D>), dim3(wgs), dim3(256), kCallShape.lds, s, b)
     if (b.item[0].dense) { if (dtype == DT_F16) KVC_CALL(DT_F16, true); else KVC_CALL(DT_BF16, true); }
     else if (dtype == DT_F16) KVC_CALL(DT_F16, false); else KVC_CALL(DT_BF16, false);
 #undef KVC_CALL

@@ -11,7 +11,7 @@ template <bool TO_PAYLOAD>
 __global__ __launch_bounds__(256) void copy_rows_kernel(QuantBatch batch)
 {
     unsigned wg;
-    const QuantArgs &a = batch.item[batch_item(batch, wg)];
+    const QuantArgs &a = batch.item[place_item(batch.at, blockIdx.x, wg)];
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
     if (!TO_PAYLOAD && (*a.status & KVC_DEV_BAD_HEADER)) return;
@@ -69,7 +69,7 @@ int launch_compress_tensor(int is_v, int bits, int group, int dtype, const Quant
     case 3: return launch_compress_bits3(is_v, group, dtype, b, s);
     case 4: return launch_compress_bits4(is_v, group, dtype, b, s);
     case 8: return launch_compress_bits8(is_v, group, dtype, b, s);
-    case 16: KVC_LAUNCH(copy_rows_kernel<true>, b, 0, s);
+    case 16: KVC_LAUNCH(copy_rows_kernel<true>, b, LaunchShape{}, s);
     }
     return KVC_ERR_UNSUPPORTED;
 }
@@ -82,7 +82,7 @@ int launch_decompress_tensor(int is_v, int bits, int group, int dtype, const Qua
     case 3: return launch_decompress_bits3(is_v, dtype, b, s);
     case 4: return launch_decompress_bits4(is_v, dtype, b, s);
     case 8: return launch_decompress_bits8(is_v, dtype, b, s);
-    case 16: KVC_LAUNCH(copy_rows_kernel<false>, b, 0, s);
+    case 16: KVC_LAUNCH(copy_rows_kernel<false>, b, LaunchShape{}, s);
     }
     return KVC_ERR_UNSUPPORTED;
 }

@@ -374,33 +374,36 @@ __device__ __forceinline__ void v_emit(const u32x4 raw[8], const VParams &vp, ui
 }
 
 // Reconstruct the lane's 8 channels of one row: x^ = round(code * scale + zero), one fused fp32
-// multiply-add, then the output rounding.  CLAMP: see pack_out.
+// multiply-add, then the output rounding.  CLAMP: see pack_out.  scale[e] carries code_factor<BITS>(e & 3).
 template <int BITS, int DT, bool CLAMP>
 __device__ __forceinline__ u32x4 dequant_row(u32x2 codes, const float scale[8], const float zero[8])
 {
-    float q[8];
-    unpack8<BITS>(codes, q);
+    uint32_t p[4];
+    unpack8<BITS>(codes, p);
     u32x4 out;
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-        out[w] = pack_out<DT, CLAMP>(__builtin_fmaf(q[2 * w], scale[2 * w], zero[2 * w]),
-                                     __builtin_fmaf(q[2 * w + 1], scale[2 * w + 1], zero[2 * w + 1]));
+    for (int w = 0; w < 4; ++w) {
+        const int e = 2 * w, k = e & 3;
+        const float a = e < 4 ? lo_f32<DT_F16>(p[k]) : hi_f32<DT_F16>(p[k]), b = e < 4 ? lo_f32<DT_F16>(p[k + 1]) : hi_f32<DT_F16>(p[k + 1]);
+        out[w] = pack_out<DT, CLAMP>(__builtin_fmaf(a, scale[e], zero[e]), __builtin_fmaf(b, scale[e + 1], zero[e + 1]));
+    }
     return out;
 }
 
+// The same with one group for the lane's 8 channels; `s` carries 2^24.
 template <int BITS, int DT, bool CLAMP>
 __device__ __forceinline__ u32x4 dequant_row_uniform(u32x2 codes, float s, float z)
 {
-    float q[8];
-    unpack8<BITS>(codes, q);
-    u32x4 out;
+    float scale[8], zero[8];
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-        out[w] = pack_out<DT, CLAMP>(__builtin_fmaf(q[2 * w], s, z), __builtin_fmaf(q[2 * w + 1], s, z));
-    return out;
+    for (int e = 0; e < 8; ++e) {
+        scale[e] = s * (code_factor<BITS>(e & 3) * 0x1p-24f);
+        zero[e] = z;
+    }
+    return dequant_row<BITS, DT, CLAMP>(codes, scale, zero);
 }
 
-// Scale and zero of the lane's 8 channels from two 16-byte metadata loads (K), and whether any
+// Scale (with code_factor) and zero of the lane's 8 channels from two 16-byte metadata loads (K), and whether any
 // reconstruction of this token block can exceed the fp16 range (largest code * scale + zero).
 template <int BITS, int DT>
 __device__ __forceinline__ bool k_meta_floats(const u32x4 &m0, const u32x4 &m1, float scale[8], float zero[8])
@@ -408,18 +411,18 @@ __device__ __forceinline__ bool k_meta_floats(const u32x4 &m0, const u32x4 &m1, 
     constexpr float qmax = (float)((1 << BITS) - 1);
     float top = -65504.0f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint32_t w0 = m0[e], w1 = m1[e];
-        scale[e] = f16_bits_to_f32(w0 & 0xffffu); zero[e] = f16_bits_to_f32(w0 >> 16);
-        scale[4 + e] = f16_bits_to_f32(w1 & 0xffffu); zero[4 + e] = f16_bits_to_f32(w1 >> 16);
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t w = e < 4 ? m0[e & 3] : m1[e & 3];
+        scale[e] = f16_bits_to_f32(w & 0xffffu) * code_factor<BITS>(e & 3);
+        zero[e] = f16_bits_to_f32(w >> 16);
     }
     if (DT != DT_F16) return false;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) top = fmaxf(top, __builtin_fmaf(qmax, scale[e], zero[e]));
+    for (int e = 0; e < 8; ++e) top = fmaxf(top, __builtin_fmaf(qmax / code_factor<BITS>(e & 3), scale[e], zero[e]));
     return __builtin_amdgcn_ballot_w64(top > 65504.0f) != 0;
 }
 
-// Same for the lane's group in each of its 8 rows (V), from one metadata word per row.
+// Same for the lane's group in each of its 8 rows (V), from one metadata word per row; the scales carry 2^24.
 template <int BITS, int DT>
 __device__ __forceinline__ bool v_meta_floats(const uint32_t mw[8], float scale[8], float zero[8])
 {
@@ -427,12 +430,12 @@ __device__ __forceinline__ bool v_meta_floats(const uint32_t mw[8], float scale[
     float top = -65504.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        scale[i] = f16_bits_to_f32(mw[i] & 0xffffu);
+        scale[i] = f16_bits_to_f32(mw[i] & 0xffffu) * 0x1p24f;
         zero[i] = f16_bits_to_f32(mw[i] >> 16);
     }
     if (DT != DT_F16) return false;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) top = fmaxf(top, __builtin_fmaf(qmax, scale[i], zero[i]));
+    for (int i = 0; i < 8; ++i) top = fmaxf(top, __builtin_fmaf(qmax * 0x1p-24f, scale[i], zero[i]));
     return __builtin_amdgcn_ballot_w64(top > 65504.0f) != 0;
 }
 
@@ -586,12 +589,17 @@ __device__ __forceinline__ void pass_fetch(PassFetch &f, uint8_t *codes, const T
 
 // TR: the inverse of stage T applied to every row (0 none, 1 Hadamard, 2 plus the anchor of the row's
 // run, runs of 32 tokens or more, 3 the same for runs of 8 or 16 tokens)
-template <int BITS, int DT, bool IS_V, bool DENSE, bool CLAMP, int TR>
+// PACED: a wait of `pace` times 64 cycles follows every row store but the last (see launch_shape).
+template <int BITS, int DT, bool IS_V, bool DENSE, bool CLAMP, int TR, bool PACED>
 __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const float scale[8], const float zero[8],
                                                   const TensorView &x, long long head_off, long long row0, int rows,
-                                                  const uint16_t *anchors, int anchor_shift, const u32x4 *loaded_anchor)
+                                                  const uint16_t *anchors, int anchor_shift, const u32x4 *loaded_anchor, int pace)
 {
     const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
+    auto wait = [&](int i) {
+        if (PACED && i < 7)
+            for (int k = 0; k < pace; ++k) __builtin_amdgcn_s_sleep(1);
+    };
     // delta transform: a run of 32 tokens or more covers the whole pass (row0 is a multiple of 32), and
     // the caller may have that one anchor in flight already; runs of 16 or 8 tokens take two or four
     // anchors per pass, one per 16 or 8 rows (an anchor past the end of the sequence is replaced by
@@ -625,6 +633,7 @@ __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const floa
             if (TR == 1) out = hadamard_row<DT>(out, true);
             if (TR >= 2) out = add_anchor<DT>(out, anchor_of(i), anchor_shift, row0 + 4 * i + rsub);
             __builtin_nontemporal_store(out, dst + i * 64);
+            wait(i);
         }
         return;
     }
@@ -636,21 +645,22 @@ __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const floa
         if (TR == 1) out = hadamard_row<DT>(out, true);     // (all 16 lanes of a row take part)
         if (TR >= 2) out = add_anchor<DT>(out, anchor_of(i), anchor_shift, row0 + (r < rows ? r : 0));
         if (r < rows && !f.bad) __builtin_nontemporal_store(out, (u32x4 *)(x.base + f.off[i] + col * 8));
+        wait(i);
     }
 }
 
 // Dequantize the fetched pass and store its `rows` existing rows at token rows row0... of head
 // `head_off`, after the inverse of stage T (TR 1: Hadamard; 2: the head's anchor rows of the delta
 // transform).  K: scale / zero per channel of the lane; V: per row of the lane.
-template <int BITS, int DT, bool IS_V, bool DENSE, int TR = 0>
+template <int BITS, int DT, bool IS_V, bool DENSE, int TR = 0, bool PACED = false>
 __device__ __forceinline__ void dequant_pass(const PassFetch &f, const float scale[8], const float zero[8], bool clamp,
                                              const TensorView &x, long long head_off, long long row0, int rows, bool &bad,
                                              const uint16_t *anchors = nullptr, int anchor_shift = 0,
-                                             const u32x4 *loaded_anchor = nullptr)
+                                             const u32x4 *loaded_anchor = nullptr, int pace = 0)
 {
     bad |= f.bad;
-    if (clamp) dequant_pass_rows<BITS, DT, IS_V, DENSE, true, TR>(f, scale, zero, x, head_off, row0, rows, anchors, anchor_shift, loaded_anchor);
-    else dequant_pass_rows<BITS, DT, IS_V, DENSE, false, TR>(f, scale, zero, x, head_off, row0, rows, anchors, anchor_shift, loaded_anchor);
+    if (clamp) dequant_pass_rows<BITS, DT, IS_V, DENSE, true, TR, PACED>(f, scale, zero, x, head_off, row0, rows, anchors, anchor_shift, loaded_anchor, pace);
+    else dequant_pass_rows<BITS, DT, IS_V, DENSE, false, TR, PACED>(f, scale, zero, x, head_off, row0, rows, anchors, anchor_shift, loaded_anchor, pace);
 }
 
 // the same with the transform chosen at run time (one copy of the pass per transform; a launch

@@ -273,3 +273,50 @@ def test_both_tensors_of_large_requests(ref, bits, T, dtype):
     n = L * H * -(-T // 128)
     picks = [(0, 0), (0, n - 1), (1, 0), (1, n - 1), (0, n // 3), (1, n // 2 + 1)]
     check_sampled_bodies(ref, buf, lambda l, kv, h: x[l, kv, h].cpu(), L, H, T, dt, bits, bits, 32, 32, picks)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_every_code_at_extreme_scales(ref, bits, dtype):
+    """Codes enter the multiply-add as fp16 subnormals beside a scale that carries a power of two: every code under
+    scales from the smallest subnormal to the largest that fits, with zero points on both sides and at the limit."""
+    T, n, top = 256, 2 ** bits - 1, 65504.0
+    g = torch.Generator().manual_seed(bits)
+    x = torch.empty((1, 2, 2, T, 128), dtype=torch.float64)
+    scales = 2.0 ** torch.randint(-24, 9 if bits == 8 else 13, x.shape[:-2] + (T // 32, 4), generator=g).double()
+    zeros = torch.randn(scales.shape, generator=g).double() * scales * 100
+    zeros[..., 0, :] = top - n * scales[..., 0, :]                # the largest code meets the end of the fp16 range
+    codes = torch.randint(0, n + 1, x.shape, generator=g)
+    codes[..., 0::32], codes[..., 1::32] = 0, n                   # (a group of 32 channels has both ends, a group of 32 tokens too)
+    codes[..., 0::32, :], codes[..., 1::32, :] = 0, n
+    s = scales.repeat_interleave(32, -2).repeat_interleave(32, -1)
+    z = zeros.repeat_interleave(32, -2).repeat_interleave(32, -1)
+    x = (z + codes * s).clamp(-top, top).to(dtype)
+    check_contiguous(ref, x, bits, bits, 32, 32)
+    check_contiguous(ref, x, bits, bits, 32, 32, codec=1)
+
+
+@pytest.mark.parametrize("T", [2032, 2048, 2064, 4080, 4176])
+def test_places_given_out_in_runs(ref, T):
+    """128 places in a round: launches just below, at and above one and two of them (eight heads, 128 rows a place)."""
+    x = kvgen.make_kv(500 + T, 1, 8, 128, T, torch.float16)
+    check_contiguous(ref, x, 4, 2, 32, 64)              # (three launches)
+    check_contiguous(ref, x, 8, 8, 32, 32)              # (one, behind the request's own workgroup)
+
+
+@pytest.mark.parametrize("bits,L,T", [(2, 25, 8000), (3, 12, 8192), (4, 13, 8192), (4, 25, 8000)])
+def test_decoder_places_given_out_in_runs(bits, L, T):
+    """512 places in a round of the decoder, whole rounds and incomplete ones: the same tensor as without the coder."""
+    x = kvgen.make_kv(600 + bits, L, 8, 128, T, torch.float16, "cuda")
+    out = []
+    for codec in (kvc.CODEC_NONE, kvc.CODEC_HUFF8):
+        plan = kvc.Plan(kvc.F16, L, 8, 128, bits, bits, 32, 32, codec, max_tokens=T)
+        buf = kvc.Buffers(plan, [T])
+        stream = torch.cuda.current_stream().cuda_stream
+        buf.compress([kvc.contiguous_request(x)], stream)
+        y = torch.zeros_like(x)
+        buf.decompress([kvc.contiguous_request(y)], stream)
+        torch.cuda.synchronize()
+        assert int(buf.status[0]) == 0
+        out.append(y)
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
