@@ -35,6 +35,15 @@ struct TensorView {
 };
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+// The octet of channels that the lane holds of its row.  Turned (launches with the rotation): the octets of every other
+// quad of lanes in reverse order, so that the lane whose octet differs in bit 2 of its number is the mirror image
+// within eight lanes, an exchange that a vector operation can carry (see hadamard_row).  A quad holds the
+// same four octets either way.
+__device__ __forceinline__ int lane_octet(bool turned = false)
+{
+    const int col = lane_id() & 15;
+    return turned && (col & 4) ? col ^ 3 : col;
+}
 // The wave's index inside its workgroup, as a value the compiler knows to be the same in all lanes:
 // everything derived from it (unit and chunk numbers, head offsets, block-table entries) is then
 // computed once per wave by the scalar unit instead of once per lane.
@@ -183,6 +192,7 @@ constexpr int DPP_QUAD_XOR1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int DPP_QUAD_XOR2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141;     // reverse within 8 lanes
 constexpr int DPP_MIRROR = 0x140;          // reverse within 16 lanes
+constexpr int DPP_QUAD_REVERSE = 0x1B;     // quad_perm [3,2,1,0]
 constexpr int DPP_QUAD_NEXT = 0xF9;        // quad_perm [1,2,3,3]: lane k reads lane k+1
 constexpr int DPP_QUAD_PREV = 0x90;        // quad_perm [0,0,1,2]: lane k reads lane k-1
 
@@ -206,21 +216,13 @@ template <int LANES> __device__ __forceinline__ void group_minmax(float &mn, flo
 // ---- transform (KVServe section 5.1, stage T: the Hadamard rotation among the transformer
 //      modules) ---------------------------------------------------------------------------------
 
-// The value of lane (lane ^ MASK), MASK = 1, 2, 4 or 8: within the 16 lanes that hold one row.
-template <int MASK> __device__ __forceinline__ float xor_lane_f32(float v)
-{
-    if (MASK == 1) return dpp_f32<DPP_QUAD_XOR1>(v);
-    if (MASK == 2) return dpp_f32<DPP_QUAD_XOR2>(v);
-    // ds_swizzle, bit-mask mode: and 0x1f, or 0, xor MASK (no LDS memory is touched)
-    return __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)__float_as_uint(v), (MASK << 10) | 0x1f));
-}
-
-// One row of 128 values, 8 per lane over 16 lanes (lane & 15 = col holds channels 8*col ...):
+// One row of 128 values, 8 per lane over 16 lanes (lane_octet(true) = col: channels 8*col ...):
 // y = H x * scale, H the Walsh-Hadamard matrix in natural order, as the fast transform with the
 // strides 1, 2, 4 (inside the lane), 8, 16, 32, 64 (across lanes) in this order, every sum and
 // difference one fp32 operation; scale = 1/8 on the way in, 1/16 on the way back (both exact);
-// the result is limited to the finite range of the type and rounded to it.  All 16 lanes of a
-// row must be active.
+// the result is limited to the finite range of the type and rounded to it, or (LIMIT = false) only rounded,
+// infinity above the range: for a caller who looks at the extremes anyway and limits the rows where that is
+// needed.  All 16 lanes of a row must be active.
 //
 // How the same bits are reached with fewer instructions: the scale, a power of two, is applied
 // in the first stage, which for fp16 input is computed straight from the packed halves by the
@@ -229,9 +231,9 @@ template <int MASK> __device__ __forceinline__ float xor_lane_f32(float v)
 // from the other lane, so that the lane exchange can ride on the multiply-add; the lane that
 // should hold a - b then holds b - a, and a lane's values are negated once for every set bit
 // of col.  That sign is folded into the first stage's factor, which flips the roles of c.
-template <int DT> __device__ __forceinline__ u32x4 hadamard_row(const u32x4 &in, bool inverse)
+template <int DT, bool LIMIT> __device__ __forceinline__ u32x4 hadamard_row(const u32x4 &in, bool inverse)
 {
-    const int col = lane_id() & 15;
+    const int col = lane_octet(true);
     const float factor = (__builtin_popcount(col) & 1 ? -1.0f : 1.0f) * (inverse ? 0.0625f : 0.125f);
     float x[8];
 #pragma unroll
@@ -249,10 +251,12 @@ template <int DT> __device__ __forceinline__ u32x4 hadamard_row(const u32x4 &in,
                 x[j] = a + b;
                 x[j + h] = a - b;
             }
-    // x[e] += c * (x[e] of lane ^ m): for m = 1, 2 and 8 the lane exchange is a DPP pattern (two quad
-    // permutations, a rotation of the row of 16 by 8) that the multiply-add itself can carry
-    // (v_fmac_f32 with a DPP source: one instruction, the same single rounding); the compiler does not
-    // form it and keeps a separate move, so the eight of a stage are written out.  A DPP source must
+    // x[e] += c * (x[e] of the lane whose octet is col ^ m): the lane exchange is a DPP pattern (two quad
+    // permutations, the mirror image within 8 lanes thanks to the turned octets, a rotation of the row of 16 by 8)
+    // that the multiply-add itself can carry (v_fmac_f32 with a DPP source: one instruction, the same single
+    // rounding); the compiler does not form it and keeps a separate move, so the eight of a stage are written out.
+    // (With the octets in order the exchange by 4 went through ds_swizzle, whose 64 round trips per 32 rows the
+    // compiler did not overlap.)  A DPP source must
     // not have been written by the two instructions before it (five, if that was a vector write of
     // EXEC): inside a block the writer of x[e] is eight instructions back, and the block opens with five
     // wait states.
@@ -274,18 +278,15 @@ template <int DT> __device__ __forceinline__ u32x4 hadamard_row(const u32x4 &in,
         if (m == 1) KVC_FMAC_DPP8("quad_perm:[1,0,3,2]");
         else if (m == 2) KVC_FMAC_DPP8("quad_perm:[2,3,0,1]");
         else if (m == 8) KVC_FMAC_DPP8("row_ror:8");
-        else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                x[e] = __builtin_fmaf(xor_lane_f32<4>(x[e]), c, x[e]);         // exact product, one rounded sum
-        }
+        else KVC_FMAC_DPP8("row_half_mirror");
     }
 #undef KVC_FMAC_DPP8
     constexpr float top = DT == DT_F16 ? 65504.0f : 3.3895313892515355e38f;
     u32x4 out;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        f32x2_t v = {__builtin_amdgcn_fmed3f(x[2 * w], -top, top), __builtin_amdgcn_fmed3f(x[2 * w + 1], -top, top)};
+        f32x2_t v = {x[2 * w], x[2 * w + 1]};
+        if (LIMIT) v = {__builtin_amdgcn_fmed3f(v[0], -top, top), __builtin_amdgcn_fmed3f(v[1], -top, top)};
         if (DT == DT_F16) out[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));
         else out[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
     }
@@ -471,6 +472,13 @@ __device__ __forceinline__ uint32_t quad_24_from_words(uint32_t word)
     return (lo | hi) & 0xffffffu;
 }
 
+// 3-bit codes of quads some of which hold their octets in reverse order (lane_octet, turned), back in order or the other way round.
+__device__ __forceinline__ uint32_t quad_24_in_order(uint32_t c24)
+{
+    const uint32_t reversed = dpp_u32<DPP_QUAD_REVERSE>(c24);
+    return lane_octet(true) != lane_octet() ? reversed : c24;
+}
+
 // Stores to the payload pass the caches by (STREAM): it is written once and not read again by the call,
 // and memory takes the mix of reads and writes better that way (a kernel that only reads 32 KB and
 // writes 10 KB per wave: 5.2 -> 5.8 TB/s; the compress calls with it, and with the metadata of
@@ -487,9 +495,9 @@ template <bool STREAM, typename T> __device__ __forceinline__ void put_at(void *
 // Byte offset of a lane's packed codes inside a row of 16*BITS bytes, and the store itself.
 // 2 bits: u16 per lane; 3 bits: word per lane for 3 lanes of 4 (w[0] has been through
 // quad_words_from_24); 4 bits: word; 8 bits: 2 words.
-template <int BITS, bool STREAM> __device__ __forceinline__ void store_row_codes(uint8_t *row, u32x2 w)
+template <int BITS, bool STREAM, bool TURNED> __device__ __forceinline__ void store_row_codes(uint8_t *row, u32x2 w)
 {
-    int col = lane_id() & 15;
+    const int col = lane_octet(TURNED && BITS != 3);
     if (BITS == 2) {
         put_at<STREAM>(row + col * 2, (uint16_t)w[0]);
     } else if (BITS == 3) {
@@ -501,9 +509,9 @@ template <int BITS, bool STREAM> __device__ __forceinline__ void store_row_codes
     }
 }
 
-template <int BITS> __device__ __forceinline__ u32x2 load_row_codes(const uint8_t *row)
+template <int BITS, bool TURNED> __device__ __forceinline__ u32x2 load_row_codes(const uint8_t *row)
 {
-    int col = lane_id() & 15;
+    const int col = lane_octet(TURNED && BITS != 3);
     u32x2 w;
     w[1] = 0;
     if (BITS == 2) {
@@ -512,6 +520,7 @@ template <int BITS> __device__ __forceinline__ u32x2 load_row_codes(const uint8_
         int k = col & 3;
         uint32_t word = *(const uint32_t *)(row + (col >> 2) * 12 + (k == 3 ? 2 : k) * 4);
         w[0] = quad_24_from_words(word);
+        if (TURNED) w[0] = quad_24_in_order(w[0]);
     } else if (BITS == 4) {
         w[0] = *(const uint32_t *)(row + col * 4);
     } else {

@@ -77,7 +77,7 @@ __device__ __forceinline__ ChunkPos chunk_pos(const QuantArgs &a, long long chun
 // Quantize and pack the chunk's rows into the wave's LDS region (sub-block layout) and
 // store the group metadata to the payload.  K group parameters are
 // exchanged through the 16 padding bytes that follow each sub-block.
-// XF = false leaves the code of stage T out (for launches that have no transform): in one kernel
+// XF = kNoTransform leaves the code of stage T out (for launches that have no transform): in one kernel
 // with the plain path it costs the plain path its registers, most of all for token blocks of 64
 // and 128 rows.
 template <int BITS, int G, int DT, bool IS_V> struct UnitGeom {
@@ -87,7 +87,7 @@ template <int BITS, int G, int DT, bool IS_V> struct UnitGeom {
 
 // One unit of a chunk: the rows [u * kRows, ...) of the chunk are loaded, transformed, quantized and
 // packed; their codes go to the rows lds_row0 ... of the LDS region.
-template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF = true>
+template <int BITS, int G, int DT, bool IS_V, bool DENSE, int XF>
 __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos &c, int u, uint8_t *lds, int lds_row0,
                                               bool &bad, bool have_blocks = false, const int *blocks = nullptr)
 {
@@ -96,29 +96,29 @@ __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos
     u32x4 raw[PU * 8];
 #pragma unroll
     for (int p = 0; p < PU; ++p)
-        load_pass<DENSE>(a.x, c.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad, have_blocks, have_blocks ? blocks[p] : 0);
-    if (XF && a.rotate) rotate_rows<DT, PU * 8>(raw);
-    if (XF && a.anchors)
+        load_pass<DENSE, XF == kRotation>(a.x, c.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad, have_blocks, have_blocks ? blocks[p] : 0);
+    if (XF == kRotation) rotate_rows<DT, PU * 8, false>(raw);
+    if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, PU * 8>(a.x, c.head_off, row0, a.tokens, a.anchor_shift,
                                       head_anchors(a.anchors, c.lh, a.tokens, a.anchor_shift), true, raw, bad);
     if (!IS_V) {
         const long long nb = (a.tokens + G - 1) / G;
         KParams kp;
         uint8_t *meta_block = a.meta + (c.lh * nb + row0 / G) * (kDim * 4);
-        k_group_params<BITS, DT, PU * 8, ChunkGeom<BITS>::kSubStride>(raw, lds + ChunkGeom<BITS>::kSubBytes, meta_block, kp);
+        k_group_params<BITS, DT, PU * 8, ChunkGeom<BITS>::kSubStride, XF == kRotation>(raw, lds + ChunkGeom<BITS>::kSubBytes, meta_block, kp);
         forget_unpacked<DT, PU * 8>(raw);
-        k_emit<BITS, DT, PU, true>(raw, kp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU);
+        k_emit<BITS, DT, PU, true, XF == kRotation>(raw, kp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU);
     } else {
         constexpr int NG = kDim / G;
         VParams vp;
-        v_pass_params<BITS, G, DT>(raw, vp);
+        v_pass_params<BITS, G, DT, XF == kRotation>(raw, vp);
         forget_unpacked<DT, PU * 8>(raw);
         uint32_t *meta = (uint32_t *)a.meta + (c.lh * a.tokens + row0) * NG;
-        v_emit<BITS, G, DT, true>(raw, vp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU, meta);
+        v_emit<BITS, G, DT, true, XF == kRotation>(raw, vp, code_row<BITS, true>(lds, lds_row0), c.rows - u * RU, meta);
     }
 }
 
-template <int BITS, int G, int DT, bool IS_V, bool DENSE, bool XF = true>
+template <int BITS, int G, int DT, bool IS_V, bool DENSE, int XF>
 __device__ __forceinline__ void quantize_chunk(const QuantArgs &a, const ChunkPos &c, uint8_t *lds, bool &bad)
 {
     constexpr int RU = UnitGeom<BITS, G, DT, IS_V>::kRows, NU = UnitGeom<BITS, G, DT, IS_V>::kUnits;

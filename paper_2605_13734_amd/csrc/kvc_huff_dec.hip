@@ -71,9 +71,8 @@ template <int W> __device__ __forceinline__ void decode_half(uint32_t *sym, cons
 
 // metadata of the 32 rows starting at chunk row `r0`: K = the lane's 8 channels of that token
 // block (two 16-byte loads), V = the lane's group in each of its 8 rows
-__device__ __forceinline__ void load_meta_k(const QuantArgs &q, const ChunkPos &c, int r0, u32x4 &m0, u32x4 &m1)
+__device__ __forceinline__ void load_meta_k(const QuantArgs &q, const ChunkPos &c, int r0, int col, u32x4 &m0, u32x4 &m1)
 {
-    const int col = lane_id() & 15;
     const long long nb = (q.tokens + q.group - 1) / q.group;
     const u32x4 *m = (const u32x4 *)(q.meta + ((c.lh * nb + (c.row0 + r0) / q.group) * kDim + col * 8) * 4);
     m0 = m[0];
@@ -117,13 +116,13 @@ __device__ __forceinline__ void dequant_chunk(const CoderArgs &a, const ChunkPos
         float scale[8], zero[8];
         const bool clamp = IS_V ? v_meta_floats<BITS, DT>(mv, scale, zero) : k_meta_floats<BITS, DT>(mk0, mk1, scale, zero);
         if ((p + 1) * kPassRows < c.rows) {
-            if (!IS_V) load_meta_k(a.q, c, (p + 1) * kPassRows, mk0, mk1);
+            if (!IS_V) load_meta_k(a.q, c, (p + 1) * kPassRows, lane_octet(TR == 1), mk0, mk1);
             else load_meta_v(a.q, c, (p + 1) * kPassRows, mv);
             if (one_anchor) anchor_next = load_anchor(anchors, a.q.anchor_shift, c.row0 + (p + 1) * kPassRows);
             if (paged) blocks_next = pass_blocks(a.q.x, c.row0 + (p + 1) * kPassRows, c.row0 + c.rows);
         }
         PassFetch f;
-        pass_fetch<BITS, DENSE, Dec::kLayout>(f, lds, a.q.x, c.head_off, c.row0 + p * kPassRows, c.rows - p * kPassRows, p * kPassRows,
+        pass_fetch<BITS, DENSE, Dec::kLayout, TR == 1>(f, lds, a.q.x, c.head_off, c.row0 + p * kPassRows, c.rows - p * kPassRows, p * kPassRows,
                                               paged, blocks);
         dequant_pass<BITS, DT, IS_V, DENSE, TR>(f, scale, zero, clamp, a.q.x, c.head_off, c.row0 + p * kPassRows,
                                                 c.rows - p * kPassRows, bad, anchors, a.q.anchor_shift,
@@ -211,7 +210,7 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
             const uint32_t o = (k * 64 + lane) * 16;
             if (o < size) bodyv[k] = __builtin_nontemporal_load((const u32x4 *)(body + o));
         }
-        if (!is_v) load_meta_k(a.q, c, 0, meta0, meta1);
+        if (!is_v) load_meta_k(a.q, c, 0, lane_octet(TR == 1), meta0, meta1);
         else load_meta_v(a.q, c, 0, metav);
         if (!DENSE && a.q.x.block_table != nullptr && a.q.x.bt_wave) blocks0 = pass_blocks(a.q.x, c.row0, c.row0 + c.rows);
         if (TR == 2)

@@ -99,13 +99,13 @@ template <int W> __device__ __forceinline__ void encode_two(const uint32_t *sym,
 
 // KV: the launch's tensor, K (0), V (1) or both (2: the items of the batch are then a K and a V launch of
 // every request, one after the other).
-template <int BITS, int G, int DT, int KV, bool DENSE, bool XF, int NW>
+template <int BITS, int G, int DT, int KV, bool DENSE, bool DELTA, int NW, bool ROTATION = false>
 __global__ __launch_bounds__(NW * 64)
-__attribute__((amdgpu_waves_per_eu(enc_min_waves(BITS, G, DT, DENSE || KV == 2, KV == 1, XF))))
+__attribute__((amdgpu_waves_per_eu(enc_min_waves(BITS, G, DT, DENSE || KV == 2, KV == 1, DELTA || ROTATION))))
 void encode_kernel(CoderBatch batch)
 {
     using Geo = ChunkGeom<BITS>;
-    constexpr int W = Geo::kWords;
+    constexpr int W = Geo::kWords, XF = ROTATION ? kRotation : DELTA ? kDelta : kNoTransform;
     constexpr int kItems = KV == 2 ? 2 : 1;                      // items per request
     unsigned wg;
     const int item = kItems * place_item(batch.at, blockIdx.x, wg);
@@ -285,18 +285,21 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
     close_places(placed.at, placed.n, need, 0);
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
-#define KVC_ENCODE(D, X) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, X, NW>), grid, block, 0, s, placed)
+#define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, 0, s, placed)
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
     // transform (its code costs the plain path registers); both tensors together run without one only
     constexpr bool kPlain = KV != 1 || G == 32;
-    if (kPlain && !a.q.rotate && !a.q.anchors) {
-        if (a.q.dense) KVC_ENCODE(true, !kPlain); else KVC_ENCODE(false, !kPlain);
+    if (!a.q.rotate && !(a.q.anchors && kPlain)) {
+        if (a.q.dense) KVC_ENCODE(true, !kPlain, NW); else KVC_ENCODE(false, !kPlain, NW);
         return launched();
     }
-    if (KV == 2) return KVC_ERR_UNSUPPORTED;
-    if (a.q.dense) KVC_ENCODE(true, KV != 2); else KVC_ENCODE(false, KV != 2);
+    if constexpr (KV != 2) {
+        if (a.q.rotate) { if (a.q.dense) KVC_ENCODE(true, false, NW, true); else KVC_ENCODE(false, false, NW, true); }
+        else if (a.q.dense) KVC_ENCODE(true, true, NW); else KVC_ENCODE(false, true, NW);
+        return launched();
+    }
+    return KVC_ERR_UNSUPPORTED;
 #undef KVC_ENCODE
-    return launched();
 }
 
 // (the kernels for both tensors come with four and, where the registers allow, with eight chunks per

@@ -63,15 +63,19 @@ __device__ __forceinline__ void sample_chunk(const SetupArgs &a, const SetupItem
         if (t.is_v) x.base = it.v_base;
         bool bad = false;                                       // (reported by the encoder, which reads the same rows)
         u32x4 raw[8];
-        load_pass<false>(x, head_off, row0, it.tokens, raw, bad);
-        if (t.rotate) rotate_rows<DT, 8>(raw);
+        if (t.rotate) {
+            load_pass<false, true>(x, head_off, row0, it.tokens, raw, bad);
+            rotate_rows<DT, 8, true>(raw);
+        } else {
+            load_pass<false>(x, head_off, row0, it.tokens, raw, bad);
+        }
         if (t.anchor_shift >= 0) delta_rows<DT, false, 8>(x, head_off, row0, it.tokens, t.anchor_shift, nullptr, false, raw, bad);
         const float qmax = (float)((1 << t.bits) - 1);
         const float c = t.bits == 2 ? 1.0f / 3 : t.bits == 3 ? 1.0f / 7 : t.bits == 4 ? 1.0f / 15 : 1.0f / 255;
         float zero[8], inv[8];
         if (!t.is_v) {
             float mn2[2], mx2[2];
-            k_stats_own<DT, 8>(raw, mn2, mx2);
+            k_stats_own<DT, 8, false>(raw, mn2, mx2);
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 low[wave][col * 8 + rsub * 2 + e] = mn2[e];

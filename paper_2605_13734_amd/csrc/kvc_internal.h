@@ -8,6 +8,11 @@
 
 namespace kvc {
 
+// The stage T that a kernel has (XF): none, the delta transform, the rotation.  Every one has kernels of its own: what the plain
+// ones do not use costs them registers (64 and 128 rows of K: 98 and 162 fp16 registers, 205 and 402 with both) and moves their
+// loads, and the lanes of the rotation hold their rows in another order (lane_octet).
+constexpr int kNoTransform = 0, kDelta = 1, kRotation = 2;
+
 // Arguments of the codec-free quantize / dequantize kernels for one tensor of one request.
 struct QuantArgs {
     TensorView x;               // source (compress) or destination (decompress)

@@ -93,6 +93,9 @@ static inline unsigned place_items(QuantBatch &b, int run)
 //            and V 0; below 2^20 rows, where the tensor is a few generations of workgroups, 0 to +2 %
 //            in runs from 2^22 rows (2^23.3 rows without / with): 4 bits 1137 / 1090, 2 bits 1068 / 1023, 8 bits 1361 / 1307 (run
 //            64; with 16 1336), bf16 4 bits 1138 / 1099, 2 bits 1071 / 1026; at 2^21 level
+//   V and K at groups of 32 have few registers since the transforms have kernels of their own, and need a hold where their
+//            registers were one: from 3 * 2^19 rows V 40000 (2^23.3 rows, 4 bits 1138 without, 1095 with; 2^21 rows 241, 227; bf16 2
+//            bits groups of 64 217, 212), strided fp16 32000, bf16 24000 (2^21 rows paged 239, 232)
 //   strided  K, groups of 32: fp16 4 bits and 8 bits -1 to -3 % with 32000, 2 and 3 bits and bf16 4 bits +2 to +7 %;
 //            V: fp16 0 to -2 % with 32000, bf16 0 to +2 %; runs 0 to +3 %
 struct LaunchShape {
@@ -108,10 +111,14 @@ static inline LaunchShape launch_shape(const QuantBatch &b, bool compress, bool 
     long long rows = 0;
     for (int i = 0; i < b.n; ++i) rows += b.item[i].total_units * (compress && !is_v ? group : kPassRows);
     if (compress) {
-        if (!a.dense) return {is_v ? (dtype == DT_F16 ? 32000u : 0u) : group == 32 && (bits == 8 || (bits == 4 && dtype == DT_F16)) ? 32000u : 0u};
+        const bool f16 = dtype == DT_F16, wide = bits == 8 || (bits == 4 && f16), some = rows >= 3ll << 19;
+        if (!a.dense) {
+            if (is_v ? f16 : group == 32 && wide) return {32000};
+            return {!some || group > 32 ? 0u : f16 ? 32000u : 24000u};
+        }
         const int run = rows < (1ll << 22) ? 0 : bits == 8 ? 64 : 16;
-        if (is_v || rows < (1ll << 20)) return {0, run};
-        return {group > 32 || bits == 8 || (bits == 4 && dtype == DT_F16) ? 40000u : 36000u, run};
+        if (is_v) return {some ? 40000u : 0u, run};
+        return {rows < (1ll << 20) ? 0u : group > 32 || wide ? 40000u : 36000u, run};
     }
     if (a.dense) {
         const bool one = b.n == 1;

@@ -26,9 +26,9 @@ constexpr int min_waves(int bits, int rows, int dtype, bool dense)
 
 // ---- K: groups along tokens, one per channel ------------------------------------------------
 
-// XF = false leaves the code of stage T out (for launches without a transform): sharing a kernel
-// with it doubles the registers of the plain path for token blocks of 64 and 128 rows.
-template <int BITS, int G, int DT, bool DENSE, bool XF>
+// XF: see kNoTransform.  Sharing a kernel with the code of stage T doubles the registers of the plain path for token blocks
+// of 64 and 128 rows.
+template <int BITS, int G, int DT, bool DENSE, int XF>
 __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg, float *xch_all)
 {
     UnitPos u;
@@ -38,22 +38,22 @@ __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg,
     bool bad = false;
     u32x4 raw[P * 8];
 #pragma unroll
-    for (int p = 0; p < P; ++p) load_pass<DENSE>(a.x, u.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad);
-    if (XF && a.rotate) rotate_rows<DT, P * 8>(raw);
-    if (XF && a.anchors)
+    for (int p = 0; p < P; ++p) load_pass<DENSE, XF == kRotation>(a.x, u.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad);
+    if (XF == kRotation) rotate_rows<DT, P * 8, false>(raw);
+    if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, P * 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,
                                      head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift), true, raw, bad);
     KParams kp;
     uint8_t *meta_block = a.meta + (u.lh * a.units_per_head + u.blk) * (kDim * 4);
-    k_group_params<BITS, DT, P * 8, 16>(raw, (uint8_t *)(xch_all + wave_id() * kXchFloats), meta_block, kp);
+    k_group_params<BITS, DT, P * 8, 16, XF == kRotation>(raw, (uint8_t *)(xch_all + wave_id() * kXchFloats), meta_block, kp);
     forget_unpacked<DT, P * 8>(raw);
     uint8_t *codes = head_codes<BITS>(a, u.lh) + row0 * (16 * BITS);
     const long long left = a.tokens - row0;
-    k_emit<BITS, DT, P, false>(raw, kp, codes, left < G ? (int)left : G);
+    k_emit<BITS, DT, P, false, XF == kRotation>(raw, kp, codes, left < G ? (int)left : G);
     report(a.status, bad);
 }
 
-template <int BITS, int G, int DT, bool DENSE, bool XF>
+template <int BITS, int G, int DT, bool DENSE, int XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(BITS, G, DT, DENSE))))
 void compress_k_kernel(QuantBatch b)
 {
@@ -64,13 +64,13 @@ void compress_k_kernel(QuantBatch b)
 }
 
 // `refused()`: the request's payload does not fit the plan; asked once everything a unit reads is requested.
-// XF = false leaves the inverse transforms out.  PACED: with waits between the row stores (without a transform only).
-template <int BITS, int DT, bool DENSE, bool XF, bool PACED, class Refused>
+// XF: the inverse transform that it has.  PACED: with waits between the row stores (without a transform only).
+template <int BITS, int DT, bool DENSE, int XF, bool PACED, class Refused>
 __device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned wg, int pace, Refused &&refused)
 {
     UnitPos u;
     if (!unit_pos(a, wg, u)) return;
-    const int col = lane_id() & 15;
+    const int col = lane_octet(XF == kRotation);
     const long long row0 = u.blk * kPassRows;
     const long long tb = row0 / a.group, nb = (a.tokens + a.group - 1) / a.group;
     const u32x4 *m = (const u32x4 *)(a.meta + ((u.lh * nb + tb) * kDim + col * 8) * 4);
@@ -79,20 +79,20 @@ __device__ __forceinline__ void decompress_k_unit(const QuantArgs &a, unsigned w
     const long long left = a.tokens - row0;
     const int rows = left < kPassRows ? (int)left : kPassRows;
     PassFetch f;
-    pass_fetch<BITS, DENSE, 0>(f, codes, a.x, u.head_off, row0, rows);
+    pass_fetch<BITS, DENSE, 0, XF == kRotation>(f, codes, a.x, u.head_off, row0, rows);
     if (refused()) return;
     float scale[8], zero[8];
     const bool clamp = k_meta_floats<BITS, DT>(m0, m1, scale, zero);
     bool bad = false;
-    if (XF)
-        dequant_pass_any<BITS, DT, false, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
-                                                 a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
-                                                 a.anchor_shift);
+    const uint16_t *anchors = XF == kDelta ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr;
+    if (XF == kRotation) dequant_pass<BITS, DT, false, DENSE, 1>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
+    else if (XF == kDelta && a.anchor_shift >= 5) dequant_pass<BITS, DT, false, DENSE, 2>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, anchors, a.anchor_shift);
+    else if (XF == kDelta) dequant_pass<BITS, DT, false, DENSE, 3>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, anchors, a.anchor_shift);
     else dequant_pass<BITS, DT, false, DENSE, 0, PACED>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, nullptr, 0, nullptr, pace);
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE, bool XF, bool PACED>
+template <int BITS, int DT, bool DENSE, int XF, bool PACED>
 __global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
 {
     unsigned wg;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void decompress_k_kernel(QuantBatch b)
 
 // ---- V: groups along channels, one set per token -----------------------------------------------
 
-template <int BITS, int GV, int DT, bool DENSE, bool XF>
+template <int BITS, int GV, int DT, bool DENSE, int XF>
 __device__ __forceinline__ void compress_v_unit(const QuantArgs &a, unsigned wg)
 {
     UnitPos u;
@@ -112,31 +112,31 @@ __device__ __forceinline__ void compress_v_unit(const QuantArgs &a, unsigned wg)
     const long long row0 = u.blk * kPassRows;
     bool bad = false;
     u32x4 raw[8];
-    load_pass<DENSE>(a.x, u.head_off, row0, a.tokens, raw, bad);
-    if (XF && a.rotate) rotate_rows<DT, 8>(raw);
-    if (XF && a.anchors)
+    load_pass<DENSE, XF == kRotation>(a.x, u.head_off, row0, a.tokens, raw, bad);
+    if (XF == kRotation) rotate_rows<DT, 8, false>(raw);
+    if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,
                                  head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift), true, raw, bad);
     VParams vp;
-    v_pass_params<BITS, GV, DT>(raw, vp);
+    v_pass_params<BITS, GV, DT, XF == kRotation>(raw, vp);
     forget_unpacked<DT, 8>(raw);
     uint8_t *codes = head_codes<BITS>(a, u.lh) + row0 * (16 * BITS);
     uint32_t *meta = (uint32_t *)a.meta + (u.lh * a.tokens + row0) * NG;
     const long long left = a.tokens - row0;
-    v_emit<BITS, GV, DT, false>(raw, vp, codes, left < kPassRows ? (int)left : kPassRows, meta);
+    v_emit<BITS, GV, DT, false, XF == kRotation>(raw, vp, codes, left < kPassRows ? (int)left : kPassRows, meta);
     report(a.status, bad);
 }
 
-template <int BITS, int GV, int DT, bool DENSE>
+template <int BITS, int GV, int DT, bool DENSE, int XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(BITS, kPassRows, DT, DENSE))))
 void compress_v_kernel(QuantBatch b)
 {
     unsigned wg;
     const QuantArgs &a = b.item[place_item(b.at, place_of_workgroup(b.at), wg)];
-    compress_v_unit<BITS, GV, DT, DENSE, true>(a, wg);
+    compress_v_unit<BITS, GV, DT, DENSE, XF>(a, wg);
 }
 
-template <int BITS, int DT, bool DENSE, bool XF, bool PACED, class Refused>
+template <int BITS, int DT, bool DENSE, int XF, bool PACED, class Refused>
 __device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned wg, int pace, Refused &&refused)
 {
     UnitPos u;
@@ -152,20 +152,20 @@ __device__ __forceinline__ void decompress_v_unit(const QuantArgs &a, unsigned w
     for (int i = 0; i < 8; ++i) mw[i] = meta[(4 * i + rsub < rows ? 4 * i + rsub : 0) * ng];
     uint8_t *codes = head_codes<BITS>(a, u.lh) + row0 * (16 * BITS);
     PassFetch f;
-    pass_fetch<BITS, DENSE, 0>(f, codes, a.x, u.head_off, row0, rows);
+    pass_fetch<BITS, DENSE, 0, XF == kRotation>(f, codes, a.x, u.head_off, row0, rows);
     if (refused()) return;
     float scale[8], zero[8];
     const bool clamp = v_meta_floats<BITS, DT>(mw, scale, zero);
     bool bad = false;
-    if (XF)
-        dequant_pass_any<BITS, DT, true, DENSE>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, a.rotate != 0,
-                                                a.anchors ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr,
-                                                a.anchor_shift);
+    const uint16_t *anchors = XF == kDelta ? head_anchors(a.anchors, u.lh, a.tokens, a.anchor_shift) : nullptr;
+    if (XF == kRotation) dequant_pass<BITS, DT, true, DENSE, 1>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad);
+    else if (XF == kDelta && a.anchor_shift >= 5) dequant_pass<BITS, DT, true, DENSE, 2>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, anchors, a.anchor_shift);
+    else if (XF == kDelta) dequant_pass<BITS, DT, true, DENSE, 3>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, anchors, a.anchor_shift);
     else dequant_pass<BITS, DT, true, DENSE, 0, PACED>(f, scale, zero, clamp, a.x, u.head_off, row0, rows, bad, nullptr, 0, nullptr, pace);
     report(a.status, bad);
 }
 
-template <int BITS, int DT, bool DENSE, bool XF, bool PACED>
+template <int BITS, int DT, bool DENSE, int XF, bool PACED>
 __global__ __launch_bounds__(256) void decompress_v_kernel(QuantBatch b)
 {
     unsigned wg;
@@ -190,8 +190,8 @@ __global__ __launch_bounds__(256) void compress_call_kernel(SmallCompressArgs b)
     }
     unsigned wg;
     const int i = place_item(b.at, blockIdx.x, wg);
-    if (i & 1) compress_v_unit<BITS, G, DT, DENSE, false>(b.item[i], wg);
-    else compress_k_unit<BITS, G, DT, DENSE, false>(b.item[i], wg, xch_all);
+    if (i & 1) compress_v_unit<BITS, G, DT, DENSE, kNoTransform>(b.item[i], wg);
+    else compress_k_unit<BITS, G, DT, DENSE, kNoTransform>(b.item[i], wg, xch_all);
 }
 
 // The same for decompression: every wave compares the header with the plan's for itself (its 128 bytes travel
@@ -213,35 +213,37 @@ __global__ __launch_bounds__(256) void decompress_call_kernel(SmallDecompressArg
         if (threadIdx.x == 0) *b.item[i].status = bad ? KVC_DEV_BAD_HEADER : 0;
         return;
     }
-    if (i & 1) decompress_v_unit<BITS, DT, DENSE, false, false>(b.item[i], wg, 0, refused);
-    else decompress_k_unit<BITS, DT, DENSE, false, false>(b.item[i], wg, 0, refused);
+    if (i & 1) decompress_v_unit<BITS, DT, DENSE, kNoTransform, false>(b.item[i], wg, 0, refused);
+    else decompress_k_unit<BITS, DT, DENSE, kNoTransform, false>(b.item[i], wg, 0, refused);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
 
-template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, int group, const QuantBatch &b, hipStream_t s)
+template <int BITS, int DT, bool DENSE, int XF> static int compress_bits_xf(int is_v, int group, const QuantBatch &b, hipStream_t s)
 {
-    const QuantArgs &a = b.item[0];
     const LaunchShape shape = launch_shape(b, true, is_v, BITS, group, DT);
     if (!is_v) {
-        const bool xf = a.rotate || a.anchors;
         switch (group) {
-        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, true>), b, shape, s);
-        case 64:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, true>), b, shape, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, false>), b, shape, s);
-        case 128:
-            if (xf) KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, true>), b, shape, s);
-            KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, false>), b, shape, s);
+        case 32: KVC_LAUNCH((compress_k_kernel<BITS, 32, DT, DENSE, XF>), b, shape, s);
+        case 64: KVC_LAUNCH((compress_k_kernel<BITS, 64, DT, DENSE, XF>), b, shape, s);
+        case 128: KVC_LAUNCH((compress_k_kernel<BITS, 128, DT, DENSE, XF>), b, shape, s);
         }
     } else {
         switch (group) {
-        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE>), b, shape, s);
-        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE>), b, shape, s);
-        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE>), b, shape, s);
+        case 32: KVC_LAUNCH((compress_v_kernel<BITS, 32, DT, DENSE, XF>), b, shape, s);
+        case 64: KVC_LAUNCH((compress_v_kernel<BITS, 64, DT, DENSE, XF>), b, shape, s);
+        case 128: KVC_LAUNCH((compress_v_kernel<BITS, 128, DT, DENSE, XF>), b, shape, s);
         }
     }
     return KVC_ERR_UNSUPPORTED;
+}
+
+template <int BITS, int DT, bool DENSE> static int compress_bits_dt(int is_v, int group, const QuantBatch &b, hipStream_t s)
+{
+    const QuantArgs &a = b.item[0];
+    if (a.rotate) return compress_bits_xf<BITS, DT, DENSE, kRotation>(is_v, group, b, s);
+    if (a.anchors) return compress_bits_xf<BITS, DT, DENSE, kDelta>(is_v, group, b, s);
+    return compress_bits_xf<BITS, DT, DENSE, kNoTransform>(is_v, group, b, s);
 }
 
 // Launches with a transform have kernels of their own, and paced ones, too: what the plain ones do not use costs them
@@ -250,16 +252,20 @@ template <int BITS, int DT, bool DENSE> static int decompress_bits_dt(int is_v, 
 {
     const QuantArgs &a = b.item[0];
     const LaunchShape shape = launch_shape(b, false, is_v, BITS, 0, DT);
-    if (a.rotate || a.anchors) {
-        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, true, false>), b, shape, s);
-        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, true, false>), b, shape, s);
+    if (a.rotate) {
+        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, kRotation, false>), b, shape, s);
+        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, kRotation, false>), b, shape, s);
+    }
+    if (a.anchors) {
+        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, kDelta, false>), b, shape, s);
+        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, kDelta, false>), b, shape, s);
     }
     if (shape.pace) {
-        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, false, true>), b, shape, s);
-        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, false, true>), b, shape, s);
+        if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, kNoTransform, true>), b, shape, s);
+        KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, kNoTransform, true>), b, shape, s);
     }
-    if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, false, false>), b, shape, s);
-    KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, false, false>), b, shape, s);
+    if (!is_v) KVC_LAUNCH((decompress_k_kernel<BITS, DT, DENSE, kNoTransform, false>), b, shape, s);
+    KVC_LAUNCH((decompress_v_kernel<BITS, DT, DENSE, kNoTransform, false>), b, shape, s);
 }
 
 #define KVC_PASTE2(a, b) a##b

@@ -20,11 +20,11 @@ __device__ __forceinline__ void wave_sync()
 // re-read the last valid row, which leaves every group's min and max unchanged.
 // DENSE: rows of one head are contiguous (stride_token == head_dim, no block table), so a
 // full pass is eight loads at constant offsets from one address.
-template <bool DENSE>
+template <bool DENSE, bool TURNED = false>
 __device__ __forceinline__ void load_pass(const TensorView &v, long long head_off, long long row0,
                                           long long tokens, u32x4 raw[8], bool &bad, bool have_blocks = false, int blocks = 0)
 {
-    const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
+    const int rsub = lane_id() >> 4, col = lane_octet(TURNED);
     if (DENSE && row0 + kPassRows <= tokens) {
         const u32x4 *p = (const u32x4 *)(v.base + head_off + (row0 + rsub) * kDim + col * 8);
 #pragma unroll
@@ -73,6 +73,19 @@ __device__ __forceinline__ uint32_t pk_min_neg_f16(uint32_t a, uint32_t b)
     asm("v_pk_min_f16 %0, %1, %2 neg_lo:[1,1] neg_hi:[1,1]" : "=v"(d) : "v"(a), "v"(b));
     return d;
 }
+// the same over three operands, which also hand on a NaN where the two above drop it
+__device__ __forceinline__ uint32_t pk_min3_f16(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t d;
+    asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ uint32_t pk_max3_f16(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t d;
+    asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
 // both halves = min(a.lo, a.hi)
 __device__ __forceinline__ uint32_t pk_min_halves_f16(uint32_t a)
 {
@@ -86,32 +99,72 @@ template <typename T> __device__ __forceinline__ T pick4(int k, T v0, T v1, T v2
     return (k & 2) ? ((k & 1) ? v3 : v2) : ((k & 1) ? v1 : v0);
 }
 
+// both halves = min(a.lo, a.hi); NEG: of -a
+template <bool NEG> __device__ __forceinline__ uint32_t pk_min3_halves_f16(uint32_t a)
+{
+    uint32_t d;
+    if (NEG) asm("v_pk_minimum3_f16 %0, %1, %1, %1 op_sel:[0,1,0] op_sel_hi:[1,0,1] neg_lo:[1,1,1] neg_hi:[1,1,1]" : "=v"(d) : "v"(a));
+    else asm("v_pk_minimum3_f16 %0, %1, %1, %1 op_sel:[0,1,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a));
+    return d;
+}
+
+// rows as hadamard_row<LIMIT = false> left them, limited to the finite range of fp16 (of infinities and NaNs the same as the
+// median of a value and the two limits gives)
+template <int N> __device__ __forceinline__ void limit_rows_f16(u32x4 *raw)
+{
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) raw[n][w] = pk_min_f16(pk_max_f16(raw[n][w], 0xfbfffbffu), 0x7bff7bffu);
+}
+
+__device__ __forceinline__ bool beyond_f16(float x) { return !(__builtin_fabsf(x) <= 65504.0f); }
+
+// min / max of the lane's channels over N loaded rows and the other three lanes that hold rows of the same channels,
+// fp16: the words of channels 2*rsub and 2*rsub+1.  THREE: see pk_min3_f16.
+template <int N, bool THREE> __device__ __forceinline__ void k_extremes_f16(const u32x4 *raw, uint32_t &pa, uint32_t &pb)
+{
+    uint32_t a[4], b[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) a[w] = b[w] = raw[0][w];
+#pragma unroll
+    for (int n = 1; n < N; n += THREE ? 2 : 1)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t x = raw[n][w], y = raw[n + 1 < N ? n + 1 : n][w];
+            a[w] = THREE ? pk_min3_f16(a[w], x, y) : pk_min_f16(a[w], x);
+            b[w] = THREE ? pk_max3_f16(b[w], x, y) : pk_max_f16(b[w], x);
+        }
+#pragma unroll
+    for (int m = 16; m <= 32; m <<= 1)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t x = xlane_u32(a[w], m), y = xlane_u32(b[w], m);
+            a[w] = THREE ? pk_min3_f16(a[w], x, x) : pk_min_f16(a[w], x);
+            b[w] = THREE ? pk_max3_f16(b[w], y, y) : pk_max_f16(b[w], y);
+        }
+    const int rsub = lane_id() >> 4;
+    pa = pick4(rsub, a[0], a[1], a[2], a[3]);
+    pb = pick4(rsub, b[0], b[1], b[2], b[3]);
+}
+
 // K statistics: min / max of the lane's channels over N loaded rows and over the 4 lanes
 // (rsub = 0..3) that hold the other rows of the same channels.  The lane keeps the result for
 // channels 2*rsub and 2*rsub+1 only (mn2 / mx2).
-template <int DT, int N>
-__device__ __forceinline__ void k_stats_own(const u32x4 *raw, float mn2[2], float mx2[2])
+// ROTATED, fp16: rows of hadamard_row<LIMIT = false>.  The extremes show whether a row left the finite range (three-operand
+// minima and maxima, half as many operations, hand on a NaN as well); the rows are limited and looked at again if so.
+template <int DT, int N, bool ROTATED>
+__device__ __forceinline__ void k_stats_own(u32x4 *raw, float mn2[2], float mx2[2])
 {
     const int rsub = lane_id() >> 4;
     if (DT == DT_F16) {
-        uint32_t a[4], b[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) a[w] = b[w] = raw[0][w];
-#pragma unroll
-        for (int n = 1; n < N; ++n)
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                a[w] = pk_min_f16(a[w], raw[n][w]);
-                b[w] = pk_max_f16(b[w], raw[n][w]);
-            }
-#pragma unroll
-        for (int m = 16; m <= 32; m <<= 1)
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                a[w] = pk_min_f16(a[w], xlane_u32(a[w], m));
-                b[w] = pk_max_f16(b[w], xlane_u32(b[w], m));
-            }
-        const uint32_t pa = pick4(rsub, a[0], a[1], a[2], a[3]), pb = pick4(rsub, b[0], b[1], b[2], b[3]);
+        uint32_t pa, pb;
+        k_extremes_f16<N, ROTATED>(raw, pa, pb);
+        if (ROTATED && __builtin_amdgcn_ballot_w64(beyond_f16(lo_f32<DT_F16>(pa)) || beyond_f16(hi_f32<DT_F16>(pa)) ||
+                                                   beyond_f16(lo_f32<DT_F16>(pb)) || beyond_f16(hi_f32<DT_F16>(pb)))) {
+            limit_rows_f16<N>(raw);
+            k_extremes_f16<N, false>(raw, pa, pb);
+        }
         mn2[0] = lo_f32<DT_F16>(pa); mn2[1] = hi_f32<DT_F16>(pa);
         mx2[0] = lo_f32<DT_F16>(pb); mx2[1] = hi_f32<DT_F16>(pb);
     } else {
@@ -160,18 +213,18 @@ struct KParams {
 // share a channel octet computes two channels, stores their metadata (scale, zero as fp16)
 // and publishes (zero, 1/scale) through 64 LDS slots of 16 bytes, XSTRIDE bytes apart, at `xch`.
 // meta_block: the 512 bytes of this token block's metadata.
-template <int BITS, int DT, int N, int XSTRIDE>
-__device__ __forceinline__ void k_group_params(const u32x4 *raw, uint8_t *xch, uint8_t *meta_block, KParams &kp)
+template <int BITS, int DT, int N, int XSTRIDE, bool ROTATED>
+__device__ __forceinline__ void k_group_params(u32x4 *raw, uint8_t *xch, uint8_t *meta_block, KParams &kp)
 {
     const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
     float mn2[2], mx2[2];
-    k_stats_own<DT, N>(raw, mn2, mx2);
+    k_stats_own<DT, N, ROTATED>(raw, mn2, mx2);
     const GroupParams g0 = make_group<BITS, DT>(mn2[0], mx2[0]);
     const GroupParams g1 = make_group<BITS, DT>(mn2[1], mx2[1]);
     u32x2 m;
     m[0] = g0.meta;
     m[1] = g1.meta;
-    put_at<true>(meta_block + (col * 8 + rsub * 2) * 4, m);
+    put_at<true>(meta_block + (lane_octet(ROTATED) * 8 + rsub * 2) * 4, m);
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     f32x4 mine = {g0.zero, g0.inv, g1.zero, g1.inv};
     wave_sync();                                  // earlier readers of xch are done
@@ -196,21 +249,34 @@ __device__ __forceinline__ u32x2 k_quant_row(const u32x4 &raw, const KParams &kp
     return codes8<BITS, CLAMP>(t);
 }
 
+// (min, -max) of a V group in one row, fp16: everything stays packed, reduced over the lane's 8 values and the
+// group's lanes by packed minima.  THREE: see pk_min3_f16.
+template <int GV, bool THREE> __device__ __forceinline__ uint32_t v_row_extremes_f16(const u32x4 &raw)
+{
+    uint32_t a, b;
+    if (THREE) {
+        a = pk_min3_halves_f16<false>(pk_min3_f16(pk_min3_f16(raw[0], raw[1], raw[2]), raw[3], raw[3]));
+        b = pk_min3_halves_f16<true>(pk_max3_f16(pk_max3_f16(raw[0], raw[1], raw[2]), raw[3], raw[3]));
+    } else {
+        a = pk_min_halves_f16(pk_min_f16(pk_min_f16(raw[0], raw[1]), pk_min_f16(raw[2], raw[3])));
+        b = pk_min_halves_f16(pk_min_f16(pk_min_neg_f16(raw[0], raw[1]), pk_min_neg_f16(raw[2], raw[3])));
+    }
+    uint32_t p = (a & 0xffffu) | (b & 0xffff0000u);
+    auto reduce = [&](uint32_t o) { p = THREE ? pk_min3_f16(p, o, o) : pk_min_f16(p, o); };
+    constexpr int LANES = GV / 8;
+    reduce(dpp_u32<DPP_QUAD_XOR1>(p));
+    reduce(dpp_u32<DPP_QUAD_XOR2>(p));
+    if (LANES >= 8) reduce(dpp_u32<DPP_HALF_MIRROR>(p));
+    if (LANES >= 16) reduce(dpp_u32<DPP_MIRROR>(p));
+    return p;
+}
+
 // V: the lane's 8 channels of a row belong to one group shared with GV/8 - 1 neighbouring lanes.
 template <int GV, int DT>
 __device__ __forceinline__ void v_row_minmax(const u32x4 &raw, float &mn, float &mx)
 {
     if (DT == DT_F16) {
-        // everything stays packed: (min, -max) of the lane's 8 values in one register, reduced
-        // over the group's lanes by packed minima, converted once at the end
-        const uint32_t a = pk_min_halves_f16(pk_min_f16(pk_min_f16(raw[0], raw[1]), pk_min_f16(raw[2], raw[3])));
-        const uint32_t b = pk_min_halves_f16(pk_min_f16(pk_min_neg_f16(raw[0], raw[1]), pk_min_neg_f16(raw[2], raw[3])));
-        uint32_t p = (a & 0xffffu) | (b & 0xffff0000u);
-        constexpr int LANES = GV / 8;
-        p = pk_min_f16(p, dpp_u32<DPP_QUAD_XOR1>(p));
-        p = pk_min_f16(p, dpp_u32<DPP_QUAD_XOR2>(p));
-        if (LANES >= 8) p = pk_min_f16(p, dpp_u32<DPP_HALF_MIRROR>(p));
-        if (LANES >= 16) p = pk_min_f16(p, dpp_u32<DPP_MIRROR>(p));
+        const uint32_t p = v_row_extremes_f16<GV, false>(raw);
         mn = lo_f32<DT_F16>(p);
         mx = -hi_f32<DT_F16>(p);
         return;
@@ -241,14 +307,32 @@ template <int GV> __device__ __forceinline__ int v_own_row()
 // Parameters of the lane's group in each of its 8 rows.  The GV/8 lanes of a group hold the
 // same (min, max) after the reduction; each of them finishes one or two of the 8 rows and the
 // results travel back through ds_bpermute.
-template <int BITS, int GV, int DT>
-__device__ __forceinline__ void v_pass_params(const u32x4 raw[8], VParams &vp)
+template <int BITS, int GV, int DT, bool ROTATED>
+__device__ __forceinline__ void v_pass_params(u32x4 raw[8], VParams &vp)
 {
     constexpr int LANES = GV / 8;
     const int lane = lane_id(), k = lane & (LANES - 1), base = lane & ~(LANES - 1);
     float mn[8], mx[8];
+    if (DT == DT_F16 && ROTATED) {
+        // (as in k_stats_own; the least of all words shows whether a row has an infinity or a NaN)
+        uint32_t p[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v_row_minmax<GV, DT>(raw[i], mn[i], mx[i]);
+        for (int i = 0; i < 8; ++i) p[i] = v_row_extremes_f16<GV, true>(raw[i]);
+        const uint32_t least = pk_min3_f16(pk_min3_f16(pk_min3_f16(p[0], p[1], p[2]), p[3], p[4]), pk_min3_f16(p[5], p[6], p[7]), p[7]);
+        if (__builtin_amdgcn_ballot_w64(beyond_f16(lo_f32<DT_F16>(least)) || beyond_f16(hi_f32<DT_F16>(least)))) {
+            limit_rows_f16<8>(raw);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) p[i] = v_row_extremes_f16<GV, false>(raw[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            mn[i] = lo_f32<DT_F16>(p[i]);
+            mx[i] = -hi_f32<DT_F16>(p[i]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v_row_minmax<GV, DT>(raw[i], mn[i], mx[i]);
+    }
     bool c = false;
     if (LANES == 4) {
         // lane k of the quad finishes rows k and k + 4
@@ -299,7 +383,7 @@ template <int BITS, bool SUB> __device__ __forceinline__ uint8_t *code_row(uint8
     return base + r * (16 * BITS);
 }
 
-template <int BITS, int DT, int P, bool SUB, bool CLAMP, bool FULL>
+template <int BITS, int DT, int P, bool SUB, bool TURNED, bool CLAMP, bool FULL>
 __device__ __forceinline__ void k_emit_rows(const u32x4 *raw, const KParams &kp, uint8_t *base, int rows)
 {
     const int rsub = lane_id() >> 4;
@@ -310,8 +394,8 @@ __device__ __forceinline__ void k_emit_rows(const u32x4 *raw, const KParams &kp,
         for (int i = 0; i < 8; ++i) {
             const int r = p * kPassRows + 4 * i + rsub;
             u32x2 w = k_quant_row<BITS, DT, CLAMP>(raw[p * 8 + i], kp, one);
-            if (BITS == 3) w[0] = quad_words_from_24(w[0]);
-            if (FULL || r < rows) store_row_codes<BITS, !SUB>(code_row<BITS, SUB>(base, r), w);
+            if (BITS == 3) w[0] = quad_words_from_24(TURNED ? quad_24_in_order(w[0]) : w[0]);
+            if (FULL || r < rows) store_row_codes<BITS, !SUB, TURNED>(code_row<BITS, SUB>(base, r), w);
             // a token block of 64 or 128 rows: keep the scheduler from interleaving all rows, which
             // would hold the floats of every row at once (255 registers and more)
             if (P >= 2) __builtin_amdgcn_sched_barrier(0);
@@ -319,16 +403,16 @@ __device__ __forceinline__ void k_emit_rows(const u32x4 *raw, const KParams &kp,
 }
 
 // Quantize, pack and store the P*32 rows of a K token block (`rows` of them exist).
-template <int BITS, int DT, int P, bool SUB>
+template <int BITS, int DT, int P, bool SUB, bool TURNED>
 __device__ __forceinline__ void k_emit(const u32x4 *raw, const KParams &kp, uint8_t *base, int rows)
 {
     const bool full = rows >= P * kPassRows;
     if (kp.clamp) {
-        if (full) k_emit_rows<BITS, DT, P, SUB, true, true>(raw, kp, base, rows);
-        else k_emit_rows<BITS, DT, P, SUB, true, false>(raw, kp, base, rows);
+        if (full) k_emit_rows<BITS, DT, P, SUB, TURNED, true, true>(raw, kp, base, rows);
+        else k_emit_rows<BITS, DT, P, SUB, TURNED, true, false>(raw, kp, base, rows);
     } else {
-        if (full) k_emit_rows<BITS, DT, P, SUB, false, true>(raw, kp, base, rows);
-        else k_emit_rows<BITS, DT, P, SUB, false, false>(raw, kp, base, rows);
+        if (full) k_emit_rows<BITS, DT, P, SUB, TURNED, false, true>(raw, kp, base, rows);
+        else k_emit_rows<BITS, DT, P, SUB, TURNED, false, false>(raw, kp, base, rows);
     }
 }
 
@@ -344,7 +428,7 @@ template <int GV> __device__ __forceinline__ void v_store_meta(const VParams &vp
     if (LANES == 4 && r + 16 < rows) put_at<true>(m + 16 * NG, vp.meta[1]);
 }
 
-template <int BITS, int GV, int DT, bool SUB, bool CLAMP, bool FULL>
+template <int BITS, int GV, int DT, bool SUB, bool TURNED, bool CLAMP, bool FULL>
 __device__ __forceinline__ void v_emit_rows(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows)
 {
     const int rsub = lane_id() >> 4;
@@ -353,23 +437,23 @@ __device__ __forceinline__ void v_emit_rows(const u32x4 raw[8], const VParams &v
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + rsub;
         u32x2 w = v_quant_row<BITS, DT, CLAMP>(raw[i], vp.zero[i], vp.inv[i], one);
-        if (BITS == 3) w[0] = quad_words_from_24(w[0]);
-        if (FULL || r < rows) store_row_codes<BITS, !SUB>(code_row<BITS, SUB>(base, r), w);
+        if (BITS == 3) w[0] = quad_words_from_24(TURNED ? quad_24_in_order(w[0]) : w[0]);
+        if (FULL || r < rows) store_row_codes<BITS, !SUB, TURNED>(code_row<BITS, SUB>(base, r), w);
     }
 }
 
 // One pass (32 rows, `rows` of them exist) of V; base / meta point at the pass's first row.
-template <int BITS, int GV, int DT, bool SUB>
+template <int BITS, int GV, int DT, bool SUB, bool TURNED>
 __device__ __forceinline__ void v_emit(const u32x4 raw[8], const VParams &vp, uint8_t *base, int rows, uint32_t *meta)
 {
     const bool full = rows >= kPassRows;
     v_store_meta<GV>(vp, rows, meta);
     if (vp.clamp) {
-        if (full) v_emit_rows<BITS, GV, DT, SUB, true, true>(raw, vp, base, rows);
-        else v_emit_rows<BITS, GV, DT, SUB, true, false>(raw, vp, base, rows);
+        if (full) v_emit_rows<BITS, GV, DT, SUB, TURNED, true, true>(raw, vp, base, rows);
+        else v_emit_rows<BITS, GV, DT, SUB, TURNED, true, false>(raw, vp, base, rows);
     } else {
-        if (full) v_emit_rows<BITS, GV, DT, SUB, false, true>(raw, vp, base, rows);
-        else v_emit_rows<BITS, GV, DT, SUB, false, false>(raw, vp, base, rows);
+        if (full) v_emit_rows<BITS, GV, DT, SUB, TURNED, false, true>(raw, vp, base, rows);
+        else v_emit_rows<BITS, GV, DT, SUB, TURNED, false, false>(raw, vp, base, rows);
     }
 }
 
@@ -444,11 +528,11 @@ __device__ __forceinline__ bool v_meta_floats(const uint32_t mw[8], float scale[
 // layout for 4- and 8-bit codes, sub-blocks of two rows without padding whose 16-byte pieces (eight or
 // sixteen) are rotated by the sub-block's number (piece p of sub-block s sits at position (p + s) modulo
 // their count), so that both the row-wise and the sub-block-wise accesses spread over the banks.
-template <int BITS, int LAYOUT> __device__ __forceinline__ u32x2 fetch_codes(uint8_t *codes, int r)
+template <int BITS, int LAYOUT, bool TURNED> __device__ __forceinline__ u32x2 fetch_codes(uint8_t *codes, int r)
 {
     if (LAYOUT == 2) {
         static_assert(LAYOUT != 2 || BITS == 4 || BITS == 8, "rotated layout is for 4- and 8-bit codes");
-        const int col = lane_id() & 15, sub = r >> 1;
+        const int col = lane_octet(TURNED), sub = r >> 1;
         u32x2 w;
         if (BITS == 4) {
             const int piece = ((r & 1) << 2) + (col >> 2);
@@ -460,7 +544,7 @@ template <int BITS, int LAYOUT> __device__ __forceinline__ u32x2 fetch_codes(uin
         }
         return w;
     }
-    return load_row_codes<BITS>(code_row<BITS, LAYOUT == 1>(codes, r));
+    return load_row_codes<BITS, TURNED>(code_row<BITS, LAYOUT == 1>(codes, r));
 }
 
 // ---- stage T, delta transform (KVServe section 5.1 names the difference from an anchor token
@@ -566,7 +650,7 @@ struct PassFetch {
     bool bad;           // a block-table entry out of range: nothing of the pass is stored
 };
 
-template <int BITS, bool DENSE, int LAYOUT>
+template <int BITS, bool DENSE, int LAYOUT, bool TURNED = false>
 __device__ __forceinline__ void pass_fetch(PassFetch &f, uint8_t *codes, const TensorView &x, long long head_off,
                                            long long row0, int rows, int row_base = 0, bool have_blocks = false, int blocks = 0)
 {
@@ -574,14 +658,14 @@ __device__ __forceinline__ void pass_fetch(PassFetch &f, uint8_t *codes, const T
     f.bad = false;
     if (DENSE && rows >= kPassRows) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) f.w[i] = fetch_codes<BITS, LAYOUT>(codes, row_base + 4 * i + rsub);
+        for (int i = 0; i < 8; ++i) f.w[i] = fetch_codes<BITS, LAYOUT, TURNED>(codes, row_base + 4 * i + rsub);
         return;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + rsub;
         const bool ok = r < rows;                       // uniform over each quad of lanes
-        f.w[i] = fetch_codes<BITS, LAYOUT>(codes, row_base + (ok ? r : 0));
+        f.w[i] = fetch_codes<BITS, LAYOUT, TURNED>(codes, row_base + (ok ? r : 0));
         if (DENSE) f.off[i] = head_off + (row0 + (ok ? r : 0)) * kDim;
     }
     if (!DENSE) pass_offsets(x, head_off, row0, row0 + rows, f.off, f.bad, have_blocks, blocks);
@@ -595,7 +679,7 @@ __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const floa
                                                   const TensorView &x, long long head_off, long long row0, int rows,
                                                   const uint16_t *anchors, int anchor_shift, const u32x4 *loaded_anchor, int pace)
 {
-    const int lane = lane_id(), col = lane & 15, rsub = lane >> 4;
+    const int rsub = lane_id() >> 4, col = lane_octet(TR == 1);
     auto wait = [&](int i) {
         if (PACED && i < 7)
             for (int k = 0; k < pace; ++k) __builtin_amdgcn_s_sleep(1);
@@ -630,7 +714,7 @@ __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const floa
         for (int i = 0; i < 8; ++i) {
             u32x4 out = IS_V ? dequant_row_uniform<BITS, DT, CLAMP>(f.w[i], scale[i], zero[i])
                              : dequant_row<BITS, DT, CLAMP>(f.w[i], scale, zero);
-            if (TR == 1) out = hadamard_row<DT>(out, true);
+            if (TR == 1) out = hadamard_row<DT, true>(out, true);
             if (TR >= 2) out = add_anchor<DT>(out, anchor_of(i), anchor_shift, row0 + 4 * i + rsub);
             __builtin_nontemporal_store(out, dst + i * 64);
             wait(i);
@@ -642,7 +726,7 @@ __device__ __forceinline__ void dequant_pass_rows(const PassFetch &f, const floa
         const int r = 4 * i + rsub;
         u32x4 out = IS_V ? dequant_row_uniform<BITS, DT, CLAMP>(f.w[i], scale[i], zero[i])
                          : dequant_row<BITS, DT, CLAMP>(f.w[i], scale, zero);
-        if (TR == 1) out = hadamard_row<DT>(out, true);     // (all 16 lanes of a row take part)
+        if (TR == 1) out = hadamard_row<DT, true>(out, true);     // (all 16 lanes of a row take part)
         if (TR >= 2) out = add_anchor<DT>(out, anchor_of(i), anchor_shift, row0 + (r < rows ? r : 0));
         if (r < rows && !f.bad) __builtin_nontemporal_store(out, (u32x4 *)(x.base + f.off[i] + col * 8));
         wait(i);
@@ -663,19 +747,6 @@ __device__ __forceinline__ void dequant_pass(const PassFetch &f, const float sca
     else dequant_pass_rows<BITS, DT, IS_V, DENSE, false, TR, PACED>(f, scale, zero, x, head_off, row0, rows, anchors, anchor_shift, loaded_anchor, pace);
 }
 
-// the same with the transform chosen at run time (one copy of the pass per transform; a launch
-// only ever runs one of them)
-template <int BITS, int DT, bool IS_V, bool DENSE>
-__device__ __forceinline__ void dequant_pass_any(const PassFetch &f, const float scale[8], const float zero[8], bool clamp,
-                                                 const TensorView &x, long long head_off, long long row0, int rows, bool &bad,
-                                                 bool rotate, const uint16_t *anchors, int anchor_shift)
-{
-    if (rotate) dequant_pass<BITS, DT, IS_V, DENSE, 1>(f, scale, zero, clamp, x, head_off, row0, rows, bad);
-    else if (anchors && anchor_shift >= 5) dequant_pass<BITS, DT, IS_V, DENSE, 2>(f, scale, zero, clamp, x, head_off, row0, rows, bad, anchors, anchor_shift);
-    else if (anchors) dequant_pass<BITS, DT, IS_V, DENSE, 3>(f, scale, zero, clamp, x, head_off, row0, rows, bad, anchors, anchor_shift);
-    else dequant_pass<BITS, DT, IS_V, DENSE, 0>(f, scale, zero, clamp, x, head_off, row0, rows, bad);
-}
-
 // bf16 rows are widened to fp32 once for the statistics and once for the quantizer.  Left alone, the
 // compiler keeps the widened copy of the whole unit alive from one to the other (64 registers per
 // pass, against 32 for the rows themselves); after this statement it no longer knows that the rows
@@ -687,11 +758,12 @@ template <int DT, int N> __device__ __forceinline__ void forget_unpacked(u32x4 *
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(raw[i][0]), "+v"(raw[i][1]), "+v"(raw[i][2]), "+v"(raw[i][3]));
 }
 
-// Stage T on the rows just loaded (see hadamard_row).
-template <int DT, int N> __device__ __forceinline__ void rotate_rows(u32x4 *raw)
+// Stage T on the rows just loaded, octets turned (see hadamard_row; fp16 rows that are not LIMITed go through k_stats_own or
+// v_pass_params with ROTATED).
+template <int DT, int N, bool LIMIT> __device__ __forceinline__ void rotate_rows(u32x4 *raw)
 {
 #pragma unroll
-    for (int i = 0; i < N; ++i) raw[i] = hadamard_row<DT>(raw[i], false);
+    for (int i = 0; i < N; ++i) raw[i] = hadamard_row<DT, LIMIT || DT != DT_F16>(raw[i], false);
 }
 
 }  // namespace kvc

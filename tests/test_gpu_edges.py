@@ -320,3 +320,20 @@ def test_decoder_places_given_out_in_runs(bits, L, T):
         assert int(buf.status[0]) == 0
         out.append(y)
     assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("T", [31, 96, 200])
+def test_rotation_beyond_the_range(ref, T, group, bits):
+    """Rotated rows above 65504: the extremes of a unit show it and the unit starts again with limited rows, beside
+    units that do not; also where a single value or a whole group leaves the range."""
+    g = torch.Generator().manual_seed(T + bits)
+    x = torch.randn((1, 2, 2, T, 128), generator=g)
+    x[:, :, 0, ::40] *= 2.0 ** 14
+    x[:, :, 0, 5] = 60000.0                             # one channel collects the row: 960000, the others 0
+    x[:, :, 1, 7] = -60000.0
+    x[:, :, 1, 20:28] = 65504.0 * torch.sign(torch.randn((1, 2, 8, 128), generator=g))
+    x = x.clamp(-65504, 65504).half()
+    check_contiguous(ref, x, bits, bits, group, group, transform=1)
+    check_contiguous(ref, x, bits, bits, group, group, transform=1, codec=1)
