@@ -504,6 +504,13 @@ static int launch_tensor(const kvc_plan_t *p, int is_v, bool compress, QuantBatc
 // finding its item costs every workgroup of a shared launch a look at the batch (measured: a batch of
 // four 20k- to 30k-token requests ran 4 % slower shared than one after the other).  Empty requests
 // have no work in any launch and fit every window.
+
+// Requests of a coder window: K and V apart eight at a time, of sixteen requests and more twelve (32 requests of 512 to 2048
+// tokens, compression: six launches instead of eight, each with a start and a tail of its own, 1414 -> 1364 us); where K
+// and V share a launch, or the codes have 8 bits, four.
+static int coder_window(int32_t n) { return n >= 16 ? kCoderBatch : 8; }
+static const int kSharedWindow = 4;
+
 static bool dense_layout(const kvc_request *r) { return !r->block_table && r->stride_token == kDim; }
 
 static const long long kSmallRows = 1ll << 21;           // token rows per tensor: 64 Ki work units of 32 rows
@@ -605,7 +612,7 @@ static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int
 
 static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
 {
-    if (!tensors_share(p) || end - first > kCoderBatch / 2) return false;
+    if (!tensors_share(p) || end - first > kSharedWindow) return false;
     const long long rows = (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens;
     if (p->strat.group_k == 32) return rows < 4 * kSmallRows;
     if (rows >= kSmallRows) return false;
@@ -640,7 +647,7 @@ static int common_widths(const kvc_plan_t *p)
 // 66 81 208 us apart, 88 100 203 shared; K 8, 4 and 2 bits, V 8 and 2: 106 120 304 and 125 139 291).
 static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
 {
-    return common_widths(p) > 0 && end - first <= kCoderBatch / 2 &&
+    return common_widths(p) > 0 && end - first <= kSharedWindow &&
            (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens < 4 * kSmallRows;
 }
 
@@ -944,11 +951,11 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
     }
     for (int first = 0; first < n;) {
         int lead;
-        int end = request_window(plan, reqs, n, first, st.codec ? kCoderBatch : kQuantBatch, &lead);
+        int end = request_window(plan, reqs, n, first, st.codec ? coder_window(n) : kQuantBatch, &lead);
         bool share = st.codec && share_kv(plan, reqs, first, end, lead);
-        if (st.codec && st.bits_k == 8 && end - first > kCoderBatch / 2) {
+        if (st.codec && st.bits_k == 8 && end - first > kSharedWindow) {
             int lead_half;
-            const int half = request_window(plan, reqs, n, first, kCoderBatch / 2, &lead_half);
+            const int half = request_window(plan, reqs, n, first, kSharedWindow, &lead_half);
             share = share_kv(plan, reqs, first, half, lead_half);
             if (share) {
                 end = half;
@@ -1136,7 +1143,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
-    const int coder_limit = common_widths(plan) == 2 ? kCoderBatch / 2 : kCoderBatch;
+    const int coder_limit = common_widths(plan) == 2 ? kSharedWindow : coder_window(n);
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);

@@ -289,7 +289,7 @@ struct CoderArgs {
 // One launch of the encoder or decoder for the requests of a window (see request_window), the items' workgroups one
 // after the other: a launch of every request (one tensor and width), or, where K and V share a launch, a
 // K and a V item of every request.  All items have one width and take the same kernel.
-constexpr int kCoderBatch = 8;      // (the argument block stays below 4 KB)
+constexpr int kCoderBatch = 12;     // (the argument block stays below 4 KB)
 struct CoderBatch {
     CoderArgs item[kCoderBatch];
     Places<kCoderBatch> at;             // (encoder, both tensors together: the items are the requests; set by the launcher)

@@ -337,3 +337,23 @@ def test_rotation_beyond_the_range(ref, T, group, bits):
     x = x.clamp(-65504, 65504).half()
     check_contiguous(ref, x, bits, bits, group, group, transform=1)
     check_contiguous(ref, x, bits, bits, group, group, transform=1, codec=1)
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 25, 29])
+def test_many_requests_with_the_coder(ref, n):
+    """From sixteen requests on a coder window holds twelve of them: whole windows and remainders, against calls of one."""
+    lens = [int(v) for v in torch.randint(1, 300, (n,), generator=torch.Generator().manual_seed(n))]
+    plan = kvc.Plan(kvc.F16, 1, 2, 128, 4, 4, 32, 32, kvc.CODEC_HUFF8, max_tokens=300, max_batch=n)
+    xs = [kvgen.make_kv(700 + i, 1, 2, 128, t, torch.float16, "cuda") for i, t in enumerate(lens)]
+    buf = gpu_compress(plan, [kvc.contiguous_request(x) for x in xs], lens)
+    ys = [torch.zeros_like(x) for x in xs]
+    buf.decompress([kvc.contiguous_request(y) for y in ys], torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert not buf.status.any()
+    for i, (x, y) in enumerate(zip(xs, ys)):
+        one = gpu_compress(plan, [kvc.contiguous_request(x)], [lens[i]])
+        assert np.array_equal(buf.payload_of(i), one.payload_of(0)), i
+        z = torch.zeros_like(x)
+        one.decompress([kvc.contiguous_request(z)], torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), z.view(torch.int16)), i
