@@ -11,7 +11,8 @@ the same fault for gfx90a only.  A kernel that trips the check gets register hea
 asm statement naming a higher register (see decode_kernel).
 
 A second check keeps kernels whose time depends on their waves (min_waves in kvc_quant.hip) within the
-registers that leave room for them.
+registers that leave room for them, a third one looks for rows that are requested and waited for one at a time
+(rows_requested in kvc_tile.h).
 """
 import os
 import re
@@ -84,6 +85,33 @@ def over_budget(asm_path):
     return out
 
 
+# (kernel symbol, most such waits): dense rows without the delta transform.  The codec-free kernels have one at their start (the
+# head list); the encoders have seven more, behind which no row is loaded.
+LONE_LOADS = [(r"compress_[kv]_kernelILi\d+ELi\d+ELi\dELb1ELi[02]E", 1),
+              (r"encode_kernelILi\d+ELi\d+ELi\dELi[01]ELb1ELb0E", 8)]
+
+
+def lone_loads(asm_path):
+    """[(kernel symbol, waits, most)] of the kernels that wait for a single load, with none behind it in flight,
+    more often than LONE_LOADS has it."""
+    text = open(asm_path).read()
+    out = []
+    for k, body in re.findall(r"^(\w+):[^\n]*\n(.*?)^\.Lfunc_end", text, re.S | re.M):
+        limits = [most for pattern, most in LONE_LOADS if re.search(pattern, k)]
+        if not limits:
+            continue
+        loads = found = 0
+        for line in body.split("\n"):
+            code = line.split(";")[0]
+            loads += "global_load" in code
+            m = re.search(r"vmcnt\((\d+)\)", code)
+            if m:
+                found += m.group(1) == "0" and loads == 1
+                loads = 0
+        out += [(k, found, most) for most in limits if found > most]
+    return out
+
+
 def _compile(job):
     name, width = job
     stem = name.replace(".hip", "") + ("_b%d" % width if width else "")
@@ -107,6 +135,10 @@ def _compile(job):
     if over:
         raise RuntimeError("%s: more registers than the kernel's waves leave room for:\n%s" % (
             name, "\n".join("  %s: %d of %d" % h for h in over[:20])))
+    lone = lone_loads(asm)
+    if lone:
+        raise RuntimeError("%s: rows waited for one at a time:\n%s" % (
+            name, "\n".join("  %s: %d waits, %d allowed" % h for h in lone[:20])))
     spills = spilling_kernels(asm)
     if spills:
         err += "\n%s: %d kernels spill registers (most: %d bytes per lane): %s" % (

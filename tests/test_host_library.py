@@ -247,6 +247,24 @@ def test_build_check_finds_kernels_over_their_registers(tmp_path):
         assert build.over_budget(str(p)) == ([(name, regs, 96 if "ILi8" in name else 80)] if want else []), name
 
 
+def test_build_check_finds_rows_waited_for_one_at_a_time(tmp_path):
+    """The build's check of the loads: kernels for dense rows request the rows of a unit together."""
+    from paper_2605_13734_amd import build
+    load, one = "\tglobal_load_dwordx4 v[4:7], v[2:3], off nt\n", "\ts_waitcnt vmcnt(0)\n\tv_add_f32_e32 v4, v4, v5\n"
+    together = 8 * load + "".join("\ts_waitcnt vmcnt(%d)\n" % n for n in range(7, -1, -1))
+    quant, enc = "_ZN3kvc17compress_k_kernelILi4ELi%dELi%dELb%dELi%dEEEvNS_10QuantBatchE", "_ZN3kvc13encode_kernelILi4ELi64ELi1ELi0ELb1ELb%dELi4ELb1EEEvNS_10CoderBatchE"
+    cases = [(quant % (64, 1, 1, 2), load + one + together, 0),
+             (quant % (64, 1, 1, 2), load + one + together + 8 * (load + one), 9),
+             (quant % (32, 2, 1, 0), load + one + 6 * load + one + 2 * (load + one), 3),
+             (quant % (32, 2, 0, 0), 9 * (load + one), 0),              # not dense
+             (quant % (32, 2, 1, 1), 9 * (load + one), 0),              # delta transform
+             (enc % 0, 8 * (load + one), 0), (enc % 0, 16 * (load + one), 16), (enc % 1, 16 * (load + one), 0)]
+    for i, (name, body, want) in enumerate(cases):
+        p = tmp_path / ("k%d.s" % i)
+        p.write_text("\t.text\n%s:                                   ; @kern\n%s\ts_endpgm\n.Lfunc_end0:\n" % (name, body))
+        assert build.lone_loads(str(p)) == ([(name, want, 8 if "encode" in name else 1)] if want else []), i
+
+
 def test_inspect_never_accepts_a_damaged_header(lib, ref):
     """Every single-byte change of a valid header is either rejected by kvc_payload_inspect or
     leaves a header that the oracle also accepts with the same sections; without the lossless stage
