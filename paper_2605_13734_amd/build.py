@@ -85,9 +85,12 @@ def over_budget(asm_path):
     return out
 
 
-# (kernel symbol, most such waits): dense rows without the delta transform.  The codec-free kernels have one at their start (the
-# head list); the encoders have seven more, behind which no row is loaded.
-LONE_LOADS = [(r"compress_[kv]_kernelILi\d+ELi\d+ELi\dELb1ELi[02]E", 1),
+# (kernel symbol, most such waits): dense rows without the delta transform.  The codec-free K kernels have one at their start (the
+# head list); the encoders have seven more, behind which no row is loaded.  Rotated K blocks of 64 and 128 strided fp16 rows: the
+# look-ups of their pages, as without the rotation.
+LONE_LOADS = [(r"compress_k_kernelILi\d+ELi64ELi1ELb0ELi2E", 18), (r"compress_k_kernelILi\d+ELi128ELi1ELb0ELi2E", 34),
+              (r"encode_kernelILi\d+ELi64ELi1ELi0ELb0ELb0ELi\dELb1E", 24), (r"encode_kernelILi\d+ELi128ELi1ELi0ELb0ELb0ELi\dELb1E", 38),
+              (r"compress_k_kernelILi\d+ELi\d+ELi\dELb1ELi[02]E", 1),
               (r"encode_kernelILi\d+ELi\d+ELi\dELi[01]ELb1ELb0E", 8)]
 
 

@@ -97,7 +97,7 @@ __device__ __forceinline__ void quantize_unit(const QuantArgs &a, const ChunkPos
 #pragma unroll
     for (int p = 0; p < PU; ++p)
         load_pass<DENSE, XF == kRotation>(a.x, c.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad, have_blocks, have_blocks ? blocks[p] : 0);
-    rows_requested<DENSE, DT, XF>();
+    if (!IS_V) rows_requested<DENSE, DT, XF, PU>();
     if (XF == kRotation) rotate_rows<DT, PU * 8, false>(raw);
     if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, PU * 8>(a.x, c.head_off, row0, a.tokens, a.anchor_shift,

@@ -28,8 +28,9 @@ constexpr int min_waves(int bits, int rows, int dtype, bool dense)
 
 // XF: see kNoTransform.  Sharing a kernel with the code of stage T doubles the registers of the plain path for token blocks
 // of 64 and 128 rows.
-// IN_CALL: a unit of compress_call_kernel, which leaves bf16 loads where the compiler puts them for 8-bit codes: where all of its workgroups
-// are resident, requesting them together loses 3 % (bf16, groups of 32, 2^16 and 2^17 rows 11.3 -> 11.6, 19.7 -> 20.5 us; 4 bits gain 3).
+// IN_CALL: a unit of compress_call_kernel.  There 8-bit bf16 loads stay where the compiler puts them: where all workgroups
+// are resident, requesting them together loses 3 % (groups of 32, 2^16 and 2^17 rows 11.3 -> 11.6, 19.7 -> 20.5 us), and narrower
+// ones are requested together for V as well (4 bits, 2^16 rows 10.8, K alone 11.0, both 10.5).
 template <int BITS, int G, int DT, bool DENSE, int XF, bool IN_CALL = false>
 __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg, float *xch_all)
 {
@@ -41,7 +42,7 @@ __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg,
     u32x4 raw[P * 8];
 #pragma unroll
     for (int p = 0; p < P; ++p) load_pass<DENSE, XF == kRotation>(a.x, u.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad);
-    if (BITS < 8 || !IN_CALL) rows_requested<DENSE, DT, XF>();
+    if (BITS < 8 || !IN_CALL) rows_requested<DENSE, DT, XF, P>();
     if (XF == kRotation) rotate_rows<DT, P * 8, false>(raw);
     if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, P * 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,
@@ -116,7 +117,7 @@ __device__ __forceinline__ void compress_v_unit(const QuantArgs &a, unsigned wg)
     bool bad = false;
     u32x4 raw[8];
     load_pass<DENSE, XF == kRotation>(a.x, u.head_off, row0, a.tokens, raw, bad);
-    if (BITS < 8 || !IN_CALL) rows_requested<DENSE, DT, XF>();
+    if (BITS < 8 && IN_CALL) rows_requested<DENSE, DT, XF, 1>();
     if (XF == kRotation) rotate_rows<DT, 8, false>(raw);
     if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,

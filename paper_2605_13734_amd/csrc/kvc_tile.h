@@ -46,14 +46,16 @@ __device__ __forceinline__ void load_pass(const TensorView &v, long long head_of
     for (int i = 0; i < 8; ++i) raw[i] = __builtin_nontemporal_load((const u32x4 *)(v.base + off[i] + col * 8));
 }
 
-// Between the loads of a unit's rows and their use.  Where it saves registers for another wave the compiler
+// Between the loads of a K block's rows and their use.  Where it saves registers for another wave the compiler
 // otherwise moves loads behind the arithmetic on earlier rows, each with a wait for it alone: two of eight for dense bf16 rows (4 and
-// 2 bits, 2^21 rows, compress call 234 -> 225, 226 -> 210 us), half of the sixteen of a rotated K block of 64 rows (2^13 rows, 4 bits, one
-// memory round trip after the other: 20.8 -> 18.0 us, with the coder 77.5 -> 70.6).  fp16 rows without the rotation
-// are requested together as it is.
-template <bool DENSE, int DT, int XF> __device__ __forceinline__ void rows_requested()
+// 2 bits, 2^21 rows, compress call 234 -> 226, 225 -> 210 us), eight of a rotated block of 64 or 128 fp16 rows (64 rows, 2^13 in all,
+// 4 bits, one memory round trip after the other: 20.8 -> 18.0 us, with the coder 77.5 -> 70.6; paged 22.3 -> 19.0, with the
+// coder 82.0 -> 74.6).  The others are requested together as it is, but for one row of a bf16 V unit (groups of 64 lose
+// 0.6 % by waiting for all, of 128 gain 1 %) and strided rows, whose addresses arrive one by one (2 to 5 % slower).
+template <bool DENSE, int DT, int XF, int PASSES> __device__ __forceinline__ void rows_requested()
 {
-    if (DENSE && (DT == DT_BF16 || XF == kRotation)) __builtin_amdgcn_sched_barrier(0);
+    constexpr bool kMoved = XF == kRotation ? DT == DT_F16 && PASSES > 1 : XF == kNoTransform && DENSE && DT == DT_BF16 && PASSES == 1;
+    if (kMoved) __builtin_amdgcn_sched_barrier(0);
 }
 
 __device__ __forceinline__ uint32_t xlane_u32(uint32_t v, int xor_mask)
