@@ -272,6 +272,16 @@ void encode_kernel(CoderBatch batch)
 
 // ---- launchers ----------------------------------------------------------------------------------
 
+// LDS that nothing uses, for rotated K blocks of 64 rows: the kernel leaves room for three workgroups on a compute unit, and a
+// launch of more than three and up to five per unit takes three and then one or two beside an idle rest.  With 40000
+// bytes more they go two at a time (fp16, 880, 1024, 1136 and 1264 workgroups, compress call of 4 bits without / with: 153 143, 161
+// 155, 190 185, 197 196 us; 3 bits 154 145, 161 155, 191 189, 199 201; bf16 5 % up to four per unit, level above).  8-bit codes
+// have two workgroups by their LDS, groups of 128 by their registers, groups of 32 have four.
+static unsigned encode_hold(int bits, int group, bool is_v, bool rotate, unsigned wgs)
+{
+    return rotate && !is_v && group == 64 && bits < 8 && wgs > 3 * 256 && wgs <= 5 * 256 ? 40000 : 0;
+}
+
 template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(const CoderBatch &b, hipStream_t s)
 {
     const CoderArgs &a = b.item[0];
@@ -285,7 +295,8 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
     close_places(placed.at, placed.n, need, 0);
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
-#define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, 0, s, placed)
+    const unsigned lds = encode_hold(BITS, G, KV == 1, a.q.rotate != 0, need);
+#define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, lds, s, placed)
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
     // transform (its code costs the plain path registers); both tensors together run without one only
     constexpr bool kPlain = KV != 1 || G == 32;

@@ -164,6 +164,19 @@ def test_encoder_shares_a_launch_where_it_pays(dtype, paged, bits, group, L, T, 
     assert [kv for kv, _ in encoders(found)] == ([2] if shared else [0, 1])
 
 
+@pytest.mark.parametrize("T,lds", [(6144, 0), (6145, 40000), (10240, 40000), (10241, 0)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_bound_of_rotated_encoders(dtype, T, lds):
+    """More than three and up to five workgroups per compute unit, 16 per 128 tokens: K blocks of 64 rows go two at a time."""
+    def bounds(**kw):
+        found = launches(call_of("compress", 8, 8, T, dtype=dtype, codec=1, transform=1, **kw))
+        return [size for name, _, size in found if "encode_kernel" in name]
+    assert bounds(bits_k=4, bits_v=4, group_k=64, group_v=64) == [lds, 0]
+    assert bounds(bits_k=2, bits_v=3, group_k=64, group_v=32) == [lds, 0]
+    for kw in (dict(bits_k=8, bits_v=8, group_k=64), dict(bits_k=4, bits_v=4, group_k=32), dict(bits_k=4, bits_v=4, group_k=128)):
+        assert bounds(group_v=64, **kw) == [0, 0]
+
+
 @pytest.mark.parametrize("n,want", [(1, [2]), (4, [2]), (5, [0, 1]), (8, [0, 1]), (11, [0, 1, 2])])
 def test_encoder_windows(n, want):
     """Up to four requests share a launch for K and V, more of them take the passes apart, eight at a time."""
