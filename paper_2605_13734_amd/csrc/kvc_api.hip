@@ -505,10 +505,7 @@ static int launch_tensor(const kvc_plan_t *p, int is_v, bool compress, QuantBatc
 // four 20k- to 30k-token requests ran 4 % slower shared than one after the other).  Empty requests
 // have no work in any launch and fit every window.
 
-// Requests of a coder window: K and V apart eight at a time, of sixteen requests and more twelve (32 requests of 512 to 2048
-// tokens, compression: six launches instead of eight, each with a start and a tail of its own, 1414 -> 1364 us); where K
-// and V share a launch, or the codes have 8 bits, four.
-static int coder_window(int32_t n) { return n >= 16 ? kCoderBatch : 8; }
+// Requests of a coder window where K and V share a launch (coder_window: where they go apart).
 static const int kSharedWindow = 4;
 
 static bool dense_layout(const kvc_request *r) { return !r->block_table && r->stride_token == kDim; }
@@ -608,6 +605,42 @@ static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int
         *largest = c > *largest ? c : *largest;
     }
     return chunks;
+}
+
+// Requests of a coder window with K and V apart: eight, from seventeen on twelve.  A window is a start and a tail per launch, but
+// where a launch of twelve of the widest codes has up to a quarter more chunks than are resident (16 per compute unit, at 8 bits 8; with width
+// tables, whose launches are smaller, up to a half) its rest has the chip to itself, and eight is better unless twelve takes a
+// window less for every such rest.  Time with twelve / with eight, 17, 24 and 32 requests, 64 heads of 400 to 2100 tokens each or 8
+// and 256 heads of 300 to 2000, fp16 and bf16:
+//   where twelve is taken   compression 0.70 to 0.99, decompression 0.56 to 1.00 (K 4 and V 2 bits, a rest of a third or half 1.02 to 1.04)
+//   where eight is taken    compression, half of the heads at 8 bits 1.01 to 1.05, rotation and 8 bits 1.09, 4 bits 1.02 (2 bits groups
+//                           of 128, rotation and 4 bits 0.94 to 0.98); decompression, K 4 and V 2 bits 1.06 to 1.10, 8 bits 1.14
+//   sixteen requests take two windows either way: 12 + 4 against 8 + 8 0.82 to 1.17
+// (Nine to twelve requests would gain by one window, 0.58 to 0.97, but for 1.03 at one size; they take eight and the rest.)
+static int coder_window(const kvc_plan_t *p, const kvc_request *reqs, int n)
+{
+    const int most = kCoderBatch;
+    if (n <= 16) return 8;
+    if (2 * (n / most) + (n % most > 0) <= (n + 7) / 8) return most;
+    long long per_head = 0, heads[2] = {0, 0};
+    for (int i = 0; i < n; ++i) per_head += chunks_per_head(reqs[i].tokens);
+    int widest = 0;
+    for (int w = 0; w < 4; ++w) {
+        long long has[2];
+        for (int is_v = 0; is_v < 2; ++is_v)
+            has[is_v] = p->has_table[is_v] ? p->width_count[is_v][w]
+                        : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k) ? (long long)p->model.layers * p->model.kv_heads : 0;
+        if (has[0] + has[1] == 0) continue;
+        widest = kWidths[w];
+        heads[0] = has[0];
+        heads[1] = has[1];
+    }
+    const long long resident = (widest == 8 ? 8ll : 16ll) * kUnits * n;                  // (times n, as the chunks)
+    for (int is_v = 0; is_v < 2; ++is_v) {
+        const long long chunks = heads[is_v] * per_head * most;
+        if (chunks > resident && 4 * chunks <= (p->has_table[is_v] ? 6 : 5) * resident) return 8;
+    }
+    return most;
 }
 
 static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
@@ -949,9 +982,10 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             KVC_TRY(launch_compress_prologue(pa, s));
         }
     }
+    const int coder_limit = coder_window(plan, reqs, n);
     for (int first = 0; first < n;) {
         int lead;
-        int end = request_window(plan, reqs, n, first, st.codec ? coder_window(n) : kQuantBatch, &lead);
+        int end = request_window(plan, reqs, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
         bool share = st.codec && share_kv(plan, reqs, first, end, lead);
         if (st.codec && st.bits_k == 8 && end - first > kSharedWindow) {
             int lead_half;
@@ -1143,7 +1177,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
-    const int coder_limit = common_widths(plan) == 2 ? kSharedWindow : coder_window(n);
+    const int coder_limit = common_widths(plan) == 2 ? kSharedWindow : coder_window(plan, dst, n);
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);

@@ -339,11 +339,14 @@ def test_rotation_beyond_the_range(ref, T, group, bits):
     check_contiguous(ref, x, bits, bits, group, group, transform=1, codec=1)
 
 
+@pytest.mark.parametrize("kw", [dict(bits_k=4, bits_v=4), dict(bits_k=4, bits_v=2), dict(bits_k=8, bits_v=3),
+                                dict(bits_k=4, bits_v=4, transform=1), dict(bits_k=2, bits_v=2, transform=2, anchor_period=16)])
 @pytest.mark.parametrize("n", [15, 16, 17, 25, 29])
-def test_many_requests_with_the_coder(ref, n):
-    """From sixteen requests on a coder window holds twelve of them: whole windows and remainders, against calls of one."""
+def test_many_requests_with_the_coder(ref, n, kw):
+    """From seventeen requests on a coder window holds twelve of them: whole windows and remainders, against calls of one.  In
+    decompressions as well where K and V have no width in common or a transform (otherwise four)."""
     lens = [int(v) for v in torch.randint(1, 300, (n,), generator=torch.Generator().manual_seed(n))]
-    plan = kvc.Plan(kvc.F16, 1, 2, 128, 4, 4, 32, 32, kvc.CODEC_HUFF8, max_tokens=300, max_batch=n)
+    plan = kvc.Plan(kvc.F16, 1, 2, 128, group_k=32, group_v=32, codec=kvc.CODEC_HUFF8, max_tokens=300, max_batch=n, **kw)
     xs = [kvgen.make_kv(700 + i, 1, 2, 128, t, torch.float16, "cuda") for i, t in enumerate(lens)]
     buf = gpu_compress(plan, [kvc.contiguous_request(x) for x in xs], lens)
     ys = [torch.zeros_like(x) for x in xs]

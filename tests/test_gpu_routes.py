@@ -186,6 +186,39 @@ def test_encoder_windows(n, want):
     assert [kv for kv, _ in encoders(found)] == [2] * -(-n // 4)                  # (8 bits: four at a time)
 
 
+@pytest.mark.parametrize("n,enc,dec", [(15, [0, 1, 0, 1], 2), (16, [0, 1, 0, 1], 2), (17, [0, 1, 0, 1], 2), (24, [0, 1, 0, 1], 2),
+                                        (25, [0, 1, 0, 1, 2], 3), (36, [0, 1] * 3, 3)])
+def test_coder_windows_of_many_requests(n, enc, dec):
+    """Eight requests a window, from seventeen on twelve; a rest of up to four shares its launch for K and V."""
+    found = launches(call_of("compress", 1, 4, 700, n=n, bits_k=4, bits_v=4, codec=1))
+    assert [kv for kv, _ in encoders(found)] == enc
+    for kw in (dict(bits_k=4, bits_v=2), dict(bits_k=4, bits_v=4, transform=1), dict(bits_k=4, bits_v=4, transform=2, anchor_period=16)):
+        found = launches(call_of("decompress", 1, 4, 700, n=n, codec=1, **kw))
+        assert sum("decode_kernel" in name for name, _, _ in found) == 2 * dec
+        found = launches(call_of("compress", 1, 4, 700, n=n, codec=1, **kw))
+        assert sum("encode_kernel" in name for name, _, _ in found) == 2 * dec
+
+
+_MIXED = dict(head_bits_k=[8, 2] * 32, head_bits_v=[2, 8] * 32)
+
+
+@pytest.mark.parametrize("kw,T,n,windows", [
+    (dict(bits_k=8, bits_v=8, transform=1), 256, 24, 2), (dict(bits_k=8, bits_v=8, transform=1), 257, 24, 3),      # 1536 and 2304 of 2048
+    (dict(bits_k=8, bits_v=8, transform=1), 385, 24, 2), (dict(bits_k=8, bits_v=8, transform=1), 257, 23, 2),      # 3072; a window less
+    (dict(bits_k=4, bits_v=4, transform=1), 640, 24, 2), (dict(bits_k=4, bits_v=4, transform=1), 641, 24, 3),      # 3840 and 4608 of 4096
+    (dict(bits_k=4, bits_v=4, transform=1), 769, 24, 2), (dict(bits_k=4, bits_v=8, transform=1), 257, 32, 4),      # 5376; V alone
+    (dict(bits_k=4, bits_v=8, transform=1), 641, 32, 3),                                                           # (K is not the widest)
+    (_MIXED, 640, 24, 2), (_MIXED, 641, 24, 3), (_MIXED, 1024, 24, 3), (_MIXED, 1025, 24, 2)])
+def test_coder_windows_with_a_small_rest(kw, T, n, windows):
+    """Requests of 64 heads: windows of twelve, but eight where the launches of twelve of the widest codes have up to a quarter more chunks
+    than are resident (16 per compute unit, at 8 bits 8), with width tables up to a half."""
+    found = launches(call_of("compress", 8, 8, T, n=n, codec=1, **kw))
+    assert sum("encode_kernel" in name for name, _, _ in found) == (4 if "head_bits_k" in kw else 2) * windows
+    if "transform" in kw:
+        found = launches(call_of("decompress", 8, 8, T, n=n, codec=1, **kw))
+        assert sum("decode_kernel" in name for name, _, _ in found) == 2 * windows
+
+
 @pytest.mark.parametrize("n", [1, 4, 5, 8])
 def test_decoder_windows(n):
     """Width tables: where K or V has a width of its own, more than four requests keep K and V apart."""
