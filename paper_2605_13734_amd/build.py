@@ -90,7 +90,7 @@ def over_budget(asm_path):
 # look-ups of their pages, as without the rotation.
 LONE_LOADS = [(r"compress_k_kernelILi\d+ELi64ELi1ELb0ELi2E", 18), (r"compress_k_kernelILi\d+ELi128ELi1ELb0ELi2E", 34),
               (r"encode_kernelILi\d+ELi64ELi1ELi0ELb0ELb0ELi\dELb1E", 24), (r"encode_kernelILi\d+ELi128ELi1ELi0ELb0ELb0ELi\dELb1E", 38),
-              (r"compress_k_kernelILi\d+ELi\d+ELi\dELb1ELi[02]E", 1),
+              (r"compress_k_kernelILi(?!8ELi128ELi1ELb1ELi2E)\d+ELi\d+ELi\dELb1ELi[02]E", 1),
               (r"encode_kernelILi\d+ELi\d+ELi\dELi[01]ELb1ELb0E", 8)]
 
 

@@ -30,7 +30,8 @@ constexpr int min_waves(int bits, int rows, int dtype, bool dense)
 // of 64 and 128 rows.
 // IN_CALL: a unit of compress_call_kernel.  There 8-bit bf16 loads stay where the compiler puts them: where all workgroups
 // are resident, requesting them together loses 3 % (groups of 32, 2^16 and 2^17 rows 11.3 -> 11.6, 19.7 -> 20.5 us), and narrower
-// ones are requested together for V as well (4 bits, 2^16 rows 10.8, K alone 11.0, both 10.5).
+// ones are requested together for V as well (4 bits, 2^16 rows 10.8, K alone 11.0, both 10.5).  Dense rotated blocks of 128 rows at 8 bits
+// stay as they are, too: from 2^21 rows on requesting them together is 3 % slower (below it was up to 9 % faster).
 template <int BITS, int G, int DT, bool DENSE, int XF, bool IN_CALL = false>
 __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg, float *xch_all)
 {
@@ -42,7 +43,7 @@ __device__ __forceinline__ void compress_k_unit(const QuantArgs &a, unsigned wg,
     u32x4 raw[P * 8];
 #pragma unroll
     for (int p = 0; p < P; ++p) load_pass<DENSE, XF == kRotation>(a.x, u.head_off, row0 + p * kPassRows, a.tokens, raw + p * 8, bad);
-    if (BITS < 8 || !IN_CALL) rows_requested<DENSE, DT, XF, P>();
+    if (BITS < 8 || !(IN_CALL || (DENSE && XF == kRotation && P == 4))) rows_requested<DENSE, DT, XF, P>();
     if (XF == kRotation) rotate_rows<DT, P * 8, false>(raw);
     if (XF == kDelta && a.anchors)
         delta_rows<DT, DENSE, P * 8>(a.x, u.head_off, row0, a.tokens, a.anchor_shift,
@@ -304,7 +305,7 @@ template <class Args> static unsigned place_call(Args &b, int run)
     return total;
 }
 
-// LDS that nothing uses and runs, as in launch_shape, for decompression calls; compression calls gain nothing from the LDS (2^21
+// LDS that nothing uses and runs, as in launch_shape, for decompression calls; most compression calls gain nothing from the LDS (2^21
 // rows, fp16, with 32000 bytes: 2 bits g64 210 and 210 us, 4 bits g64 227 and 229, 4 bits g32 230 and 224; bf16 231 and 233).
 // Call times in us, without / with runs of 16:
 //   4 bits g32  2^18 rows 27.2 26.6,  2^20 118 112;  bf16 27.4 26.8, 118 113;  2 bits g64  24.4 23.9, 91 87;  bf16 24.3 23.8, 92 85
@@ -313,7 +314,10 @@ constexpr LaunchShape kCallShape = {40000, 16};
 
 template <int G> static void compress_call(int dtype, const SmallCompressArgs &b, unsigned wgs, hipStream_t s)
 {
-#define KVC_CALL(DT, D) hipLaunchKernelGGL((compress_call_kernel<KVC_BITS, G, DT, D>), dim3(wgs), dim3(256), 0, s, b)
+    // (bf16 rows requested together, groups of 32: 2^20 rows 2 bits 108 -> 103, 4 bits 116 -> 110 us with 32000, 2^20.55 158 -> 151, 178 ->
+    // 162, which without was 174 before; 8 bits 2^20 level, 2^20.55 206 -> 199)
+    const unsigned lds = G == 32 && dtype == DT_BF16 && b.item[0].dense && wgs >= (1u << 14) ? 32000 : 0;
+#define KVC_CALL(DT, D) hipLaunchKernelGGL((compress_call_kernel<KVC_BITS, G, DT, D>), dim3(wgs), dim3(256), lds, s, b)
     if (b.item[0].dense) { if (dtype == DT_F16) KVC_CALL(DT_F16, true); else KVC_CALL(DT_BF16, true); }
     else if (dtype == DT_F16) KVC_CALL(DT_F16, false); else KVC_CALL(DT_BF16, false);
 #undef KVC_CALL

@@ -129,6 +129,12 @@ def test_bound_of_decompressions_of_many_requests(bits, lds):
         assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
 
 
+def test_bound_of_one_launch_bf16_compressions():
+    for dtype, group, T, want in ((torch.bfloat16, 32, 4064, 0), (torch.bfloat16, 32, 4096, 32000), (torch.bfloat16, 64, 4096, 0), (torch.float16, 32, 4096, 0)):
+        found = launches(call_of("compress", 32, 8, T, dtype=dtype, bits_k=4, bits_v=4, group_k=group, group_v=group))
+        assert len(found) == 1 and lds_of(found, "compress_call_kernel") == want
+
+
 @pytest.mark.parametrize("kw", [dict(transform=1), dict(transform=2, anchor_period=16)])
 def test_no_bound_with_a_transform(kw):
     for direction in ("compress", "decompress"):
