@@ -1,5 +1,7 @@
 """GPU parity at the edges of tiles, units and launches (run with -m gpu): payload bytes and
 reconstruction against the oracle, both bit for bit (the wire format fixes them)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -283,7 +285,7 @@ def test_every_code_at_extreme_scales(ref, bits, dtype):
     T, n, top = 256, 2 ** bits - 1, 65504.0
     g = torch.Generator().manual_seed(bits)
     x = torch.empty((1, 2, 2, T, 128), dtype=torch.float64)
-    scales = 2.0 ** torch.randint(-24, 9 if bits == 8 else 13, x.shape[:-2] + (T // 32, 4), generator=g).double()
+    scales = 2.0 ** torch.randint(-24, int(math.log2(top / n)) + 1, x.shape[:-2] + (T // 32, 4), generator=g).double()
     zeros = torch.randn(scales.shape, generator=g).double() * scales * 100
     zeros[..., 0, :] = top - n * scales[..., 0, :]                # the largest code meets the end of the fp16 range
     codes = torch.randint(0, n + 1, x.shape, generator=g)
@@ -360,3 +362,56 @@ def test_many_requests_with_the_coder(ref, n, kw):
         one.decompress([kvc.contiguous_request(z)], torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert torch.equal(y.view(torch.int16), z.view(torch.int16)), i
+
+
+def _pages(x, T, table):
+    """A pool that holds x, [layer, kv, head, T, 128], behind the block table."""
+    L, _, H = x.shape[:3]
+    nb = -(-T // 16)
+    rows = torch.zeros((L, 2, nb * 16, H, 128), dtype=x.dtype, device=x.device)
+    rows[:, :, :T] = x.permute(0, 1, 3, 2, 4)
+    pool = torch.empty((L, 2, nb, 16, H, 128), dtype=x.dtype, device=x.device)
+    pool[:, :, table.long()] = rows.view(L, 2, nb, 16, H, 128)
+    return pool
+
+
+@pytest.mark.parametrize("bits,group", [(2, 32), (2, 64), (3, 32), (4, 32), (4, 128), (8, 64)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("T", [16391, 40967])
+def test_paced_stores(dtype, bits, group, T):
+    """Decompression into pages with waits between the row stores (2^20 rows and more), runs of workgroups beside it and a last
+    pass that is not whole, against the contiguous one of the same payload."""
+    L, H = 8, 8
+    x = kvgen.make_kv(800 + bits, L, H, 128, T, dtype, "cuda")
+    plan = kvc.Plan(kvc.F16 if dtype == torch.float16 else kvc.BF16, L, H, 128, bits, bits, group, group, 0, max_tokens=T)
+    buf = kvc.Buffers(plan, [T])
+    stream = torch.cuda.current_stream().cuda_stream
+    buf.compress([kvc.contiguous_request(x)], stream)
+    want = torch.zeros_like(x)
+    buf.decompress([kvc.contiguous_request(want)], stream)
+    nb = -(-T // 16)
+    table = kvgen.block_table(5, nb, nb, "cuda")
+    pool = torch.zeros((L, 2, nb, 16, H, 128), dtype=dtype, device="cuda")
+    buf.decompress([kvc.paged_request(pool, table, T)], stream)
+    torch.cuda.synchronize()
+    assert int(buf.status[0]) == 0
+    assert torch.equal(pool.view(torch.int16), _pages(want, T, table).view(torch.int16))
+
+
+@pytest.mark.parametrize("bits,group_k,group_v", [(3, 32, 64), (8, 32, 128), (2, 128, 32)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_large_compressions_in_runs(dtype, bits, group_k, group_v):
+    """Dense compression gives its workgroups out in runs from 2^22 rows on: the same payload as from pages, where it does not."""
+    L, H, T = 8, 8, 65543
+    x = kvgen.make_kv(900 + bits, L, H, 128, T, dtype, "cuda")
+    plan = kvc.Plan(kvc.F16 if dtype == torch.float16 else kvc.BF16, L, H, 128, bits, bits, group_k, group_v, 0, max_tokens=T)
+    table = kvgen.block_table(6, -(-T // 16), -(-T // 16), "cuda")
+    payloads = []
+    for request in (kvc.contiguous_request(x), kvc.paged_request(_pages(x, T, table), table, T)):
+        buf = kvc.Buffers(plan, [T])
+        buf.payload.zero_()
+        buf.compress([request], torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int(buf.status[0]) == 0
+        payloads.append(buf.payload)
+    assert torch.equal(payloads[0], payloads[1])

@@ -129,8 +129,91 @@ def test_bound_of_decompressions_of_many_requests(bits, lds):
         assert lds_of(found, "decompress_k_kernel") == want and lds_of(found, "decompress_v_kernel") == want
 
 
+def decompress_shape(found, bits):
+    """(dynamic LDS, waits between the stores) of the decompressions of one width, the same for K and V."""
+    shapes = set()
+    for name, _, lds in found:
+        m = re.search(r"decompress_[kv]_kernelILi%dELi\dELb\dELi\dELb(\d)E" % bits, name)
+        if m:
+            shapes.add((lds, int(m.group(1))))
+    assert len(shapes) == 1, found
+    return shapes.pop()
+
+
+_HALF, _BF = torch.float16, torch.bfloat16
+
+
+@pytest.mark.parametrize("dtype,bits,group,lines", [
+    (_HALF, 4, 32, [(8192, 40000, 1), (32736, 40000, 1), (32768, 52000, 1), (98272, 52000, 1), (98304, 52000, 0)]),
+    (_HALF, 4, 128, [(32736, 40000, 1), (32768, 52000, 0), (98304, 52000, 0)]),
+    (_BF, 4, 64, [(32768, 52000, 1), (98304, 52000, 0)]),
+    (_HALF, 2, 64, [(10208, 52000, 1), (10240, 40000, 0), (14304, 40000, 0), (14336, 32000, 1), (98304, 40000, 0)]),
+    (_HALF, 2, 32, [(10208, 52000, 1), (10240, 32000, 1), (98304, 32000, 1)]),
+    (_BF, 2, 128, [(10240, 40000, 0), (14336, 40000, 1)]),
+    (_BF, 2, 32, [(10240, 40000, 1)]),
+    (_HALF, 3, 32, [(8160, 32000, 0), (8192, 40000, 0)]), (_BF, 3, 32, [(8160, 32000, 0), (8192, 40000, 1)]),
+    (_BF, 8, 32, [(4096, 52000, 0), (8160, 52000, 0), (8192, 52000, 1)])])
+def test_shapes_of_paged_decompressions(dtype, bits, group, lines):
+    """Both sides of every line that the type, the group and the rows (256 heads of T tokens) draw."""
+    for T, lds, paced in lines:
+        found = launches(call_of("decompress", 32, 8, T, dtype=dtype, paged=True, bits_k=bits, bits_v=bits, group_k=group, group_v=group))
+        assert decompress_shape(found, bits) == (lds, paced), T
+
+
+@pytest.mark.parametrize("dtype,bits,group,lines", [
+    (_HALF, 3, 64, [(10208, 80000), (10240, 40000), (98272, 40000), (98304, 80000)]),
+    (_HALF, 3, 32, [(10240, 80000)]), (_BF, 3, 64, [(10240, 80000)]), (_BF, 3, 128, [(10240, 40000)]),
+    (_HALF, 2, 64, [(24544, 80000), (24576, 40000), (98272, 40000), (98304, 80000)]),
+    (_HALF, 2, 32, [(24576, 80000)]), (_BF, 2, 64, [(24576, 80000)]),
+    (_HALF, 8, 32, [(8192, 80000)]), (_HALF, 4, 32, [(24544, 32000), (24576, 80000)])])
+def test_shapes_of_dense_decompressions(dtype, bits, group, lines):
+    for T, lds in lines:
+        found = launches(call_of("decompress", 32, 8, T, dtype=dtype, bits_k=bits, bits_v=bits, group_k=group, group_v=group))
+        assert decompress_shape(found, bits) == (lds, 0), T
+
+
+@pytest.mark.parametrize("paged,dtype,bits,group,lines", [
+    (False, _HALF, 2, 32, [(3040, 40000, 0), (3072, 80000, 0)]), (False, _HALF, 3, 64, [(3040, 32000, 0), (3072, 40000, 0)]),
+    (False, _BF, 2, 64, [(3072, 40000, 0)]), (False, _HALF, 4, 64, [(6112, 32000, 0), (6144, 80000, 0)]),
+    (True, _HALF, 2, 32, [(2528, 52000, 1), (2560, 40000, 0)]), (True, _BF, 2, 32, [(2560, 40000, 1)]),
+    (True, _BF, 2, 64, [(2560, 40000, 0)]), (True, _HALF, 4, 32, [(8160, 40000, 1)])])
+def test_shapes_of_decompressions_of_four_requests(paged, dtype, bits, group, lines):
+    for T, lds, paced in lines:
+        found = launches(call_of("decompress", 32, 8, T, n=4, dtype=dtype, paged=paged, bits_k=bits, bits_v=bits, group_k=group, group_v=group))
+        assert decompress_shape(found, bits) == (lds, paced), T
+
+
+def test_shapes_of_paged_decompressions_by_head():
+    """Launches over some of the heads (width tables) have no waits below 5 * 2^19 rows."""
+    tab = dict(head_bits_k=[8, 2] * 128, head_bits_v=[2, 8] * 128)
+    for T, want in ((20448, ((40000, 0), (40000, 0))), (20480, ((52000, 1), (40000, 1)))):
+        found = launches(call_of("decompress", 32, 8, T, dtype=_BF, paged=True, **tab))
+        assert (decompress_shape(found, 8), decompress_shape(found, 2)) == want
+
+
+def test_shapes_of_large_decompressions_with_a_transform():
+    def lds(T, paged=False, **kw):
+        found = launches(call_of("decompress", 32, 8, T, paged=paged, bits_v=kw["bits_k"], **kw))
+        return lds_of(found, "decompress_k_kernel"), lds_of(found, "decompress_v_kernel")
+    for paged, want in ((False, 32000), (True, 40000)):
+        assert lds(98304, paged, bits_k=8, transform=1) == (want, want) and lds(98272, paged, bits_k=8, transform=1) == (0, 0)
+        assert lds(98304, paged, bits_k=4, transform=1) == (0, 0)
+    delta = dict(bits_k=4, transform=2, anchor_period=32)
+    assert lds(16384, **delta) == (40000, 40000) and lds(16352, **delta) == (0, 0) and lds(16384, True, **delta) == (0, 0)
+    assert lds(16384, bits_k=4, transform=2, anchor_period=16) == (0, 0)
+
+
+@pytest.mark.parametrize("bits,lds", [(2, 24000), (4, 24000), (8, 32000)])
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_bound_of_paged_bf16_v_compressions(group, bits, lds):
+    """V units are one pass of few registers whatever their group."""
+    for T, want in ((6112, 0), (6144, lds)):
+        found = launches(call_of("compress", 32, 8, T, dtype=_BF, paged=True, bits_k=bits, bits_v=bits, group_k=64, group_v=group))
+        assert lds_of(found, "compress_v_kernel") == want and lds_of(found, "compress_k_kernel") == 0
+
+
 def test_bound_of_one_launch_bf16_compressions():
-    for dtype, group, T, want in ((torch.bfloat16, 32, 4064, 0), (torch.bfloat16, 32, 4096, 32000), (torch.bfloat16, 64, 4096, 0), (torch.float16, 32, 4096, 0)):
+    for dtype, group, T, want in ((_BF, 32, 4064, 0), (_BF, 32, 4096, 32000), (_BF, 64, 4096, 0), (_HALF, 32, 4096, 0)):
         found = launches(call_of("compress", 32, 8, T, dtype=dtype, bits_k=4, bits_v=4, group_k=group, group_v=group))
         assert len(found) == 1 and lds_of(found, "compress_call_kernel") == want
 
