@@ -319,6 +319,23 @@ def test_decoder_windows(n):
     assert decoders([3, 3, 3, 3], [4, 2, 4, 2]) == 3
 
 
+@pytest.mark.parametrize("paged,bits,group,n,lines", [
+    (False, 3, 64, 1, [(2432, 0), (2560, 14000), (3072, 14000)]), (False, 3, 32, 1, [(2944, 0), (3072, 40000)]),
+    (False, 2, 64, 1, [(2944, 0), (3072, 14000)]),
+    (False, 4, 64, 1, [(32640, 0), (32768, 14000), (98304, 0)]), (False, 4, 32, 1, [(32768, 0)]),
+    (False, 3, 32, 4, [(8064, 14000), (8192, 40000), (24576, 14000)]), (False, 2, 32, 4, [(8064, 0), (8192, 14000), (24576, 0)]),
+    (False, 3, 64, 4, [(24448, 40000), (24576, 14000)]), (False, 3, 128, 4, [(24576, 40000)]),
+    (True, 2, 64, 1, [(2432, 0), (2560, 14000), (32768, 14000), (98304, 0)]), (True, 2, 32, 1, [(2560, 14000), (32768, 0)]),
+    (True, 3, 64, 1, [(32640, 14000), (32768, 0)]), (True, 3, 32, 4, [(8064, 0), (8192, 14000), (24576, 0)]), (True, 4, 64, 1, [(8192, 0)])])
+def test_shapes_of_decoders(paged, bits, group, n, lines):
+    """Both sides of the lines: 256 heads of T tokens, or four requests of 64 heads, are T workgroups for K and V together, T / 2
+    for one of them (from 2^23 rows on)."""
+    for T, lds in lines:
+        layers = 32 if n == 1 else 8
+        found = launches(call_of("decompress", layers, 8, T, n=n, paged=paged, bits_k=bits, bits_v=bits, group_k=group, group_v=group, codec=1))
+        assert lds_of(found, "decode_kernel") == lds, T
+
+
 @pytest.mark.parametrize("n,T,waves", [
     (1, 8192, 4), (1, 8193, 8), (1, 16384, 8), (1, 16385, 4), (1, 20480, 4), (1, 20481, 8), (1, 32768, 8), (1, 32769, 4),
     (2, 8192, 8), (2, 8193, 4), (4, 4800, 4), (4, 6144, 4), (4, 6145, 8), (4, 8192, 8), (4, 8193, 4)])
