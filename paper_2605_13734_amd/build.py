@@ -86,12 +86,12 @@ def over_budget(asm_path):
 
 
 # (kernel symbol, most such waits): dense rows without the delta transform.  The codec-free K kernels have one at their start (the
-# head list); the encoders have seven more, behind which no row is loaded.  Rotated K blocks of 64 and 128 strided fp16 rows: the
+# head list); the encoders have nine more (tables, samples and places), behind which no row is loaded.  Rotated K blocks of 64 and 128 strided fp16 rows: the
 # look-ups of their pages, as without the rotation.
 LONE_LOADS = [(r"compress_k_kernelILi\d+ELi64ELi1ELb0ELi2E", 18), (r"compress_k_kernelILi\d+ELi128ELi1ELb0ELi2E", 34),
-              (r"encode_kernelILi\d+ELi64ELi1ELi0ELb0ELb0ELi\dELb1E", 24), (r"encode_kernelILi\d+ELi128ELi1ELi0ELb0ELb0ELi\dELb1E", 38),
+              (r"encode_kernelILi\d+ELi64ELi1ELi0ELb0ELb0ELi\dELb1E", 26), (r"encode_kernelILi\d+ELi128ELi1ELi0ELb0ELb0ELi\dELb1E", 40),
               (r"compress_k_kernelILi(?!8ELi128ELi1ELb1ELi2E)\d+ELi\d+ELi\dELb1ELi[02]E", 1),
-              (r"encode_kernelILi\d+ELi\d+ELi\dELi[01]ELb1ELb0E", 8)]
+              (r"encode_kernelILi\d+ELi\d+ELi\dELi[01]ELb1ELb0E", 10)]
 
 
 def lone_loads(asm_path):

@@ -700,6 +700,39 @@ static int shared_waves(const kvc_plan_t *p, const kvc_request *reqs, int first,
     return chunks > 8 * kUnits && chunks <= 12 * kUnits && largest <= 10 * kUnits ? 0 : 8;
 }
 
+// Whether the workgroups that build the code tables of a window's requests have no chunks of their own.  They are better apart: the
+// scan starts at the first tickets, and those who build have their chunks late.  But where the window's first launch is resident at
+// once and with them it would not be, as many workgroups would start when the first of the others end.  Compress call, fp16, 4
+// bits, groups of 32, with chunks / apart (in a launch of their own before): one request of 8 heads, 30000 tokens 55.2 / 51.7 us, 32768
+// (exactly resident) 57.4 / 68.1 (66.1), 36000 76.8 / 72.7; four of 8192 56.6 / 63.5, of 24000 132.7 / 122.7, 32 of 256 heads and 512 to
+// 2048 tokens 1448 / 1348 (1365); 8 bits, 12288 tokens 58.9 / 53.7, 16384 64.2 / 74.9, 20000 85.3 / 80.3; groups of 128, 16384 tokens
+// 45.3 / 54.1, 32768 79.1 / 74.9; half of the heads at 2 bits, half at 8, 64 heads of 8192 166.9 / 162.3.
+static bool builders_apart(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, bool share, int waves, bool dense)
+{
+    int tables = 0, bits = 0;                            // of the first launch (K): its width and heads
+    long long heads = 0;
+    for (int is_v = 0; is_v < 2; ++is_v)
+        for (int w = 0; w < 4; ++w) {
+            const long long has = p->has_table[is_v] ? p->width_count[is_v][w]
+                                  : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k) ? (long long)p->model.layers * p->model.kv_heads : 0;
+            if (has == 0) continue;
+            if (tables++ > 0) continue;
+            bits = kWidths[w];
+            heads = has;
+        }
+    const int nw = waves ? waves : enc_waves(bits), builders = tables * kCandidates;
+    long long wgs = 0;
+    for (int i = first; i < end; ++i) {
+        const long long w = ((share ? 2 : 1) * heads * chunks_per_head(reqs[i].tokens) + nw - 1) / nw;
+        if (w < builders) return true;                   // (not enough of them)
+        wgs += w;
+    }
+    // waves of a compute unit: 16 KB of LDS each at 8 bits, otherwise what the registers leave room for
+    const int unit = p->strat.group_k == 128 ? (p->model.dtype == KVC_BF16 && !dense ? 4 : 8) : bits == 8 ? 8 : p->strat.group_k == 64 ? 12 : 16;
+    const long long resident = (long long)kUnits * unit / nw;
+    return wgs > resident || wgs + (long long)(end - first) * builders <= resident;
+}
+
 // K and V of the first n requests of a window as one batch
 static CoderBatch coder_batch_both(const CoderLaunch cl[][kTableSlots], int n)
 {
@@ -707,6 +740,7 @@ static CoderBatch coder_batch_both(const CoderLaunch cl[][kTableSlots], int n)
     memset(&b, 0, sizeof b);
     for (int k = 0; k < 2 * n; ++k) b.item[k] = cl[k / 2][k & 1].a;
     b.n = 2 * n;
+    b.front = (unsigned)b.item[0].apart;
     return b;
 }
 
@@ -717,12 +751,13 @@ static CoderBatch coder_batch(const CoderLaunch cl[][kTableSlots], int n, int j)
     memset(&b, 0, sizeof b);
     for (int k = 0; k < n; ++k) b.item[k] = cl[k][j].a;
     b.n = n;
+    b.front = j == 0 ? (unsigned)b.item[0].apart : 0;       // (the tables of all launches are built in the first)
     return b;
 }
 
 static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *payload, const Geometry &g, uint8_t *ws,
                           long long capacity, uint64_t *out_bytes, int *status, bool compress, const uint8_t *dev_tables,
-                          CoderLaunch out[kTableSlots], int waves = 0)
+                          CoderLaunch out[kTableSlots], int waves = 0, bool apart = false)
 {
     const bool any_table = table_slots(p) == kTableSlots;
     const long long LH = (long long)p->model.layers * p->model.kv_heads, cph = chunks_per_head(r->tokens);
@@ -740,6 +775,7 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     base.ws.ticket = (uint32_t *)(ws + ticket_offset(p));
     base.ws.state = (unsigned long long *)(ws + p->ws_state_off);
     base.out_bytes = (unsigned long long *)out_bytes;
+    base.slots = table_slots(p) << 8;
     int n = 0;
     long long chunk_at = 0, wg_at = 0, k_wgs = 0;
     for (int is_v = 0; is_v < 2; ++is_v) {
@@ -763,6 +799,7 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
             L.group = group;
             L.a.is_v = is_v;
             L.a.tab = any_table ? 4 * is_v + w : is_v;
+            base.slots |= 1 << L.a.tab;
             L.a.chunks = heads * cph;
             L.a.chunk_base = chunk_at;
             L.a.wg_base = wg_at;
@@ -775,6 +812,9 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     for (int i = 0; i < n; ++i) {
         out[i].a.k_wgs = k_wgs;
         out[i].a.total_wgs = wg_at;
+        out[i].a.slots = base.slots;
+        out[i].a.builders = compress ? n * kCandidates : 0;       // (a launch has a table of its own)
+        out[i].a.apart = apart ? out[i].a.builders : 0;
     }
     return n;
 }
@@ -848,12 +888,12 @@ static void prologue_item(const kvc_plan_t *plan, const kvc_request *r, uint8_t 
         it.write_total = 1;
         return;
     }
-    // ticket and scan state start from zero
+    // candidate tables, ticket and scan state start from zero
     CoderLaunch cl[kTableSlots];
     coder_launches(plan, r, payload, g, ws, 0, nullptr, status, true, (const uint8_t *)workspace, cl);
     const CoderArgs &c = cl[0].a;              // (a request has at least one K and one V launch)
-    it.zero = c.ws.ticket;
-    it.zero_words = 64 + 2 * c.total_wgs + 2;
+    it.zero = (uint32_t *)candidate_tables(c.ws.ticket, table_slots(plan) - 1);
+    it.zero_words = (c.ws.ticket - it.zero) + 64 + 2 * c.total_wgs + 2;
     if (c.total_chunks == 0) {
         // empty request: no workgroup runs that could close the directory and header
         put64((uint8_t *)it.header.w + 40, (uint64_t)g.off_codes_k);
@@ -864,7 +904,7 @@ static void prologue_item(const kvc_plan_t *plan, const kvc_request *r, uint8_t 
     }
 }
 
-// Set-up of all requests of a call with the coder: prologues and table samples, then the code tables.
+// Set-up of all requests of a call with the coder: prologues and table samples (the first encoder launch builds the tables).
 static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t n, void *payload, const uint64_t *payload_off,
                        uint64_t *out_bytes, int32_t *dev_status, void *workspace, hipStream_t s)
 {
@@ -874,9 +914,7 @@ static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
     SetupArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.heads = plan->model.kv_heads;
-    BuildArgs ba;
-    memset(&ba, 0, sizeof ba);
-    ba.slots = table_slots(plan);
+    const bool all_slots = table_slots(plan) == kTableSlots;
     for (int is_v = 0; is_v < 2; ++is_v) {
         const int *list = plan->has_table[is_v] ? (const int *)((const uint8_t *)workspace + t.head_list[is_v]) : nullptr;
         for (int w = 0; w < 4; ++w) {
@@ -888,7 +926,7 @@ static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             tab.head_list = list;
             if (list) list += heads;
             tab.heads_covered = (int)heads;
-            tab.slot = ba.slots == kTableSlots ? 4 * is_v + w : is_v;
+            tab.slot = all_slots ? 4 * is_v + w : is_v;
             tab.is_v = is_v;
             tab.bits = kWidths[w];
             tab.group = is_v ? st.group_v : st.group_k;
@@ -898,7 +936,6 @@ static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                 tab.anchor_shift = 0;
                 while ((1 << tab.anchor_shift) < st.anchor_period) ++tab.anchor_shift;
             }
-            ba.slot_mask |= 1 << tab.slot;
         }
     }
     for (int first = 0; first < n; first += kSetupBatch) {
@@ -915,19 +952,6 @@ static int coder_setup(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             it.sample = (uint16_t *)ws;
         }
         KVC_TRY(launch_setup(plan->model.dtype, sa, s));
-    }
-    for (int first = 0; first < n; first += kBuildBatch) {
-        ba.n = n - first < kBuildBatch ? n - first : kBuildBatch;
-        for (int j = 0; j < ba.n; ++j) {
-            const int i = first + j;
-            Geometry g;
-            geometry(plan, reqs[i].tokens, &g);
-            uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
-            ba.item[j].sample = (const uint16_t *)ws;
-            ba.item[j].lut = (uint16_t *)(ws + lut_offset(plan));
-            ba.item[j].lengths = (uint8_t *)payload + payload_off[i] + g.off_aux;
-        }
-        KVC_TRY(launch_build_tables(ba, s));
     }
     return KVC_OK;
 }
@@ -1010,6 +1034,7 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             CoderLaunch cl[kCoderBatch][kTableSlots];
             int launches = 0;
             const int waves = share ? shared_waves(plan, reqs, first, end) : 0;
+            const bool apart = builders_apart(plan, reqs, first, end, share, waves, dense_layout(&reqs[lead]));
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);
                 Geometry g;
@@ -1017,7 +1042,7 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                 uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
                 launches = coder_launches(plan, &reqs[i], (uint8_t *)payload + payload_off[i], g, ws,
                                           (long long)(payload_off[i + 1] - payload_off[i]), out_bytes + i, dev_status + i, true,
-                                          (const uint8_t *)workspace, cl[k], waves);
+                                          (const uint8_t *)workspace, cl[k], waves, apart);
             }
             marks.window(first, end, 1);
             if (share) {

@@ -13,8 +13,8 @@
 // Decoding mirrors it: body -> LDS, every lane decodes one sub-block with a 4096-entry
 // table, the packed rows are rebuilt in LDS and dequantized from there.
 //
-// The kernels live in three sources: kvc_huff_tables.hip (table sample, code construction,
-// decode tables), kvc_huff_enc.hip and kvc_huff_dec.hip (compiled once per code width, KVC_BITS).
+// The kernels live in three sources: kvc_huff_tables.hip (table sample, decode tables), kvc_huff_enc.hip (with
+// kvc_huff_build.h, the code construction) and kvc_huff_dec.hip (compiled once per code width, KVC_BITS).
 #pragma once
 
 #include "kvc_internal.h"

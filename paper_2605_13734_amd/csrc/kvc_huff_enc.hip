@@ -1,8 +1,9 @@
-// Lossless stage, encoder: quantize + pack + Huffman-code one chunk per wave and place the body
+// Lossless stage, encoder: build the code tables, quantize + pack + Huffman-code one chunk per wave and place the body
 // through a single-pass prefix sum over workgroups.  Compiled once per code width (-DKVC_BITS=2, 3,
 // 4 or 8).  See kvc_huff.h for the format and the division of work, kvc_scan.h for
-// the prefix sum.
+// the prefix sum, kvc_huff_build.h for the tables.
 
+#include "kvc_huff_build.h"
 #include "kvc_scan.h"
 
 #ifndef KVC_BITS
@@ -15,10 +16,73 @@ namespace kvc {
 
 // Encoder tables in LDS: code lengths as bytes, and code | length << 12 as 16-bit entries
 // (narrow entries keep the hot byte values of a section in distinct banks).
-struct EncTables {
+struct __attribute__((aligned(8))) EncTables {
     uint8_t len[256];
     uint16_t code[256];
 };
+
+// two symbols of a code table (a word of CandidateTables)
+__device__ __forceinline__ void put_entries(EncTables &t, int word, uint32_t e)
+{
+    ((uint32_t *)t.code)[word] = e;
+    ((uint16_t *)t.len)[word] = (uint16_t)(((e >> 12) & 15u) | (e >> 28 << 8));
+}
+
+template <bool CACHED = false> __device__ __forceinline__ uint32_t table_word(const uint32_t *p)
+{
+    return CACHED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                  : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The code table of the launch to LDS, by one wave, if it has been built: the candidate with the fewest halvings that meets the
+// length limit.  Returns its number, or -1 while it is not there (the same in all lanes).  CACHED: the entries may come from L2, where
+// they are for all but the first workgroups of an XCD; what L2 may have instead, zeros from before they were built, shows.
+template <bool CACHED> __device__ __forceinline__ int fetch_table(const CandidateTables *tables, EncTables &t)
+{
+    const int lane = lane_id();
+    const uint32_t state = lane < kCandidates ? table_word(&tables->state[lane]) : 0;
+    const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(state != kTooLong));
+    if (__builtin_amdgcn_readlane((int)state, pick) == 0) return -1;
+    const uint32_t e0 = table_word<CACHED>(tables->entry[pick] + lane), e1 = table_word<CACHED>(tables->entry[pick] + 64 + lane);
+    if (__builtin_amdgcn_ballot_w64(e0 == 0 || e1 == 0) != 0) return -1;
+    put_entries(t, lane, e0);
+    put_entries(t, 64 + lane, e1);
+    return pick;
+}
+
+// The state of a workgroup's table in LDS.
+constexpr uint32_t kNobody = 0, kFetching = 1, kThere = 2, kGivenUp = 3;
+
+// Waits for the code table: the first wave of the workgroup to need it polls for it, the others wait at an LDS word (four
+// thousand waves asking for the same lines of memory would take turns).  Returns whether it is there.
+// The workgroups that build the tables have earlier tickets, so they are running, and they wait for nobody: the wait
+// ends; it is bounded all the same.
+__device__ __forceinline__ bool wait_for_table(const CoderArgs &a, EncTables &t, uint32_t *state, int &pick)
+{
+    uint32_t now = kNobody;
+    if (lane_id() == 0) now = atomicCAS(state, kNobody, kFetching);
+    now = (uint32_t)__builtin_amdgcn_readfirstlane((int)now);
+    if (now == kNobody) {
+        const CandidateTables *tables = candidate_tables(a.ws.ticket, a.tab);
+        now = kThere;
+        for (int spins = 1; (pick = fetch_table<false>(tables, t)) < 0; ++spins) {
+            if ((spins & (kSpinCheck - 1)) == 0 && (spins > kSpinLimit || scan_failed(a))) {
+                give_up(a);
+                now = kGivenUp;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(4);
+        }
+        wave_sync();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane_id() == 0) __hip_atomic_store(state, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return now == kThere;
+    }
+    // (the fetching wave always ends: it finds the table or its limit)
+    while ((now = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) == kFetching) __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    return now == kThere;
+}
 
 // bit count of HALF (0 or 1) of the lane's sub-block
 template <int W> __device__ __forceinline__ uint32_t half_bits(const uint32_t *sym, const EncTables &t, int half)
@@ -107,13 +171,15 @@ void encode_kernel(CoderBatch batch)
     using Geo = ChunkGeom<BITS>;
     constexpr int W = Geo::kWords, XF = ROTATION ? kRotation : DELTA ? kDelta : kNoTransform;
     constexpr int kItems = KV == 2 ? 2 : 1;                      // items per request
-    unsigned wg;
-    const int item = kItems * place_item(batch.at, blockIdx.x, wg);
+    // the places of the workgroups that only build tables come first, so that those of all requests start early
+    const unsigned front = (unsigned)batch.n * batch.front;
+    unsigned wg = 0;
+    const int item = kItems * (blockIdx.x < front ? (int)(blockIdx.x / batch.front) : place_item(batch.at, blockIdx.x - front, wg));
     const CoderArgs &first = batch.item[item];
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Geo::kLds];
     __shared__ EncTables enc;
     __shared__ uint32_t s_units[NW];
-    __shared__ uint32_t s_ticket, s_sum, s_reported;
+    __shared__ uint32_t s_ticket, s_sum, s_reported, s_table;
     __shared__ unsigned long long s_excl;
 
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
@@ -122,28 +188,30 @@ void encode_kernel(CoderBatch batch)
         s_sum = s_reported = 0;
         s_excl = 0;
     }
-    // the candidate with the fewest halvings that meets the length limit (two short loads one after the
-    // other, in the time the ticket takes)
-    int pick = 0;
-    auto load_table = [&](const CoderArgs &a) {
-        const CandidateTables *tables = candidate_tables(a.ws.lut, a.tab);
-        const uint32_t complete = lane < kCandidates ? tables->complete[lane] : 0;
-        pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(complete != 0) | (1ull << (kCandidates - 1)));
-        for (int k = tid; k < 256; k += NW * 64) {
-            const uint16_t e = tables->entry[pick][k];
-            enc.len[k] = (uint8_t)(e >> 12);
-            enc.code[k] = e;
-        }
+    // The table, if it has been built already, in the time the ticket takes (both tensors in one launch: the workgroup's
+    // number says which of them it most likely has, its ticket which it has).
+    int second = KV == 2 && wg >= first.k_wgs ? 1 : 0, pick = -1;
+    if (wave == 0) {
+        const CoderArgs &a = batch.item[item + second];
+        pick = fetch_table<true>(candidate_tables(a.ws.ticket, a.tab), enc);
+        if (lane == 0) s_table = pick < 0 ? kNobody : kThere;
+    }
+    __syncthreads();
+    // global order over table, K and V workgroups (the same in all lanes)
+    const unsigned taken = (unsigned)__builtin_amdgcn_readfirstlane((int)s_ticket);
+    if (taken < (unsigned)first.builders) {
+        static_assert(sizeof(BuildLds) <= NW * Geo::kLds, "the construction uses the LDS of the chunks");
+        build_table<NW * 64>(first, (int)taken, *(BuildLds *)lds_all);
+        if (taken < (unsigned)first.apart) return;
         __syncthreads();
-    };
-    // (both tensors in one launch: the workgroup's number says which it most likely is, its ticket which it is)
-    int second = KV == 2 && wg >= first.k_wgs ? 1 : 0;
-    load_table(batch.item[item + second]);
-    const long long ticket = (unsigned)__builtin_amdgcn_readfirstlane((int)s_ticket);     // global order over K and V workgroups (the same in all lanes)
+    }
+    const long long ticket = (long long)(taken - (unsigned)first.apart);
     if (KV == 2 && second != (ticket >= first.k_wgs ? 1 : 0)) {
         second = 1 - second;
+        __syncthreads();                                         // (no wave is left that may look at the other tensor's)
+        if (tid == 0) s_table = kNobody;
+        pick = -1;
         __syncthreads();
-        load_table(batch.item[item + second]);
     }
     const CoderArgs &a = batch.item[item + second];
     const long long chunk = (ticket - a.wg_base) * NW + wave;
@@ -158,9 +226,6 @@ void encode_kernel(CoderBatch batch)
         before = *(const volatile unsigned long long *)scan_carry(a);
         asm volatile("" : "+v"(before));
     }
-    // the table's lengths in the payload, unless the construction without halvings has written them already
-    if (pick != 0 && ticket == a.wg_base)
-        for (int k = tid; k < 256; k += NW * 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
 
     // the wave's chunk size is known; the last wave of the workgroup to say so passes the sum on
     int last_to_report = 0;
@@ -176,7 +241,7 @@ void encode_kernel(CoderBatch batch)
         __hip_atomic_store(&a.ws.state[ticket], kFlagSize | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     uint32_t body_units = 0;      // body size in 16-byte units
-    bool coded = false;
+    bool coded = false, coding = false;
     int rows = 0;
     uint32_t sym[W];
     if (live) {
@@ -187,8 +252,13 @@ void encode_kernel(CoderBatch batch)
         else quantize_chunk<BITS, G, DT, false, DENSE, XF>(a.q, c, lds, bad);
         if (bad) atomicOr(a.q.status, KVC_DEV_BAD_BLOCK);
         wave_sync();
+        coding = wait_for_table(a, enc, &s_table, pick);
+        // the table's lengths in the payload, unless the construction without halvings has written them already (by the wave that
+        // brought the table)
+        if (pick > 0 && ticket == a.wg_base)
+            for (int k = lane; k < 256; k += 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
         load_sub<BITS>(lds, sym);
-        const int have = min(max(rows - 2 * lane, 0), 2);        // valid rows of this sub-block
+        const int have = coding ? min(max(rows - 2 * lane, 0), 2) : 0;        // valid rows of this sub-block
         uint32_t bits0 = 0, bits = 0;
         if (have > 0) bits0 = half_bits<W>(sym, enc, 0);
         bits = bits0;
@@ -242,7 +312,7 @@ void encode_kernel(CoderBatch batch)
         while (((excl = __hip_atomic_load(&s_excl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) >> 62) != 2) __builtin_amdgcn_s_sleep(1);
     }
     excl &= kValueMask;
-    if (excl == kNoPlace || !live) return;
+    if (excl == kNoPlace || !coding) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // (the sizes of the other waves are older than the prefix)
     unsigned long long mine = excl;
     for (int w = 0; w < wave; ++w) mine += s_units[w];
@@ -293,8 +363,9 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
         need += KV == 2 ? (unsigned)b.item[2 * i].total_wgs : (unsigned)((b.item[i].chunks + NW - 1) / NW);
     }
     close_places(placed.at, placed.n, need, 0);
-    if (need == 0) return KVC_OK;
-    const dim3 grid(need), block(NW * 64);
+    const unsigned front = placed.front * (unsigned)placed.n;
+    if (front + need == 0) return KVC_OK;
+    const dim3 grid(front + need), block(NW * 64);
     const unsigned lds = encode_hold(BITS, G, KV == 1, a.q.rotate != 0, need);
 #define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, lds, s, placed)
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a

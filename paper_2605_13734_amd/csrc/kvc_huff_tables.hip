@@ -1,5 +1,5 @@
-// Lossless stage, set-up kernels: the call's prologue and the table samples (byte counts of up to 16 chunks per section),
-// the code construction (Huffman lengths, canonical codes) and the decode tables.  See kvc_huff.h.
+// Lossless stage, set-up kernels: the call's prologue and the table samples (byte counts of up to 16 chunks per section), and the
+// decode tables.  See kvc_huff.h; the code construction is in kvc_huff_build.h, a part of the encoder.
 
 #include "kvc_huff.h"
 
@@ -124,8 +124,7 @@ __device__ __forceinline__ void sample_chunk(const SetupArgs &a, const SetupItem
 // Everything of a compress call with the coder that depends on nothing: grid = (kSampleChunks workgroups per
 // table, then the slices of the zero fills; requests).  The sample leaves its counts chunk by chunk, so
 // that no histogram has to be cleared first.  One request: 7 us, where a prologue, a K and a V sample in
-// a launch each took 17 us; with the build behind it for all requests of the call at once, the set-up
-// of 32 requests takes 52 us instead of 134 us (four windows of two samples and a build).
+// a launch each took 17 us.  The encoder builds the tables from the counts (kvc_huff_build.h).
 template <int DT> __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
 {
     const SetupItem &it = a.item[blockIdx.y];
@@ -135,202 +134,6 @@ template <int DT> __global__ __launch_bounds__(256) void setup_kernel(SetupArgs 
         return;
     }
     sample_chunk<DT>(a, it, a.table[blockIdx.x / kSampleChunks], (int)(blockIdx.x % kSampleChunks));
-}
-
-// ---- code construction ----------------------------------------------------------------------------
-
-constexpr uint32_t kNone = 1u << 28;           // a queue entry that does not exist: above every weight, and two of them still add up
-constexpr int kWeightBits = 19;                // weights are below 2^19 (a table sample is at most 16 chunks of 16 KB)
-
-struct BuildLds {
-    uint32_t key[256];             // weight << 8 | symbol
-    uint32_t sw[512];              // leaf weights by (weight, symbol): the first queue, then kNone
-    uint32_t wi[512];              // weights of the joined nodes in order of creation, the second queue, then kNone
-    uint16_t parent_leaf[256];     // by queue position: the joined node above the leaf
-    uint16_t parent_int[256];      // by joined node: the joined node above it
-};
-
-// bits << 1, with a one at the bottom if a < b (both below 2^31): the sign of the difference is shifted in,
-// without the wait states between a compare and the use of its mask
-__device__ __forceinline__ uint32_t push_less(uint32_t bits, uint32_t a, uint32_t b)
-{
-    return __builtin_amdgcn_alignbit(bits, a - b, 31);
-}
-
-// How many of the queue entries q[0], q[1], ... weigh less than `w`: N entries at once, STEP apart, per
-// level.  The queues end in entries above every weight, and a round's counts are below 64, or at
-// most 256 (`wide`), so no index needs a check.
-template <int N, int STEP> __device__ __forceinline__ void search_level(const uint32_t *q, uint32_t w, int &below)
-{
-    uint32_t x[N], less = 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = q[below + (i + 1) * STEP - 1];
-#pragma unroll
-    for (int i = 0; i < N; ++i) less = push_less(less, x[i], w);
-    below += __builtin_popcount(less) * STEP;
-}
-
-// Huffman's algorithm over 256 symbols, always joining the two nodes with the smallest (weight, id):
-// leaves have id = symbol, the k-th joined node has id 256 + k.  Leaves sorted by (weight, symbol)
-// form one queue, joined nodes (created in non-decreasing weight order) the other.
-//
-// The joins are made in rounds by one wave.  With s the sum of the two smallest weights present, every
-// node of weight <= s is joined before any node that does not exist yet: a later node weighs at least
-// s and has a higher id.  So all nodes of weight <= s, merged from the two queues (a leaf before a joined
-// node of the same weight), are joined pair by pair in that order; an odd one out waits for the next
-// round.  The weights of a round span a factor of two, so a code takes about as many rounds as it
-// has lengths (8 to 24), and a round is a search for every node's place in the other queue (two LDS
-// round trips, eight ways each).  One join after the other, an LDS round trip each, this kernel
-// took 37 us per call, 55 us for eight requests together; now 15.5 us for either, of which 11 rounds
-// take 8 us and the sort 3 us (bound by the LDS reads of the keys).
-__device__ __forceinline__ void join_rounds(BuildLds &s)
-{
-    const int lane = lane_id();
-    int lo = 0, jo = 0, made = 0;              // leaves and joined nodes already used, joined nodes made
-    for (int round = 0; round < 255 && made < 255; ++round) {      // (a round makes one join at least)
-        const uint32_t *leaves = s.sw + lo, *joined = s.wi + jo;
-        uint32_t wl = leaves[lane], wj = joined[lane];
-        const uint32_t a0 = __builtin_amdgcn_readlane(wl, 0), a1 = __builtin_amdgcn_readlane(wl, 1);
-        const uint32_t b0 = __builtin_amdgcn_readlane(wj, 0), b1 = __builtin_amdgcn_readlane(wj, 1);
-        const uint32_t sum = min(min(a0 + a1, a0 + b0), b0 + b1);
-        int nl = __builtin_popcountll(__builtin_amdgcn_ballot_w64(wl <= sum));      // nodes of weight <= sum in the two queues
-        int ni = __builtin_popcountll(__builtin_amdgcn_ballot_w64(wj <= sum));
-        const bool wide = nl == 64 || ni == 64;
-        if (wide) {
-#pragma unroll
-            for (int first = 64; first < 256; first += 64) {
-                nl += __builtin_popcountll(__builtin_amdgcn_ballot_w64(leaves[first + lane] <= sum));
-                ni += __builtin_popcountll(__builtin_amdgcn_ballot_w64(joined[first + lane] <= sum));
-            }
-        }
-        const int most = nl > ni ? nl : ni, used = (nl + ni) & ~1;
-        bool leaf_left = false;
-        for (int first = 0; first < most; first += 64) {
-            const int e = first + lane;
-            if (first > 0) {
-                wl = leaves[e];
-                wj = joined[e];
-            }
-            wl = e < nl ? wl : 0;              // (nothing weighs less: an idle lane's search stays at the front)
-            wj = e < ni ? wj : 0;
-            int below_l = 0, below_i = 0;      // joined nodes before the leaf; leaves before the joined node
-            if (wide) {
-                search_level<4, 64>(joined, wl, below_l);
-                search_level<4, 64>(leaves, wj + 1, below_i);
-            }
-            if (most > 7) {
-                search_level<7, 8>(joined, wl, below_l);
-                search_level<7, 8>(leaves, wj + 1, below_i);
-            }
-            search_level<7, 1>(joined, wl, below_l);
-            search_level<7, 1>(leaves, wj + 1, below_i);
-            const int rank_l = e + below_l, rank_i = e + below_i;
-            // the first of a pair finds its partner, the next node of the merged order, and makes the joined node
-            // (a weight of `sum` or more, behind everything that this round looks for)
-            const uint32_t after_l = min(leaves[e + 1], joined[below_l]), after_i = min(leaves[below_i], joined[e + 1]);
-            if (e < nl && rank_l < used) {
-                s.parent_leaf[lo + e] = (uint16_t)(made + (rank_l >> 1));
-                if (!(rank_l & 1)) s.wi[made + (rank_l >> 1)] = wl + after_l;
-            }
-            if (e < ni && rank_i < used) {
-                s.parent_int[jo + e] = (uint16_t)(made + (rank_i >> 1));
-                if (!(rank_i & 1)) s.wi[made + (rank_i >> 1)] = wj + after_i;
-            }
-            leaf_left |= __builtin_amdgcn_ballot_w64(e < nl && rank_l >= used) != 0;
-        }
-        wave_sync();
-        const int odd = (nl + ni) & 1;
-        lo += nl - (odd && leaf_left ? 1 : 0);
-        jo += ni - (odd && !leaf_left ? 1 : 0);
-        made += used >> 1;
-    }
-}
-
-// One construction of code lengths, by a workgroup of 256 threads with one symbol of weight w each:
-// returns the symbol's length.
-__device__ __forceinline__ int build_once(BuildLds &s, uint32_t w)
-{
-    const int tid = threadIdx.x;
-    const uint32_t key = (w << 8) | (uint32_t)tid;
-    s.key[tid] = key;
-    s.wi[tid] = s.wi[256 + tid] = s.sw[256 + tid] = kNone;
-    __syncthreads();
-    // position of the thread's leaf among all leaves
-    int pos = 0;
-#pragma unroll 2
-    for (int t = 0; t < 256; t += 32) {
-        uint32_t less = 0;
-#pragma unroll
-        for (int i = 0; i < 32; i += 4) {
-            const u32x4 k = *(const u32x4 *)(s.key + t + i);
-            less = push_less(push_less(push_less(push_less(less, k[0], key), k[1], key), k[2], key), k[3], key);
-        }
-        pos += __builtin_popcount(less);
-    }
-    s.sw[pos] = w;
-    __syncthreads();
-    if (tid < 64) join_rounds(s);
-    __syncthreads();
-    int d = 1;
-    for (int i = s.parent_leaf[pos]; i != 254 && d < 256; i = s.parent_int[i]) ++d;
-    return d;
-}
-
-// The format's length limit: while the longest code exceeds kMaxLen all weights are halved (rounded
-// up) and the construction is repeated.  k halvings turn a weight w into ceil(w / 2^k), so the
-// constructions do not depend on each other: all of them run side by side, one workgroup each, every
-// one that meets the limit leaves a complete table, and the encoder takes the one with the fewest
-// halvings.  (Groups along 128 tokens or channels give strongly peaked codes that need
-// five or six halvings.)
-// Ten halvings are always enough: a code of 13 bits needs weights that add up to Fibonacci(15) = 610 or
-// more (every weight being 1 or more), and a sample of 2^18 bytes plus one per symbol, halved ten times,
-// adds up to less than (2^18 + 256) / 1024 + 256 = 513.
-static_assert(kWeightBits >= 19 && (1 << 18) + 256 < (1 << kWeightBits), "sample weights");
-
-__device__ __forceinline__ uint32_t halved(uint32_t w, int k) { return (w + ((1u << k) - 1u)) >> k; }
-
-// grid = kCandidates workgroups of 256 threads (one symbol each) per table slot of the format.
-__global__ __launch_bounds__(256) void build_tables_kernel(BuildArgs a)
-{
-    const BuildItem &it = a.item[blockIdx.y];
-    const int sec = blockIdx.x / kCandidates, k = blockIdx.x - sec * kCandidates;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
-    if (!((a.slot_mask >> sec) & 1)) {                 // a width the tensor does not use: an empty table
-        if (k == 0) it.lengths[256 * sec + tid] = 0;
-        return;
-    }
-    __shared__ __attribute__((aligned(16))) BuildLds s;
-    __shared__ uint32_t block_count[4][16];            // symbols of each length in each block of 64 symbols
-    uint32_t count = 0;
-#pragma unroll
-    for (int i = 0; i < kSampleChunks; ++i) count += it.sample[(sec * kSampleChunks + i) * 256 + tid];
-    const int L = build_once(s, halved(min(count, 1u << 18) + 1, k));
-    CandidateTables *out = candidate_tables(it.lut, sec);
-    const int too_long = __syncthreads_or(L > kMaxLen);
-    if (tid == 0) out->complete[k] = too_long ? 0 : 1;
-    if (too_long) return;
-    // canonical codes: first code of every length, and the symbol's place among the symbols of
-    // its length (those of lower blocks, then the lower lanes of its own block)
-    int within = 0;
-#pragma unroll
-    for (int l = 1; l <= kMaxLen; ++l) {
-        const unsigned long long same = __builtin_amdgcn_ballot_w64(L == l);
-        if (lane == 0) block_count[wave][l] = (uint32_t)__builtin_popcountll(same);
-        if (L == l) within = __builtin_popcountll(same & ((1ull << lane) - 1));
-    }
-    __syncthreads();
-    uint32_t next = 0, first = 0;
-#pragma unroll
-    for (int l = 1; l <= kMaxLen; ++l) {
-        if (L == l) first = next;
-        next = (next + block_count[0][l] + block_count[1][l] + block_count[2][l] + block_count[3][l]) << 1;
-    }
-    uint32_t rank = (uint32_t)within;
-    for (int w = 0; w < wave; ++w) rank += block_count[w][L];
-    out->entry[k][tid] = (uint16_t)((first + rank) | ((uint32_t)L << 12));
-    // no halving is the usual pick (and the only one of an empty request); the encoder's first workgroup
-    // writes the lengths of any other
-    if (k == 0) it.lengths[256 * sec + tid] = (uint8_t)L;
 }
 
 // ---- set-up of a decompress call with the coder ---------------------------------------------------
@@ -422,12 +225,6 @@ int launch_setup(int dtype, const SetupArgs &a, hipStream_t s)
     const dim3 grid((unsigned)a.tables * kSampleChunks + fill_slices(most), (unsigned)a.n);
     if (dtype == DT_F16) hipLaunchKernelGGL(setup_kernel<DT_F16>, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(setup_kernel<DT_BF16>, grid, dim3(256), 0, s, a);
-    return launched();
-}
-
-int launch_build_tables(const BuildArgs &a, hipStream_t s)
-{
-    hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)(a.slots * kCandidates), (unsigned)a.n), dim3(256), 0, s, a);
     return launched();
 }
 

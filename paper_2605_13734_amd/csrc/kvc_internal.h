@@ -134,7 +134,7 @@ struct PrologueItem {
     int pad_words[2];
     const uint32_t *aux_src;        // device image of the width tables, copied to payload + aux_off
     long long aux_off, aux_words;
-    uint32_t *zero;                 // coder scratch that starts from zero: ticket and scan state
+    uint32_t *zero;                 // coder scratch that starts from zero: candidate tables, ticket and scan state
     long long zero_words;
     unsigned long long *out_bytes;  // the request's size word
     unsigned long long total;
@@ -150,7 +150,7 @@ struct PrologueArgs {
 static_assert(sizeof(PrologueArgs) <= 4000, "kernel arguments are limited to 4 KB");
 
 // The request's status word and header, the zero padding between the parts of the payload, the width
-// tables (copied from their device image), the coder's work-order counter and scan state, and whatever the
+// tables (copied from their device image), the coder's candidate tables, work-order counter and scan state, and whatever the
 // host already knows of the result (the payload size without the coder; the closed directory of an empty
 // request).  By `step` threads together, the calling one being number `first`.
 __device__ __forceinline__ void write_prologue(const PrologueItem &it, long long first, long long step)
@@ -229,23 +229,28 @@ constexpr int kSampleChunks = 16;
 // Per-request scratch inside the caller's workspace (device memory).
 struct CoderScratch {
     uint16_t *sample;           // [slots][kSampleChunks][256] byte counts of the sample chunks
-    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol << 8 | (256 - length); while compressing, the
-                                // candidates for the slot's code table (CandidateTables)
+    uint16_t *lut;              // [kTableSlots][4096] decode table: symbol << 8 | (256 - length); while compressing, its end holds
+                                // the candidates for the slots' code tables (CandidateTables)
     unsigned long long *state;  // scan state, one word per encode workgroup (in launch order)
-    uint32_t *ticket;           // work-order counter
+    uint32_t *ticket;           // work-order counter, right behind `lut`
 };
 
-// The code tables of a slot for 0, 1, ... halvings of the sample's weights (see build_tables_kernel).
+// The code tables of a slot for 0, 1, ... halvings of the sample's weights (see build_table).  They are built by workgroups of the
+// launch that uses them, so every word says by itself whether it has been written: it starts from zero (the prologue's zero
+// fill), and no entry is zero (a length is 1 or more).
 constexpr int kCandidates = 11;
+constexpr uint32_t kComplete = 1, kTooLong = 2;
 struct CandidateTables {
-    uint16_t entry[kCandidates][256];       // code | length << 12, by byte value
-    uint32_t complete[kCandidates];         // the code meets the length limit: the entries exist
+    uint32_t state[32];                     // of every candidate (one line of memory for those who wait): kComplete, or kTooLong:
+                                            // it exceeds the length limit and has no entries
+    uint32_t entry[kCandidates][128];       // two per word: code | length << 12, by byte value
 };
-static_assert(sizeof(CandidateTables) <= 4096 * 2, "fits the slot's decode table");
+static_assert(sizeof(CandidateTables) <= 4096 * 2 && sizeof(CandidateTables) % 128 == 0, "fits the slot's decode table");
 
-__device__ __forceinline__ CandidateTables *candidate_tables(uint16_t *lut, int slot)
+// slot 0 lies right in front of the ticket, the others in front of it: one range to fill with zeros
+__host__ __device__ __forceinline__ CandidateTables *candidate_tables(uint32_t *ticket, int slot)
 {
-    return (CandidateTables *)(lut + 4096 * slot);
+    return (CandidateTables *)ticket - (slot + 1);
 }
 
 // Chunks (= waves) per encoder workgroup, 8-bit chunks with twice the LDS: two.
@@ -282,6 +287,9 @@ struct CoderArgs {
     long long total_chunks;     // K and V together
     int is_v;
     int tab;                    // table slot of this launch
+    int builders;               // workgroups of the request that build code tables: those with the first tickets (see build_table)
+    int apart;                  // ... and have no chunks: tickets in front of the first chunk's (builders or 0)
+    int slots;                  // table slots of the format (bits 31:8) and those in use (bits 7:0, a bit each)
     CoderScratch ws;
     unsigned long long *out_bytes;   // device: true payload size (written by the last workgroup)
 };
@@ -295,12 +303,14 @@ struct CoderBatch {
     Places<kCoderBatch> at;             // (encoder, both tensors together: the items are the requests; set by the launcher)
     int n;
     int waves;                          // encoder, both tensors together: chunks per workgroup
+    unsigned front;                     // encoder: workgroups of every request in front of the items' places (the request's
+                                        // first launch: CoderArgs::apart; others: none)
 };
 static_assert(sizeof(CoderBatch) <= 4000, "kernel arguments are limited to 4 KB");
 static_assert(sizeof(QuantBatch) <= 4000, "kernel arguments are limited to 4 KB");
 
 // Set-up of the requests of a call that is compressed with the coder: the prologue and the table samples
-// of every request in one launch, then the code tables of all requests.
+// of every request in one launch.
 struct SetupTable {             // a table of the plan, the same for all requests
     const int *head_list;       // the heads it covers (null: all in their own order)
     int heads_covered, slot, is_v, bits, group;
@@ -322,18 +332,6 @@ struct SetupArgs {
 };
 static_assert(sizeof(SetupArgs) <= 4000, "kernel arguments are limited to 4 KB");
 
-struct BuildItem {
-    const uint16_t *sample;
-    uint16_t *lut;
-    uint8_t *lengths;           // the payload's code tables
-};
-constexpr int kBuildBatch = 128;
-struct BuildArgs {
-    BuildItem item[kBuildBatch];
-    int n, slots, slot_mask;
-};
-static_assert(sizeof(BuildArgs) <= 4000, "kernel arguments are limited to 4 KB");
-
 // Set-up of the requests of a call that is decompressed with the coder (see decode_setup_kernel).
 struct DecodeSetupItem {
     const uint32_t *payload;
@@ -353,7 +351,6 @@ struct DecodeSetupArgs {
 static_assert(sizeof(DecodeSetupArgs) <= 4000, "kernel arguments are limited to 4 KB");
 
 int launch_setup(int dtype, const SetupArgs &a, hipStream_t s);
-int launch_build_tables(const BuildArgs &a, hipStream_t s);
 // kv: the tensor of the launch, K (0), V (1) or both (2: a K and a V item of every request in turn)
 int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
 int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s);

@@ -27,6 +27,7 @@ constexpr long long kStartLimit = 1000000000;      // ticks of 10 ns: the longes
 // The scanner waits for running workgroups too, but also for tickets that nobody has taken, for as long as
 // other work keeps the rest of the launch off the chip: looks count only in the first kind of wait, the second
 // ends after ten seconds (calls that overlap on one workspace may have taken each other's tickets).
+// (Tickets are counted from behind those of the workgroups that only build code tables, kvc_huff_build.h.)
 // Whoever gives up marks the request's carry word: everybody else who waits stops too, no later launch of the
 // request places a body, and directory and header stay open.
 // (Without a scanner every workgroup looked back over 64 predecessors for itself, after its barrier:
@@ -98,7 +99,7 @@ __device__ __forceinline__ void scan_sizes(const CoderArgs &a, long long end, in
             since = 0;
             nobody = false;
         } else if ((++spins & (kSpinCheck - 1)) == 0) {
-            nobody = (unsigned)next >= __hip_atomic_load(a.ws.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            nobody = (unsigned)(next + a.apart) >= __hip_atomic_load(a.ws.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (scan_failed(a)) return;
             if (nobody) {
                 const long long now = wall_clock64();
