@@ -154,16 +154,20 @@ template <int BITS> __device__ __forceinline__ void load_sub(const uint8_t *lds,
     }
 }
 
-// inclusive prefix sum over the 64 lanes
+// Inclusive prefix sum over the 64 lanes (all of them active), by DPP patterns: within rows of 16 lanes, then the ends of the
+// rows to the rows behind them.  Six additions, where six rounds through ds_bpermute wait for each other.
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t add_from(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
 __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
 {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute((lane - d) << 2, (int)v);
-        if (lane >= d) v += o;
-    }
-    return v;
+    v = add_from<0x111, 0xf>(v);               // row_shr:1, 2, 4, 8
+    v = add_from<0x112, 0xf>(v);
+    v = add_from<0x114, 0xf>(v);
+    v = add_from<0x118, 0xf>(v);
+    v = add_from<0x142, 0xa>(v);               // row_bcast:15 into rows 1 and 3
+    return add_from<0x143, 0xc>(v);            // row_bcast:31 into rows 2 and 3
 }
 
 static inline int launched() { return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE; }
