@@ -505,7 +505,7 @@ static int launch_tensor(const kvc_plan_t *p, int is_v, bool compress, QuantBatc
 // four 20k- to 30k-token requests ran 4 % slower shared than one after the other).  Empty requests
 // have no work in any launch and fit every window.
 
-// Requests of a coder window where K and V share a launch (coder_window: where they go apart).
+// Requests of a coder window where K and V share a launch, but for wide windows.
 static const int kSharedWindow = 4;
 
 static bool dense_layout(const kvc_request *r) { return !r->block_table && r->stride_token == kDim; }
@@ -568,6 +568,7 @@ extern "C" int kvc_workspace_init(const kvc_plan_t *plan, void *workspace, void 
 // launch per width present (2, 3, 4, 8) over the heads of that width, otherwise one launch.
 struct CoderLaunch {
     CoderArgs a;
+    long long heads;            // heads it covers
     int bits, group;
 };
 
@@ -607,6 +608,23 @@ static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int
     return chunks;
 }
 
+// Whether the windows of a call are as wide as the coder's batches: from five requests on, where they have 2^21 rows per tensor together.
+// Every launch less saves a start and a tail.  Time with wide windows / with windows of four (K and V together), eight and twelve
+// (apart), the least and the most of 2, 3, 4 and 8 bits, K 4 and V 2, rotation and half of the heads at 8 bits, fp16 and bf16:
+//   requests      5 to 8, 2^21 to 2^23 rows        9 to 16, 2^21.5 to 2^24.2    20 to 40, 2^21.5 to 2^25.1
+//   compression   0.89 to 1.00 (rotation 1.01)     0.86 to 0.99                 0.73 to 0.99
+//   decompression 0.91 to 1.01                     0.86 to 1.00                 0.76 to 0.99
+// (calls with fewer rows have the windows below, whose lines were measured with batches of twelve)
+static bool wide_window(const kvc_plan_t *p, const kvc_request *reqs, int n)
+{
+    long long per_head = 0;
+    for (int i = 0; i < n; ++i) per_head += chunks_per_head(reqs[i].tokens);
+    return n > kSharedWindow && per_head * p->model.layers * p->model.kv_heads >= kSmallRows / kChunkRows;
+}
+
+// Requests of a coder window where K and V share a launch (coder_window: where they go apart).
+static int shared_window(const kvc_plan_t *p, const kvc_request *reqs, int n) { return wide_window(p, reqs, n) ? kCoderBatch / 2 : kSharedWindow; }
+
 // Requests of a coder window with K and V apart: eight, from seventeen on twelve.  A window is a start and a tail per launch, but
 // where a launch of twelve of the widest codes has up to a quarter more chunks than are resident (16 per compute unit, at 8 bits 8; with width
 // tables, whose launches are smaller, up to a half) its rest has the chip to itself, and eight is better unless twelve takes a
@@ -619,7 +637,8 @@ static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int
 // (Nine to twelve requests would gain by one window, 0.58 to 0.97, but for 1.03 at one size; they take eight and the rest.)
 static int coder_window(const kvc_plan_t *p, const kvc_request *reqs, int n)
 {
-    const int most = kCoderBatch;
+    const int most = 12;
+    if (wide_window(p, reqs, n)) return kCoderBatch;
     if (n <= 16) return 8;
     if (2 * (n / most) + (n % most > 0) <= (n + 7) / 8) return most;
     long long per_head = 0, heads[2] = {0, 0};
@@ -643,15 +662,16 @@ static int coder_window(const kvc_plan_t *p, const kvc_request *reqs, int n)
     return most;
 }
 
-static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
+static bool share_kv(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead, int limit)
 {
-    if (!tensors_share(p) || end - first > kSharedWindow) return false;
+    if (!tensors_share(p) || end - first > limit) return false;
     const long long rows = (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens;
     if (p->strat.group_k == 32) return rows < 4 * kSmallRows;
     if (rows >= kSmallRows) return false;
-    if (p->strat.group_k == 64) return true;
     long long largest;
     const long long chunks = window_chunks(p, reqs, first, end, &largest);
+    // (more than four requests of groups of 64: shared up to 3 * 2^21 rows 0.93 to 0.98 of the time apart, above 1.01 to 1.02)
+    if (p->strat.group_k == 64) return end - first <= kSharedWindow || chunks <= 6 * kSmallRows / kChunkRows;
     if (p->model.dtype == KVC_BF16 && !dense_layout(&reqs[lead])) return chunks <= 4 * kUnits;
     return p->strat.bits_k == 8 || chunks <= kSmallRows / kChunkRows;        // 2^20 rows of K and of V
 }
@@ -678,9 +698,9 @@ static int common_widths(const kvc_plan_t *p)
 // as one of eight with K and V apart; where one of them has a width of its own they take more, and
 // windows of more than four requests stay apart (K 4 and 3 bits, V 4 and 2, five requests of 2^14, 2^16 and 2^18 rows:
 // 66 81 208 us apart, 88 100 203 shared; K 8, 4 and 2 bits, V 8 and 2: 106 120 304 and 125 139 291).
-static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead)
+static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead, int limit)
 {
-    return common_widths(p) > 0 && end - first <= kSharedWindow &&
+    return common_widths(p) > 0 && end - first <= limit &&
            (long long)p->model.layers * p->model.kv_heads * reqs[lead].tokens < 4 * kSmallRows;
 }
 
@@ -733,25 +753,55 @@ static bool builders_apart(const kvc_plan_t *p, const kvc_request *reqs, int fir
     return wgs > resident || wgs + (long long)(end - first) * builders <= resident;
 }
 
-// K and V of the first n requests of a window as one batch
-static CoderBatch coder_batch_both(const CoderLaunch cl[][kTableSlots], int n)
+// A launch of a request, `number` behind the window's first, as the batch's next item.
+static void add_item(CoderBatch &b, const CoderLaunch &l, int number)
 {
-    CoderBatch b;
-    memset(&b, 0, sizeof b);
-    for (int k = 0; k < 2 * n; ++k) b.item[k] = cl[k / 2][k & 1].a;
-    b.n = 2 * n;
-    b.front = (unsigned)b.item[0].apart;
-    return b;
+    const CoderArgs &a = l.a;
+    CoderItem &it = b.item[b.n++];
+    it.base = a.q.x.base;
+    it.stride_layer = a.q.x.stride_layer;
+    it.stride_head = a.q.x.stride_head;
+    it.stride_token = a.q.x.stride_token;
+    it.stride_block = a.q.x.stride_block;
+    it.block_table = a.q.x.block_table;
+    it.payload = a.payload;
+    it.capacity = a.capacity;
+    it.tokens = a.q.tokens;
+    it.num_phys_blocks = a.q.x.num_phys_blocks;
+    it.off_meta = (uint32_t)((a.q.meta - a.payload) / 16);
+    it.off_aux = (uint32_t)(a.off_aux / 16);
+    it.off_bodies = (uint32_t)(a.off_bodies / 16);
+    it.off_anchors = a.q.anchors ? (uint32_t)(((uint8_t *)a.q.anchors - a.payload) / 16) : 0;
+    it.chunk_base = (uint32_t)a.chunk_base;
+    it.wg_base = (uint32_t)a.wg_base;
+    it.k_wgs = (uint32_t)a.k_wgs;
+    it.total_wgs = (uint32_t)a.total_wgs;
+    it.flags = (uint32_t)(a.q.x.bt_shift | a.q.x.bt_wave << 5 | a.q.head_minor << 6 | a.is_v << 7 | a.tab << 8 | number << 16);
+    b.head_list[a.is_v] = a.q.head_list;
+    b.heads_covered[a.is_v] = (int)l.heads;
+    b.group[a.is_v] = a.q.group;
 }
 
-// launch j of the first n requests of a window as one batch
-static CoderBatch coder_batch(const CoderLaunch cl[][kTableSlots], int n, int j)
+// A batch without items.  `lead`: a launch of the window's leader, the first item to come; first: the window's first request.
+static CoderBatch coder_batch(const kvc_plan_t *p, const CoderLaunch &lead, int first, uint8_t *ws, uint64_t *out_bytes, int *status)
 {
     CoderBatch b;
     memset(&b, 0, sizeof b);
-    for (int k = 0; k < n; ++k) b.item[k] = cl[k][j].a;
-    b.n = n;
-    b.front = j == 0 ? (unsigned)b.item[0].apart : 0;       // (the tables of all launches are built in the first)
+    b.ws_request = (long long)p->ws_request;
+    b.ws = ws + p->blob_bytes + first * b.ws_request;
+    b.status = status + first;
+    b.out_bytes = out_bytes ? (unsigned long long *)out_bytes + first : nullptr;
+    b.ws_lut = (uint32_t)lut_offset(p);
+    b.ws_ticket = (uint32_t)ticket_offset(p);
+    b.ws_state = (uint32_t)p->ws_state_off;
+    b.heads = p->model.kv_heads;
+    b.all_heads = p->model.layers * p->model.kv_heads;
+    b.dense = lead.a.q.dense;
+    b.rotate = lead.a.q.rotate;
+    b.anchor_shift = lead.a.q.anchor_shift;
+    b.builders = lead.a.builders;
+    b.apart = lead.a.apart;
+    b.slots = lead.a.slots;
     return b;
 }
 
@@ -800,6 +850,7 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
             L.a.is_v = is_v;
             L.a.tab = any_table ? 4 * is_v + w : is_v;
             base.slots |= 1 << L.a.tab;
+            L.heads = heads;
             L.a.chunks = heads * cph;
             L.a.chunk_base = chunk_at;
             L.a.wg_base = wg_at;
@@ -818,6 +869,9 @@ static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *pa
     }
     return n;
 }
+
+// Whether the coder's items can hold the places of a request (CoderItem); a payload beyond has more than 64 GB in front of the bodies.
+static bool places_fit(const Geometry &g) { return g.off_codes_k >> 36 == 0 && (g.chunks_k + g.chunks_v) >> 31 == 0; }
 
 static int check_batch(const kvc_plan_t *p, const kvc_request *reqs, int32_t n, const void *payload,
                        const uint64_t *off, const void *workspace)
@@ -968,6 +1022,7 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
         Geometry g;
         geometry(plan, reqs[i].tokens, &g);
         if (payload_off[i + 1] - payload_off[i] < (uint64_t)g.total) return KVC_ERR_CAPACITY;
+        if (plan->strat.codec && !places_fit(g)) return KVC_ERR_UNSUPPORTED;
     }
     const kvc_strategy &st = plan->strat;
     const int dt = plan->model.dtype;
@@ -1006,15 +1061,15 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             KVC_TRY(launch_compress_prologue(pa, s));
         }
     }
-    const int coder_limit = coder_window(plan, reqs, n);
+    const int coder_limit = coder_window(plan, reqs, n), shared_limit = shared_window(plan, reqs, n);
     for (int first = 0; first < n;) {
         int lead;
         int end = request_window(plan, reqs, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
-        bool share = st.codec && share_kv(plan, reqs, first, end, lead);
-        if (st.codec && st.bits_k == 8 && end - first > kSharedWindow) {
+        bool share = st.codec && share_kv(plan, reqs, first, end, lead, shared_limit);
+        if (st.codec && st.bits_k == 8 && end - first > kSharedWindow && shared_limit == kSharedWindow) {
             int lead_half;
             const int half = request_window(plan, reqs, n, first, kSharedWindow, &lead_half);
-            share = share_kv(plan, reqs, first, half, lead_half);
+            share = share_kv(plan, reqs, first, half, lead_half, shared_limit);
             if (share) {
                 end = half;
                 lead = lead_half;
@@ -1044,9 +1099,13 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                                           (long long)(payload_off[i + 1] - payload_off[i]), out_bytes + i, dev_status + i, true,
                                           (const uint8_t *)workspace, cl[k], waves, apart);
             }
+            const auto batch_for = [&](const CoderLaunch &l) { return coder_batch(plan, l, first, (uint8_t *)workspace, out_bytes, dev_status); };
             marks.window(first, end, 1);
             if (share) {
-                CoderBatch both = coder_batch_both(cl, end - first);
+                CoderBatch both = batch_for(cl[0][0]);
+                for (int k = 0; k < end - first; ++k)
+                    for (int j = 0; j < 2; ++j) add_item(both, cl[k][j], window_item(first, end, lead, k) - first);
+                both.front = (unsigned)both.apart;
                 both.waves = waves;
                 KVC_TRY(launch_encode_section(2, cl[0][0].bits, cl[0][0].group, dt, both, s));
                 marks.window(first, end, 2);
@@ -1054,12 +1113,16 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                 first = end;
                 continue;
             }
-            for (int j = 0; j < launches; ++j)
-                if (!cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].a.is_v, cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
-            marks.window(first, end, 2);
-            for (int j = 0; j < launches; ++j)
-                if (cl[0][j].a.is_v) KVC_TRY(launch_encode_section(cl[0][j].a.is_v, cl[0][j].bits, cl[0][j].group, dt, coder_batch(cl, end - first, j), s));
-            marks.window(first, end, 3);
+            for (int is_v = 0; is_v < 2; ++is_v) {
+                for (int j = 0; j < launches; ++j) {
+                    if (cl[0][j].a.is_v != is_v) continue;
+                    CoderBatch b = batch_for(cl[0][j]);
+                    for (int k = 0; k < end - first; ++k) add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
+                    b.front = j == 0 ? (unsigned)b.apart : 0;         // (the tables of all launches are built in the first)
+                    KVC_TRY(launch_encode_section(is_v, cl[0][j].bits, cl[0][j].group, dt, b, s));
+                }
+                marks.window(first, end, 2 + is_v);
+            }
         }
         first = end;
     }
@@ -1123,6 +1186,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
         geometry(plan, dst[i].tokens, &g);
         const long long cap = (long long)(payload_off[i + 1] - payload_off[i]);
         if (cap < kHeader || (!st.codec && cap < g.total) || (st.codec && cap < g.off_codes_k)) return KVC_ERR_CAPACITY;
+        if (st.codec && !places_fit(g)) return KVC_ERR_UNSUPPORTED;
     }
     hipStream_t s = (hipStream_t)hip_stream;
     const int dt = plan->model.dtype;
@@ -1202,7 +1266,8 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
             KVC_TRY(launch_decompress_prologue(ca, s));
         }
     }
-    const int coder_limit = common_widths(plan) == 2 ? kSharedWindow : coder_window(plan, dst, n);
+    const int shared_limit = shared_window(plan, dst, n);
+    const int coder_limit = common_widths(plan) == 2 ? shared_limit : coder_window(plan, dst, n);
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
@@ -1226,17 +1291,17 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                           (long long)(payload_off[i + 1] - payload_off[i]), nullptr, dev_status + i, false,
                                           (const uint8_t *)workspace, cl[k]);
             }
+            const auto batch_for = [&](const CoderLaunch &l) { return coder_batch(plan, l, first, (uint8_t *)workspace, nullptr, dev_status); };
             marks.window(first, end, 1);
-            if (widths_share(plan, dst, first, end, lead)) {
+            if (widths_share(plan, dst, first, end, lead, shared_limit)) {
                 // width by width, K and V together
                 for (int w = 0; w < 4; ++w) {
-                    CoderBatch b;
-                    memset(&b, 0, sizeof b);
+                    CoderBatch b = batch_for(cl[0][0]);
                     int kinds = 0;                        // bit 0: K, bit 1: V
                     for (int k = 0; k < end - first; ++k)
                         for (int j = 0; j < launches; ++j)
                             if (cl[k][j].bits == kWidths[3 - w]) {
-                                b.item[b.n++] = cl[k][j].a;
+                                add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
                                 kinds |= 1 << cl[k][j].a.is_v;
                             }
                     if (b.n > 0) KVC_TRY(launch_decode_section(kinds == 3 ? 2 : kinds - 1, kWidths[3 - w], dt, b, s));
@@ -1246,12 +1311,15 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                 first = end;
                 continue;
             }
-            for (int j = 0; j < launches; ++j)
-                if (!cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].a.is_v, cl[0][j].bits, dt, coder_batch(cl, end - first, j), s));
-            marks.window(first, end, 2);
-            for (int j = 0; j < launches; ++j)
-                if (cl[0][j].a.is_v) KVC_TRY(launch_decode_section(cl[0][j].a.is_v, cl[0][j].bits, dt, coder_batch(cl, end - first, j), s));
-            marks.window(first, end, 3);
+            for (int is_v = 0; is_v < 2; ++is_v) {
+                for (int j = 0; j < launches; ++j) {
+                    if (cl[0][j].a.is_v != is_v) continue;
+                    CoderBatch b = batch_for(cl[0][j]);
+                    for (int k = 0; k < end - first; ++k) add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
+                    KVC_TRY(launch_decode_section(is_v, cl[0][j].bits, dt, b, s));
+                }
+                marks.window(first, end, 2 + is_v);
+            }
         }
         first = end;
     }

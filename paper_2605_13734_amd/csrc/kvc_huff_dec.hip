@@ -143,7 +143,13 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
     using Dec = DecGeom<BITS>;
     constexpr int W = Geo::kWords, NW = Geo::kDecWaves;
     unsigned wg;
-    const CoderArgs &a = batch.item[place_item_at_once(batch.at, place_of_workgroup(batch.at), wg)];
+    // (what the batch has for all items comes with the table of places)
+    int covered0 = batch.heads_covered[0], covered1 = batch.heads_covered[1], slots = batch.slots;
+    int *status = batch.status;
+    uint8_t *scratch = batch.ws;
+    long long scratch_bytes = batch.ws_request;
+    asm volatile("" ::"s"(covered0), "s"(covered1), "s"(slots), "s"(status), "s"(scratch), "s"(scratch_bytes));
+    const CoderArgs a = coder_args<KV, true>(batch, place_item_of_many(batch.at, place_of_workgroup(batch.at), wg));
     const bool is_v = KV == 2 ? a.is_v != 0 : KV == 1;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Dec::kLds];
     __shared__ uint16_t lut[4096];
@@ -326,27 +332,26 @@ template <int BITS> static DecodeShape decode_shape(unsigned wgs, bool both, boo
 template <int BITS, int DT, int KV> static int decode_launch(const CoderBatch &b, hipStream_t s)
 {
     constexpr int NW = ChunkGeom<BITS>::kDecWaves;
-    const CoderArgs &a = b.item[0];
     CoderBatch placed = b;
     unsigned need = 0;
     for (int i = 0; i < b.n; ++i) {
         placed.at.start[i] = need;
-        need += (unsigned)((b.item[i].chunks + NW - 1) / NW);
+        need += (unsigned)((item_chunks(b, i) + NW - 1) / NW);
     }
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
-    const int tr = a.q.rotate ? 1 : !a.q.anchors ? 0 : a.q.anchor_shift >= 5 ? 2 : 3;
-    const DecodeShape shape = decode_shape<BITS>(need, KV == 2, a.q.dense != 0, tr != 0, a.q.group, b.n <= (KV == 2 ? 2 : 1));
+    const int tr = b.rotate ? 1 : !b.item[0].off_anchors ? 0 : b.anchor_shift >= 5 ? 2 : 3;
+    const DecodeShape shape = decode_shape<BITS>(need, KV == 2, b.dense != 0, tr != 0, b.group[b.item[0].flags >> 7 & 1], b.n <= (KV == 2 ? 2 : 1));
     close_places(placed.at, b.n, need, shape.run);
 #define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, KV, D, T>), grid, block, shape.lds, s, placed)
     if (KV == 2) {
         if (tr != 0) return KVC_ERR_UNSUPPORTED;
-        if (a.q.dense) KVC_DECODE(true, 0); else KVC_DECODE(false, 0);
+        if (b.dense) KVC_DECODE(true, 0); else KVC_DECODE(false, 0);
         return launched();
     }
     // (the transforms are not instantiated for both tensors together)
     constexpr int kRot = KV == 2 ? 0 : 1, kOne = KV == 2 ? 0 : 2, kShort = KV == 2 ? 0 : 3;
-    if (a.q.dense) {
+    if (b.dense) {
         if (tr == 0) KVC_DECODE(true, 0); else if (tr == 1) KVC_DECODE(true, kRot); else if (tr == 2) KVC_DECODE(true, kOne); else KVC_DECODE(true, kShort);
     } else {
         if (tr == 0) KVC_DECODE(false, 0); else if (tr == 1) KVC_DECODE(false, kRot); else if (tr == 2) KVC_DECODE(false, kOne); else KVC_DECODE(false, kShort);

@@ -174,8 +174,8 @@ void encode_kernel(CoderBatch batch)
     // the places of the workgroups that only build tables come first, so that those of all requests start early
     const unsigned front = (unsigned)batch.n * batch.front;
     unsigned wg = 0;
-    const int item = kItems * (blockIdx.x < front ? (int)(blockIdx.x / batch.front) : place_item(batch.at, blockIdx.x - front, wg));
-    const CoderArgs &first = batch.item[item];
+    const int item = kItems * (blockIdx.x < front ? (int)(blockIdx.x / batch.front) : place_item_of_many(batch.at, blockIdx.x - front, wg));
+    const CoderArgs first = coder_args<KV>(batch, item);
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Geo::kLds];
     __shared__ EncTables enc;
     __shared__ uint32_t s_units[NW];
@@ -192,7 +192,7 @@ void encode_kernel(CoderBatch batch)
     // number says which of them it most likely has, its ticket which it has).
     int second = KV == 2 && wg >= first.k_wgs ? 1 : 0, pick = -1;
     if (wave == 0) {
-        const CoderArgs &a = batch.item[item + second];
+        const CoderArgs a = coder_args<KV>(batch, item + second);
         pick = fetch_table<true>(candidate_tables(a.ws.ticket, a.tab), enc);
         if (lane == 0) s_table = pick < 0 ? kNobody : kThere;
     }
@@ -213,7 +213,7 @@ void encode_kernel(CoderBatch batch)
         pick = -1;
         __syncthreads();
     }
-    const CoderArgs &a = batch.item[item + second];
+    const CoderArgs a = coder_args<KV>(batch, item + second);
     const long long chunk = (ticket - a.wg_base) * NW + wave;
     const bool live = chunk < a.chunks;
     uint8_t *lds = lds_all + wave * Geo::kLds;
@@ -354,30 +354,29 @@ static unsigned encode_hold(int bits, int group, bool is_v, bool rotate, unsigne
 
 template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(const CoderBatch &b, hipStream_t s)
 {
-    const CoderArgs &a = b.item[0];
     CoderBatch placed = b;
     if (KV == 2) placed.n = b.n / 2;                  // requests
     unsigned need = 0;
     for (int i = 0; i < placed.n; ++i) {
         placed.at.start[i] = need;
-        need += KV == 2 ? (unsigned)b.item[2 * i].total_wgs : (unsigned)((b.item[i].chunks + NW - 1) / NW);
+        need += KV == 2 ? b.item[2 * i].total_wgs : (unsigned)((item_chunks(b, i) + NW - 1) / NW);
     }
     close_places(placed.at, placed.n, need, 0);
     const unsigned front = placed.front * (unsigned)placed.n;
     if (front + need == 0) return KVC_OK;
     const dim3 grid(front + need), block(NW * 64);
-    const unsigned lds = encode_hold(BITS, G, KV == 1, a.q.rotate != 0, need);
+    const unsigned lds = encode_hold(BITS, G, KV == 1, b.rotate != 0, need);
 #define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, lds, s, placed)
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
     // transform (its code costs the plain path registers); both tensors together run without one only
     constexpr bool kPlain = KV != 1 || G == 32;
-    if (!a.q.rotate && !(a.q.anchors && kPlain)) {
-        if (a.q.dense) KVC_ENCODE(true, !kPlain, NW); else KVC_ENCODE(false, !kPlain, NW);
+    if (!b.rotate && !(b.item[0].off_anchors && kPlain)) {
+        if (b.dense) KVC_ENCODE(true, !kPlain, NW); else KVC_ENCODE(false, !kPlain, NW);
         return launched();
     }
     if constexpr (KV != 2) {
-        if (a.q.rotate) { if (a.q.dense) KVC_ENCODE(true, false, NW, true); else KVC_ENCODE(false, false, NW, true); }
-        else if (a.q.dense) KVC_ENCODE(true, true, NW); else KVC_ENCODE(false, true, NW);
+        if (b.rotate) { if (b.dense) KVC_ENCODE(true, false, NW, true); else KVC_ENCODE(false, false, NW, true); }
+        else if (b.dense) KVC_ENCODE(true, true, NW); else KVC_ENCODE(false, true, NW);
         return launched();
     }
     return KVC_ERR_UNSUPPORTED;

@@ -76,21 +76,32 @@ template <int N> __device__ __forceinline__ int place_item(const Places<N> &at, 
     return i;
 }
 
-// The same with all starts read together and compared without branches instead of one scalar load after the other at the
-// start of every wave: for the decoder, whose waves have a long chain of loads before them (one layer of 32k tokens, 4 bits,
-// decompress call 44 -> 41.6 us).  The codec-free compressions lose 3 % by it.
-template <int N> __device__ __forceinline__ int place_item_at_once(const Places<N> &at, unsigned place, unsigned &wg)
+// The same for the coder's many items: the first eight starts are read together and compared without branches, instead of one
+// scalar load after the other at the start of every wave (one layer of 32k tokens, 4 bits, decompress call 44 -> 41.6 us; the codec-free
+// compressions lose 3 % by it).  Launches with more items look up the eight and then the one of it (for all launches: 1 us of 41).
+template <int N> __device__ __forceinline__ int place_item_of_many(const Places<N> &at, unsigned place, unsigned &wg)
 {
-    int item = 0;
-    unsigned first = at.start[0];
+    const auto one_of_eight = [&](const unsigned *start, int eight) {
+        int item = eight;
+        unsigned first = start[0];
 #pragma unroll
-    for (int k = 1; k < N; ++k) {
-        const bool here = place >= at.start[k];
-        item += here ? 1 : 0;
-        first = here ? at.start[k] : first;
-    }
-    wg = place - first;
-    return item;
+        for (int k = 1; k < 8; ++k) {
+            const bool here = place >= start[k];
+            item += here ? 1 : 0;
+            first = here ? start[k] : first;
+        }
+        wg = place - first;
+        return item;
+    };
+    unsigned s[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s[k] = at.start[k];
+    asm volatile("" : "+s"(s[0]), "+s"(s[1]), "+s"(s[2]), "+s"(s[3]), "+s"(s[4]), "+s"(s[5]), "+s"(s[6]), "+s"(s[7]), "+s"(s[8]));
+    if (__builtin_expect(place < s[8], 1)) return one_of_eight(s, 0);
+    int eight = 8;
+#pragma unroll
+    for (int k = 16; k < N; k += 8) eight += place >= at.start[k] ? 8 : 0;
+    return one_of_eight(at.start + eight, eight);
 }
 
 // The same tensor (K or V) of several requests of a call in one launch, their workgroups one request
@@ -297,15 +308,111 @@ struct CoderArgs {
 // One launch of the encoder or decoder for the requests of a window (see request_window), the items' workgroups one
 // after the other: a launch of every request (one tensor and width), or, where K and V share a launch, a
 // K and a V item of every request.  All items have one width and take the same kernel.
-constexpr int kCoderBatch = 12;     // (the argument block stays below 4 KB)
+// A launch costs a start and a tail of about 29 us with the encoder (4 bits, launches of 5000 to 9000 workgroups: 29 us + 0.031 a
+// workgroup), so a batch holds as many requests as 4 KB of arguments allow: an item has what differs from request to request
+// in 112 bytes, the batch what does not, and the kernels put CoderArgs together from both (coder_args).  32 requests of 512 to 2048
+// tokens, 256 heads, 4 bits, in windows of twelve with CoderArgs for items / in one: 1356 / 1224 us.
+struct CoderItem {
+    uint16_t *base;             // TensorView
+    long long stride_layer, stride_head, stride_token, stride_block;
+    const int *block_table;
+    uint8_t *payload;
+    long long capacity;
+    long long tokens;
+    int num_phys_blocks;
+    // of 16 bytes, inside the payload (what lies before the last of these is smaller than 64 GB wherever the bodies, which the format
+    // counts in the same units, are)
+    uint32_t off_meta, off_aux, off_bodies, off_anchors;      // (off_anchors: 0 = no delta transform)
+    uint32_t chunk_base, wg_base, k_wgs, total_wgs;
+    uint32_t flags;             // bits 4:0 TensorView::bt_shift, 5 bt_wave, 6 QuantArgs::head_minor, 7 is_v, 10:8 tab, 31:16 number of the
+                                // request behind the window's first
+};
+static_assert(sizeof(CoderItem) == 112, "what a batch of 32 has room for");
+constexpr int kCoderBatch = 32;     // (the argument block stays below 4 KB)
 struct CoderBatch {
-    CoderArgs item[kCoderBatch];
+    CoderItem item[kCoderBatch];
     Places<kCoderBatch> at;             // (encoder, both tensors together: the items are the requests; set by the launcher)
+    // The same for all items.  (Whole words only: a 16-bit member, indexed by the tensor, made the compiler take the address of
+    // the word-sized ones apart into a base and an offset of two bytes too many and too few, and scalar loads drop the two lowest
+    // bits of either, so that the V launches with width tables read half of each of two pointers.)
+    // The window's first request's scratch (and its size), status and size words
+    uint8_t *ws;
+    long long ws_request;
+    int *status;
+    unsigned long long *out_bytes;
+    const int *head_list[2];            // of K and of V, like the next two
+    int heads_covered[2];               // heads of the launch
+    int group[2];
+    uint32_t ws_lut, ws_ticket, ws_state;       // places inside a request's scratch
+    int heads, all_heads;               // KV heads of a layer, of all layers
+    int dense, rotate, anchor_shift;
+    int builders, apart, slots;
     int n;
     int waves;                          // encoder, both tensors together: chunks per workgroup
     unsigned front;                     // encoder: workgroups of every request in front of the items' places (the request's
                                         // first launch: CoderArgs::apart; others: none)
 };
+
+static inline long long item_chunks(const CoderBatch &b, int item)
+{
+    return b.heads_covered[(b.item[item].flags >> 7) & 1] * ((b.item[item].tokens + kChunkRows - 1) / kChunkRows);
+}
+
+// KV: the launch's tensor, K (0), V (1) or both (2).  AT_ONCE: what a wave's first loads need of the item is requested together, not
+// where it is used (decoder).
+template <int KV, bool AT_ONCE = false> __device__ __forceinline__ CoderArgs coder_args(const CoderBatch &b, int item)
+{
+    CoderItem it = b.item[item];
+    if (AT_ONCE)
+        asm volatile("" ::"s"(it.payload), "s"(it.capacity), "s"(it.tokens), "s"(it.off_aux), "s"(it.off_bodies), "s"(it.chunk_base), "s"(it.flags));
+    const bool is_v = KV == 2 ? ((it.flags >> 7) & 1) != 0 : KV == 1;
+    CoderArgs a = {};
+    a.q.x.base = it.base;
+    a.q.x.stride_layer = it.stride_layer;
+    a.q.x.stride_head = it.stride_head;
+    a.q.x.stride_token = it.stride_token;
+    a.q.x.stride_block = it.stride_block;
+    a.q.x.block_table = it.block_table;
+    a.q.x.bt_shift = it.flags & 31;
+    a.q.x.num_phys_blocks = it.num_phys_blocks;
+    a.q.x.bt_wave = (it.flags >> 5) & 1;
+    a.q.meta = it.payload + 16ll * it.off_meta;
+    a.q.tokens = it.tokens;
+    a.q.heads = b.heads;
+    a.q.group = is_v ? b.group[1] : b.group[0];
+    a.q.dense = b.dense;
+    a.q.head_minor = (it.flags >> 6) & 1;
+    a.q.rotate = b.rotate;
+    a.q.anchors = it.off_anchors ? (uint16_t *)(it.payload + 16ll * it.off_anchors) : nullptr;
+    a.q.anchor_shift = b.anchor_shift;
+    a.q.head_list = is_v ? b.head_list[1] : b.head_list[0];
+    const int request = (int)(it.flags >> 16);
+    a.q.status = b.status + request;
+    a.payload = it.payload;
+    a.off_aux = 16ll * it.off_aux;
+    a.off_dir = a.off_aux + 256 * (b.slots >> 8);
+    a.off_bodies = 16ll * it.off_bodies;
+    a.capacity = it.capacity;
+    const uint32_t per_head = (uint32_t)((unsigned long long)(it.tokens + kChunkRows - 1) / kChunkRows);     // (no request has 2^31 chunks)
+    a.chunks = (uint32_t)(is_v ? b.heads_covered[1] : b.heads_covered[0]) * per_head;
+    a.chunk_base = it.chunk_base;
+    a.wg_base = it.wg_base;
+    a.k_wgs = it.k_wgs;
+    a.total_wgs = it.total_wgs;
+    a.total_chunks = 2 * (uint32_t)b.all_heads * per_head;
+    a.is_v = is_v;
+    a.tab = (it.flags >> 8) & 7;
+    a.builders = b.builders;
+    a.apart = b.apart;
+    a.slots = b.slots;
+    uint8_t *ws = b.ws + request * b.ws_request;
+    a.ws.sample = (uint16_t *)ws;
+    a.ws.lut = (uint16_t *)(ws + b.ws_lut);
+    a.ws.state = (unsigned long long *)(ws + b.ws_state);
+    a.ws.ticket = (uint32_t *)(ws + b.ws_ticket);
+    a.out_bytes = b.out_bytes + request;
+    return a;
+}
 static_assert(sizeof(CoderBatch) <= 4000, "kernel arguments are limited to 4 KB");
 static_assert(sizeof(QuantBatch) <= 4000, "kernel arguments are limited to 4 KB");
 
