@@ -10,6 +10,11 @@ count in about one execution of eight (a stand-alone kernel that does nothing el
 the same fault for gfx90a only.  A kernel that trips the check gets register headroom: an empty
 asm statement naming a higher register (see decode_kernel).
 
+The assembly is also searched for scalar loads at places that are no multiple of four.  Scalar loads drop the two
+lowest bits of the base and of the offset, each by itself, and the compiler does not know: with a 16-bit member between the words of a
+kernel's arguments, indexed at run time, it took the address of a word apart into a base two bytes too far and an offset of -2, and the
+kernel read half of each of two pointers (and faulted).  A kernel's arguments have members of whole words only (CoderBatch).
+
 A second check keeps kernels whose time depends on their waves (min_waves in kvc_quant.hip) within the
 registers that leave room for them, a third one looks for rows that are requested and waited for one at a time
 (rows_requested in kvc_tile.h).
@@ -55,6 +60,20 @@ def shift_count_in_last_vgpr(asm_path):
             m = shift.match(line)
             if m and int(m.group(1)) % 8 == 7 and int(m.group(1)) + 1 >= next_free[cur]:
                 hits.append((cur, line.strip()))
+    return hits
+
+
+def scalar_loads_off_words(asm_path):
+    """[(function or kernel symbol, instruction)] for scalar loads whose offset is no multiple of four."""
+    load = re.compile(r"\s+s_(?:buffer_)?load_dword\w*\s+(.*)")
+    hits, cur = [], None
+    for line in open(asm_path).read().split("\n"):
+        m = re.match(r"^(\w+):", line)
+        if m:
+            cur = m.group(1)
+        m = load.match(line.split(";")[0])
+        if m and any(int(n, 0) % 4 for n in re.findall(r"(?:,\s*|offset:)(-?(?:0x[0-9a-f]+|\d+))\b", m.group(1))):
+            hits.append((cur, line.strip()))
     return hits
 
 
@@ -134,6 +153,10 @@ def _compile(job):
     if hits:
         raise RuntimeError("%s: 64-bit shift with its count in the last allocated VGPR (give the kernel register "
                            "headroom):\n%s" % (name, "\n".join("  %s: %s" % h for h in hits[:20])))
+    off = scalar_loads_off_words(asm)
+    if off:
+        raise RuntimeError("%s: scalar loads that are not at whole words (a kernel argument with a member of fewer than four "
+                           "bytes?):\n%s" % (name, "\n".join("  %s: %s" % h for h in off[:20])))
     over = over_budget(asm)
     if over:
         raise RuntimeError("%s: more registers than the kernel's waves leave room for:\n%s" % (

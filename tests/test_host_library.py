@@ -231,6 +231,19 @@ def test_build_check_finds_a_shift_count_in_the_last_vgpr(tmp_path):
         assert all(h[0] == "kern" for h in hits)
 
 
+def test_build_check_finds_scalar_loads_that_are_not_at_words(tmp_path):
+    """The build's check of the scalar loads: an offset that is no multiple of four, in any of the forms, is reported."""
+    from paper_2605_13734_amd import build
+    cases = [("s_load_dwordx2 s[4:5], s[0:1], 0xe30", 0), ("s_load_dwordx2 s[4:5], s[0:1], 0xe32", 1),
+             ("s_load_dword s4, s[0:1], -0x2", 1), ("s_load_dwordx4 s[4:7], s[0:1], s9 offset:0xe2e", 1),
+             ("s_load_dword s4, s[0:1], s9 offset:0x10", 0), ("s_load_dwordx8 s[4:11], s[0:1], s9", 0), ("s_load_dword s4, s[0:1], 6", 1),
+             ("s_buffer_load_dword s4, s[0:3], 0x6", 1), ("global_load_ushort v1, v2, s[2:3] offset:2", 0), ("; s_load_dword s4, s[0:1], 0x2", 0)]
+    for i, (line, want) in enumerate(cases):
+        p = tmp_path / ("k%d.s" % i)
+        p.write_text("kern:\n\t%s\n\ts_endpgm\n" % line)
+        assert [k for k, _ in build.scalar_loads_off_words(str(p))] == ["kern"] * want, line
+
+
 def test_build_check_finds_kernels_over_their_registers(tmp_path):
     """The build's register check: the kernels for strided bf16 rows may take 80 registers (8-bit codes 96), others what they need."""
     from paper_2605_13734_amd import build
