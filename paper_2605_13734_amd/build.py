@@ -89,8 +89,12 @@ def spilling_kernels(asm_path):
 
 
 # (kernel symbol, registers): six waves per SIMD for the compress kernels of one pass for bf16 rows that are not
-# dense, five for 8-bit codes
-REGISTERS = [(r"compress_(?:k_kernelILi[234]ELi32|v_kernelILi[234]ELi\d+)ELi2ELb0E", 80),
+# dense, five for 8-bit codes.  Decoders below 8 bits: four, but for two kinds with short runs of the delta transform and fp16 (4 bits dense,
+# 3 bits V strided).
+# Encoders: three for dense K blocks of 64 bf16 rows with the delta transform.
+REGISTERS = [(r"decode_kernelILi[234]ELi\dELi\dELb\dELi[012]E", 128), (r"decode_kernelILi(?!4ELi1ELi\dELb1|3ELi1ELi1ELb0)[234]ELi\dELi\dELb\dELi3E", 128),
+             (r"encode_kernelILi[234]ELi64ELi2ELi0ELb1ELb1ELi4E", 168),
+             (r"compress_(?:k_kernelILi[234]ELi32|v_kernelILi[234]ELi\d+)ELi2ELb0E", 80),
              (r"compress_(?:k_kernelILi8ELi32|v_kernelILi8ELi\d+)ELi2ELb0E", 96)]
 
 
@@ -101,6 +105,23 @@ def over_budget(asm_path):
     for k, body in re.findall(r"\.amdhsa_kernel (\w+)\n(.*?)\.end_amdhsa_kernel", text, re.S):
         n = int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", body).group(1))
         out += [(k, n, most) for pattern, most in REGISTERS if re.search(pattern, k) and n > most]
+    return out
+
+
+# (kernel symbol, scalars): scalar registers that the coder's kernels may move to vector registers and back: in encoders with the delta
+# transform a few (8-bit encoders as many as they do)
+SCALARS = [(r"decode_kernelILi", 0), (r"encode_kernelILi[234]ELi\d+ELi\dELi\dELb\dELb0E", 0), (r"encode_kernelILi[234]", 16)]
+
+
+def scalar_spills(asm_path):
+    """[(kernel symbol, scalars, most)] of the kernels that spill more scalar registers than SCALARS has it."""
+    text = open(asm_path).read()
+    out = []
+    for k, n in re.findall(r"\.name:\s+(\w+)\n(?:(?!\.name:).*\n)*?\s+\.sgpr_spill_count:\s*(\d+)", text):
+        for pattern, most in SCALARS:
+            if re.search(pattern, k):
+                out += [(k, int(n), most)] * (int(n) > most)
+                break
     return out
 
 
@@ -161,6 +182,10 @@ def _compile(job):
     if over:
         raise RuntimeError("%s: more registers than the kernel's waves leave room for:\n%s" % (
             name, "\n".join("  %s: %d of %d" % h for h in over[:20])))
+    scalars = scalar_spills(asm)
+    if scalars:
+        raise RuntimeError("%s: more scalar registers spilled than allowed:\n%s" % (
+            name, "\n".join("  %s: %d of %d" % h for h in scalars[:20])))
     lone = lone_loads(asm)
     if lone:
         raise RuntimeError("%s: rows waited for one at a time:\n%s" % (

@@ -74,6 +74,13 @@ __device__ __forceinline__ ChunkPos chunk_pos(const QuantArgs &a, long long chun
     return c;
 }
 
+// A place that is the same in all lanes, as one the compiler knows to be.
+__device__ __forceinline__ long long uniform(long long v)
+{
+    const uint32_t low = (uint32_t)__builtin_amdgcn_readfirstlane((int)v), high = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return (long long)((unsigned long long)high << 32 | low);
+}
+
 // Quantize and pack the chunk's rows into the wave's LDS region (sub-block layout) and
 // store the group metadata to the payload.  K group parameters are
 // exchanged through the 16 padding bytes that follow each sub-block.

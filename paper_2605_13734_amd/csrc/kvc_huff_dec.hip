@@ -125,7 +125,7 @@ __device__ __forceinline__ void dequant_chunk(const CoderArgs &a, const ChunkPos
         pass_fetch<BITS, DENSE, Dec::kLayout, TR == 1>(f, lds, a.q.x, c.head_off, c.row0 + p * kPassRows, c.rows - p * kPassRows, p * kPassRows,
                                               paged, blocks);
         dequant_pass<BITS, DT, IS_V, DENSE, TR>(f, scale, zero, clamp, a.q.x, c.head_off, c.row0 + p * kPassRows,
-                                                c.rows - p * kPassRows, bad, anchors, a.q.anchor_shift,
+                                                c.rows - p * kPassRows, bad, anchors, TR == 3 ? anew(a.q.anchor_shift) : a.q.anchor_shift,
                                                 one_anchor ? &anchor : nullptr);
         anchor = anchor_next;
         blocks = blocks_next;
@@ -276,7 +276,20 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
         wave_sync();
     }
 
-    // dequantize the rows from LDS
+    // Dequantize the rows from LDS.  Until here the chunk's place is kept per lane (see `wave`).  In scalar registers from here on it leaves
+    // the strided kernels with the transforms, and the fp16 ones for 3-bit K and V together, the vector registers of their fourth
+    // wave per SIMD, once the anchor period of short runs is taken anew as well (which rows are anchors would otherwise be computed for
+    // all passes and kept).  Registers and decompress calls, paged, without / with: 3 bits fp16, one layer of 32k tokens 131 / 128, 42.7 /
+    // 38.7 us; 2^20 rows, runs of 8 tokens, fp16, 2 and 4 bits 142 / 128, 203 / 177 and 144 / 128, 225 / 196 us; runs of 32, 4 bits 133 / 128,
+    // 155 / 149 us, 3 bits bf16 129 / 128, 142 / 132; the rotation (128 either way) 0.993 to 0.999 of the time; others up to 1.01, so they keep it per
+    // lane.  (The view read where it lies, not copied, takes no registers either, but then a row's place in its block is
+    // computed in every pass: 0.99 to 1.10 of the time.)
+    if (!DENSE && BITS != 8 && (TR != 0 || (BITS == 3 && DT == DT_F16 && KV == 2))) {
+        c.lh = uniform(c.lh);
+        c.head_off = uniform(c.head_off);
+        c.row0 = uniform(c.row0);
+        c.rows = __builtin_amdgcn_readfirstlane(c.rows);
+    }
     bool bad = false;
     if (is_v) dequant_chunk<BITS, DT, true, DENSE, TR>(a, c, lds, meta0, meta1, metav, anchor0, blocks0, bad);
     else dequant_chunk<BITS, DT, false, DENSE, TR>(a, c, lds, meta0, meta1, metav, anchor0, blocks0, bad);

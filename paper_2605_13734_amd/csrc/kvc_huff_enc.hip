@@ -213,7 +213,14 @@ void encode_kernel(CoderBatch batch)
         pick = -1;
         __syncthreads();
     }
-    const CoderArgs a = coder_args<KV>(batch, item + second);
+    // From here on every part of the kernel takes its arguments anew.  (Kept from the start, they were more than the scalar registers hold:
+    // nearly every encoder moved scalars to vector registers and back, and 3-bit dense K blocks of 64 bf16 rows with the delta transform lost
+    // a wave per SIMD by it, 169 registers.  Compress call of 2^21 rows without / with: those 403 / 370 us; rotation, 4 bits, 359 / 347;
+    // without a transform 1.00.  8-bit codes, two chunks per workgroup, feel the loads: one layer of 16k tokens 60.0 / 60.7.  Five waves
+    // per SIMD for strided 2-bit K, 96 registers in place of 97, by a view read where it lies: 301 / 304.)
+    const int mine_item = BITS == 8 ? item + second : anew(item + second);
+    const CoderArgs a = coder_args<KV>(batch, mine_item);
+    const auto args_again = [&](const CoderArgs &had, int i) { return BITS == 8 ? had : coder_args<KV>(batch, anew(i)); };
     const long long chunk = (ticket - a.wg_base) * NW + wave;
     const bool live = chunk < a.chunks;
     uint8_t *lds = lds_all + wave * Geo::kLds;
@@ -238,7 +245,8 @@ void encode_kernel(CoderBatch batch)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         const uint32_t sum = *(volatile uint32_t *)&s_sum;
         last_to_report = 1;
-        __hip_atomic_store(&a.ws.state[ticket], kFlagSize | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const CoderArgs now = args_again(a, mine_item);
+        __hip_atomic_store(&now.ws.state[ticket], kFlagSize | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     uint32_t body_units = 0;      // body size in 16-byte units
     bool coded = false, coding = false;
@@ -252,11 +260,12 @@ void encode_kernel(CoderBatch batch)
         else quantize_chunk<BITS, G, DT, false, DENSE, XF>(a.q, c, lds, bad);
         if (bad) atomicOr(a.q.status, KVC_DEV_BAD_BLOCK);
         wave_sync();
-        coding = wait_for_table(a, enc, &s_table, pick);
+        const CoderArgs now = args_again(a, mine_item);
+        coding = wait_for_table(now, enc, &s_table, pick);
         // the table's lengths in the payload, unless the construction without halvings has written them already (by the wave that
         // brought the table)
-        if (pick > 0 && ticket == a.wg_base)
-            for (int k = lane; k < 256; k += 64) a.payload[a.off_aux + 256 * a.tab + k] = enc.len[k];
+        if (pick > 0 && ticket == now.wg_base)
+            for (int k = lane; k < 256; k += 64) now.payload[now.off_aux + 256 * now.tab + k] = enc.len[k];
         load_sub<BITS>(lds, sym);
         const int have = coding ? min(max(rows - 2 * lane, 0), 2) : 0;        // valid rows of this sub-block
         uint32_t bits0 = 0, bits = 0;
@@ -296,6 +305,7 @@ void encode_kernel(CoderBatch batch)
         }
     }
     if (!live) report_size(0);
+    const CoderArgs out = args_again(a, mine_item);
     // The workgroup's prefix, left in its state word by the scanner once all its waves have reported.  The wave
     // that reported last polls for it, the others wait at an LDS word: four thousand waves polling memory would
     // slow the scanner down.  (The first workgroup of the launch, whose first wave is the scanner, knows its
@@ -305,7 +315,7 @@ void encode_kernel(CoderBatch batch)
         excl = before;
         while (wave > 0 && __hip_atomic_load(&s_reported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != (uint32_t)NW) __builtin_amdgcn_s_sleep(1);
     } else if (__builtin_amdgcn_readfirstlane(last_to_report)) {
-        excl = wait_for_place(a, ticket);
+        excl = wait_for_place(out, ticket);
         if (lane == 0) __hip_atomic_store(&s_excl, excl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {
         // (the polling wave always ends: it finds the prefix or its spin limit)
@@ -316,9 +326,9 @@ void encode_kernel(CoderBatch batch)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // (the sizes of the other waves are older than the prefix)
     unsigned long long mine = excl;
     for (int w = 0; w < wave; ++w) mine += s_units[w];
-    if (lane == 0) ((uint32_t *)(a.payload + a.off_dir))[a.chunk_base + chunk] = (uint32_t)mine;
-    uint8_t *dst = a.payload + a.off_bodies + mine * 16;
-    if ((long long)(a.off_bodies + (mine + body_units) * 16) > a.capacity) {
+    if (lane == 0) ((uint32_t *)(out.payload + out.off_dir))[out.chunk_base + chunk] = (uint32_t)mine;
+    uint8_t *dst = out.payload + out.off_bodies + mine * 16;
+    if ((long long)(out.off_bodies + (mine + body_units) * 16) > out.capacity) {
         // cannot happen: bodies never exceed raw size
     } else if (coded) {
         // (every store instruction covers whole lines of memory, but for the body's ends)
@@ -337,7 +347,10 @@ void encode_kernel(CoderBatch batch)
                 p[k] = v;
             }
     }
-    if (leads && wave == 0) scan_sizes(first, KV == 2 ? first.total_wgs : first.wg_base + (first.chunks + NW - 1) / NW);
+    if (leads && wave == 0) {
+        const CoderArgs scan = args_again(first, item);
+        scan_sizes(scan, KV == 2 ? scan.total_wgs : scan.wg_base + (scan.chunks + NW - 1) / NW);
+    }
 }
 
 // ---- launchers ----------------------------------------------------------------------------------

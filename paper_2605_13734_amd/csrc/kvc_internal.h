@@ -413,6 +413,16 @@ template <int KV, bool AT_ONCE = false> __device__ __forceinline__ CoderArgs cod
     a.out_bytes = b.out_bytes + request;
     return a;
 }
+
+// The same number (in a scalar register), but one that the compiler knows nothing of.  What is put together from an item's number taken
+// this way is put together there, and not kept in registers from an earlier part of the kernel; what depends on an anchor period taken
+// this way is not computed in front of a loop for all its passes.
+__device__ __forceinline__ int anew(int number)
+{
+    int n = __builtin_amdgcn_readfirstlane(number);
+    asm volatile("" : "+s"(n));
+    return n;
+}
 static_assert(sizeof(CoderBatch) <= 4000, "kernel arguments are limited to 4 KB");
 static_assert(sizeof(QuantBatch) <= 4000, "kernel arguments are limited to 4 KB");
 

@@ -245,7 +245,8 @@ def test_build_check_finds_scalar_loads_that_are_not_at_words(tmp_path):
 
 
 def test_build_check_finds_kernels_over_their_registers(tmp_path):
-    """The build's register check: the kernels for strided bf16 rows may take 80 registers (8-bit codes 96), others what they need."""
+    """The build's register check: the kernels for strided bf16 rows may take 80 registers (8-bit codes 96), decoders below 8 bits 128
+    but for two kinds, one kind of encoder what its waves leave, others what they need."""
     from paper_2605_13734_amd import build
     cases = [("_ZN3kvc17compress_k_kernelILi4ELi32ELi2ELb0ELb1EEEvNS_10QuantBatchE", 118, 1),
              ("_ZN3kvc17compress_k_kernelILi4ELi32ELi2ELb0ELb1EEEvNS_10QuantBatchE", 80, 0),
@@ -254,10 +255,28 @@ def test_build_check_finds_kernels_over_their_registers(tmp_path):
              ("_ZN3kvc17compress_v_kernelILi8ELi64ELi2ELb0EEEvNS_10QuantBatchE", 82, 0),
              ("_ZN3kvc17compress_v_kernelILi4ELi32ELi2ELb1EEEvNS_10QuantBatchE", 114, 0),       # dense
              ("_ZN3kvc17compress_k_kernelILi4ELi64ELi2ELb0ELb0EEEvNS_10QuantBatchE", 109, 0)]   # two passes
+    code = "_ZN3kvc13decode_kernelILi%dELi%dELi%dELb%dELi%dEEEvNS_10CoderBatchE"
+    cases += [(code % (3, 1, 2, 0, 0), 131, 128), (code % (2, 1, 0, 0, 2), 133, 128), (code % (4, 1, 0, 0, 2), 133, 128),
+              (code % (3, 2, 1, 0, 2), 129, 128), (code % (2, 2, 1, 0, 3), 134, 128), (code % (4, 2, 1, 0, 3), 134, 128),
+              (code % (3, 1, 0, 0, 3), 145, 128), (code % (3, 1, 2, 0, 0), 128, 0), (code % (4, 1, 0, 1, 3), 133, 0), (code % (3, 1, 1, 0, 3), 129, 0), (code % (8, 1, 0, 0, 0), 256, 0),
+              ("_ZN3kvc13encode_kernelILi3ELi64ELi2ELi0ELb1ELb1ELi4ELb0EEEvNS_10CoderBatchE", 169, 168)]
     for i, (name, regs, want) in enumerate(cases):
         p = tmp_path / ("k%d.s" % i)
         p.write_text("\t.amdhsa_kernel %s\n\t\t.amdhsa_next_free_vgpr %d\n\t.end_amdhsa_kernel\n" % (name, regs))
-        assert build.over_budget(str(p)) == ([(name, regs, 96 if "ILi8" in name else 80)] if want else []), name
+        assert build.over_budget(str(p)) == ([(name, regs, want if want > 1 else 96 if "ILi8" in name else 80)] if want else []), name
+
+
+def test_build_check_finds_spilled_scalars(tmp_path):
+    """The build's check of the coder's scalar registers, as the assembly's notes count them."""
+    from paper_2605_13734_amd import build
+    cases = [("_ZN3kvc13encode_kernelILi4ELi32ELi1ELi0ELb1ELb0ELi4ELb0EEEvNS_10CoderBatchE", 4, 0),
+             ("_ZN3kvc13encode_kernelILi4ELi32ELi1ELi0ELb1ELb1ELi4ELb0EEEvNS_10CoderBatchE", 13, 16),      # delta transform
+             ("_ZN3kvc13encode_kernelILi4ELi32ELi1ELi0ELb0ELb1ELi4ELb0EEEvNS_10CoderBatchE", 32, 16),
+             ("_ZN3kvc13decode_kernelILi3ELi1ELi0ELb0ELi3EEEvNS_10CoderBatchE", 2, 0), ("_ZN3kvc12setup_kernelILi1EEEvNS_9SetupArgsE", 9, 99)]
+    note = "  - .agpr_count:     0\n    .name:           %s\n    .sgpr_count:     106\n    .sgpr_spill_count: %d\n    .symbol:         %s.kd\n"
+    p = tmp_path / "k.s"
+    p.write_text("".join(note % (k, n, k) for k, n, _ in cases))
+    assert build.scalar_spills(str(p)) == [(k, n, most) for k, n, most in cases if n > most]
 
 
 def test_build_check_finds_rows_waited_for_one_at_a_time(tmp_path):
