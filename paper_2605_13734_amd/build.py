@@ -36,10 +36,11 @@ JOBS = ([("kvc_huff_enc.hip", b) for b in WIDTHS] + [("kvc_quant.hip", b) for b 
         [("kvc_huff_dec.hip", b) for b in WIDTHS] +
         [("kvc_huff_tables.hip", None), ("kvc_selftest.hip", None), ("kvc_service.hip", None), ("kvc_probe.hip", None),
          ("kvc_api.hip", None), ("kvc_policy.hip", None)])
-# packed fp32 instructions are switched off for the device pass (flag for hipcc only)
+# packed fp32 instructions are switched off for the device pass (flag for hipcc only); host functions may take 44 KB of stack, which
+# the calls need for the items of a full window (they run on threads of other programs)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall",
-         "-Wno-unused-command-line-argument"]
+         "-Xarch_host", "-Wframe-larger-than=45056", "-Xarch_host", "-Werror=frame-larger-than", "-Wno-unused-command-line-argument"]
 
 
 def shift_count_in_last_vgpr(asm_path):

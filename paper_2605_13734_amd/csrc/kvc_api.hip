@@ -564,12 +564,16 @@ extern "C" int kvc_workspace_init(const kvc_plan_t *plan, void *workspace, void 
                ? KVC_OK : KVC_ERR_DEVICE;
 }
 
-// The coder launches of one request, in chunk order: K before V; a tensor with a width table is one
-// launch per width present (2, 3, 4, 8) over the heads of that width, otherwise one launch.
+// The coder launches of a request, the same for all requests of a plan, in chunk order: K before V; a tensor with a width table
+// is one launch per width present (2, 3, 4, 8) over the heads of that width, otherwise one launch.
 struct CoderLaunch {
-    CoderArgs a;
-    long long heads;            // heads it covers
-    int bits, group;
+    int is_v, bits, group, tab;
+    int heads;                  // heads it covers
+    const int *head_list;       // ... (null without a width table: the heads in their own order)
+};
+struct CoderLaunches {
+    CoderLaunch of[kTableSlots];
+    int n, slots;               // CoderArgs::slots
 };
 
 // Whether K and V of the requests of a window share a launch with the coder.  The kernels for both tensors
@@ -753,42 +757,103 @@ static bool builders_apart(const kvc_plan_t *p, const kvc_request *reqs, int fir
     return wgs > resident || wgs + (long long)(end - first) * builders <= resident;
 }
 
-// A launch of a request, `number` behind the window's first, as the batch's next item.
-static void add_item(CoderBatch &b, const CoderLaunch &l, int number)
+static CoderLaunches coder_launches(const kvc_plan_t *p, const uint8_t *dev_tables)
 {
-    const CoderArgs &a = l.a;
-    CoderItem &it = b.item[b.n++];
-    it.base = a.q.x.base;
-    it.stride_layer = a.q.x.stride_layer;
-    it.stride_head = a.q.x.stride_head;
-    it.stride_token = a.q.x.stride_token;
-    it.stride_block = a.q.x.stride_block;
-    it.block_table = a.q.x.block_table;
-    it.payload = a.payload;
-    it.capacity = a.capacity;
-    it.tokens = a.q.tokens;
-    it.num_phys_blocks = a.q.x.num_phys_blocks;
-    it.off_meta = (uint32_t)((a.q.meta - a.payload) / 16);
-    it.off_aux = (uint32_t)(a.off_aux / 16);
-    it.off_bodies = (uint32_t)(a.off_bodies / 16);
-    it.off_anchors = a.q.anchors ? (uint32_t)(((uint8_t *)a.q.anchors - a.payload) / 16) : 0;
-    it.chunk_base = (uint32_t)a.chunk_base;
-    it.wg_base = (uint32_t)a.wg_base;
-    it.k_wgs = (uint32_t)a.k_wgs;
-    it.total_wgs = (uint32_t)a.total_wgs;
-    it.flags = (uint32_t)(a.q.x.bt_shift | a.q.x.bt_wave << 5 | a.q.head_minor << 6 | a.is_v << 7 | a.tab << 8 | number << 16);
-    b.head_list[a.is_v] = a.q.head_list;
-    b.heads_covered[a.is_v] = (int)l.heads;
-    b.group[a.is_v] = a.q.group;
+    const bool any_table = table_slots(p) == kTableSlots;
+    const long long LH = (long long)p->model.layers * p->model.kv_heads;
+    const TableLayout t = table_layout(LH, p->has_table[0] + p->has_table[1]);
+    CoderLaunches all;
+    memset(&all, 0, sizeof all);
+    all.slots = table_slots(p) << 8;
+    for (int is_v = 0; is_v < 2; ++is_v) {
+        const int *list = p->has_table[is_v] ? (const int *)(dev_tables + t.head_list[is_v]) : nullptr;
+        for (int w = 0; w < 4; ++w) {
+            long long heads = 0;
+            if (p->has_table[is_v]) heads = p->width_count[is_v][w];
+            else if (kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k)) heads = LH;
+            if (heads == 0) continue;
+            CoderLaunch &l = all.of[all.n++];
+            l.is_v = is_v;
+            l.bits = kWidths[w];
+            l.group = is_v ? p->strat.group_v : p->strat.group_k;
+            l.tab = any_table ? 4 * is_v + w : is_v;
+            l.heads = (int)heads;
+            l.head_list = list;
+            if (list) list += heads;
+            all.slots |= 1 << l.tab;
+        }
+    }
+    return all;
 }
 
-// A batch without items.  `lead`: a launch of the window's leader, the first item to come; first: the window's first request.
-static CoderBatch coder_batch(const kvc_plan_t *p, const CoderLaunch &lead, int first, uint8_t *ws, uint64_t *out_bytes, int *status)
+// encode workgroups of all launches of a request; *k_wgs: of its K launches.  waves: chunks per workgroup (0: enc_waves)
+static long long encode_workgroups(const CoderLaunches &all, long long tokens, int waves, long long *k_wgs)
+{
+    long long wgs = 0;
+    *k_wgs = 0;
+    for (int j = 0; j < all.n; ++j) {
+        const int nw = waves ? waves : enc_waves(all.of[j].bits);
+        wgs += (all.of[j].heads * chunks_per_head(tokens) + nw - 1) / nw;
+        if (!all.of[j].is_v) *k_wgs = wgs;
+    }
+    return wgs;
+}
+
+// The items of a request, `number` behind the window's first, for all launches.
+static void coder_items(const kvc_plan_t *p, const CoderLaunches &all, const kvc_request *r, uint8_t *payload, long long capacity, int number,
+                        int waves, CoderItem out[kTableSlots])
+{
+    Geometry g;
+    geometry(p, r->tokens, &g);
+    const QuantArgs q[2] = {quant_args(p, r, 0, payload, g, nullptr, true), quant_args(p, r, 1, payload, g, nullptr, true)};
+    long long k_wgs, chunk_at = 0, wg_at = 0;
+    const long long total_wgs = encode_workgroups(all, r->tokens, waves, &k_wgs);
+    for (int j = 0; j < all.n; ++j) {
+        const CoderLaunch &l = all.of[j];
+        CoderItem &it = out[j];
+        const TensorView &x = q[l.is_v].x;
+        it.base = x.base;
+        it.stride_layer = x.stride_layer;
+        it.stride_head = x.stride_head;
+        it.stride_token = x.stride_token;
+        it.stride_block = x.stride_block;
+        it.block_table = x.block_table;
+        it.num_phys_blocks = x.num_phys_blocks;
+        it.payload = payload;
+        it.capacity = capacity;
+        it.tokens = r->tokens;
+        it.off_meta = (uint32_t)((l.is_v ? g.off_meta_v : g.off_meta_k) / 16);
+        it.off_aux = (uint32_t)(g.off_aux / 16);
+        it.off_bodies = (uint32_t)(g.off_codes_k / 16);
+        it.off_anchors = q[l.is_v].anchors ? (uint32_t)((l.is_v ? g.off_anchors_v : g.off_anchors_k) / 16) : 0;
+        it.chunk_base = (uint32_t)chunk_at;
+        it.wg_base = (uint32_t)wg_at;
+        it.k_wgs = (uint32_t)k_wgs;
+        it.total_wgs = (uint32_t)total_wgs;
+        it.flags = (uint32_t)(x.bt_shift | x.bt_wave << 5 | q[l.is_v].head_minor << 6 | l.is_v << 7 | l.tab << 8 | number << 16);
+        const int nw = waves ? waves : enc_waves(l.bits);
+        const long long chunks = l.heads * chunks_per_head(r->tokens);
+        chunk_at += chunks;
+        wg_at += (chunks + nw - 1) / nw;
+    }
+}
+
+static void add_item(CoderBatch &b, const CoderLaunch &l, const CoderItem &it)
+{
+    b.item[b.n++] = it;
+    b.head_list[l.is_v] = l.head_list;
+    b.heads_covered[l.is_v] = l.heads;
+    b.group[l.is_v] = l.group;
+}
+
+// A batch without items for a window from request `first` on whose rows lie as those of `lead` do.
+static CoderBatch coder_batch(const kvc_plan_t *p, const CoderLaunches &all, const kvc_request *lead, int first, void *workspace, uint64_t *out_bytes,
+                              int *status)
 {
     CoderBatch b;
     memset(&b, 0, sizeof b);
     b.ws_request = (long long)p->ws_request;
-    b.ws = ws + p->blob_bytes + first * b.ws_request;
+    b.ws = (uint8_t *)workspace + p->blob_bytes + first * b.ws_request;
     b.status = status + first;
     b.out_bytes = out_bytes ? (unsigned long long *)out_bytes + first : nullptr;
     b.ws_lut = (uint32_t)lut_offset(p);
@@ -796,78 +861,11 @@ static CoderBatch coder_batch(const kvc_plan_t *p, const CoderLaunch &lead, int 
     b.ws_state = (uint32_t)p->ws_state_off;
     b.heads = p->model.kv_heads;
     b.all_heads = p->model.layers * p->model.kv_heads;
-    b.dense = lead.a.q.dense;
-    b.rotate = lead.a.q.rotate;
-    b.anchor_shift = lead.a.q.anchor_shift;
-    b.builders = lead.a.builders;
-    b.apart = lead.a.apart;
-    b.slots = lead.a.slots;
+    b.dense = dense_layout(lead) ? 1 : 0;
+    b.rotate = p->strat.transform == KVC_T_HADAMARD ? 1 : 0;
+    while ((1 << b.anchor_shift) < p->strat.anchor_period) ++b.anchor_shift;
+    b.slots = all.slots;
     return b;
-}
-
-static int coder_launches(const kvc_plan_t *p, const kvc_request *r, uint8_t *payload, const Geometry &g, uint8_t *ws,
-                          long long capacity, uint64_t *out_bytes, int *status, bool compress, const uint8_t *dev_tables,
-                          CoderLaunch out[kTableSlots], int waves = 0, bool apart = false)
-{
-    const bool any_table = table_slots(p) == kTableSlots;
-    const long long LH = (long long)p->model.layers * p->model.kv_heads, cph = chunks_per_head(r->tokens);
-    const TableLayout t = table_layout(LH, p->has_table[0] + p->has_table[1]);
-    CoderArgs base;
-    memset(&base, 0, sizeof base);
-    base.payload = payload;
-    base.off_aux = g.off_aux;
-    base.off_dir = g.off_dir;
-    base.off_bodies = g.off_codes_k;
-    base.capacity = capacity;
-    base.total_chunks = g.chunks_k + g.chunks_v;
-    base.ws.sample = (uint16_t *)ws;
-    base.ws.lut = (uint16_t *)(ws + lut_offset(p));
-    base.ws.ticket = (uint32_t *)(ws + ticket_offset(p));
-    base.ws.state = (unsigned long long *)(ws + p->ws_state_off);
-    base.out_bytes = (unsigned long long *)out_bytes;
-    base.slots = table_slots(p) << 8;
-    int n = 0;
-    long long chunk_at = 0, wg_at = 0, k_wgs = 0;
-    for (int is_v = 0; is_v < 2; ++is_v) {
-        const QuantArgs q = quant_args(p, r, is_v, payload, g, status, compress);
-        const int group = is_v ? p->strat.group_v : p->strat.group_k;
-        const int *list = p->has_table[is_v] ? (const int *)(dev_tables + t.head_list[is_v]) : nullptr;
-        for (int w = 0; w < 4; ++w) {
-            long long heads = 0;
-            if (p->has_table[is_v]) heads = p->width_count[is_v][w];
-            else if (kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k)) heads = LH;
-            if (heads == 0) continue;
-            CoderLaunch &L = out[n++];
-            L.a = base;
-            L.a.q = q;
-            L.a.q.head_list = list;                    // (null without a table: the heads in their own order)
-            if (list) {
-                L.a.q.bits_before = (const long long *)(dev_tables + t.bits_before[is_v]);
-                list += heads;
-            }
-            L.bits = kWidths[w];
-            L.group = group;
-            L.a.is_v = is_v;
-            L.a.tab = any_table ? 4 * is_v + w : is_v;
-            base.slots |= 1 << L.a.tab;
-            L.heads = heads;
-            L.a.chunks = heads * cph;
-            L.a.chunk_base = chunk_at;
-            L.a.wg_base = wg_at;
-            const int nw = waves ? waves : enc_waves(L.bits);
-            chunk_at += L.a.chunks;
-            wg_at += (L.a.chunks + nw - 1) / nw;
-        }
-        if (!is_v) k_wgs = wg_at;
-    }
-    for (int i = 0; i < n; ++i) {
-        out[i].a.k_wgs = k_wgs;
-        out[i].a.total_wgs = wg_at;
-        out[i].a.slots = base.slots;
-        out[i].a.builders = compress ? n * kCandidates : 0;       // (a launch has a table of its own)
-        out[i].a.apart = apart ? out[i].a.builders : 0;
-    }
-    return n;
 }
 
 // Whether the coder's items can hold the places of a request (CoderItem); a payload beyond has more than 64 GB in front of the bodies.
@@ -943,12 +941,11 @@ static void prologue_item(const kvc_plan_t *plan, const kvc_request *r, uint8_t 
         return;
     }
     // candidate tables, ticket and scan state start from zero
-    CoderLaunch cl[kTableSlots];
-    coder_launches(plan, r, payload, g, ws, 0, nullptr, status, true, (const uint8_t *)workspace, cl);
-    const CoderArgs &c = cl[0].a;              // (a request has at least one K and one V launch)
-    it.zero = (uint32_t *)candidate_tables(c.ws.ticket, table_slots(plan) - 1);
-    it.zero_words = (c.ws.ticket - it.zero) + 64 + 2 * c.total_wgs + 2;
-    if (c.total_chunks == 0) {
+    uint32_t *ticket = (uint32_t *)(ws + ticket_offset(plan));
+    long long k_wgs;
+    it.zero = (uint32_t *)candidate_tables(ticket, table_slots(plan) - 1);
+    it.zero_words = (ticket - it.zero) + 64 + 2 * encode_workgroups(coder_launches(plan, (const uint8_t *)workspace), r->tokens, 0, &k_wgs) + 2;
+    if (r->tokens == 0) {
         // empty request: no workgroup runs that could close the directory and header
         put64((uint8_t *)it.header.w + 40, (uint64_t)g.off_codes_k);
         put64((uint8_t *)it.header.w + 112, (uint64_t)g.off_codes_k);
@@ -1062,6 +1059,7 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
         }
     }
     const int coder_limit = coder_window(plan, reqs, n), shared_limit = shared_window(plan, reqs, n);
+    const CoderLaunches all = coder_launches(plan, (const uint8_t *)workspace);
     for (int first = 0; first < n;) {
         int lead;
         int end = request_window(plan, reqs, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
@@ -1084,42 +1082,38 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
                                   (const uint8_t *)workspace, s));
             marks.window(first, end, 3);
         } else {
-            // the coder launches of every request of the window (the same list for all: K before V,
-            // widths ascending), then launch by launch over the requests together
-            CoderLaunch cl[kCoderBatch][kTableSlots];
-            int launches = 0;
+            // launch by launch (K before V, widths ascending) over the requests of the window together
+            CoderItem items[kCoderBatch][kTableSlots];
             const int waves = share ? shared_waves(plan, reqs, first, end) : 0;
             const bool apart = builders_apart(plan, reqs, first, end, share, waves, dense_layout(&reqs[lead]));
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);
-                Geometry g;
-                geometry(plan, reqs[i].tokens, &g);
-                uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
-                launches = coder_launches(plan, &reqs[i], (uint8_t *)payload + payload_off[i], g, ws,
-                                          (long long)(payload_off[i + 1] - payload_off[i]), out_bytes + i, dev_status + i, true,
-                                          (const uint8_t *)workspace, cl[k], waves, apart);
+                coder_items(plan, all, &reqs[i], (uint8_t *)payload + payload_off[i], (long long)(payload_off[i + 1] - payload_off[i]), i - first, waves,
+                            items[k]);
             }
-            const auto batch_for = [&](const CoderLaunch &l) { return coder_batch(plan, l, first, (uint8_t *)workspace, out_bytes, dev_status); };
+            CoderBatch none = coder_batch(plan, all, &reqs[lead], first, workspace, out_bytes, dev_status);
+            none.builders = all.n * kCandidates;          // (a launch has a table of its own)
+            none.apart = apart ? none.builders : 0;
             marks.window(first, end, 1);
             if (share) {
-                CoderBatch both = batch_for(cl[0][0]);
+                CoderBatch both = none;
                 for (int k = 0; k < end - first; ++k)
-                    for (int j = 0; j < 2; ++j) add_item(both, cl[k][j], window_item(first, end, lead, k) - first);
+                    for (int j = 0; j < 2; ++j) add_item(both, all.of[j], items[k][j]);
                 both.front = (unsigned)both.apart;
                 both.waves = waves;
-                KVC_TRY(launch_encode_section(2, cl[0][0].bits, cl[0][0].group, dt, both, s));
+                KVC_TRY(launch_encode_section(2, all.of[0].bits, all.of[0].group, dt, both, s));
                 marks.window(first, end, 2);
                 marks.window(first, end, 3);
                 first = end;
                 continue;
             }
             for (int is_v = 0; is_v < 2; ++is_v) {
-                for (int j = 0; j < launches; ++j) {
-                    if (cl[0][j].a.is_v != is_v) continue;
-                    CoderBatch b = batch_for(cl[0][j]);
-                    for (int k = 0; k < end - first; ++k) add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
+                for (int j = 0; j < all.n; ++j) {
+                    if (all.of[j].is_v != is_v) continue;
+                    CoderBatch b = none;
+                    for (int k = 0; k < end - first; ++k) add_item(b, all.of[j], items[k][j]);
                     b.front = j == 0 ? (unsigned)b.apart : 0;         // (the tables of all launches are built in the first)
-                    KVC_TRY(launch_encode_section(is_v, cl[0][j].bits, cl[0][j].group, dt, b, s));
+                    KVC_TRY(launch_encode_section(is_v, all.of[j].bits, all.of[j].group, dt, b, s));
                 }
                 marks.window(first, end, 2 + is_v);
             }
@@ -1268,6 +1262,7 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
     }
     const int shared_limit = shared_window(plan, dst, n);
     const int coder_limit = common_widths(plan) == 2 ? shared_limit : coder_window(plan, dst, n);
+    const CoderLaunches all = coder_launches(plan, (const uint8_t *)workspace);
     for (int first = 0; first < n;) {
         int lead;
         const int end = request_window(plan, dst, n, first, st.codec ? coder_limit : kQuantBatch, &lead);
@@ -1280,29 +1275,24 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                                   (const uint8_t *)workspace, s));
             marks.window(first, end, 3);
         } else {
-            CoderLaunch cl[kCoderBatch][kTableSlots];
-            int launches = 0;
+            CoderItem items[kCoderBatch][kTableSlots];
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);
-                Geometry g;
-                geometry(plan, dst[i].tokens, &g);
-                uint8_t *ws = (uint8_t *)workspace + plan->blob_bytes + (size_t)i * plan->ws_request;
-                launches = coder_launches(plan, &dst[i], (uint8_t *)payload + payload_off[i], g, ws,
-                                          (long long)(payload_off[i + 1] - payload_off[i]), nullptr, dev_status + i, false,
-                                          (const uint8_t *)workspace, cl[k]);
+                coder_items(plan, all, &dst[i], (uint8_t *)const_cast<void *>(payload) + payload_off[i], (long long)(payload_off[i + 1] - payload_off[i]),
+                            i - first, 0, items[k]);
             }
-            const auto batch_for = [&](const CoderLaunch &l) { return coder_batch(plan, l, first, (uint8_t *)workspace, nullptr, dev_status); };
+            const CoderBatch none = coder_batch(plan, all, &dst[lead], first, workspace, nullptr, dev_status);
             marks.window(first, end, 1);
             if (widths_share(plan, dst, first, end, lead, shared_limit)) {
                 // width by width, K and V together
                 for (int w = 0; w < 4; ++w) {
-                    CoderBatch b = batch_for(cl[0][0]);
+                    CoderBatch b = none;
                     int kinds = 0;                        // bit 0: K, bit 1: V
                     for (int k = 0; k < end - first; ++k)
-                        for (int j = 0; j < launches; ++j)
-                            if (cl[k][j].bits == kWidths[3 - w]) {
-                                add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
-                                kinds |= 1 << cl[k][j].a.is_v;
+                        for (int j = 0; j < all.n; ++j)
+                            if (all.of[j].bits == kWidths[3 - w]) {
+                                add_item(b, all.of[j], items[k][j]);
+                                kinds |= 1 << all.of[j].is_v;
                             }
                     if (b.n > 0) KVC_TRY(launch_decode_section(kinds == 3 ? 2 : kinds - 1, kWidths[3 - w], dt, b, s));
                 }
@@ -1312,11 +1302,11 @@ extern "C" int kvc_decompress(const kvc_plan_t *plan, const void *payload, const
                 continue;
             }
             for (int is_v = 0; is_v < 2; ++is_v) {
-                for (int j = 0; j < launches; ++j) {
-                    if (cl[0][j].a.is_v != is_v) continue;
-                    CoderBatch b = batch_for(cl[0][j]);
-                    for (int k = 0; k < end - first; ++k) add_item(b, cl[k][j], window_item(first, end, lead, k) - first);
-                    KVC_TRY(launch_decode_section(is_v, cl[0][j].bits, dt, b, s));
+                for (int j = 0; j < all.n; ++j) {
+                    if (all.of[j].is_v != is_v) continue;
+                    CoderBatch b = none;
+                    for (int k = 0; k < end - first; ++k) add_item(b, all.of[j], items[k][j]);
+                    KVC_TRY(launch_decode_section(is_v, all.of[j].bits, dt, b, s));
                 }
                 marks.window(first, end, 2 + is_v);
             }

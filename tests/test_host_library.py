@@ -266,6 +266,17 @@ def test_build_check_finds_kernels_over_their_registers(tmp_path):
         assert build.over_budget(str(p)) == ([(name, regs, want if want > 1 else 96 if "ILi8" in name else 80)] if want else []), name
 
 
+def test_build_refuses_large_stack_frames(tmp_path):
+    """Host functions with more than 44 KB of stack do not compile; the calls, which need 37, do (they are built)."""
+    import subprocess
+    from paper_2605_13734_amd import build
+    for kb, ok in ((40, True), (64, False)):
+        src = tmp_path / ("s%d.hip" % kb)
+        src.write_text("void use(char *);\nextern \"C\" int f(int n) { char big[%d]; use(big); return big[n]; }\n" % (kb << 10))
+        r = subprocess.run(["hipcc"] + build.FLAGS + ["-c", str(src), "-o", str(tmp_path / "s.o")], capture_output=True, text=True)
+        assert (r.returncode == 0) == ok, r.stderr
+
+
 def test_build_check_finds_spilled_scalars(tmp_path):
     """The build's check of the coder's scalar registers, as the assembly's notes count them."""
     from paper_2605_13734_amd import build
