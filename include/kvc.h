@@ -291,8 +291,8 @@ int kvc_stream_probe(int mode, const void *src, void *dst, int64_t rows, int32_t
  *   counts[5]     x - zero read from a packed fp16 pair: all pairs of finite fp16 values
  *   counts[6]     float -> byte with insertion: round-to-nearest-even, all floats in [0, 255]
  *   counts[7]     workgroups of the encoder's prefix sum that do not end as they should when one of them
- *                 starts late, never starts or never reports (the device memory of this check is static: one
- *                 self-test at a time per GPU)
+ *                 starts late, never starts or never reports, and waves that do not when a code table comes late or never
+ *                 (the device memory of these checks is static: one self-test at a time per GPU)
  * `counts` is DEVICE memory, KVC_SELFTEST_COUNTS 64-bit words, 8-byte aligned, owned by the
  * caller; it is cleared and filled on `stream` (asynchronous: synchronize before reading).
  * Returns KVC_OK, KVC_ERR_ARG for a null pointer, KVC_ERR_DEVICE if a launch failed.

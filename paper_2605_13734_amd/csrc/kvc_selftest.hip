@@ -1,8 +1,8 @@
 // Exhaustive device-side checks of the arithmetic shortcuts the quantizer kernels rely on.
 // Each check counts, over the whole domain on which the kernels use a shortcut, the inputs for
 // which it differs from the plain IEEE operation it stands for; all counts must be zero.
-// The last count is for the waits of the encoder's prefix sum.
-#include "kvc_scan.h"
+// The last count is for the waits of the encoder's prefix sum and of its code tables.
+#include "kvc_huff_fetch.h"
 
 namespace kvc {
 
@@ -216,6 +216,75 @@ __global__ __launch_bounds__(64) void selftest_scan_open_kernel(unsigned long lo
     if (!good) atomicAdd(slot, 1ull);
 }
 
+// ---- the wait for a code table (kvc_huff_fetch.h) ----------------------------------------------------
+
+static __device__ struct __attribute__((aligned(128))) TableTestMemory {
+    CandidateTables tables[1];                     // (right in front of the ticket)
+    uint32_t ticket[64];
+    int status;
+} table_test;
+
+__device__ __forceinline__ CoderArgs table_test_args()
+{
+    CoderArgs a = {};
+    a.ws.ticket = table_test.ticket;
+    a.q.status = &table_test.status;
+    return a;
+}
+
+__device__ __forceinline__ uint32_t table_test_entry(int word) { return 0x30005000u | (uint32_t)(2 * word + 1) << 16 | (uint32_t)(2 * word); }
+
+__global__ __launch_bounds__(256) void selftest_table_start_kernel()
+{
+    uint32_t *words = (uint32_t *)&table_test;
+    for (unsigned i = threadIdx.x; i < sizeof table_test / 4; i += 256) words[i] = 0;
+}
+
+// Workgroup 0, four waves, waits for its table; workgroup 1 (where there is one) leaves it after `naps` times 3 us, the first
+// candidate too long and one word of the second later than all others, and `short_of` words of it never.
+// there: whether all four waves have to find it, or have to give up within 50 ms.
+__global__ __launch_bounds__(256) void selftest_table_wait_kernel(unsigned long long *slot, int limit, int naps, int short_of, int there)
+{
+    const CoderArgs a = table_test_args();
+    const int tid = threadIdx.x;
+    CandidateTables *tables = candidate_tables(a.ws.ticket, 0);
+    if (blockIdx.x == 1) {
+        if (tid >= 64) return;
+        for (int i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(127);
+        if (tid == 0) {
+            __hip_atomic_store(&tables->state[1], kComplete, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&tables->state[0], kTooLong, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        for (int w = tid; w < 127; w += 64) __hip_atomic_store(&tables->entry[1][w], table_test_entry(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(127);
+        if (tid == 0 && short_of == 0) __hip_atomic_store(&tables->entry[1][127], table_test_entry(127), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    __shared__ EncTables enc;
+    __shared__ uint32_t state;
+    if (tid == 0) state = kNobody;
+    __syncthreads();
+    const long long start = wall_clock64();                     // (100 MHz)
+    int pick = -1;
+    const bool found = wait_for_table(a, enc, &state, pick, limit);
+    bool good = found == (there != 0) && (pick == -1 || (there && pick == 1));
+    good = good && (there || wall_clock64() - start < 5000000);
+    __syncthreads();
+    if (there) {
+        const uint32_t e = table_test_entry(tid >> 1) >> 16 * (tid & 1) & 0xffffu;
+        good = good && enc.code[tid] == (uint16_t)e && enc.len[tid] == (uint8_t)(e >> 12);
+    }
+    if (__builtin_amdgcn_ballot_w64(!good) != 0 && lane_id() == 0) atomicAdd(slot, 1ull);
+}
+
+// The status word and the carry say that somebody gave up, or nothing.
+__global__ __launch_bounds__(64) void selftest_table_end_kernel(unsigned long long *slot, int failed)
+{
+    if (threadIdx.x != 0) return;
+    const bool good = table_test.status == (failed ? KVC_DEV_SCAN_TIMEOUT : 0) && scan_failed(table_test_args()) == (failed != 0);
+    if (!good) atomicAdd(slot, 1ull);
+}
+
 } // namespace kvc
 
 extern "C" int kvc_selftest(uint64_t *counts, void *stream)
@@ -242,5 +311,15 @@ extern "C" int kvc_selftest(uint64_t *counts, void *stream)
     selftest_scan_start_kernel<<<1, 64, 0, s>>>();
     selftest_scan_absent_kernel<<<1, 64, 0, s>>>(c + 7);
     selftest_scan_open_kernel<<<1, 64, 0, s>>>(c + 7);
+    // a table that comes late, word by word; one that never does; one that stays a word short
+    selftest_table_start_kernel<<<1, 256, 0, s>>>();
+    selftest_table_wait_kernel<<<2, 256, 0, s>>>(c + 7, kSpinLimit, 600, 0, 1);
+    selftest_table_end_kernel<<<1, 64, 0, s>>>(c + 7, 0);
+    selftest_table_start_kernel<<<1, 256, 0, s>>>();
+    selftest_table_wait_kernel<<<1, 256, 0, s>>>(c + 7, kScanTestLimit, 0, 0, 0);
+    selftest_table_end_kernel<<<1, 64, 0, s>>>(c + 7, 1);
+    selftest_table_start_kernel<<<1, 256, 0, s>>>();
+    selftest_table_wait_kernel<<<2, 256, 0, s>>>(c + 7, kScanTestLimit, 0, 1, 0);
+    selftest_table_end_kernel<<<1, 64, 0, s>>>(c + 7, 1);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_DEVICE;
 }

@@ -30,3 +30,12 @@ def test_place_scan_waits():
     assert kvc.selftest(counts.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert counts.cpu().tolist()[7] == 0
+
+
+def test_code_table_waits():
+    """The encoder's wait for a code table (same count): found by all waves of a workgroup when its words come one after the other and
+    the first candidate is too long; given up, with status and carry word marked, where no table or one word of it never comes."""
+    counts = torch.full((kvc.SELFTEST_COUNTS,), -1, dtype=torch.int64, device="cuda:0")
+    assert kvc.selftest(counts.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert counts.cpu().tolist()[7] == 0
