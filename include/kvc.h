@@ -188,6 +188,8 @@ int kvc_workspace_init(const kvc_plan_t *plan, void *workspace, void *hip_stream
  *   hip_stream   hipStream_t the kernels are enqueued on (NULL = default stream)
  * Each payload is independent of the others in the batch (the profile is fixed per
  * request, section 3.1) and identical to compressing that request alone.
+ * With the codec, a request with 1 TB or more in front of its codes (metadata, tables, directory, anchors) or 2^31
+ * chunks is refused with KVC_ERR_UNSUPPORTED, here and by kvc_decompress.
  */
 int kvc_compress(const kvc_plan_t *plan, const kvc_request *reqs, int32_t n, void *payload,
                  const uint64_t *payload_off, uint64_t *out_bytes, int32_t *dev_status,
@@ -226,7 +228,7 @@ int kvc_compress_static(const kvc_plan_t *plan, const kvc_request *reqs, int32_t
  * The device checks each header (and width table) against the plan and sets KVC_DEV_BAD_HEADER,
  * writing nothing for that request, on a mismatch; a damaged table, directory or chunk sets
  * KVC_DEV_BAD_TABLE / KVC_DEV_BAD_CHUNK and the affected chunks are not written.  Host-visible
- * errors (KVC_ERR_ARG, KVC_ERR_CAPACITY) are returned before anything is launched.
+ * errors (KVC_ERR_ARG, KVC_ERR_CAPACITY, KVC_ERR_UNSUPPORTED) are returned before anything is launched.
  * Reconstruction: x^ = round(code*scale + zero) in the model dtype, then the inverse of stage T.
  */
 int kvc_decompress(const kvc_plan_t *plan, const void *payload, const uint64_t *payload_off,

@@ -822,15 +822,18 @@ static void coder_items(const kvc_plan_t *p, const CoderLaunches &all, const kvc
         it.payload = payload;
         it.capacity = capacity;
         it.tokens = r->tokens;
-        it.off_meta = (uint32_t)((l.is_v ? g.off_meta_v : g.off_meta_k) / 16);
-        it.off_aux = (uint32_t)(g.off_aux / 16);
-        it.off_bodies = (uint32_t)(g.off_codes_k / 16);
-        it.off_anchors = q[l.is_v].anchors ? (uint32_t)((l.is_v ? g.off_anchors_v : g.off_anchors_k) / 16) : 0;
+        const long long places[4] = {l.is_v ? g.off_meta_v : g.off_meta_k, g.off_aux, g.off_codes_k,
+                                     !q[l.is_v].anchors ? 0 : l.is_v ? g.off_anchors_v : g.off_anchors_k};
+        it.off_meta = (uint32_t)(places[0] / 16);
+        it.off_aux = (uint32_t)(places[1] / 16);
+        it.off_bodies = (uint32_t)(places[2] / 16);
+        it.off_anchors = (uint32_t)(places[3] / 16);
         it.chunk_base = (uint32_t)chunk_at;
         it.wg_base = (uint32_t)wg_at;
         it.k_wgs = (uint32_t)k_wgs;
         it.total_wgs = (uint32_t)total_wgs;
-        it.flags = (uint32_t)(x.bt_shift | x.bt_wave << 5 | q[l.is_v].head_minor << 6 | l.is_v << 7 | l.tab << 8 | number << 16);
+        it.flags = (uint32_t)(x.bt_shift | x.bt_wave << 5 | q[l.is_v].head_minor << 6 | l.is_v << 7 | l.tab << 8 | number << 11);
+        for (int k = 0; k < 4; ++k) it.flags |= (uint32_t)(places[k] >> 36) << (16 + 4 * k);
         const int nw = waves ? waves : enc_waves(l.bits);
         const long long chunks = l.heads * chunks_per_head(r->tokens);
         chunk_at += chunks;
@@ -868,8 +871,9 @@ static CoderBatch coder_batch(const kvc_plan_t *p, const CoderLaunches &all, con
     return b;
 }
 
-// Whether the coder's items can hold the places of a request (CoderItem); a payload beyond has more than 64 GB in front of the bodies.
-static bool places_fit(const Geometry &g) { return g.off_codes_k >> 36 == 0 && (g.chunks_k + g.chunks_v) >> 31 == 0; }
+// Whether the coder's items can hold the places of a request (CoderItem).  What they cannot is beyond any buffer of a GPU, and a launch
+// has fewer than 2^26 chunks (2^24 workgroups of 256 threads).
+static bool places_fit(const Geometry &g) { return g.off_codes_k >> 40 == 0 && (g.chunks_k + g.chunks_v) >> 31 == 0; }
 
 static int check_batch(const kvc_plan_t *p, const kvc_request *reqs, int32_t n, const void *payload,
                        const uint64_t *off, const void *workspace)

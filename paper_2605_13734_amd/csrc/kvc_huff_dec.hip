@@ -361,7 +361,7 @@ template <int BITS, int DT, int KV> static int decode_launch(const CoderBatch &b
     }
     if (need == 0) return KVC_OK;
     const dim3 grid(need), block(NW * 64);
-    const int tr = b.rotate ? 1 : !b.item[0].off_anchors ? 0 : b.anchor_shift >= 5 ? 2 : 3;
+    const int tr = b.rotate ? 1 : !item_has_anchors(b.item[0]) ? 0 : b.anchor_shift >= 5 ? 2 : 3;
     const DecodeShape shape = decode_shape<BITS>(need, KV == 2, b.dense != 0, tr != 0, b.group[b.item[0].flags >> 7 & 1], b.n <= (KV == 2 ? 2 : 1));
     close_places(placed.at, b.n, need, shape.run);
 #define KVC_DECODE(D, T) hipLaunchKernelGGL((decode_kernel<BITS, DT, KV, D, T>), grid, block, shape.lds, s, placed)

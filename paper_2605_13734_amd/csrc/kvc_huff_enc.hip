@@ -313,7 +313,7 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
     // transform (its code costs the plain path registers); both tensors together run without one only
     constexpr bool kPlain = KV != 1 || G == 32;
-    if (!b.rotate && !(b.item[0].off_anchors && kPlain)) {
+    if (!b.rotate && !(item_has_anchors(b.item[0]) && kPlain)) {
         if (b.dense) KVC_ENCODE(true, !kPlain, NW); else KVC_ENCODE(false, !kPlain, NW);
         return launched();
     }

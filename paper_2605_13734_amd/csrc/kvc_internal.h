@@ -320,15 +320,14 @@ struct CoderItem {
     long long capacity;
     long long tokens;
     int num_phys_blocks;
-    // of 16 bytes, inside the payload (what lies before the last of these is smaller than 64 GB wherever the bodies, which the format
-    // counts in the same units, are)
+    // inside the payload, of 16 bytes: the low words; four bits more of each are in `flags` (1 TB)
     uint32_t off_meta, off_aux, off_bodies, off_anchors;      // (off_anchors: 0 = no delta transform)
     uint32_t chunk_base, wg_base, k_wgs, total_wgs;
-    uint32_t flags;             // bits 4:0 TensorView::bt_shift, 5 bt_wave, 6 QuantArgs::head_minor, 7 is_v, 10:8 tab, 31:16 number of the
-                                // request behind the window's first
+    uint32_t flags;             // bits 4:0 TensorView::bt_shift, 5 bt_wave, 6 QuantArgs::head_minor, 7 is_v, 10:8 tab, 15:11 number of the
+                                // request behind the window's first, 19:16, 23:20, 27:24, 31:28 bits 35:32 of the places above
 };
 static_assert(sizeof(CoderItem) == 112, "what a batch of 32 has room for");
-constexpr int kCoderBatch = 32;     // (the argument block stays below 4 KB)
+constexpr int kCoderBatch = 32;     // (the argument block stays below 4 KB, a request's number has five bits)
 struct CoderBatch {
     CoderItem item[kCoderBatch];
     Places<kCoderBatch> at;             // (encoder, both tensors together: the items are the requests; set by the launcher)
@@ -353,9 +352,17 @@ struct CoderBatch {
                                         // first launch: CoderArgs::apart; others: none)
 };
 
+static inline bool item_has_anchors(const CoderItem &it) { return (it.off_anchors | (it.flags >> 28)) != 0; }
+
 static inline long long item_chunks(const CoderBatch &b, int item)
 {
     return b.heads_covered[(b.item[item].flags >> 7) & 1] * ((b.item[item].tokens + kChunkRows - 1) / kChunkRows);
+}
+
+// The k-th of an item's places inside the payload, in bytes; `low` is its low word.
+__host__ __device__ __forceinline__ long long item_place(uint32_t low, uint32_t flags, int k)
+{
+    return (long long)((unsigned long long)((flags >> (16 + 4 * k)) & 15u) << 32 | low) << 4;
 }
 
 // KV: the launch's tensor, K (0), V (1) or both (2).  AT_ONCE: what a wave's first loads need of the item is requested together, not
@@ -376,22 +383,22 @@ template <int KV, bool AT_ONCE = false> __device__ __forceinline__ CoderArgs cod
     a.q.x.bt_shift = it.flags & 31;
     a.q.x.num_phys_blocks = it.num_phys_blocks;
     a.q.x.bt_wave = (it.flags >> 5) & 1;
-    a.q.meta = it.payload + 16ll * it.off_meta;
+    a.q.meta = it.payload + item_place(it.off_meta, it.flags, 0);
     a.q.tokens = it.tokens;
     a.q.heads = b.heads;
     a.q.group = is_v ? b.group[1] : b.group[0];
     a.q.dense = b.dense;
     a.q.head_minor = (it.flags >> 6) & 1;
     a.q.rotate = b.rotate;
-    a.q.anchors = it.off_anchors ? (uint16_t *)(it.payload + 16ll * it.off_anchors) : nullptr;
+    a.q.anchors = it.off_anchors | (it.flags >> 28) ? (uint16_t *)(it.payload + item_place(it.off_anchors, it.flags, 3)) : nullptr;
     a.q.anchor_shift = b.anchor_shift;
     a.q.head_list = is_v ? b.head_list[1] : b.head_list[0];
-    const int request = (int)(it.flags >> 16);
+    const int request = (int)((it.flags >> 11) & 31);
     a.q.status = b.status + request;
     a.payload = it.payload;
-    a.off_aux = 16ll * it.off_aux;
+    a.off_aux = item_place(it.off_aux, it.flags, 1);
     a.off_dir = a.off_aux + 256 * (b.slots >> 8);
-    a.off_bodies = 16ll * it.off_bodies;
+    a.off_bodies = item_place(it.off_bodies, it.flags, 2);
     a.capacity = it.capacity;
     const uint32_t per_head = (uint32_t)((unsigned long long)(it.tokens + kChunkRows - 1) / kChunkRows);     // (no request has 2^31 chunks)
     a.chunks = (uint32_t)(is_v ? b.heads_covered[1] : b.heads_covered[0]) * per_head;

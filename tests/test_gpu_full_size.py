@@ -283,3 +283,37 @@ def test_paged_128k_with_lossless_stage(ref):
             check_sampled_bodies(ref, buf, lambda l, kv, h: logical(pool, idx1, l, kv, h), L, H, T, 1, 4, 4, 32, 32, picks)
         del buf
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+def test_places_beyond_64_gb():
+    """More than 64 GB of metadata and anchors in front of the codes: 1024 heads that are all the same 2^19.5 tokens (strides of zero), runs
+    of 8 tokens.  The reconstruction, where the heads overwrite each other with the same rows, is that of a single head."""
+    T, L, H = 720_000, 128, 8
+    if torch.cuda.mem_get_info()[0] < 140 << 30:
+        pytest.skip("needs 140 GB of free device memory")
+    kw = dict(codec=kvc.CODEC_HUFF8, max_tokens=T, max_batch=1, transform=2, anchor_period=8)
+    s = torch.cuda.current_stream().cuda_stream
+    x = kvgen.make_kv(5, 1, 1, 128, T, torch.float16, "cuda")
+    got = []
+    for layers, heads in ((1, 1), (L, H)):
+        plan = kvc.Plan(kvc.F16, layers, heads, 128, 2, 2, 32, 32, **kw)
+        size = plan.payload_size(T)[0]
+        payload = torch.empty(size, dtype=torch.uint8, device="cuda")
+        words = torch.zeros(2, dtype=torch.int64, device="cuda")
+        ws = torch.empty(plan.workspace_size(), dtype=torch.uint8, device="cuda")
+        y = torch.zeros_like(x)
+        kvc.compress(plan, [kvc.request(x[0, 0].data_ptr(), x[0, 1].data_ptr(), T, 0, 0, 128)], payload.data_ptr(), [0, size], words.data_ptr(),
+                     words[1:].data_ptr(), ws.data_ptr(), s)
+        torch.cuda.synchronize()
+        assert words.tolist()[1] == 0
+        if layers > 1:
+            rc, _, _, _, total, sec = kvc.payload_inspect(payload[:128].cpu().numpy())
+            assert rc == 0 and sec[6] > 1 << 36 and total == words.tolist()[0] <= size
+        kvc.decompress(plan, payload.data_ptr(), [0, size], [kvc.request(y[0, 0].data_ptr(), y[0, 1].data_ptr(), T, 0, 0, 128)], words[1:].data_ptr(),
+                       ws.data_ptr(), s)
+        torch.cuda.synchronize()
+        assert words.tolist()[1] == 0
+        got.append(y)
+        del payload, ws
+        torch.cuda.empty_cache()
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))

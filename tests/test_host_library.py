@@ -124,6 +124,24 @@ def test_host_errors_before_launch(lib):
     assert e.value.status == -2                                   # block size not a power of two
 
 
+@pytest.mark.parametrize("T,want", [(1 << 18, -6), (1 << 21, -6), (12 << 20, -2)])
+def test_places_far_behind_the_header(lib, T, want):
+    """2^10 heads with runs of 8 tokens and groups of 32: 96 bytes per row and tensor pair in front of the codes, 24 GB, 192 GB and 1.1 TB.
+    The first two are accepted and end at the device that is not there, the third is refused."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch")
+    plan = kvc.Plan(1, 128, 8, 128, 2, 2, 32, 32, 1, max_tokens=T, max_batch=1, transform=2, anchor_period=8)
+    size = plan.payload_size(T)[0]
+    assert (size - (T << 16) >= 1 << 40) == (want == -2) and ((T << 10) * 96 > 1 << 36) == (T > 1 << 18)
+    r = kvc.request(0x100000, 0x200000, T, 0, 0, 128)
+    for call in (lambda: kvc.compress(plan, [r], 0x10000, [0, size], 0x100, 0x200, 0x100000),
+                 lambda: kvc.decompress(plan, 0x10000, [0, size], [r], 0x200, 0x100000)):
+        with pytest.raises(kvc.KvcError) as e:
+            call()
+        assert e.value.status == want
+
+
 def test_newer_entry_points_refuse_on_the_host(lib):
     """kvc_stream_probe, kvc_workspace_init, kvc_table_bytes and kvc_compress_static: what the host can
     see is refused before a device is touched (there is none here)."""
