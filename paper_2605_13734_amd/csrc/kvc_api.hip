@@ -724,39 +724,6 @@ static int shared_waves(const kvc_plan_t *p, const kvc_request *reqs, int first,
     return chunks > 8 * kUnits && chunks <= 12 * kUnits && largest <= 10 * kUnits ? 0 : 8;
 }
 
-// Whether the workgroups that build the code tables of a window's requests have no chunks of their own.  They are better apart: the
-// scan starts at the first tickets, and those who build have their chunks late.  But where the window's first launch is resident at
-// once and with them it would not be, as many workgroups would start when the first of the others end.  Compress call, fp16, 4
-// bits, groups of 32, with chunks / apart (in a launch of their own before): one request of 8 heads, 30000 tokens 55.2 / 51.7 us, 32768
-// (exactly resident) 57.4 / 68.1 (66.1), 36000 76.8 / 72.7; four of 8192 56.6 / 63.5, of 24000 132.7 / 122.7, 32 of 256 heads and 512 to
-// 2048 tokens 1448 / 1348 (1365); 8 bits, 12288 tokens 58.9 / 53.7, 16384 64.2 / 74.9, 20000 85.3 / 80.3; groups of 128, 16384 tokens
-// 45.3 / 54.1, 32768 79.1 / 74.9; half of the heads at 2 bits, half at 8, 64 heads of 8192 166.9 / 162.3.
-static bool builders_apart(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, bool share, int waves, bool dense)
-{
-    int tables = 0, bits = 0;                            // of the first launch (K): its width and heads
-    long long heads = 0;
-    for (int is_v = 0; is_v < 2; ++is_v)
-        for (int w = 0; w < 4; ++w) {
-            const long long has = p->has_table[is_v] ? p->width_count[is_v][w]
-                                  : kWidths[w] == (is_v ? p->strat.bits_v : p->strat.bits_k) ? (long long)p->model.layers * p->model.kv_heads : 0;
-            if (has == 0) continue;
-            if (tables++ > 0) continue;
-            bits = kWidths[w];
-            heads = has;
-        }
-    const int nw = waves ? waves : enc_waves(bits), builders = tables * kCandidates;
-    long long wgs = 0;
-    for (int i = first; i < end; ++i) {
-        const long long w = ((share ? 2 : 1) * heads * chunks_per_head(reqs[i].tokens) + nw - 1) / nw;
-        if (w < builders) return true;                   // (not enough of them)
-        wgs += w;
-    }
-    // waves of a compute unit: 16 KB of LDS each at 8 bits, otherwise what the registers leave room for
-    const int unit = p->strat.group_k == 128 ? (p->model.dtype == KVC_BF16 && !dense ? 4 : 8) : bits == 8 ? 8 : p->strat.group_k == 64 ? 12 : 16;
-    const long long resident = (long long)kUnits * unit / nw;
-    return wgs > resident || wgs + (long long)(end - first) * builders <= resident;
-}
-
 static CoderLaunches coder_launches(const kvc_plan_t *p, const uint8_t *dev_tables)
 {
     const bool any_table = table_slots(p) == kTableSlots;
@@ -847,6 +814,28 @@ static void add_item(CoderBatch &b, const CoderLaunch &l, const CoderItem &it)
     b.head_list[l.is_v] = l.head_list;
     b.heads_covered[l.is_v] = l.heads;
     b.group[l.is_v] = l.group;
+}
+
+// Whether the workgroups that build the code tables of a window's requests have no chunks of their own.  They are better apart: the
+// scan starts at the first tickets, and those who build have their chunks late.  But where the window's first launch is resident at
+// once and with them it would not be, as many workgroups would start when the first of the others end.  Compress call, fp16, 4
+// bits, groups of 32, with chunks / apart (in a launch of their own before): one request of 8 heads, 30000 tokens 55.2 / 51.7 us, 32768
+// (exactly resident) 57.4 / 68.1 (66.1), 36000 76.8 / 72.7; four of 8192 56.6 / 63.5, of 24000 132.7 / 122.7; 8 bits, 12288 tokens 58.9 /
+// 53.7, 16384 64.2 / 74.9, 20000 85.3 / 80.3; groups of 128, 16384 tokens 45.3 / 54.1, 32768 79.1 / 74.9; half of the heads at 2 bits,
+// half at 8, 64 heads of 8192 166.9 / 162.3.  (32 requests of 256 heads and 512 to 2048 tokens, in windows of twelve, 1448 / 1348 (1365).)
+// first: the window's first launch; how many of its workgroups are resident the runtime knows, by kernel.  kv, dtype: of that launch
+static bool builders_apart(const CoderBatch &first, const CoderLaunch &l, int kv, int dtype, int builders)
+{
+    const int nw = first.waves ? first.waves : enc_waves(l.bits);
+    long long wgs = 0;
+    for (int i = 0; i < first.n; i += kv == 2 ? 2 : 1) {
+        const long long w = kv == 2 ? (long long)first.item[i].total_wgs : (item_chunks(first, i) + nw - 1) / nw;
+        if (w < builders) return true;                   // (not enough of them)
+        wgs += w;
+    }
+    int resident = 0;
+    if (launch_encode_section(kv, l.bits, l.group, dtype, first, nullptr, &resident) != KVC_OK) return true;
+    return wgs > resident || wgs + (long long)(kv == 2 ? first.n / 2 : first.n) * builders <= resident;
 }
 
 // A batch without items for a window from request `first` on whose rows lie as those of `lead` do.
@@ -1089,34 +1078,33 @@ static int compress_on(const kvc_plan_t *plan, const kvc_request *reqs, int32_t 
             // launch by launch (K before V, widths ascending) over the requests of the window together
             CoderItem items[kCoderBatch][kTableSlots];
             const int waves = share ? shared_waves(plan, reqs, first, end) : 0;
-            const bool apart = builders_apart(plan, reqs, first, end, share, waves, dense_layout(&reqs[lead]));
             for (int k = 0; k < end - first; ++k) {
                 const int i = window_item(first, end, lead, k);
                 coder_items(plan, all, &reqs[i], (uint8_t *)payload + payload_off[i], (long long)(payload_off[i + 1] - payload_off[i]), i - first, waves,
                             items[k]);
             }
             CoderBatch none = coder_batch(plan, all, &reqs[lead], first, workspace, out_bytes, dev_status);
-            none.builders = all.n * kCandidates;          // (a launch has a table of its own)
-            none.apart = apart ? none.builders : 0;
+            none.waves = waves;
+            // the first launch: K of the narrowest width, or K and V; it builds the tables of all
+            CoderBatch b = none;
+            for (int k = 0; k < end - first; ++k)
+                for (int j = 0; j < (share ? 2 : 1); ++j) add_item(b, all.of[j], items[k][j]);
+            b.builders = none.builders = all.n * kCandidates;          // (a launch has a table of its own)
+            if (builders_apart(b, all.of[0], share ? 2 : 0, dt, none.builders)) b.apart = none.apart = none.builders;
+            b.front = (unsigned)none.apart;
             marks.window(first, end, 1);
+            KVC_TRY(launch_encode_section(share ? 2 : 0, all.of[0].bits, all.of[0].group, dt, b, s));
             if (share) {
-                CoderBatch both = none;
-                for (int k = 0; k < end - first; ++k)
-                    for (int j = 0; j < 2; ++j) add_item(both, all.of[j], items[k][j]);
-                both.front = (unsigned)both.apart;
-                both.waves = waves;
-                KVC_TRY(launch_encode_section(2, all.of[0].bits, all.of[0].group, dt, both, s));
                 marks.window(first, end, 2);
                 marks.window(first, end, 3);
                 first = end;
                 continue;
             }
             for (int is_v = 0; is_v < 2; ++is_v) {
-                for (int j = 0; j < all.n; ++j) {
+                for (int j = 1; j < all.n; ++j) {
                     if (all.of[j].is_v != is_v) continue;
-                    CoderBatch b = none;
+                    b = none;
                     for (int k = 0; k < end - first; ++k) add_item(b, all.of[j], items[k][j]);
-                    b.front = j == 0 ? (unsigned)b.apart : 0;         // (the tables of all launches are built in the first)
                     KVC_TRY(launch_encode_section(is_v, all.of[j].bits, all.of[j].group, dt, b, s));
                 }
                 marks.window(first, end, 2 + is_v);

@@ -6,6 +6,8 @@
 #include "kvc_huff_build.h"
 #include "kvc_huff_fetch.h"
 
+#include <atomic>
+
 #ifndef KVC_BITS
 #error "compile with -DKVC_BITS=2, 3, 4 or 8"
 #endif
@@ -295,7 +297,27 @@ static unsigned encode_hold(int bits, int group, bool is_v, bool rotate, unsigne
     return rotate && !is_v && group == 64 && bits < 8 && wgs > 3 * 256 && wgs <= 5 * 256 ? 40000 : 0;
 }
 
-template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(const CoderBatch &b, hipStream_t s)
+// Launches the kernel, or (with `resident`) says how many of its workgroups the chip has at once: asked once per kernel, where a launch
+// has no LDS besides the kernel's own; 0 where there is no answer.
+template <void (*KERNEL)(CoderBatch), int NW> static int encode_start(const CoderBatch &placed, unsigned wgs, unsigned lds, hipStream_t s, int *resident)
+{
+    if (resident) {
+        static std::atomic<int> known{-1};
+        int per_unit = lds == 0 ? known.load(std::memory_order_relaxed) : -1;
+        if (per_unit < 0) {
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_unit, (const void *)KERNEL, NW * 64, lds) != hipSuccess) {
+                (void)hipGetLastError();
+                per_unit = 0;
+            } else if (lds == 0) known.store(per_unit, std::memory_order_relaxed);
+        }
+        *resident = per_unit * 256;
+        return KVC_OK;
+    }
+    hipLaunchKernelGGL(KERNEL, dim3(wgs), dim3(NW * 64), lds, s, placed);
+    return launched();
+}
+
+template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(const CoderBatch &b, hipStream_t s, int *resident)
 {
     CoderBatch placed = b;
     if (KV == 2) placed.n = b.n / 2;                  // requests
@@ -306,21 +328,19 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
     }
     close_places(placed.at, placed.n, need, 0);
     const unsigned front = placed.front * (unsigned)placed.n;
+    if (resident) *resident = 0;
     if (front + need == 0) return KVC_OK;
-    const dim3 grid(front + need), block(NW * 64);
     const unsigned lds = encode_hold(BITS, G, KV == 1, b.rotate != 0, need);
-#define KVC_ENCODE(D, ...) hipLaunchKernelGGL((encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>), grid, block, lds, s, placed)
+#define KVC_ENCODE(D, ...) return encode_start<encode_kernel<BITS, G, DT, KV, D, __VA_ARGS__>, NW>(placed, front + need, lds, s, resident)
     // the K kernels and the V kernels for groups of 32 channels have variants for launches without a
     // transform (its code costs the plain path registers); both tensors together run without one only
     constexpr bool kPlain = KV != 1 || G == 32;
     if (!b.rotate && !(item_has_anchors(b.item[0]) && kPlain)) {
         if (b.dense) KVC_ENCODE(true, !kPlain, NW); else KVC_ENCODE(false, !kPlain, NW);
-        return launched();
     }
     if constexpr (KV != 2) {
         if (b.rotate) { if (b.dense) KVC_ENCODE(true, false, NW, true); else KVC_ENCODE(false, false, NW, true); }
         else if (b.dense) KVC_ENCODE(true, true, NW); else KVC_ENCODE(false, true, NW);
-        return launched();
     }
     return KVC_ERR_UNSUPPORTED;
 #undef KVC_ENCODE
@@ -328,19 +348,19 @@ template <int BITS, int G, int DT, int KV, int NW> static int encode_launch(cons
 
 // (the kernels for both tensors come with four and, where the registers allow, with eight chunks per
 // workgroup, see shared_waves)
-template <int BITS, int G, int DT, int KV> static int encode_waves(const CoderBatch &b, hipStream_t s)
+template <int BITS, int G, int DT, int KV> static int encode_waves(const CoderBatch &b, hipStream_t s, int *resident)
 {
     if constexpr (KV == 2 && G == 32 && BITS != 8)
-        if (b.waves == 8) return encode_launch<BITS, G, DT, KV, 8>(b, s);
-    return encode_launch<BITS, G, DT, KV, enc_waves(BITS)>(b, s);
+        if (b.waves == 8) return encode_launch<BITS, G, DT, KV, 8>(b, s, resident);
+    return encode_launch<BITS, G, DT, KV, enc_waves(BITS)>(b, s, resident);
 }
 
-template <int DT, int KV> static int encode_g(int group, const CoderBatch &a, hipStream_t s)
+template <int DT, int KV> static int encode_g(int group, const CoderBatch &a, hipStream_t s, int *resident)
 {
     switch (group) {
-    case 32: return encode_waves<KVC_BITS, 32, DT, KV>(a, s);
-    case 64: return encode_waves<KVC_BITS, 64, DT, KV>(a, s);
-    case 128: return encode_waves<KVC_BITS, 128, DT, KV>(a, s);
+    case 32: return encode_waves<KVC_BITS, 32, DT, KV>(a, s, resident);
+    case 64: return encode_waves<KVC_BITS, 64, DT, KV>(a, s, resident);
+    case 128: return encode_waves<KVC_BITS, 128, DT, KV>(a, s, resident);
     }
     return KVC_ERR_UNSUPPORTED;
 }
@@ -348,13 +368,13 @@ template <int DT, int KV> static int encode_g(int group, const CoderBatch &a, hi
 #define KVC_PASTE2(a, b) a##b
 #define KVC_PASTE(a, b) KVC_PASTE2(a, b)
 
-int KVC_PASTE(launch_encode_bits, KVC_BITS)(int kv, int group, int dtype, const CoderBatch &a, hipStream_t s)
+int KVC_PASTE(launch_encode_bits, KVC_BITS)(int kv, int group, int dtype, const CoderBatch &a, hipStream_t s, int *resident)
 {
     switch (kv) {
-    case 0: return dtype == DT_F16 ? encode_g<DT_F16, 0>(group, a, s) : encode_g<DT_BF16, 0>(group, a, s);
-    case 1: return dtype == DT_F16 ? encode_g<DT_F16, 1>(group, a, s) : encode_g<DT_BF16, 1>(group, a, s);
+    case 0: return dtype == DT_F16 ? encode_g<DT_F16, 0>(group, a, s, resident) : encode_g<DT_BF16, 0>(group, a, s, resident);
+    case 1: return dtype == DT_F16 ? encode_g<DT_F16, 1>(group, a, s, resident) : encode_g<DT_BF16, 1>(group, a, s, resident);
     }
-    return dtype == DT_F16 ? encode_g<DT_F16, 2>(group, a, s) : encode_g<DT_BF16, 2>(group, a, s);
+    return dtype == DT_F16 ? encode_g<DT_F16, 2>(group, a, s, resident) : encode_g<DT_BF16, 2>(group, a, s, resident);
 }
 
 }  // namespace kvc

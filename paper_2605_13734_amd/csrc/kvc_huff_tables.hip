@@ -234,13 +234,13 @@ int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s)
     return launched();
 }
 
-int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &a, hipStream_t s)
+int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &a, hipStream_t s, int *resident)
 {
     switch (bits) {
-    case 2: return launch_encode_bits2(kv, group, dtype, a, s);
-    case 3: return launch_encode_bits3(kv, group, dtype, a, s);
-    case 4: return launch_encode_bits4(kv, group, dtype, a, s);
-    case 8: return launch_encode_bits8(kv, group, dtype, a, s);
+    case 2: return launch_encode_bits2(kv, group, dtype, a, s, resident);
+    case 3: return launch_encode_bits3(kv, group, dtype, a, s, resident);
+    case 4: return launch_encode_bits4(kv, group, dtype, a, s, resident);
+    case 8: return launch_encode_bits8(kv, group, dtype, a, s, resident);
     }
     return KVC_ERR_UNSUPPORTED;
 }

@@ -476,12 +476,13 @@ static_assert(sizeof(DecodeSetupArgs) <= 4000, "kernel arguments are limited to 
 
 int launch_setup(int dtype, const SetupArgs &a, hipStream_t s);
 // kv: the tensor of the launch, K (0), V (1) or both (2: a K and a V item of every request in turn)
-int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &b, hipStream_t s);
+// resident: launch nothing, but say how many workgroups of the kernel the chip has at once (0: unknown)
+int launch_encode_section(int kv, int bits, int group, int dtype, const CoderBatch &b, hipStream_t s, int *resident = nullptr);
 int launch_decode_setup(const DecodeSetupArgs &a, hipStream_t s);
 int launch_decode_section(int kv, int bits, int dtype, const CoderBatch &b, hipStream_t s);
 // one translation unit per code width (kvc_huff_enc.hip / kvc_huff_dec.hip compiled with -DKVC_BITS=...)
 #define KVC_DECLARE_CODER(B)                                                                  \
-    int launch_encode_bits##B(int kv, int group, int dtype, const CoderBatch &b, hipStream_t s); \
+    int launch_encode_bits##B(int kv, int group, int dtype, const CoderBatch &b, hipStream_t s, int *resident); \
     int launch_decode_bits##B(int kv, int dtype, const CoderBatch &b, hipStream_t s);
 KVC_DECLARE_CODER(2) KVC_DECLARE_CODER(3) KVC_DECLARE_CODER(4) KVC_DECLARE_CODER(8)
 #undef KVC_DECLARE_CODER
