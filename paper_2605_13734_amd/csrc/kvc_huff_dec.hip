@@ -143,15 +143,16 @@ __global__ __launch_bounds__(ChunkGeom<BITS>::kDecWaves * 64) void decode_kernel
     using Dec = DecGeom<BITS>;
     constexpr int W = Geo::kWords, NW = Geo::kDecWaves;
     unsigned wg;
-    // What the batch has for all items comes with the table of places, and an item's members in one trip: at 4 bits only (one layer of
-    // 32k tokens 41.8 -> 41.3 us; half of the heads at 8 and half at 2 bits 313.2 -> 315.8).
-    constexpr bool kAtOnce = BITS == 4;
+    // What the batch has for all items comes with the table of places, and an item's members in one trip.  Decompress calls without / with,
+    // one layer of 1000 tokens, of 32k, 2^21 rows, seven requests of 2^17.6, fp16: 2 bits 16.4 / 16.1, 37.5 / 37.1, 216 / 216, 156.9 / 156.2 us; 3
+    // bits 14.2 / 14.0, 34.4 / 34.1, 210 / 210, 155.9 / 155.4; 4 bits 19.6 / 19.4, 41.9 / 41.4, 247 / 246, 179 / 177; 8 bits 24.8 / 24.6, 73.4 / 72.9,
+    // 359 / 359, 267.9 / 269.2; paged and bf16 layers as fp16 ones; half of the heads at 8 and half at 2 bits 311.5 / 312.0.
     int covered0 = batch.heads_covered[0], covered1 = batch.heads_covered[1], slots = batch.slots;
     int *status = batch.status;
     uint8_t *scratch = batch.ws;
     long long scratch_bytes = batch.ws_request;
-    if (kAtOnce) asm volatile("" ::"s"(covered0), "s"(covered1), "s"(slots), "s"(status), "s"(scratch), "s"(scratch_bytes));
-    const CoderArgs a = coder_args<KV, kAtOnce>(batch, place_item_of_many(batch.at, place_of_workgroup(batch.at), wg));
+    asm volatile("" ::"s"(covered0), "s"(covered1), "s"(slots), "s"(status), "s"(scratch), "s"(scratch_bytes));
+    const CoderArgs a = coder_args<KV, true>(batch, place_item_of_many(batch.at, place_of_workgroup(batch.at), wg));
     const bool is_v = KV == 2 ? a.is_v != 0 : KV == 1;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * Dec::kLds];
     __shared__ uint16_t lut[4096];
