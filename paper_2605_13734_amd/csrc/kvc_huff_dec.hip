@@ -323,11 +323,11 @@ struct DecodeShape {
 //            2 bits, groups of 32, 32 of 2^18.3 rows 1 / 1.04 / 1.00
 //   paged    2 bits, groups of 64 and 128, 2^23.2 to 2^24 rows 1 / 1.07 to 1.10 / 0.99; groups of 32, 7 of 2^20.8 rows and 6 of 2^21 1 /
 //            1.10 / 0.97, 32 of 2^18.3 1 / 1.07 / 0.97, 3 bits 1 / 1.04 / 1.00
-// One paged request, 3 bits, groups of 32, K and V together, two workgroups per unit in place of three (three with arguments read where they are
-// used, as the kernels were for a while / now three / two): 2^20 rows 128.5 / 132.6 / 127.9 us, 2^21 242 / 254 / 242, 2^22 525 / 512 /
-// 472, just below 2^23 - / 1001 / 957.  (Groups of 64
-// and 128 lose 19 to 23 % by it, below 2^19.3 rows it is level.  2 bits at 2^20 and 2^21 rows, whose payload the last-level cache still
-// has from the call before, had 126 and 233 us for now 128 and 246, at 2^22 554 for 495; no other shape is better.)
+// One paged request, 3 bits, groups of 32, K and V together, two workgroups per unit in place of three below 2^21.4 rows (three with
+// arguments read where they are used, as the kernels were for a while / three / two, inputs in turn): 2^19.3 rows - / 90.3 / 89.9 us, 2^20
+// 128.5 / 131.9 / 128.1, 2^21 242 / 255 / 241, 2^21.3 - / 324 / 299, 2^21.38 - / 324 / 318, 2^21.43 - / 332 / 333, 2^21.5 - / 361 / 381, 2^22 525 /
+// 494 / 518, fp16 and bf16 alike.  (Calls repeated on one payload show two as the better one up to 2^23 rows.  Groups of 64 and 128
+// lose 19 to 23 % by it.  2 bits had 126 and 233 us at 2^20 and 2^21 rows, now 128 and 246, at 2^22 554, now 495; no other shape is better.)
 // Four requests of 2^20 rows (16 workgroups for every resident one) are better off as a single one is: 0.88 to 0.98.
 template <int BITS> static DecodeShape decode_shape(unsigned wgs, bool both, bool dense, bool transform, int group, bool one)
 {
@@ -337,7 +337,7 @@ template <int BITS> static DecodeShape decode_shape(unsigned wgs, bool both, boo
     const bool several = !one && (wgs < 8 * kResident || wgs >= 24 * kResident);
     if (!dense) {
         if (BITS == 4 || wgs < 5 * kResident / 2) return {};
-        if (BITS == 3 && g32 && both && one) return {40000, 0};
+        if (BITS == 3 && g32 && both && one && wgs < 21 * kResident / 2) return {40000, 0};
         if (g32 && several) return {0, BITS == 3 ? 16 : 0};
         return {!large || (BITS == 2 && !g32 && one && wgs < 48 * kResident) ? 14000u : 0u, 0};
     }

@@ -326,7 +326,8 @@ def test_decoder_windows(n):
     (False, 3, 32, 4, [(8064, 14000), (8192, 40000), (24576, 14000)]), (False, 2, 32, 4, [(8064, 0), (8192, 14000), (24576, 0)]),
     (False, 3, 64, 4, [(24448, 40000), (24576, 14000)]), (False, 3, 128, 4, [(24576, 40000)]),
     (True, 2, 64, 1, [(2432, 0), (2560, 14000), (32768, 14000), (98304, 0)]), (True, 2, 32, 1, [(2560, 14000), (32768, 0)]),
-    (True, 3, 64, 1, [(32640, 14000), (32768, 0)]), (True, 3, 32, 4, [(8064, 0), (8192, 14000), (24576, 0)]), (True, 3, 32, 1, [(2432, 0), (2560, 40000), (32640, 40000), (32768, 0)]), (True, 4, 64, 1, [(8192, 0)])])
+    (True, 3, 64, 1, [(32640, 14000), (32768, 0)]), (True, 3, 32, 4, [(8064, 0), (8192, 14000), (24576, 0)]),
+    (True, 3, 32, 1, [(2432, 0), (2560, 40000), (10624, 40000), (10752, 14000), (32640, 14000), (32768, 0)]), (True, 4, 64, 1, [(8192, 0)])])
 def test_shapes_of_decoders(paged, bits, group, n, lines):
     """Both sides of the lines: 256 heads of T tokens, or four requests of 64 heads, are T workgroups for K and V together, T / 2
     for one of them (from 2^23 rows on)."""
