@@ -616,7 +616,7 @@ static long long window_chunks(const kvc_plan_t *p, const kvc_request *reqs, int
 // Every launch less saves a start and a tail.  Time with wide windows / with windows of four (K and V together), eight and twelve
 // (apart), the least and the most of 2, 3, 4 and 8 bits, K 4 and V 2, rotation and half of the heads at 8 bits, fp16 and bf16:
 //   requests      5 to 8, 2^21 to 2^23 rows        9 to 16, 2^21.5 to 2^24.2    20 to 40, 2^21.5 to 2^25.1
-//   compression   0.89 to 1.00 (rotation 1.01)     0.86 to 0.99                 0.73 to 0.99
+//   compression   0.89 to 1.00 (rotation, paged 1.02)  0.86 to 0.99             0.73 to 0.99
 //   decompression 0.91 to 1.01                     0.86 to 1.00                 0.76 to 0.99
 // (calls with fewer rows have the windows below, whose lines were measured with batches of twelve)
 static bool wide_window(const kvc_plan_t *p, const kvc_request *reqs, int n)
@@ -698,10 +698,12 @@ static int common_widths(const kvc_plan_t *p)
     return both == any ? 2 : 1;
 }
 
-// A shared launch takes four requests.  Where both tensors have all widths, two windows of four take as many launches
-// as one of eight with K and V apart; where one of them has a width of its own they take more, and
-// windows of more than four requests stay apart (K 4 and 3 bits, V 4 and 2, five requests of 2^14, 2^16 and 2^18 rows:
-// 66 81 208 us apart, 88 100 203 shared; K 8, 4 and 2 bits, V 8 and 2: 106 120 304 and 125 139 291).
+// A shared launch takes four requests, in a wide window sixteen.  Where both tensors have all widths, two windows of four take as many
+// launches as one of eight with K and V apart; where one of them has a width of its own they take more, and of the windows that are not
+// wide those of more than four requests stay apart (K 4 and 3 bits, V 4 and 2, five requests of 2^14, 2^16 and 2^18 rows:
+// 66 81 208 us apart, 88 100 203 shared; K 8, 4 and 2 bits, V 8 and 2: 106 120 304 and 125 139 291).  Wide ones share (256 heads, apart /
+// shared: K 4 and 3, V 4 and 2 bits, 5 requests of up to 2048 tokens 309 / 291 us, 8 of 1100 279 / 262, 16 of 1800 842 / 822; K 8, 4 and 2, V
+// 8 and 2 394 / 369, 363 / 332, 1081 / 1080).
 static bool widths_share(const kvc_plan_t *p, const kvc_request *reqs, int first, int end, int lead, int limit)
 {
     return common_widths(p) > 0 && end - first <= limit &&
